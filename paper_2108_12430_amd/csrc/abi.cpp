@@ -2,6 +2,7 @@
 // per-call item tables and kernel dispatch.  No kernel arithmetic lives here.
 #include "gwstream.h"
 
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <condition_variable>
@@ -556,6 +557,7 @@ struct StageD {
   int64_t wa, ba, wb, bb, ws, bs;
   size_t wa_bf, wb_bf, ws_bf;
   bool bf16;
+  bool f32m;  // both convolutions have an FP32 matrix-core kernel
 };
 
 constexpr int DENSE_ITEMS = 4096;  // item-table capacity for dense-input calls
@@ -722,6 +724,8 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
         sd.ws_bf = pk;
         pk += r256(2 * gw::conv_bf16_packed_elems(sd.ci, sd.co, 1, false));
       }
+      sd.f32m = gw::conv_f32m_supported(sd.ci, sd.co, 7, 2, 3, false, gw::EPI_RELU, 0) &&
+                gw::conv_f32m_supported(sd.co, sd.co, 7, 1, 3, false, gw::EPI_RESID_RELU, sd.ci);
       m.bf16_all = m.bf16_all && sd.bf16;
       m.stages.push_back(sd);
       ci = sd.co;
@@ -943,10 +947,70 @@ struct DcWs {
   std::vector<size_t> mean, invstd, z, a;  // per layer (SIZE_MAX = none)
   size_t ztmp = 0, atmp[2] = {0, 0};
   size_t partial = 0;
+  size_t wf32 = 0;  // FP32 matrix-core weight fragments, packed by each call
   int ckpt = -1;
 };
 
 constexpr size_t NONE = ~size_t(0);
+
+// A layer's forward convolution, or its adjoint (the input-gradient
+// convolution: channels exchanged, conv and transposed conv exchanged, the
+// same weights), as the FP32 matrix-core kernels take it.
+struct F32Conv {
+  bool ok, tr;
+  int ci, co, k, s, p, epi;
+  int64_t wso, wsi;
+  size_t bytes;
+};
+F32Conv f32_conv(const LayerD& ly, bool adjoint, bool last) {
+  F32Conv f{};
+  const bool conv = ly.type == GW_LAYER_CONV;
+  f.tr = adjoint ? conv : !conv;
+  f.ci = adjoint ? ly.co : ly.ci;
+  f.co = adjoint ? ly.ci : ly.co;
+  f.k = ly.k;
+  f.s = ly.s;
+  f.p = ly.p;
+  f.epi = last && !adjoint ? gw::EPI_OUT : gw::EPI_BIAS;
+  // conv weights [C_out][C_in][k], transposed [C_in][C_out][k]
+  const int64_t dout = (conv ? ly.ci : 1) * (int64_t)ly.k, din = (conv ? 1 : ly.co) * (int64_t)ly.k;
+  f.wso = adjoint ? din : dout;
+  f.wsi = adjoint ? dout : din;
+  f.ok = gw::conv_f32m_supported(f.ci, f.co, f.k, f.s, f.p, f.tr, f.epi, 0);
+  f.bytes = f.ok ? r256(4 * gw::f32m_packed_floats(f.ci, f.co, f.k, f.s, f.p, f.tr)) : 0;
+  return f;
+}
+
+// One launch packs the fragments of every layer's convolution (and adjoint)
+// into `base`; per-layer addresses (null: no matrix-core kernel) in fw, aw.
+// The packing runs in every training call, from the parameters as they are.
+size_t f32_conv_bytes(const gw_model* m, bool adjoint) {
+  size_t b = 0;
+  const int L = (int)m->layers.size();
+  for (int l = 0; l < L; ++l) b += f32_conv(m->layers[l], adjoint, l == L - 1).bytes;
+  return b;
+}
+hipError_t pack_f32_convs(const gw_model* m, bool adjoint, char* base, std::vector<const float*>& out,
+                          hipStream_t st) {
+  const int L = (int)m->layers.size();
+  out.assign(L, nullptr);
+  gw::F32PackTab t{};
+  for (int l = 0; l < L; ++l) {
+    const LayerD& ly = m->layers[l];
+    const F32Conv f = f32_conv(ly, adjoint, l == L - 1);
+    if (!f.ok) continue;
+    if (t.n == gw::kF32PackMax) {
+      const hipError_t e = gw::launch_pack_f32m(t, st);
+      if (e != hipSuccess) return e;
+      t.n = 0;
+    }
+    float* dst = reinterpret_cast<float*>(base);
+    t.e[t.n++] = gw::f32m_pack_entry(m->params + ly.w, f.wso, f.wsi, dst, f.ci, f.co, f.k, f.s, f.p, f.tr);
+    out[l] = dst;
+    base += f.bytes;
+  }
+  return gw::launch_pack_f32m(t, st);
+}
 
 int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags, DcWs& w) {
   std::vector<int> lin, lout;
@@ -1004,6 +1068,7 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
     w.atmp[1] = take(mx);
   }
   w.partial = take((size_t)maxc * maxchunk * 2 * sizeof(double));
+  w.wf32 = take(f32_conv_bytes(m, false));
   w.total = off;
   return GW_OK;
 }
@@ -1037,6 +1102,7 @@ hipError_t run_conv(const gw::ConvP& p, const LayerD& ly, int epi, int src, int 
                     hipStream_t st) {
   const bool tr = ly.type == GW_LAYER_CONVT;
   if (precision == GW_BF16) return gw::launch_conv_bf16(p, tr, epi, src, st);
+  if (p.wf32) return gw::launch_conv_f32m(p, tr, epi, st);
   return gw::launch_conv_fp32(p, tr, epi, src, st);
 }
 
@@ -1215,12 +1281,15 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   }
   // training forward: z = conv(a) + b, batch statistics, a = tanh(BN(z))
   double* partial = reinterpret_cast<double*>(wsb + w.partial);
+  std::vector<const float*> wf(L, nullptr);
+  if (precision == GW_FP32) LAUNCH("pack_f32m", st, pack_f32_convs(m, false, wsb + w.wf32, wf, st));
   const float* in = x;
   for (int l = 0; l < L; ++l) {
     const LayerD& ly = m->layers[l];
     gw::ConvP p = conv_params(m, ly, n, lin[l], lout[l]);
     p.items = dev_items;
     p.x = in;
+    p.wf32 = wf[l];
     if (precision == GW_BF16) p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
     if (l == L - 1) {
       p.noise = noise;
@@ -1469,6 +1538,7 @@ struct BwWs {
   std::vector<size_t> z, a;  // recomputed activations (recompute mode)
   size_t partial = 0;
   size_t wg = 0;
+  size_t wf32 = 0, wa32 = 0;  // FP32 matrix-core fragments: forward (recomputation) and adjoint
   size_t total = 0;
 };
 
@@ -1521,6 +1591,8 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
   }
   b.partial = take((size_t)maxc * maxchunk * 2 * sizeof(double));
   b.wg = take(mwg);
+  if (flags & GW_RECOMPUTE) b.wf32 = take(f32_conv_bytes(m, false));
+  b.wa32 = take(f32_conv_bytes(m, true));
   b.total = off;
   return GW_OK;
 }
@@ -1626,12 +1698,17 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
       A[l] = savedf(w.a[l]);
       Z[l] = m->layers[l].bn ? savedf(w.z[l]) : A[l];
     }
+  std::vector<const float*> wf(L, nullptr), wa(L, nullptr);
+  if (precision == GW_FP32 && rec) LAUNCH("pack_f32m", st, pack_f32_convs(m, false, sc + b.wf32, wf, st));
+  // the output conv's adjoint has no split-BF16 kernel: FP32 in both variants
+  LAUNCH("pack_f32m", st, pack_f32_convs(m, true, sc + b.wa32, wa, st));
   // recompute layers [l0, l1] from `in` with the saved statistics
   auto recompute = [&](int l0, int l1, const float* in) -> int {
     for (int l = l0; l <= l1; ++l) {
       const LayerD& ly = m->layers[l];
       gw::ConvP p = conv_params(m, ly, n, lin[l], lout[l]);
       p.x = in;
+      p.wf32 = wf[l];
       if (precision == GW_BF16) p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
       float* a = scf(b.a[l]);
       float* z = ly.bn ? scf(b.z[l]) : a;
@@ -1701,6 +1778,9 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
       p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wdg_lo);
       LAUNCH(nm("dgrad_bf16", "L", l), st,
              gw::launch_conv_bf16(p, ly.type == GW_LAYER_CONV, gw::EPI_BIAS, gw::SRC_DENSE, st));
+    } else if (wa[l]) {
+      p.wf32 = wa[l];
+      LAUNCH(nm("dgrad", "L", l), st, gw::launch_conv_f32m(p, ly.type == GW_LAYER_CONV, gw::EPI_BIAS, st));
     } else if (ly.type == GW_LAYER_CONV) {
       p.wsi = (int64_t)ly.ci * ly.k;  // transposed kernel reads w[i*wsi + o*wso + j], i = conv out ch
       p.wso = ly.k;
@@ -1827,6 +1907,7 @@ constexpr int kGapParts = 256;
 
 struct BbWs {
   size_t gath = NONE, h = 0, o[2] = {0, 0}, gap = 0, total = 0;
+  std::vector<std::array<size_t, 3>> wf32;  // FP32: stage fragments (conv_a, conv_b, shortcut)
 };
 int bb_layout(const gw_model* m, int n, int W, bool pool, int precision, BbWs& b) {
   const int Sn = (int)m->stages.size();
@@ -1837,7 +1918,6 @@ int bb_layout(const gw_model* m, int n, int W, bool pool, int precision, BbWs& b
     off += r256(bytes);
     return o;
   };
-  (void)precision;
   if (pool) b.gath = take((size_t)n * m->c_in * W * 4);
   size_t mh = 256;
   int L = W;
@@ -1849,6 +1929,14 @@ int bb_layout(const gw_model* m, int n, int W, bool pool, int precision, BbWs& b
   b.o[0] = take(mh);
   b.o[1] = take(mh);
   b.gap = take((size_t)n * kGapParts * sizeof(float));
+  b.wf32.assign(Sn, {NONE, NONE, NONE});
+  for (int s = 0; s < Sn && precision == GW_FP32; ++s) {
+    const StageD& sd = m->stages[s];
+    if (!sd.f32m) continue;
+    b.wf32[s][0] = take(4 * gw::f32m_packed_floats(sd.ci, sd.co, 7, 2, 3, false));
+    b.wf32[s][1] = take(4 * gw::f32m_packed_floats(sd.co, sd.co, 7, 1, 3, false));
+    b.wf32[s][2] = take(4 * gw::f32m_packed_floats(sd.ci, sd.co, 1, 1, 0, false));
+  }
   b.total = off;
   return GW_OK;
 }
@@ -1953,6 +2041,19 @@ extern "C" int bbhnet_forward(const gw_model* m, gw_pool* pool, const int32_t* s
   const float* P = m->params;
   const bool bf = precision == GW_BF16;
   const int Sn = (int)m->stages.size();
+  if (!bf) {
+    // every FP32 call packs its fragments from the parameters as they are
+    gw::F32PackTab t{};
+    for (int s = 0; s < Sn; ++s) {
+      const StageD& sd = m->stages[s];
+      if (!sd.f32m) continue;
+      auto at = [&](int k) { return reinterpret_cast<float*>(wsb + b.wf32[s][k]); };
+      t.e[t.n++] = gw::f32m_pack_entry(P + sd.wa, (int64_t)sd.ci * 7, 7, at(0), sd.ci, sd.co, 7, 2, 3, false);
+      t.e[t.n++] = gw::f32m_pack_entry(P + sd.wb, (int64_t)sd.co * 7, 7, at(1), sd.co, sd.co, 7, 1, 3, false);
+      t.e[t.n++] = gw::f32m_pack_entry(P + sd.ws, sd.ci, 1, at(2), sd.ci, sd.co, 1, 1, 0, false);
+    }
+    LAUNCH("pack_f32m", st, gw::launch_pack_f32m(t, st));
+  }
   const void* cur = in;  // stage input: fp32 for stage 0, bf16 after (BF16 path)
   for (int s = 0; s < Sn; ++s) {
     const auto& sd = m->stages[s];
@@ -2027,6 +2128,31 @@ extern "C" int bbhnet_forward(const gw_model* m, gw_pool* pool, const int32_t* s
       pb.x = pa.y;
       pb.xs = reinterpret_cast<const float*>(cur);
       pb.y = reinterpret_cast<float*>(obuf);
+      if (sd.f32m) {
+        pa.wf32 = reinterpret_cast<const float*>(wsb + b.wf32[s][0]);
+        pb.wf32 = reinterpret_cast<const float*>(wsb + b.wf32[s][1]);
+        pb.wsf32 = reinterpret_cast<const float*>(wsb + b.wf32[s][2]);
+        LAUNCH(nm("bbh_conva_fp32", "S", s), st, gw::launch_conv_f32m(pa, false, gw::EPI_RELU, st));
+        // the pooling head joins the last stage's epilogue when its partial
+        // sums fit the workspace (FP64, so half of its kGapParts floats)
+        const int parts = gw::conv_f32m_gap_parts(sd.co, Lo);
+        const bool pool_head = last && 2 * parts <= kGapParts &&
+                               gw::conv_f32m_supported(sd.co, sd.co, 7, 1, 3, false, gw::EPI_RESID_GAP, sd.ci);
+        if (pool_head) {
+          pb.hw = P + m->head_w;
+          pb.gap_part64 = reinterpret_cast<double*>(wsb + b.gap);
+        }
+        LAUNCH(nm("bbh_convb_fp32", "S", s), st,
+               gw::launch_conv_f32m(pb, false, pool_head ? gw::EPI_RESID_GAP : gw::EPI_RESID_RELU, st));
+        if (pool_head) {
+          LAUNCH("gap_finalize", st,
+                 gw::launch_gap_finalize64(pb.gap_part64, parts, P + m->head_b, logits, n, Lo, st));
+          return GW_OK;
+        }
+        cur = obuf;
+        L = Lo;
+        continue;
+      }
       LAUNCH(nm("bbh_conva_fp32", "S", s), st, gw::launch_conv_fp32(pa, false, gw::EPI_RELU, gw::SRC_DENSE, st));
       LAUNCH(nm("bbh_convb_fp32", "S", s), st,
              gw::launch_conv_fp32(pb, false, gw::EPI_RESID_RELU, gw::SRC_DENSE, st));

@@ -44,42 +44,6 @@ __device__ __forceinline__ float bf16_to_f(uint16_t h) { return __uint_as_float(
 // 2^-16 per product instead of 2^-8 (the training variant's convolutions).
 enum InFmt { IN_F32 = 0, IN_BF16 = 1, IN_RING = 2, IN_RING_F32 = 3, IN_F32S = 4 };
 
-// Geometry of the polyphase/strided column view of a layer (host + device).
-struct Geo {
-  int nph;    // phases (1 for conv, stride for transposed)
-  int kt;     // taps per phase
-  int sc;     // input step per column (stride for conv, 1 for transposed)
-  int padc;   // input position of tile row 0 is sc*col0 - padc
-  int ncol;   // output columns
-};
-
-__host__ __device__ inline Geo make_geo(bool tr, int k, int s, int p, int Lout) {
-  Geo g;
-  if (!tr) {
-    g.nph = 1;
-    g.kt = k;
-    g.sc = s;
-    g.padc = p;
-    g.ncol = Lout;
-  } else {
-    // output u = s*m + r uses input m + d with tap j = r + p - s*d, 0 <= j < k
-    int dmin = 1 << 30, dmax = -(1 << 30);
-    for (int r = 0; r < s; ++r)
-      for (int j = 0; j < k; ++j)
-        if ((r + p - j) % s == 0) {
-          const int d = (r + p - j) / s;
-          dmin = d < dmin ? d : dmin;
-          dmax = d > dmax ? d : dmax;
-        }
-    g.nph = s;
-    g.kt = dmax - dmin + 1;
-    g.sc = 1;
-    g.padc = -dmin;
-    g.ncol = (Lout + s - 1) / s;
-  }
-  return g;
-}
-
 // ---------------------------------------------------------------------------
 // Weight packing: fragment (ph, mt, ks), lane l, element e holds
 // W_ph[o = 16 mt + l%16][kappa = 32 ks + 8 (l/16) + e], zero outside.

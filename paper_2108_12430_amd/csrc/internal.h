@@ -50,6 +50,8 @@ struct ConvP {
   const uint16_t* wpk;     // packed bf16 weights (BF16 kernels)
   const uint16_t* wpk_lo;  // low bf16 terms of the weights (split FP32 input), or null
   const uint16_t* wspk;    // packed bf16 1x1 shortcut weights (BF16 residual epilogue)
+  const float* wf32;       // packed fp32 weight fragments (FP32 matrix-core kernels)
+  const float* wsf32;      // packed fp32 1x1 shortcut fragments
   const float* bias;
   const float* scale;
   const float* shift;
@@ -62,6 +64,7 @@ struct ConvP {
   // pooling head (EPI_RESID_GAP): per-block partial sums of hw[o] * y[o][t]
   const float* hw;
   float* gap_part;         // [n][gridDim.x]
+  double* gap_part64;      // the same, FP32 matrix-core kernels
   // outputs of EPI_OUT
   float* noise;            // [n][W] or null
   const float* strain;     // packed, or null
@@ -77,6 +80,42 @@ struct ConvP {
   // than from the ring, and written to the ring and its shadow by the launch
   const float* upd;
 };
+
+// Geometry of the polyphase/strided column view of a layer (host + device).
+struct Geo {
+  int nph;    // phases (1 for conv, stride for transposed)
+  int kt;     // taps per phase
+  int sc;     // input step per column (stride for conv, 1 for transposed)
+  int padc;   // input position of tile row 0 is sc*col0 - padc
+  int ncol;   // output columns
+};
+
+__host__ __device__ inline Geo make_geo(bool tr, int k, int s, int p, int Lout) {
+  Geo g;
+  if (!tr) {
+    g.nph = 1;
+    g.kt = k;
+    g.sc = s;
+    g.padc = p;
+    g.ncol = Lout;
+  } else {
+    // output u = s*m + r uses input m + d with tap j = r + p - s*d, 0 <= j < k
+    int dmin = 1 << 30, dmax = -(1 << 30);
+    for (int r = 0; r < s; ++r)
+      for (int j = 0; j < k; ++j)
+        if ((r + p - j) % s == 0) {
+          const int d = (r + p - j) / s;
+          dmin = d < dmin ? d : dmin;
+          dmax = d > dmax ? d : dmax;
+        }
+    g.nph = s;
+    g.kt = dmax - dmin + 1;
+    g.sc = 1;
+    g.padc = -dmin;
+    g.ncol = (Lout + s - 1) / s;
+  }
+  return g;
+}
 
 // ---- incremental DeepClean over per-stream activation caches ----
 // Geometry of one layer of the cached network: type 0 conv (output k reads
@@ -205,6 +244,30 @@ hipError_t launch_bbh_fused(const BbFusedP& p, hipStream_t st);
 // ---- launchers (defined in the .hip files) ----
 hipError_t launch_conv_fp32(const ConvP& p, bool transposed, int epi, int src, hipStream_t st);
 hipError_t launch_conv_bf16(const ConvP& p, bool transposed, int epi, int src, hipStream_t st);
+// FP32 matrix-core convolutions (conv_f32m.hip).  Their weight fragments are
+// packed by launch_pack_f32m, one launch for all of a network's layers.
+struct F32Pack {
+  const float* w;
+  float* out;
+  int64_t wso, wsi;  // w[o * wso + i * wsi + tap]
+  int64_t total;     // floats of the fragments
+  int Ci, Co, k, s, pad, tr, padc, kt, cip, MT, KS;
+};
+constexpr int kF32PackMax = 32;
+struct F32PackTab {
+  int n;
+  F32Pack e[kF32PackMax];
+};
+static_assert(sizeof(F32PackTab) <= 4000, "the table is a kernel argument");
+F32Pack f32m_pack_entry(const float* w, int64_t wso, int64_t wsi, float* out, int Ci, int Co, int k, int s, int pad,
+                        bool tr);
+size_t f32m_packed_floats(int Ci, int Co, int k, int s, int pad, bool tr);
+hipError_t launch_pack_f32m(const F32PackTab& t, hipStream_t st);
+// whether a compiled kernel takes the layer (Cs: shortcut channels of a
+// residual epilogue, else 0)
+bool conv_f32m_supported(int Ci, int Co, int k, int s, int pad, bool tr, int epi, int Cs);
+int conv_f32m_gap_parts(int Co, int Lout);  // GAP partial sums per window (EPI_RESID_GAP)
+hipError_t launch_conv_f32m(const ConvP& p, bool transposed, int epi, hipStream_t st);
 bool conv_bf16_supported(int Ci, int Co, int k, int stride, bool transposed);
 int conv_bf16_gap_parts(int Ci, int Co, int Lout, int n);  // GAP partial sums per window (EPI_RESID_GAP), -1 if none
 // Fused DeepClean network (21->8->16->32->64 convs, 64->32->16->8->8
@@ -244,6 +307,8 @@ hipError_t launch_fold_bn(const float* b, const float* gamma, const float* beta,
 // logits[b] = (sum_k part[b][k]) / L + bias, k < nblk, fixed order
 hipError_t launch_gap_finalize(const float* part, int nblk, const float* bias, float* logits, int n,
                                int L, hipStream_t st);
+hipError_t launch_gap_finalize64(const double* part, int nblk, const float* bias, float* logits, int n, int L,
+                                 hipStream_t st);
 hipError_t launch_gap_linear(const float* a, const float* w, const float* b, float* logits, int n,
                              int C, int L, hipStream_t st);
 

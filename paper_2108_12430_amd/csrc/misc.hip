@@ -175,18 +175,25 @@ hipError_t launch_zero_floats(float* dst, int64_t n, hipStream_t st) {
 
 namespace gw {
 
-__global__ void gap_finalize_kernel(const float* part, int nblk, const float* bias, float* logits, int n,
-                                    int L) {
+template <typename T>
+__global__ void gap_finalize_kernel(const T* part, int nblk, const float* bias, float* logits, int n, int L) {
   const int b = blockIdx.x * 256 + threadIdx.x;
   if (b >= n) return;
-  float s = 0.0f;
+  T s = 0;
   for (int k = 0; k < nblk; ++k) s += part[(int64_t)b * nblk + k];
-  logits[b] = s / (float)L + bias[0];
+  logits[b] = (float)(s / (T)L + (T)bias[0]);
 }
 
 hipError_t launch_gap_finalize(const float* part, int nblk, const float* bias, float* logits, int n,
                                int L, hipStream_t st) {
-  hipLaunchKernelGGL(gap_finalize_kernel, dim3((n + 255) / 256), dim3(256), 0, st, part, nblk, bias, logits,
+  hipLaunchKernelGGL(gap_finalize_kernel<float>, dim3((n + 255) / 256), dim3(256), 0, st, part, nblk, bias, logits,
+                     n, L);
+  return hipGetLastError();
+}
+
+hipError_t launch_gap_finalize64(const double* part, int nblk, const float* bias, float* logits, int n, int L,
+                                 hipStream_t st) {
+  hipLaunchKernelGGL(gap_finalize_kernel<double>, dim3((n + 255) / 256), dim3(256), 0, st, part, nblk, bias, logits,
                      n, L);
   return hipGetLastError();
 }
