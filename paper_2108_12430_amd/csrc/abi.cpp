@@ -549,6 +549,7 @@ struct LayerD {
   bool dg_mfma;               // the adjoint convolution has a matrix-core kernel
   size_t wf16;                // packed fp16 weights byte offset (fused-shape networks)
   size_t wfs, wfs16;          // the fused kernel's own fragment layout (bf16, fp16), where it differs
+  size_t wf32;                // fragments of the fused FP32 kernel
   bool bf16;                  // BF16 kernel available
 };
 
@@ -679,6 +680,10 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
       if (m.fused)
         for (int l = 0; l < Ln; ++l) {  // FP16 copies for the fused kernel's FP16 variant
           auto& ly = m.layers[l];
+          const size_t f32 = gw::dc_f32_special_floats(l);
+          ly.wf32 = pk;
+          pk += r256(4 * (f32 ? f32 : gw::f32m_packed_floats(ly.ci, ly.co, ly.k, ly.s, ly.p,
+                                                             ly.type == GW_LAYER_CONVT)));
           ly.wf16 = pk;
           pk += r256(2 * gw::conv_bf16_packed_elems(ly.ci, ly.co, ly.k, ly.type == GW_LAYER_CONVT));
           if (gw::dc_fused_special(l)) {
@@ -752,6 +757,20 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
 int pack_model(gw_model* m, hipStream_t st) {
   const float* P = m->params;
   if (m->kind == GW_MODEL_DEEPCLEAN) {
+    if (m->fused) {
+      gw::F32PackTab t{};
+      for (int l = 0; l < (int)m->layers.size(); ++l) {
+        const LayerD& ly = m->layers[l];
+        float* dst = reinterpret_cast<float*>(m->packed + ly.wf32);
+        const bool tr = ly.type == GW_LAYER_CONVT;
+        if (gw::dc_f32_special_floats(l))
+          HIPCHK(gw::launch_pack_dc_f32(P + ly.w, dst, l, st));
+        else
+          t.e[t.n++] = gw::f32m_pack_entry(P + ly.w, tr ? ly.k : (int64_t)ly.ci * ly.k, tr ? (int64_t)ly.co * ly.k : ly.k,
+                                           dst, ly.ci, ly.co, ly.k, ly.s, ly.p, tr);
+      }
+      HIPCHK(gw::launch_pack_f32m(t, st));
+    }
     for (int l = 0; l < (int)m->layers.size(); ++l) {
       auto& ly = m->layers[l];
       float* sc = reinterpret_cast<float*>(m->packed + ly.scale);
@@ -1098,11 +1117,12 @@ gw::ConvP conv_params(const gw_model* m, const LayerD& ly, int n, int Lin, int L
   return p;
 }
 
-hipError_t run_conv(const gw::ConvP& p, const LayerD& ly, int epi, int src, int precision,
-                    hipStream_t st) {
+// wf32: the layer's FP32 matrix-core fragments, null for the direct kernel
+hipError_t run_conv(const gw::ConvP& p, const LayerD& ly, int epi, int src, int precision, hipStream_t st,
+                    const float* wf32 = nullptr) {
   const bool tr = ly.type == GW_LAYER_CONVT;
   if (precision == GW_BF16) return gw::launch_conv_bf16(p, tr, epi, src, st);
-  if (p.wf32) return gw::launch_conv_f32m(p, tr, epi, st);
+  if (wf32) return gw::launch_conv_f32m(p, {wf32, nullptr, nullptr}, tr, epi, st);
   return gw::launch_conv_fp32(p, tr, epi, src, st);
 }
 
@@ -1250,6 +1270,28 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
            gw::launch_dc_fused_bf16(p, wpk, sc, sh, Wb, pool != nullptr, m->cu_budget, st, f16, upd != nullptr));
     return GW_OK;
   }
+  if (!(flags & GW_TRAIN) && precision == GW_FP32 && m->fused && !(flags & GW_LAYERWISE)) {
+    // the same in FP32
+    gw::ConvP p{};
+    p.n = n;
+    p.items = dev_items;
+    p.arena = arena;
+    p.x = x ? x + a_band : nullptr;
+    p.ldx = x ? W : 0;
+    p.noise = noise;
+    p.clean = clean;
+    p.strain = strain;
+    const float* wpk[9];
+    const float* sc[9];
+    const float* sh[9];
+    for (int l = 0; l < 9; ++l) {
+      wpk[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].wf32);
+      sc[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].scale);
+      sh[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].shift);
+    }
+    LAUNCH("dc_f32", st, gw::launch_dc_f32(p, wpk, sc, sh, Wb, pool != nullptr, m->cu_budget, st));
+    return GW_OK;
+  }
   if (upd) return fail(GW_EINVAL, "the fused update runs on the fused BF16 inference path only");
   if (!(flags & GW_TRAIN)) {
     const float* in = x ? x + a_band : nullptr;
@@ -1289,13 +1331,12 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
     gw::ConvP p = conv_params(m, ly, n, lin[l], lout[l]);
     p.items = dev_items;
     p.x = in;
-    p.wf32 = wf[l];
     if (precision == GW_BF16) p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
     if (l == L - 1) {
       p.noise = noise;
       p.clean = clean;
       p.strain = strain;
-      LAUNCH(nm("dc_train_conv", "L", l), st, run_conv(p, ly, gw::EPI_OUT, gw::SRC_DENSE, precision, st));
+      LAUNCH(nm("dc_train_conv", "L", l), st, run_conv(p, ly, gw::EPI_OUT, gw::SRC_DENSE, precision, st, wf[l]));
       break;
     }
     float* z = reinterpret_cast<float*>(wsb + (w.ckpt >= 0 ? w.ztmp : (ly.bn ? w.z[l] : w.a[l])));
@@ -1308,7 +1349,7 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
       a = reinterpret_cast<float*>(wsb + w.atmp[l & 1]);
     if (!ly.bn) z = a;
     p.y = z;
-    LAUNCH(nm("dc_train_conv", "L", l), st, run_conv(p, ly, gw::EPI_BIAS, gw::SRC_DENSE, precision, st));
+    LAUNCH(nm("dc_train_conv", "L", l), st, run_conv(p, ly, gw::EPI_BIAS, gw::SRC_DENSE, precision, st, wf[l]));
     if (ly.bn) {
       float* mean = reinterpret_cast<float*>(wsb + w.mean[l]);
       float* invstd = reinterpret_cast<float*>(wsb + w.invstd[l]);
@@ -1708,12 +1749,11 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
       const LayerD& ly = m->layers[l];
       gw::ConvP p = conv_params(m, ly, n, lin[l], lout[l]);
       p.x = in;
-      p.wf32 = wf[l];
       if (precision == GW_BF16) p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
       float* a = scf(b.a[l]);
       float* z = ly.bn ? scf(b.z[l]) : a;
       p.y = z;
-      LAUNCH(nm("dc_recompute_conv", "L", l), st, run_conv(p, ly, gw::EPI_BIAS, gw::SRC_DENSE, precision, st));
+      LAUNCH(nm("dc_recompute_conv", "L", l), st, run_conv(p, ly, gw::EPI_BIAS, gw::SRC_DENSE, precision, st, wf[l]));
       if (ly.bn)
         LAUNCH(nm("bn_apply", "L", l), st, gw::launch_bn_apply_tanh(z, savedf(w.mean[l]), savedf(w.invstd[l]), m->params + ly.g,
                                         m->params + ly.be, a, n, ly.co, lout[l], st));
@@ -1779,8 +1819,7 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
       LAUNCH(nm("dgrad_bf16", "L", l), st,
              gw::launch_conv_bf16(p, ly.type == GW_LAYER_CONV, gw::EPI_BIAS, gw::SRC_DENSE, st));
     } else if (wa[l]) {
-      p.wf32 = wa[l];
-      LAUNCH(nm("dgrad", "L", l), st, gw::launch_conv_f32m(p, ly.type == GW_LAYER_CONV, gw::EPI_BIAS, st));
+      LAUNCH(nm("dgrad", "L", l), st, gw::launch_conv_f32m(p, {wa[l], nullptr, nullptr}, ly.type == GW_LAYER_CONV, gw::EPI_BIAS, st));
     } else if (ly.type == GW_LAYER_CONV) {
       p.wsi = (int64_t)ly.ci * ly.k;  // transposed kernel reads w[i*wsi + o*wso + j], i = conv out ch
       p.wso = ly.k;
@@ -2129,10 +2168,10 @@ extern "C" int bbhnet_forward(const gw_model* m, gw_pool* pool, const int32_t* s
       pb.xs = reinterpret_cast<const float*>(cur);
       pb.y = reinterpret_cast<float*>(obuf);
       if (sd.f32m) {
-        pa.wf32 = reinterpret_cast<const float*>(wsb + b.wf32[s][0]);
-        pb.wf32 = reinterpret_cast<const float*>(wsb + b.wf32[s][1]);
-        pb.wsf32 = reinterpret_cast<const float*>(wsb + b.wf32[s][2]);
-        LAUNCH(nm("bbh_conva_fp32", "S", s), st, gw::launch_conv_f32m(pa, false, gw::EPI_RELU, st));
+        const auto frag = [&](int k) { return reinterpret_cast<const float*>(wsb + b.wf32[s][k]); };
+        gw::F32Frags fb{frag(1), frag(2), nullptr};
+        LAUNCH(nm("bbh_conva_fp32", "S", s), st,
+               gw::launch_conv_f32m(pa, {frag(0), nullptr, nullptr}, false, gw::EPI_RELU, st));
         // the pooling head joins the last stage's epilogue when its partial
         // sums fit the workspace (FP64, so half of its kGapParts floats)
         const int parts = gw::conv_f32m_gap_parts(sd.co, Lo);
@@ -2140,13 +2179,13 @@ extern "C" int bbhnet_forward(const gw_model* m, gw_pool* pool, const int32_t* s
                                gw::conv_f32m_supported(sd.co, sd.co, 7, 1, 3, false, gw::EPI_RESID_GAP, sd.ci);
         if (pool_head) {
           pb.hw = P + m->head_w;
-          pb.gap_part64 = reinterpret_cast<double*>(wsb + b.gap);
+          fb.gap_part = reinterpret_cast<double*>(wsb + b.gap);
         }
         LAUNCH(nm("bbh_convb_fp32", "S", s), st,
-               gw::launch_conv_f32m(pb, false, pool_head ? gw::EPI_RESID_GAP : gw::EPI_RESID_RELU, st));
+               gw::launch_conv_f32m(pb, fb, false, pool_head ? gw::EPI_RESID_GAP : gw::EPI_RESID_RELU, st));
         if (pool_head) {
           LAUNCH("gap_finalize", st,
-                 gw::launch_gap_finalize64(pb.gap_part64, parts, P + m->head_b, logits, n, Lo, st));
+                 gw::launch_gap_finalize64(fb.gap_part, parts, P + m->head_b, logits, n, Lo, st));
           return GW_OK;
         }
         cur = obuf;

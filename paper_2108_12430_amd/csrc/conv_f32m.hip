@@ -177,7 +177,7 @@ __device__ __forceinline__ void f32m_step(const float4 (&a)[NA], const float4 (&
 // further K steps from a second tile staged over the first.  Every output is
 // the same sequence of operations whatever the tile, the split and the batch.
 template <int CIP, int MTB, int NPH, int KT, int SC, int NTW, int EPI, int CSP>
-__global__ __launch_bounds__(256) void conv_f32m(ConvP p, int padc, int ncol, int MT) {
+__global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc, int ncol, int MT) {
   using namespace f32m;
   constexpr int TN = 64 * NTW;
   constexpr int ROWS = SC * (TN - 1) + KT;
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, int padc, int ncol, in
   f32m_stage<CIP, ROWS, RS, HALF, 1>(tile, xb, p.Ci, p.Lin, SC * col0 - padc,
                                      (p.Lin & 3) == 0 && (reinterpret_cast<uintptr_t>(p.x) & 15) == 0, tid);
   // A fragments of phase ph, channel tile ms MTB + m: two K steps requested ahead
-  const float4* wp = reinterpret_cast<const float4*>(p.wf32) + (int64_t)ms * MTB * KS * 64 + lane;
+  const float4* wp = reinterpret_cast<const float4*>(fr.w) + (int64_t)ms * MTB * KS * 64 + lane;
   auto frag = [&](int m, int ks) {  // m = ph MTB + channel tile
     return wp[((int64_t)(m / MTB) * MT + m % MTB) * KS * 64 + ks * 64];
   };
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, int padc, int ncol, in
     f32m_stage<CSP, TN, RSX, 0, 2>(tile, xs, p.Cs, p.Ls, 2 * col0,
                                    (p.Ls & 3) == 0 && (reinterpret_cast<uintptr_t>(p.xs) & 15) == 0, tid);
     __syncthreads();
-    const float4* sp = reinterpret_cast<const float4*>(p.wsf32) + (int64_t)ms * MTB * KSX * 64 + lane;
+    const float4* sp = reinterpret_cast<const float4*>(fr.ws) + (int64_t)ms * MTB * KSX * 64 + lane;
 #pragma unroll
     for (int ks = 0; ks < KSX; ++ks) {
       const int kappa = 16 * ks + 4 * lg, i0 = kappa < CSP ? kappa : 0;
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, int padc, int ncol, in
     if (lane == 0) wsum[wave] = gsum;
     __syncthreads();
     if (tid == 0)
-      p.gap_part64[((int64_t)b * tiles + ct) * MS + ms] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+      fr.gap_part[((int64_t)b * tiles + ct) * MS + ms] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
   }
 }
 
@@ -375,10 +375,10 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, int padc, int ncol, in
   X(128, 8, 1, 7, 1, EPI_RESID_GAP, 64, 2, 2)
 
 template <int CIP, int MT, int NPH, int KT, int SC, int EPI, int CSP, int MTB, int NTW>
-static hipError_t launch_f32m_t(const ConvP& p, const Geo& g, hipStream_t st) {
+static hipError_t launch_f32m_t(const ConvP& p, const F32Frags& f, const Geo& g, hipStream_t st) {
   const int64_t blocks = (int64_t)p.n * (MT / MTB) * ((g.ncol + 64 * NTW - 1) / (64 * NTW));
   if (blocks > ((int64_t)1 << 31) - 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((conv_f32m<CIP, MTB, NPH, KT, SC, NTW, EPI, CSP>), dim3((unsigned)blocks), dim3(256), 0, st, p,
+  hipLaunchKernelGGL((conv_f32m<CIP, MTB, NPH, KT, SC, NTW, EPI, CSP>), dim3((unsigned)blocks), dim3(256), 0, st, p, f,
                      g.padc, g.ncol, MT);
   return hipGetLastError();
 }
@@ -398,16 +398,17 @@ int conv_f32m_gap_parts(int Co, int Lout) {
   return (Lout + 127) / 128 * ((Co + 15) / 16 / 2);  // the pooled variant's column tiles x channel shares
 }
 
-hipError_t launch_conv_f32m(const ConvP& p, bool tr, int epi, hipStream_t st) {
+hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool tr, int epi, hipStream_t st) {
   const Geo g = make_geo(tr, p.k, p.stride, p.pad, p.Lout);
   const bool res = epi == EPI_RESID_RELU || epi == EPI_RESID_GAP;
-  if (!p.wf32 || !p.x || (res && (!p.wsf32 || !p.xs || p.Ls != 2 * p.Lout))) return hipErrorInvalidValue;
+  if (!f.w || !p.x || (res && (!f.ws || !p.xs || p.Ls != 2 * p.Lout))) return hipErrorInvalidValue;
+  if (epi == EPI_RESID_GAP && (!p.hw || !f.gap_part)) return hipErrorInvalidValue;
   if (p.ldx && p.ldx != p.Lin) return hipErrorInvalidValue;
   if (!conv_f32m_supported(p.Ci, p.Co, p.k, p.stride, p.pad, tr, epi, res ? p.Cs : 0)) return hipErrorNotSupported;
   const int cip = f32m::cip4(p.Ci), mt = (p.Co + 15) / 16, csp = res ? f32m::cip4(p.Cs) : 0;
 #define GW_LAUNCH(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW)                                                           \
   if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC && epi == EPI && csp == CSP)                  \
-    return launch_f32m_t<CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW>(p, g, st);
+    return launch_f32m_t<CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW>(p, f, g, st);
   GW_F32M_SHAPES(GW_LAUNCH)
 #undef GW_LAUNCH
   return hipErrorNotSupported;

@@ -50,8 +50,6 @@ struct ConvP {
   const uint16_t* wpk;     // packed bf16 weights (BF16 kernels)
   const uint16_t* wpk_lo;  // low bf16 terms of the weights (split FP32 input), or null
   const uint16_t* wspk;    // packed bf16 1x1 shortcut weights (BF16 residual epilogue)
-  const float* wf32;       // packed fp32 weight fragments (FP32 matrix-core kernels)
-  const float* wsf32;      // packed fp32 1x1 shortcut fragments
   const float* bias;
   const float* scale;
   const float* shift;
@@ -64,7 +62,6 @@ struct ConvP {
   // pooling head (EPI_RESID_GAP): per-block partial sums of hw[o] * y[o][t]
   const float* hw;
   float* gap_part;         // [n][gridDim.x]
-  double* gap_part64;      // the same, FP32 matrix-core kernels
   // outputs of EPI_OUT
   float* noise;            // [n][W] or null
   const float* strain;     // packed, or null
@@ -267,7 +264,12 @@ hipError_t launch_pack_f32m(const F32PackTab& t, hipStream_t st);
 // residual epilogue, else 0)
 bool conv_f32m_supported(int Ci, int Co, int k, int s, int pad, bool tr, int epi, int Cs);
 int conv_f32m_gap_parts(int Co, int Lout);  // GAP partial sums per window (EPI_RESID_GAP)
-hipError_t launch_conv_f32m(const ConvP& p, bool transposed, int epi, hipStream_t st);
+struct F32Frags {
+  const float* w;    // the convolution's fragments
+  const float* ws;   // the 1x1 shortcut's (residual epilogues)
+  double* gap_part;  // EPI_RESID_GAP: per-block partial sums of the pooled head
+};
+hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool transposed, int epi, hipStream_t st);
 bool conv_bf16_supported(int Ci, int Co, int k, int stride, bool transposed);
 int conv_bf16_gap_parts(int Ci, int Co, int Lout, int n);  // GAP partial sums per window (EPI_RESID_GAP), -1 if none
 // Fused DeepClean network (21->8->16->32->64 convs, 64->32->16->8->8
@@ -277,6 +279,13 @@ bool dc_fused_supported(const int* ci, const int* co, const int* type, const int
 hipError_t launch_dc_fused_bf16(const ConvP& p, const uint16_t* const* wpk, const float* const* scale,
                                 const float* const* shift, int W, bool ring, int cu_budget, hipStream_t st,
                                 bool f16 = false, bool upd = false);
+// The fused FP32 forward of the same network (dc_f32.hip): fragments of its
+// special layers (the others: launch_pack_f32m), and the launch (p as for
+// launch_dc_fused_bf16).
+size_t dc_f32_special_floats(int l);
+hipError_t launch_pack_dc_f32(const float* w, float* out, int l, hipStream_t st);
+hipError_t launch_dc_f32(const ConvP& p, const float* const* wpk, const float* const* scale, const float* const* shift,
+                         int W, bool ring, int cu_budget, hipStream_t st);
 size_t conv_bf16_packed_elems(int Ci, int Co, int k, bool transposed);
 // layers of the fused network whose weights the fused kernel takes in its own
 // fragment layout (stacked transposed layers, Toeplitz output conv)
