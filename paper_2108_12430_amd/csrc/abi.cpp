@@ -650,6 +650,7 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
       // the adjoint of a stride-2 conv is a stride-2 transposed conv and
       // vice versa, with input and output channels exchanged
       const bool conv = ly.type == GW_LAYER_CONV;
+      // (the reference network's run in FP32: backward_fused)
       ly.dg_mfma = ly.s == 2 && gw::conv_bf16_supported(ly.co, ly.ci, ly.k, 2, conv);
       if (ly.dg_mfma) {
         const size_t eb = r256(2 * gw::conv_bf16_packed_elems(ly.co, ly.ci, ly.k, conv));
@@ -680,6 +681,7 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
       if (m.fused)
         for (int l = 0; l < Ln; ++l) {  // FP16 copies for the fused kernel's FP16 variant
           auto& ly = m.layers[l];
+          ly.dg_mfma = false;
           const size_t f32 = gw::dc_f32_special_floats(l);
           ly.wf32 = pk;
           pk += r256(4 * (f32 ? f32 : gw::f32m_packed_floats(ly.ci, ly.co, ly.k, ly.s, ly.p,
@@ -1053,6 +1055,30 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
     return GW_OK;
   }
   const bool rec = flags & GW_RECOMPUTE;
+  if (m->fused) {
+    // the reference network saves every z; activations are taken from it
+    // wherever they are read (GW_TRAIN alone still reserves room for them)
+    w.mean.assign(L, NONE);
+    w.invstd.assign(L, NONE);
+    w.z.assign(L, NONE);
+    w.a.assign(L, NONE);
+    size_t part = 256;
+    for (int l = 0; l + 1 < L; ++l) {
+      const LayerD& ly = m->layers[l];
+      const bool tr = ly.type == GW_LAYER_CONVT;
+      w.mean[l] = take(4 * ly.co);
+      w.invstd[l] = take(4 * ly.co);
+      w.z[l] = take((size_t)n * ly.co * lout[l] * esz);
+      if (!rec) w.a[l] = take((size_t)n * ly.co * lout[l] * esz);
+      const int nblk = std::max(gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr),
+                                gw::conv_bf16_stats_blocks(n, lout[l], ly.k, ly.s, ly.p, tr));
+      part = std::max(part, (size_t)ly.co * nblk * 2 * sizeof(double));
+    }
+    w.partial = take(part);
+    w.wf32 = take(f32_conv_bytes(m, false));
+    w.total = off;
+    return GW_OK;
+  }
   // checkpoint: the layer with the shortest output (the bottleneck)
   int ck = 0;
   for (int l = 0; l + 1 < L; ++l)
@@ -1137,6 +1163,12 @@ extern "C" int deepclean_workspace(const gw_model* m, int32_t n, int32_t W, int3
   CHK(dc_ws_layout(m, n, W, precision, flags, w));
   *bytes = w.total;
   return GW_OK;
+}
+
+// batch normalisation of layer l of a training forward saved at `ws`
+static gw::BnP bn_params(const gw_model* m, const DcWs& w, const char* ws, int l) {
+  return {reinterpret_cast<const float*>(ws + w.mean[l]), reinterpret_cast<const float*>(ws + w.invstd[l]),
+          m->params + m->layers[l].g, m->params + m->layers[l].be};
 }
 
 // deepclean_forward; with upd set (fused BF16 inference on pool input only),
@@ -1325,6 +1357,45 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   double* partial = reinterpret_cast<double*>(wsb + w.partial);
   std::vector<const float*> wf(L, nullptr);
   if (precision == GW_FP32) LAUNCH("pack_f32m", st, pack_f32_convs(m, false, wsb + w.wf32, wf, st));
+  if (m->fused) {
+    // the reference network: each convolution takes tanh(BN(z)) of the layer
+    // before as it stages its input and sums the statistics of its own z
+    for (int l = 0; l < L; ++l) {
+      const LayerD& ly = m->layers[l];
+      const bool tr = ly.type == GW_LAYER_CONVT;
+      gw::ConvP p = conv_params(m, ly, n, lin[l], lout[l]);
+      p.x = l ? reinterpret_cast<const float*>(wsb + w.z[l - 1]) : x;
+      gw::F32Train t{};
+      if (l) t.in.bn = bn_params(m, w, wsb, l - 1);
+      t.partial = partial;
+      int epi = gw::EPI_STATS;
+      if (l == L - 1) {
+        epi = gw::EPI_OUT;
+        p.items = dev_items;
+        p.noise = noise;
+        p.clean = clean;
+        p.strain = strain;
+      } else {
+        p.y = reinterpret_cast<float*>(wsb + w.z[l]);
+      }
+      if (precision == GW_BF16) {
+        p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
+        LAUNCH(nm("dc_train_conv", "L", l), st, gw::launch_conv_bf16(p, tr, epi, gw::SRC_DENSE, st, &t));
+      } else {
+        LAUNCH(nm("dc_train_conv", "L", l), st,
+               gw::launch_conv_f32m(p, {wf[l], nullptr, nullptr}, tr, epi, st, l ? gw::PRO_ACT : gw::PRO_NONE, &t));
+      }
+      if (l == L - 1) break;
+      const int nblk = precision == GW_BF16
+                           ? gw::conv_bf16_stats_blocks(n, lout[l], ly.k, ly.s, ly.p, tr)
+                           : gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr);
+      LAUNCH(nm("bn_stats", "L", l), st,
+             gw::launch_stats_final(partial, nblk, ly.co, (int64_t)n * lout[l],
+                                    reinterpret_cast<float*>(wsb + w.mean[l]),
+                                    reinterpret_cast<float*>(wsb + w.invstd[l]), st));
+    }
+    return GW_OK;
+  }
   const float* in = x;
   for (int l = 0; l < L; ++l) {
     const LayerD& ly = m->layers[l];
@@ -1580,6 +1651,7 @@ struct BwWs {
   size_t partial = 0;
   size_t wg = 0;
   size_t wf32 = 0, wa32 = 0;  // FP32 matrix-core fragments: forward (recomputation) and adjoint
+  std::vector<size_t> wgp;    // the reference network's weight-gradient partials, per layer
   size_t total = 0;
 };
 
@@ -1593,6 +1665,25 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
     off += r256(bytes);
     return o;
   };
+  if (m->fused) {
+    size_t mg = 256, part = 256;
+    for (int l = 0; l < L; ++l) {
+      const LayerD& ly = m->layers[l];
+      const bool tr = ly.type == GW_LAYER_CONVT;
+      b.wgp.push_back(take(4 * gw::wgrad2_partial_floats(l, n, tr ? lin[l] : lout[l])));
+      if (l == L - 1) part = std::max(part, (size_t)gw::red_chunks(n, lout[l]) * 2 * sizeof(double));  // its bias
+      if (l == 0) continue;
+      mg = std::max(mg, (size_t)n * ly.ci * lin[l] * 4);
+      const int nblk = gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr);
+      part = std::max(part, (size_t)ly.ci * nblk * 2 * sizeof(double));
+    }
+    b.g[0] = take(mg);
+    b.g[1] = take(mg);
+    b.partial = take(part);
+    b.wa32 = take(f32_conv_bytes(m, true));
+    b.total = off;
+    return GW_OK;
+  }
   size_t mx = 256, mxin = 256, mwg = 256;
   int maxc = 1, maxchunk = 1;
   for (int l = 0; l < L; ++l) {
@@ -1639,6 +1730,83 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
 }
 
 }  // namespace
+
+// The reference network's backward.  Each adjoint convolution takes dz of its
+// layer from (dh, z) as it stages its input, turns its output into dh of the
+// layer before and sums that layer's (dh, dh xhat); each weight gradient takes
+// dz and the activations the same way.  FP32 products and sums in both
+// precisions (the split-BF16 variant differs in the forward's convolutions).
+static int backward_fused(const gw_model* m, int n, const float* x, const float* dnoise, const DcWs& w, const char* sv,
+                          float* dparams, const BwWs& b, char* sc, const std::vector<int>& lin,
+                          const std::vector<int>& lout, hipStream_t st) {
+  const int L = (int)m->layers.size();
+  double* partial = reinterpret_cast<double*>(sc + b.partial);
+  auto z_of = [&](int l) { return reinterpret_cast<const float*>(sv + w.z[l]); };
+  std::vector<const float*> wa;
+  LAUNCH("pack_f32m", st, pack_f32_convs(m, true, sc + b.wa32, wa, st));
+  gw::Wg2Tab red{};
+  const float* g = dnoise;  // dL/dnoise, then dh of the layer at hand
+  int gi = 0;
+  for (int l = L - 1; l >= 0; --l) {
+    const LayerD& ly = m->layers[l];
+    const bool tr = ly.type == GW_LAYER_CONVT, top = l == L - 1;
+    gw::BnBwdP dz{}, act{};
+    if (!top) {
+      dz.bn = bn_params(m, w, sv, l);
+      dz.z = z_of(l);
+      dz.sum_dh = dparams + ly.be;
+      dz.sum_dhx = dparams + ly.g;
+      dz.invN = (float)(1.0 / ((double)n * lout[l]));
+    } else {
+      // a conv bias followed by batch-statistics normalisation has an exactly
+      // zero gradient; the output conv's has not
+      LAUNCH(nm("bias_grad", "L", l), st,
+             gw::launch_channel_sum(dnoise, n, ly.co, lout[l], partial, gw::red_chunks(n, lout[l]), dparams + ly.b, st));
+    }
+    if (l) act.bn = bn_params(m, w, sv, l - 1);
+    const float* a_in = l ? z_of(l - 1) : x;
+    gw::Wg2Args wg{};
+    wg.p = tr ? a_in : g;
+    wg.q = tr ? g : a_in;
+    wg.pbn = tr ? act : dz;
+    wg.qbn = tr ? dz : act;
+    wg.n = n;
+    wg.Lp = tr ? lin[l] : lout[l];
+    wg.Lq = tr ? lout[l] : lin[l];
+    wg.partial = reinterpret_cast<float*>(sc + b.wgp[l]);
+    wg.dw = dparams + ly.w;
+    LAUNCH(nm("wgrad", "L", l), st, gw::launch_wgrad2(l, wg, &red.e[red.n], st));
+    ++red.n;
+    if (l == 0) break;
+    gw::ConvP p{};
+    p.n = n;
+    p.Ci = ly.co;
+    p.Co = ly.ci;
+    p.Lin = lout[l];
+    p.Lout = lin[l];
+    p.k = ly.k;
+    p.stride = ly.s;
+    p.pad = ly.p;
+    p.x = g;
+    float* gout = reinterpret_cast<float*>(sc + b.g[gi]);
+    gi ^= 1;
+    p.y = gout;
+    gw::F32Train t{};
+    t.in = dz;
+    t.out = act.bn;
+    t.z = z_of(l - 1);
+    t.partial = partial;
+    LAUNCH(nm("dgrad", "L", l), st,
+           gw::launch_conv_f32m(p, {wa[l], nullptr, nullptr}, !tr, gw::EPI_BNBWD, st, top ? gw::PRO_NONE : gw::PRO_DZ, &t));
+    const LayerD& lo = m->layers[l - 1];
+    LAUNCH(nm("bn_bwd", "L", l - 1), st,
+           gw::launch_bnbwd_final(partial, gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr), ly.ci,
+                                  (int64_t)n * lin[l], dparams + lo.g, dparams + lo.be, st));
+    g = gout;
+  }
+  LAUNCH("wgrad_reduce", st, gw::launch_wgrad2_reduce(red, st));
+  return GW_OK;
+}
 
 extern "C" int gw_decimate2(int32_t n, int32_t C, int32_t s, int32_t ntaps, const float* taps, const float* x,
                             float* hist, float* y, void* hip_stream) {
@@ -1727,6 +1895,10 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
   const int L = (int)m->layers.size();
   const char* sv = reinterpret_cast<const char*>(saved);
   char* sc = reinterpret_cast<char*>(scratch);
+  if (m->fused) {
+    LAUNCH("zero", st, gw::launch_zero_floats(dparams, m->n_params, st));
+    return backward_fused(m, n, x, dnoise, w, sv, dparams, b, sc, lin, lout, st);
+  }
   double* partial = reinterpret_cast<double*>(sc + b.partial);
   const bool rec = flags & GW_RECOMPUTE;
   auto savedf = [&](size_t off) { return reinterpret_cast<const float*>(sv + off); };

@@ -20,7 +20,7 @@
 // Fragment layout of v_mfma_f32_16x16x32_bf16 (lane l = 0..63):
 //   A[row = l % 16][k = 8 (l / 16) + e],  B[k = 8 (l / 16) + e][col = l % 16],
 //   D[row = 4 (l / 16) + r][col = l % 16],  e = 0..7, r = 0..3.
-#include "internal.h"
+#include "train_epi.h"
 
 namespace gw {
 
@@ -42,7 +42,9 @@ __device__ __forceinline__ float bf16_to_f(uint16_t h) { return __uint_as_float(
 // tiles; with the weights split the same way each product takes three MFMAs
 // (hi*hi + lo_w*hi_x + hi_w*lo_x), which leaves a relative error of about
 // 2^-16 per product instead of 2^-8 (the training variant's convolutions).
-enum InFmt { IN_F32 = 0, IN_BF16 = 1, IN_RING = 2, IN_RING_F32 = 3, IN_F32S = 4 };
+// IN_F32A: the same for a training layer's z, taken through tanh(BN(z)) first.
+enum InFmt { IN_F32 = 0, IN_BF16 = 1, IN_RING = 2, IN_RING_F32 = 3, IN_F32S = 4, IN_F32A = 5 };
+constexpr bool split_in(int in) { return in == IN_F32S || in == IN_F32A; }
 
 // ---------------------------------------------------------------------------
 // Weight packing: fragment (ph, mt, ks), lane l, element e holds
@@ -123,7 +125,7 @@ template <int CIP, int ROWS, int IN, int NTHR = 256>
 struct InRaw {
   static constexpr int NCHMAX = (ROWS + 7 + 7) / 8;             // 8-position chunks per channel
   static constexpr int ITEMS = (NCHMAX * CIP + NTHR - 1) / NTHR;  // (channel, chunk) items per thread
-  static constexpr int NV = (IN == IN_F32 || IN == IN_F32S) ? 2 : 1;
+  static constexpr int NV = (IN == IN_F32 || split_in(IN)) ? 2 : 1;
   static_assert(ITEMS <= 32, "one mask bit per item");
   uint4 v[ITEMS][NV];  // raw 16-byte pieces (two for FP32 input)
   uint32_t f32mask;    // items whose v[it][0..1] still hold 8 FP32 values (always, for IN_F32S)
@@ -165,14 +167,14 @@ __device__ __forceinline__ void load_input(InRaw<CIP, ROWS, IN, NTHR>& R, const 
     const int i = e % CIP, ch = e / CIP;
     const int qc = qa + 8 * ch;
     R.v[it][0] = make_uint4(0, 0, 0, 0);
-    if (IN == IN_F32S) {
+    if (split_in(IN)) {
       // split staging keeps every item in FP32 (zeros outside the signal)
       R.v[it][R.NV - 1] = make_uint4(0, 0, 0, 0);
       R.f32mask |= 1u << it;
     }
     if (ch < nch && i < Ci) {
       if (vec && qc >= 0 && qc + 8 <= Lin) {
-        if (IN == IN_F32 || IN == IN_F32S) {
+        if (IN == IN_F32 || split_in(IN)) {
           const uint4* src = reinterpret_cast<const uint4*>(fbase + (int64_t)i * ld + qc);
           R.v[it][0] = src[0];
           R.v[it][R.NV - 1] = src[1];
@@ -185,7 +187,7 @@ __device__ __forceinline__ void load_input(InRaw<CIP, ROWS, IN, NTHR>& R, const 
           }
           R.v[it][0] = *reinterpret_cast<const uint4*>(hbase + (int64_t)i * ld + ph);
         }
-      } else if (IN == IN_F32S) {
+      } else if (split_in(IN)) {
         float f[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -229,7 +231,8 @@ __device__ __forceinline__ void load_input(InRaw<CIP, ROWS, IN, NTHR>& R, const 
 // IN_F32S writes the high BF16 terms to `tile` and the low terms to `tile_lo`.
 template <int CIP, int ROWS, int RS, int IN, int NTHR = 256, int HALF = 0>
 __device__ __forceinline__ void store_input(uint16_t* tile, const InRaw<CIP, ROWS, IN, NTHR>& R, int q0,
-                                            uint16_t* tile_lo = nullptr) {
+                                            uint16_t* tile_lo = nullptr, const BnP* bn = nullptr, int Ci = 0,
+                                            int Lin = 0) {
   constexpr int ITEMS = InRaw<CIP, ROWS, IN, NTHR>::ITEMS;
   const int qa = q0 - (((q0 % 8) + 8) % 8);
   const int nch = (q0 + ROWS - qa + 7) / 8;
@@ -239,10 +242,19 @@ __device__ __forceinline__ void store_input(uint16_t* tile, const InRaw<CIP, ROW
     const int i = e % CIP, ch = e / CIP;
     if (ch >= nch) continue;
     uint16_t v[8], vl[8];
-    if (IN == IN_F32S) {
+    if (split_in(IN)) {
       const uint4 a = R.v[it][0], c = R.v[it][R.NV - 1];
-      const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+      float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
                           __uint_as_float(c.x), __uint_as_float(c.y), __uint_as_float(c.z), __uint_as_float(c.w)};
+      if (IN == IN_F32A) {  // the padding stays zero
+        const int ic = i < Ci ? i : Ci - 1;
+        const float m = bn->mean[ic], is = bn->invstd[ic], g = bn->gamma[ic], be = bn->beta[ic];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int q = qa + 8 * ch + k;
+          f[k] = i < Ci && q >= 0 && q < Lin ? bn_tanh_one(f[k], m, is, g, be) : 0.0f;
+        }
+      }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         v[k] = bf16_rne(f[k]);
@@ -266,14 +278,14 @@ __device__ __forceinline__ void store_input(uint16_t* tile, const InRaw<CIP, ROW
       const int pr = HALF ? (r & 1) * HALF + (r >> 1) : r;
       if (r >= 0 && r < ROWS) {
         tile[pr * RS + i] = v[k];
-        if (IN == IN_F32S) tile_lo[pr * RS + i] = vl[k];
+        if (split_in(IN)) tile_lo[pr * RS + i] = vl[k];
       }
     }
   }
   constexpr int PZ = HALF ? (ROWS & 1) * HALF + (ROWS >> 1) : ROWS;
   for (int e = threadIdx.x; e < RS; e += NTHR) {
     tile[PZ * RS + e] = 0;
-    if (IN == IN_F32S) tile_lo[PZ * RS + e] = 0;
+    if (split_in(IN)) tile_lo[PZ * RS + e] = 0;
   }
 }
 
@@ -363,7 +375,7 @@ __device__ __forceinline__ void fetch_kstep(u32x4 (&dst)[APT], const u32x4* wp, 
 
 template <int CIP, int MT, int NPH, int KT, int SC, int NTW, int EPI, int IN, bool OUT_F32, bool XS_F32,
           int CSP, int MS, int AM>
-__global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
+__global__ __launch_bounds__(256) void conv_mfma(ConvP p, F32Train tr, int padc, int ncol) {
   static_assert(MT % MS == 0, "the m-split divides the output-channel tiles");
   // AM = 1 (large batches): the block's weight fragments pass through LDS one
   // K step at a time, double-buffered, fetched from L2 while the previous
@@ -381,7 +393,7 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
   // the input tile's LDS is reused for the BF16 output tile [C_out][NPH*TN]
   constexpr int TILE = (ROWS + 1) * RS > 16 * MTB * TNO ? (ROWS + 1) * RS : 16 * MTB * TNO;
   // split operands (IN_F32S): a second tile of low terms, weights read per wave
-  constexpr bool SPL = IN == IN_F32S;
+  constexpr bool SPL = split_in(IN);
   static_assert(!SPL || (AM == 0 && CSP == 0 && OUT_F32), "split operands: FP32-output layers, AM = 0");
   // weights staged in LDS once per block when they fit beside the tile; only
   // then is the next tile prefetched (LDS reads do not wait on global loads)
@@ -395,6 +407,7 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
   __shared__ __attribute__((aligned(16))) uint4 achunk[2 * ACH];
   __shared__ float cst[2][16 * MTB];
   __shared__ float wsum[4];
+  __shared__ double csum[EPI == EPI_STATS ? 4 : 1][16 * MTB][2];
 
   // block j computes output-channel tiles [ms MTB, (ms + 1) MTB), ms = j mod MS,
   // of the column tiles j / MS, j / MS + gridDim.x / MS, ... (gridDim.x is a
@@ -421,7 +434,7 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
     if (EPI == EPI_AFFINE || EPI == EPI_OUT || EPI == EPI_AFFINE_TANH) {
       a = p.scale[oc];
       c = p.shift[oc];
-    } else if (EPI == EPI_RELU || EPI == EPI_BIAS) {
+    } else if (EPI == EPI_RELU || EPI == EPI_BIAS || EPI == EPI_STATS) {
       c = p.bias ? p.bias[oc] : 0.f;
     } else {
       c = p.bias[oc] + p.bs[oc];
@@ -440,7 +453,7 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
   for (int t = bi; t < total; t += tstep) {
     const int b = t / tiles_per;
     const int col0 = (t % tiles_per) * TN;
-    store_input<CIP, ROWS, RS, IN>(tile, raw, SC * col0 - padc, tile_lo);
+    store_input<CIP, ROWS, RS, IN>(tile, raw, SC * col0 - padc, tile_lo, &tr.in.bn, p.Ci, p.Lin);
     if (CSP > 0) store_shortcut<CSP, TN, RSX>(xt, sraw);
     if constexpr (AM == 1) {
       // K step 0's fragments into buffer 0 (piece e = fragment (e >> 6), lane e & 63)
@@ -459,13 +472,13 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
       }
     }
 
-    f32x4 acc[NTW][NPH][MTB];
+    f32x4 acc[NTW][NPH * MTB];
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
       for (int ph = 0; ph < NPH; ++ph)
 #pragma unroll
-        for (int mt = 0; mt < MTB; ++mt) acc[nt][ph][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < MTB; ++mt) acc[nt][ph * MTB + mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     if constexpr (AM == 1) {
       // register ring of AD stages: the fragments of step ks + AD - 1 are
@@ -502,8 +515,8 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
             for (int ph = 0; ph < NPH; ++ph)
 #pragma unroll
               for (int mt = 0; mt < MTB; ++mt)
-                acc[nt][ph][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[ph][mt]),
-                                                                         bb, acc[nt][ph][mt], 0, 0, 0);
+                acc[nt][ph * MTB + mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[ph][mt]),
+                                                                         bb, acc[nt][ph * MTB + mt], 0, 0, 0);
           }
           // step ks + 1 (requested AD - 1 steps ago, ring slot (d + 1) mod AD)
           // to the other LDS buffer; then request step ks + AD into the freed slot
@@ -548,13 +561,13 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
           for (int mt = 0; mt < MTB; ++mt) {
             if constexpr (SPL) {
               // small terms first: lo_w * hi_x + hi_w * lo_x, then hi_w * hi_x
-              acc[nt][ph][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  __builtin_bit_cast(bf16x8, afl[ph][mt]), bb, acc[nt][ph][mt], 0, 0, 0);
-              acc[nt][ph][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  __builtin_bit_cast(bf16x8, af[ph][mt]), bl, acc[nt][ph][mt], 0, 0, 0);
+              acc[nt][ph * MTB + mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, afl[ph][mt]), bb, acc[nt][ph * MTB + mt], 0, 0, 0);
+              acc[nt][ph * MTB + mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, af[ph][mt]), bl, acc[nt][ph * MTB + mt], 0, 0, 0);
             }
-            acc[nt][ph][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, af[ph][mt]), bb, acc[nt][ph][mt], 0, 0, 0);
+            acc[nt][ph * MTB + mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, af[ph][mt]), bb, acc[nt][ph * MTB + mt], 0, 0, 0);
           }
       }
     }
@@ -573,8 +586,8 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
           const bf16x8 bb = __builtin_bit_cast(bf16x8, bv);
 #pragma unroll
           for (int mt = 0; mt < MTB; ++mt)
-            acc[nt][0][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[mt]), bb,
-                                                                     acc[nt][0][mt], 0, 0, 0);
+            acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[mt]), bb,
+                                                                     acc[nt][mt], 0, 0, 0);
         }
       }
     }
@@ -582,6 +595,17 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
     // ---- epilogue
     uint16_t* otile = tile;
     if (OTILE) __syncthreads();  // every wave is done reading the input tile
+    if constexpr (EPI == EPI_STATS) {
+#pragma unroll
+      for (int mt = 0; mt < MTB; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          train_out<MTB, NPH, NTW, EPI>(p, tr, acc, csum[wave][16 * mt + 4 * lg + r], mt, r, o_lo + 16 * mt + 4 * lg + r,
+                                        b, col0 + wave * NTW * 16, ncol, lc);
+      __syncthreads();
+      train_sums<MTB>(csum, tr.partial, o_lo, p.Co, total, t, threadIdx.x);
+      continue;  // one tile per block
+    }
     float gsum = 0.0f;           // EPI_RESID_GAP: this lane's share of sum_o hw[o] y[o][t]
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) {
@@ -597,7 +621,7 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, int padc, int ncol) {
           float v[NPH];
 #pragma unroll
           for (int ph = 0; ph < NPH; ++ph) {
-            const float a = acc[nt][ph][mt][r];
+            const float a = acc[nt][ph * MTB + mt][r];
             if (EPI == EPI_AFFINE || EPI == EPI_OUT) {
               v[ph] = fmaf(a, ka, kb);
             } else if (EPI == EPI_AFFINE_TANH) {
@@ -679,17 +703,17 @@ struct Key {
 
 template <int CIP, int MT, int NPH, int KT, int SC, int EPI, int IN, bool OUT_F32, bool XS_F32, int CSP, int NTW,
           int MS, int AM>
-static hipError_t launch_t(const ConvP& p, const Geo& g, hipStream_t st) {
+static hipError_t launch_t(const ConvP& p, const F32Train& t, const Geo& g, hipStream_t st) {
   constexpr int TN = 64 * NTW, MTB = MT / MS;
   // same test as the kernel's ALDS: persistent grid only when weights fit in LDS
   constexpr int ROWS = SC * (TN - 1) + KT, RS = CIP + 8, KS = (KT * CIP + 31) / 32;
   constexpr int TILE = (ROWS + 1) * RS > 16 * MTB * NPH * TN ? (ROWS + 1) * RS : 16 * MTB * NPH * TN;
-  constexpr bool ALDS = AM == 0 && IN != IN_F32S && 2 * TILE + NPH * MTB * KS * 1024 <= 80 * 1024;
+  constexpr bool ALDS = AM == 0 && !split_in(IN) && 2 * TILE + NPH * MTB * KS * 1024 <= 80 * 1024;
   auto kern = conv_mfma<CIP, MT, NPH, KT, SC, NTW, EPI, IN, OUT_F32, XS_F32, CSP, MS, AM>;
   const int64_t tiles = (int64_t)((g.ncol + TN - 1) / TN) * p.n;
   if (tiles * MS > (int64_t)1 << 30) return hipErrorInvalidValue;
   if (!ALDS) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * MS)), dim3(256), 0, st, p, g.padc, g.ncol);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * MS)), dim3(256), 0, st, p, t, g.padc, g.ncol);
     return hipGetLastError();
   }
   // persistent grid: enough blocks to fill every CU at the kernel's occupancy
@@ -704,7 +728,7 @@ static hipError_t launch_t(const ConvP& p, const Geo& g, hipStream_t st) {
   }
   // a multiple of MS blocks: each channel share walks the same column tiles
   const int blocks = (int)std::min<int64_t>(tiles, std::max(max_blocks / MS, 1)) * MS;
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, st, p, g.padc, g.ncol);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, st, p, t, g.padc, g.ncol);
   return hipGetLastError();
 }
 
@@ -763,7 +787,18 @@ static hipError_t launch_t(const ConvP& p, const Geo& g, hipStream_t st) {
   X(16, 1, 2, 4, 1, EPI_BIAS, IN_F32S, true, false, 0, 2, 1, 0)                  \
   X(8, 1, 2, 4, 1, EPI_BIAS, IN_F32S, true, false, 0, 2, 1, 0)                   \
   X(8, 1, 1, 7, 1, EPI_OUT, IN_F32S, true, false, 0, 2, 1, 0)                    \
-  X(8, 1, 2, 4, 1, EPI_OUT, IN_F32S, true, false, 0, 2, 1, 0)                   
+  X(8, 1, 2, 4, 1, EPI_OUT, IN_F32S, true, false, 0, 2, 1, 0)                    \
+  /* the reference network's: activations taken from z as they are staged,      \
+     statistics in the epilogue */                                              \
+  X(24, 1, 1, 7, 2, EPI_STATS, IN_F32S, true, false, 0, 2, 1, 0)                 \
+  X(8, 1, 1, 7, 2, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                  \
+  X(16, 2, 1, 7, 2, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                 \
+  X(32, 4, 1, 7, 2, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                 \
+  X(64, 2, 2, 4, 1, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                 \
+  X(32, 1, 2, 4, 1, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                 \
+  X(16, 1, 2, 4, 1, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                 \
+  X(8, 1, 2, 4, 1, EPI_STATS, IN_F32A, true, false, 0, 2, 1, 0)                  \
+  X(8, 1, 1, 7, 1, EPI_OUT, IN_F32A, true, false, 0, 2, 1, 0)
 
 // Large layers take the AM = 1 variants where they exist: at least ~4 blocks
 // of 128 columns per CU, or, for layers with C_in x C_out >= 4096, at least
@@ -800,11 +835,15 @@ bool conv_bf16_supported(int Ci, int Co, int k, int stride, bool tr) {
   return false;
 }
 
+int conv_bf16_stats_blocks(int n, int Lout, int k, int s, int pad, bool tr) {
+  return n * ((make_geo(tr, k, s, pad, Lout).ncol + 127) / 128);  // NTW = 2: 128 columns
+}
+
 // The ABI passes: input format through p.x (fp32), p.xh (bf16) or ring
 // (src == SRC_RING), FP32 input split into hi + lo terms when p.wpk_lo (the
 // low weight terms) is set; output fp32 when p.y is set and p.yh is not; residual
 // shortcut input through p.xs (fp32) or p.xsh (bf16) with weights p.wspk.
-hipError_t launch_conv_bf16(const ConvP& p, bool tr, int epi, int src, hipStream_t st) {
+hipError_t launch_conv_bf16(const ConvP& p, bool tr, int epi, int src, hipStream_t st, const F32Train* t) {
   if (p.k != 7 || p.pad != 3) return hipErrorNotSupported;
   const Geo g = make_geo(tr, p.k, p.stride, p.pad, p.Lout);
   Key k;
@@ -814,7 +853,10 @@ hipError_t launch_conv_bf16(const ConvP& p, bool tr, int epi, int src, hipStream
   k.kt = g.kt;
   k.sc = g.sc;
   k.epi = epi;
-  k.in = src == SRC_RING ? IN_RING : (p.xh ? IN_BF16 : (p.wpk_lo ? IN_F32S : IN_F32));
+  const F32Train tt = t ? *t : F32Train{};
+  k.in = src == SRC_RING ? IN_RING : (p.xh ? IN_BF16 : (p.wpk_lo ? (tt.in.bn.mean ? IN_F32A : IN_F32S) : IN_F32));
+  if (epi == EPI_STATS && (!tt.partial || !p.y || (g.nph == 2 && (p.Lout & 1 || reinterpret_cast<uintptr_t>(p.y) & 7))))
+    return hipErrorInvalidValue;
   k.out_f32 = (epi == EPI_OUT || p.yh == nullptr) ? 1 : 0;
   const bool res = epi == EPI_RESID_RELU || epi == EPI_RESID_GAP;
   if (epi == EPI_RESID_GAP) k.out_f32 = 1;
@@ -825,7 +867,7 @@ hipError_t launch_conv_bf16(const ConvP& p, bool tr, int epi, int src, hipStream
 #define GW_LAUNCH(CIP, MT, NPH, KT, SC, EPI, IN, OF, XF, CS, NTW, MS, AM)                        \
   if (k.cip == CIP && k.mt == MT && k.nph == NPH && k.kt == KT && k.sc == SC && k.epi == EPI && \
       k.in == IN && k.out_f32 == (int)OF && k.xs_f32 == (int)XF && k.csp == CS && k.am == AM)   \
-    return launch_t<CIP, MT, NPH, KT, SC, EPI, IN, OF, XF, CS, NTW, MS, AM>(p, g, st);
+    return launch_t<CIP, MT, NPH, KT, SC, EPI, IN, OF, XF, CS, NTW, MS, AM>(p, tt, g, st);
   // the large-batch variant when one exists, else the general one
   k.am = large_batch(p.n, g.ncol, p.Ci, p.Co) ? 1 : 0;
   GW_BF16_VARIANTS(GW_LAUNCH)

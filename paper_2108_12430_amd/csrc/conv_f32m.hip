@@ -21,7 +21,7 @@
 // recomputed and adjoint convolutions of a training step (batch 32 x 21 x
 // 32768) 2090 -> 620 us, the step 2973 -> 1519 us; BBHnet FP32, 64 windows
 // of 2 x 2048 (9.9 GFLOP), 987 -> 147 us a call
-#include "internal.h"
+#include "train_epi.h"
 
 namespace gw {
 
@@ -102,18 +102,22 @@ hipError_t launch_pack_f32m(const F32PackTab& t, hipStream_t st) {
 // consecutive LDS rows.  STEP 2 (the residual shortcut's rows): the even
 // positions of the same loads, q0 a multiple of 8.  Lanes take consecutive
 // positions of one channel group, so the loads are coalesced; vec tells that
-// every row of the input starts 16-byte aligned.
-template <int CIP, int ROWS, int RS, int HALF, int STEP>
-__device__ __forceinline__ void f32m_stage(float* tile, const float* x, int Ci, int Lin, int q0, bool vec, int tid) {
+// every row of the input (and of z2) starts 16-byte aligned.  PRO transforms
+// the samples on the way (never the padding): cb holds the channels' constants
+// in LDS, [6][CIP] (mean, invstd, gamma, beta or gamma invstd, s1, s2), z2 the
+// second operand of PRO_DZ.
+template <int CIP, int ROWS, int RS, int HALF, int STEP, int PRO>
+__device__ __forceinline__ void f32m_stage(float* tile, const float* x, const float* z2, const float* cb, int Ci,
+                                           int Lin, int q0, bool vec, int tid) {
   constexpr int G = CIP / 4;
   constexpr int RPC = 4 / STEP;                         // rows per chunk of four positions
   constexpr int NCH = STEP == 1 ? (ROWS + 3 + 3) / 4 : ROWS / RPC;
   const int qa = q0 & ~3;                               // floor to a multiple of 4 (q0 may be negative)
   const int off = q0 - qa;                              // STEP 2: always 0
-  constexpr int ITEMS = (NCH * G + 255) / 256, BATCH = ITEMS < 4 ? ITEMS : 4;
+  constexpr int ITEMS = (NCH * G + 255) / 256, BM = PRO == PRO_DZ ? 2 : 4, BATCH = ITEMS < BM ? ITEMS : BM;
 #pragma unroll 1
   for (int i0 = 0; i0 < ITEMS; i0 += BATCH) {
-    float4 v[BATCH][4];
+    float4 v[BATCH][4], z[PRO == PRO_DZ ? BATCH : 1][4];
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
       const int e = tid + 256 * (i0 + u), g = e / NCH, ch = e - g * NCH, q = qa + 4 * ch;
@@ -121,15 +125,21 @@ __device__ __forceinline__ void f32m_stage(float* tile, const float* x, int Ci, 
       for (int k = 0; k < 4; ++k) {
         const int i = 4 * g + k;
         v[u][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (PRO == PRO_DZ) z[u][k] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (g < G && i < Ci) {
-          const float* row = x + (int64_t)i * Lin;
+          const int64_t o = (int64_t)i * Lin;
           if (vec && q >= 0 && q + 4 <= Lin) {
-            v[u][k] = *reinterpret_cast<const float4*>(row + q);
+            v[u][k] = *reinterpret_cast<const float4*>(x + o + q);
+            if (PRO == PRO_DZ) z[u][k] = *reinterpret_cast<const float4*>(z2 + o + q);
           } else {
-            if (q >= 0 && q < Lin) v[u][k].x = row[q];
-            if (q + 1 >= 0 && q + 1 < Lin) v[u][k].y = row[q + 1];
-            if (q + 2 >= 0 && q + 2 < Lin) v[u][k].z = row[q + 2];
-            if (q + 3 >= 0 && q + 3 < Lin) v[u][k].w = row[q + 3];
+            float* d = &v[u][k].x;
+            float* dz = &z[PRO == PRO_DZ ? u : 0][k].x;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (q + j >= 0 && q + j < Lin) {
+                d[j] = x[o + q + j];
+                if (PRO == PRO_DZ) dz[j] = z2[o + q + j];
+              }
           }
         }
       }
@@ -138,6 +148,23 @@ __device__ __forceinline__ void f32m_stage(float* tile, const float* x, int Ci, 
     for (int u = 0; u < BATCH; ++u) {
       const int e = tid + 256 * (i0 + u), g = e / NCH, ch = e - g * NCH;
       if (g >= G) continue;
+      if (PRO != PRO_NONE) {
+        const int q = qa + 4 * ch;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float* c = cb + 4 * g + k;
+          const float m = c[0], is = c[CIP], ga = c[2 * CIP], be = c[3 * CIP];
+          float* d = &v[u][k].x;
+          const float* dz = &z[PRO == PRO_DZ ? u : 0][k].x;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const bool live = 4 * g + k < Ci && q + j >= 0 && q + j < Lin;
+            const float t = PRO == PRO_ACT ? bn_tanh_one(d[j], m, is, ga, be)
+                                           : bn_dz_one(d[j], dz[j], m, is, be, c[4 * CIP], c[5 * CIP]);
+            d[j] = live ? t : 0.0f;
+          }
+        }
+      }
       const float4 p[4] = {make_float4(v[u][0].x, v[u][1].x, v[u][2].x, v[u][3].x),
                            make_float4(v[u][0].y, v[u][1].y, v[u][2].y, v[u][3].y),
                            make_float4(v[u][0].z, v[u][1].z, v[u][2].z, v[u][3].z),
@@ -149,6 +176,22 @@ __device__ __forceinline__ void f32m_stage(float* tile, const float* x, int Ci, 
         if (r >= 0 && r < ROWS) *reinterpret_cast<float4*>(tile + pr * RS + 4 * g) = p[k * STEP];
       }
     }
+  }
+}
+
+// The channels' constants of a PRO transform, to LDS
+template <int CIP, int PRO>
+__device__ __forceinline__ void f32m_consts(float* cb, const BnBwdP& q, int Ci, int tid) {
+  if (tid >= CIP) return;
+  const int c = tid < Ci ? tid : Ci - 1;
+  const float is = q.bn.invstd[c], g = q.bn.gamma[c];
+  cb[tid] = q.bn.mean[c];
+  cb[CIP + tid] = is;
+  cb[2 * CIP + tid] = g;
+  cb[3 * CIP + tid] = PRO == PRO_DZ ? g * is : q.bn.beta[c];
+  if (PRO == PRO_DZ) {
+    cb[4 * CIP + tid] = q.sum_dh[c] * q.invN;
+    cb[5 * CIP + tid] = q.sum_dhx[c] * q.invN;
   }
 }
 
@@ -176,8 +219,8 @@ __device__ __forceinline__ void f32m_step(const float4 (&a)[NA], const float4 (&
 // residual stage's 1x1 stride-2 shortcut, added to the same accumulators as
 // further K steps from a second tile staged over the first.  Every output is
 // the same sequence of operations whatever the tile, the split and the batch.
-template <int CIP, int MTB, int NPH, int KT, int SC, int NTW, int EPI, int CSP>
-__global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc, int ncol, int MT) {
+template <int CIP, int MTB, int NPH, int KT, int SC, int NTW, int EPI, int CSP, int PRO>
+__global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, F32Train tr, int padc, int ncol, int MT) {
   using namespace f32m;
   constexpr int TN = 64 * NTW;
   constexpr int ROWS = SC * (TN - 1) + KT;
@@ -190,14 +233,24 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc,
   static_assert(CSP == 0 || (SC == 1 && NPH == 1 && TN * RSX <= TILE), "the shortcut's tile reuses the input's");
   __shared__ __attribute__((aligned(16))) float tile[TILE];
   __shared__ double wsum[4];
+  __shared__ float cb[PRO == PRO_NONE ? 1 : 6 * CIP];
+  constexpr bool SUMS = EPI == EPI_STATS || EPI == EPI_BNBWD;
+  __shared__ double csum[SUMS ? 4 : 1][16 * MTB][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lc = lane & 15, lg = lane >> 4;
   const int MS = MT / MTB, tiles = (ncol + TN - 1) / TN;
   const int ct = (int)(blockIdx.x % tiles), bm = (int)(blockIdx.x / tiles), b = bm / MS, ms = bm - b * MS;
   const int col0 = ct * TN;
   const float* xb = p.x + (int64_t)b * p.Ci * p.Lin;
-  f32m_stage<CIP, ROWS, RS, HALF, 1>(tile, xb, p.Ci, p.Lin, SC * col0 - padc,
-                                     (p.Lin & 3) == 0 && (reinterpret_cast<uintptr_t>(p.x) & 15) == 0, tid);
+  if (PRO != PRO_NONE) {
+    f32m_consts<CIP, PRO>(cb, tr.in, p.Ci, tid);
+    __syncthreads();
+  }
+  f32m_stage<CIP, ROWS, RS, HALF, 1, PRO>(
+      tile, xb, PRO == PRO_DZ ? tr.in.z + (int64_t)b * p.Ci * p.Lin : nullptr, cb, p.Ci, p.Lin, SC * col0 - padc,
+      ((p.Lin & 3) | (reinterpret_cast<uintptr_t>(p.x) & 15) |
+       (PRO == PRO_DZ ? reinterpret_cast<uintptr_t>(tr.in.z) & 15 : 0)) == 0,
+      tid);
   // A fragments of phase ph, channel tile ms MTB + m: two K steps requested ahead
   const float4* wp = reinterpret_cast<const float4*>(fr.w) + (int64_t)ms * MTB * KS * 64 + lane;
   auto frag = [&](int m, int ks) {  // m = ph MTB + channel tile
@@ -265,8 +318,8 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc,
   if constexpr (CSP > 0) {
     __syncthreads();  // every wave is done reading the input tile
     const float* xs = p.xs + (int64_t)b * p.Cs * p.Ls;
-    f32m_stage<CSP, TN, RSX, 0, 2>(tile, xs, p.Cs, p.Ls, 2 * col0,
-                                   (p.Ls & 3) == 0 && (reinterpret_cast<uintptr_t>(p.xs) & 15) == 0, tid);
+    f32m_stage<CSP, TN, RSX, 0, 2, PRO_NONE>(tile, xs, nullptr, nullptr, p.Cs, p.Ls, 2 * col0,
+                                             (p.Ls & 3) == 0 && (reinterpret_cast<uintptr_t>(p.xs) & 15) == 0, tid);
     __syncthreads();
     const float4* sp = reinterpret_cast<const float4*>(fr.ws) + (int64_t)ms * MTB * KSX * 64 + lane;
 #pragma unroll
@@ -290,6 +343,11 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc,
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int o = 16 * (ms * MTB + m) + 4 * lg + r;
+      if constexpr (SUMS) {
+        train_out<MTB, NPH, NTW, EPI>(p, tr, acc, csum[wave][16 * m + 4 * lg + r], m, r, o, b,
+                                           col0 + wave * NTW * 16, ncol, lc);
+        continue;
+      }
       if (o >= p.Co) continue;
       float kb = 0.0f, ka = 1.0f;
       if (EPI == EPI_OUT) {
@@ -339,6 +397,10 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc,
         }
       }
     }
+  if constexpr (SUMS) {
+    __syncthreads();
+    train_sums<MTB>(csum, tr.partial, 16 * ms * MTB, p.Co, (int)(gridDim.x / MS), b * tiles + ct, tid);
+  }
   if constexpr (EPI == EPI_RESID_GAP) {
     // fixed-order reduction: lanes of a wave, then the four waves
     for (int off = 32; off > 0; off >>= 1) gsum += __shfl_down(gsum, off, 64);
@@ -355,40 +417,60 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, int padc,
 // under another's MFMAs.
 #define GW_F32M_SHAPES(X)                                                            \
   /* DeepClean training: forward and adjoint convolutions, output conv */            \
-  X(24, 1, 1, 7, 2, EPI_BIAS, 0, 1, 4)                                               \
-  X(8, 1, 1, 7, 2, EPI_BIAS, 0, 1, 4)                                                \
-  X(16, 2, 1, 7, 2, EPI_BIAS, 0, 2, 2)                                               \
-  X(32, 4, 1, 7, 2, EPI_BIAS, 0, 4, 2)                                               \
-  X(64, 2, 2, 4, 1, EPI_BIAS, 0, 2, 2)                                               \
-  X(32, 1, 2, 4, 1, EPI_BIAS, 0, 1, 4)                                               \
-  X(16, 1, 2, 4, 1, EPI_BIAS, 0, 1, 4)                                               \
-  X(8, 1, 2, 4, 1, EPI_BIAS, 0, 1, 4)                                                \
-  X(4, 1, 1, 7, 1, EPI_BIAS, 0, 1, 4)                                                \
-  X(8, 1, 1, 7, 1, EPI_OUT, 0, 1, 4)                                                 \
+  X(24, 1, 1, 7, 2, EPI_BIAS, 0, 1, 4, PRO_NONE) \
+  X(8, 1, 1, 7, 2, EPI_BIAS, 0, 1, 4, PRO_NONE) \
+  X(16, 2, 1, 7, 2, EPI_BIAS, 0, 2, 2, PRO_NONE) \
+  X(32, 4, 1, 7, 2, EPI_BIAS, 0, 4, 2, PRO_NONE) \
+  X(64, 2, 2, 4, 1, EPI_BIAS, 0, 2, 2, PRO_NONE) \
+  X(32, 1, 2, 4, 1, EPI_BIAS, 0, 1, 4, PRO_NONE) \
+  X(16, 1, 2, 4, 1, EPI_BIAS, 0, 1, 4, PRO_NONE) \
+  X(8, 1, 2, 4, 1, EPI_BIAS, 0, 1, 4, PRO_NONE) \
+  X(4, 1, 1, 7, 1, EPI_BIAS, 0, 1, 4, PRO_NONE) \
+  X(8, 1, 1, 7, 1, EPI_OUT, 0, 1, 4, PRO_NONE) \
   /* BBHnet stages */                                                                \
-  X(4, 2, 1, 7, 2, EPI_RELU, 0, 2, 2)                                                \
-  X(32, 2, 1, 7, 1, EPI_RESID_RELU, 4, 2, 2)                                         \
-  X(32, 4, 1, 7, 2, EPI_RELU, 0, 2, 2)                                               \
-  X(64, 4, 1, 7, 1, EPI_RESID_RELU, 32, 2, 2)                                        \
-  X(64, 8, 1, 7, 2, EPI_RELU, 0, 2, 2)                                               \
-  X(128, 8, 1, 7, 1, EPI_RESID_RELU, 64, 2, 2)                                       \
-  X(128, 8, 1, 7, 1, EPI_RESID_GAP, 64, 2, 2)
+  X(4, 2, 1, 7, 2, EPI_RELU, 0, 2, 2, PRO_NONE) \
+  X(32, 2, 1, 7, 1, EPI_RESID_RELU, 4, 2, 2, PRO_NONE) \
+  X(32, 4, 1, 7, 2, EPI_RELU, 0, 2, 2, PRO_NONE) \
+  X(64, 4, 1, 7, 1, EPI_RESID_RELU, 32, 2, 2, PRO_NONE) \
+  X(64, 8, 1, 7, 2, EPI_RELU, 0, 2, 2, PRO_NONE) \
+  X(128, 8, 1, 7, 1, EPI_RESID_RELU, 64, 2, 2, PRO_NONE) \
+  X(128, 8, 1, 7, 1, EPI_RESID_GAP, 64, 2, 2, PRO_NONE) \
+  /* DeepClean training, the reference network: activations taken from z as   \
+     they are staged, statistics in the epilogue; adjoint convolutions whose  \
+     input is dz and whose output is the next layer's dh */                   \
+  X(24, 1, 1, 7, 2, EPI_STATS, 0, 1, 4, PRO_NONE) \
+  X(8, 1, 1, 7, 2, EPI_STATS, 0, 1, 4, PRO_ACT) \
+  X(16, 2, 1, 7, 2, EPI_STATS, 0, 2, 2, PRO_ACT) \
+  X(32, 4, 1, 7, 2, EPI_STATS, 0, 4, 2, PRO_ACT) \
+  X(64, 2, 2, 4, 1, EPI_STATS, 0, 2, 2, PRO_ACT) \
+  X(32, 1, 2, 4, 1, EPI_STATS, 0, 1, 4, PRO_ACT) \
+  X(16, 1, 2, 4, 1, EPI_STATS, 0, 1, 4, PRO_ACT) \
+  X(8, 1, 2, 4, 1, EPI_STATS, 0, 1, 4, PRO_ACT) \
+  X(8, 1, 1, 7, 1, EPI_OUT, 0, 1, 4, PRO_ACT) \
+  X(4, 1, 1, 7, 1, EPI_BNBWD, 0, 1, 4, PRO_NONE) \
+  X(8, 1, 1, 7, 2, EPI_BNBWD, 0, 1, 4, PRO_DZ) \
+  X(16, 2, 1, 7, 2, EPI_BNBWD, 0, 2, 2, PRO_DZ) \
+  X(32, 4, 1, 7, 2, EPI_BNBWD, 0, 4, 2, PRO_DZ) \
+  X(64, 2, 2, 4, 1, EPI_BNBWD, 0, 2, 2, PRO_DZ) \
+  X(32, 1, 2, 4, 1, EPI_BNBWD, 0, 1, 4, PRO_DZ) \
+  X(16, 1, 2, 4, 1, EPI_BNBWD, 0, 1, 4, PRO_DZ)
 
-template <int CIP, int MT, int NPH, int KT, int SC, int EPI, int CSP, int MTB, int NTW>
-static hipError_t launch_f32m_t(const ConvP& p, const F32Frags& f, const Geo& g, hipStream_t st) {
+template <int CIP, int MT, int NPH, int KT, int SC, int EPI, int CSP, int MTB, int NTW, int PRO>
+static hipError_t launch_f32m_t(const ConvP& p, const F32Frags& f, const F32Train& t, const Geo& g, hipStream_t st) {
   const int64_t blocks = (int64_t)p.n * (MT / MTB) * ((g.ncol + 64 * NTW - 1) / (64 * NTW));
   if (blocks > ((int64_t)1 << 31) - 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((conv_f32m<CIP, MTB, NPH, KT, SC, NTW, EPI, CSP>), dim3((unsigned)blocks), dim3(256), 0, st, p, f,
+  hipLaunchKernelGGL((conv_f32m<CIP, MTB, NPH, KT, SC, NTW, EPI, CSP, PRO>), dim3((unsigned)blocks), dim3(256), 0, st, p, f, t,
                      g.padc, g.ncol, MT);
   return hipGetLastError();
 }
 
-bool conv_f32m_supported(int Ci, int Co, int k, int s, int pad, bool tr, int epi, int Cs) {
+bool conv_f32m_supported(int Ci, int Co, int k, int s, int pad, bool tr, int epi, int Cs, int pro) {
   if (k != 7 || pad != 3 || (tr && s != 1 && s != 2)) return false;
   const Geo g = make_geo(tr, k, s, pad, 1 << 20);
   const int cip = f32m::cip4(Ci), mt = (Co + 15) / 16, csp = Cs ? f32m::cip4(Cs) : 0;
-#define GW_SUP(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW) \
-  if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC && epi == EPI && csp == CSP) return true;
+#define GW_SUP(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW, PRO)                                                         \
+  if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC && epi == EPI && csp == CSP && pro == PRO) \
+    return true;
   GW_F32M_SHAPES(GW_SUP)
 #undef GW_SUP
   return false;
@@ -398,17 +480,37 @@ int conv_f32m_gap_parts(int Co, int Lout) {
   return (Lout + 127) / 128 * ((Co + 15) / 16 / 2);  // the pooled variant's column tiles x channel shares
 }
 
-hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool tr, int epi, hipStream_t st) {
+int conv_f32m_blocks(int Ci, int Co, int n, int Lout, int k, int s, int pad, bool tr) {
+  const Geo g = make_geo(tr, k, s, pad, Lout);
+  const int cip = f32m::cip4(Ci), mt = (Co + 15) / 16;
+#define GW_BLK(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW, PRO)                                       \
+  if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC &&                         \
+      (EPI == EPI_STATS || EPI == EPI_BNBWD))                                                        \
+    return n * ((g.ncol + 64 * NTW - 1) / (64 * NTW));
+  GW_F32M_SHAPES(GW_BLK)
+#undef GW_BLK
+  return -1;
+}
+
+hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool tr, int epi, hipStream_t st, int pro,
+                            const F32Train* t) {
   const Geo g = make_geo(tr, p.k, p.stride, p.pad, p.Lout);
   const bool res = epi == EPI_RESID_RELU || epi == EPI_RESID_GAP;
   if (!f.w || !p.x || (res && (!f.ws || !p.xs || p.Ls != 2 * p.Lout))) return hipErrorInvalidValue;
   if (epi == EPI_RESID_GAP && (!p.hw || !f.gap_part)) return hipErrorInvalidValue;
   if (p.ldx && p.ldx != p.Lin) return hipErrorInvalidValue;
-  if (!conv_f32m_supported(p.Ci, p.Co, p.k, p.stride, p.pad, tr, epi, res ? p.Cs : 0)) return hipErrorNotSupported;
+  const F32Train tt = t ? *t : F32Train{};
+  if ((epi == EPI_STATS || epi == EPI_BNBWD) && (!tt.partial || !p.y)) return hipErrorInvalidValue;
+  // the training epilogues store whole columns of both phases
+  if ((epi == EPI_STATS || epi == EPI_BNBWD) && g.nph == 2 && (p.Lout & 1 || reinterpret_cast<uintptr_t>(p.y) & 7))
+    return hipErrorInvalidValue;
+  if (epi == EPI_BNBWD && (!tt.z || (g.nph == 2 && reinterpret_cast<uintptr_t>(tt.z) & 7))) return hipErrorInvalidValue;
+  if (pro == PRO_DZ && !tt.in.z) return hipErrorInvalidValue;
   const int cip = f32m::cip4(p.Ci), mt = (p.Co + 15) / 16, csp = res ? f32m::cip4(p.Cs) : 0;
-#define GW_LAUNCH(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW)                                                           \
-  if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC && epi == EPI && csp == CSP)                  \
-    return launch_f32m_t<CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW>(p, f, g, st);
+#define GW_LAUNCH(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW, PRO)                                                       \
+  if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC && epi == EPI && csp == CSP && pro == PRO &&  \
+      p.k == 7 && p.pad == 3)                                                                                          \
+    return launch_f32m_t<CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW, PRO>(p, f, tt, g, st);
   GW_F32M_SHAPES(GW_LAUNCH)
 #undef GW_LAUNCH
   return hipErrorNotSupported;

@@ -30,7 +30,39 @@ enum Epi : int {
   EPI_RESID_RELU = 4,   // y = max(acc + bias[o] + shortcut(x_stage)[o], 0)
   EPI_OUT = 5,          // y = acc*scale + shift; noise + causal clean outputs
   EPI_RESID_GAP = 6,    // as EPI_RESID_RELU, then sum_o hw[o] * y per block (pooling head)
+  EPI_STATS = 7,        // as EPI_BIAS, and the block's per-channel sums of (y, y^2)
+  EPI_BNBWD = 8,        // y = acc (1 - a^2) with a = tanh(BN(z)), and the block's sums of (y, y xhat)
 };
+
+// Transform of a convolution's input as its tile is staged (training):
+enum Pro : int {
+  PRO_NONE = 0,
+  PRO_ACT = 1,  // the input is z: take tanh(BN(z))
+  PRO_DZ = 2,   // the input is dh = g (1 - a^2): take the gradient of z
+};
+
+// Batch normalisation with batch statistics, then tanh:
+// a = tanh(gamma xhat + beta), xhat = (z - mean) invstd
+struct BnP {
+  const float* mean;
+  const float* invstd;
+  const float* gamma;
+  const float* beta;
+};
+// Its backward: dz = gamma invstd (dh - sum_dh / N - xhat sum_dhx / N)
+struct BnBwdP {
+  BnP bn;
+  const float* z;
+  const float* sum_dh;   // sum of dh over the batch and time (= dbeta)
+  const float* sum_dhx;  // sum of dh xhat (= dgamma)
+  float invN;
+};
+__device__ __forceinline__ float bn_tanh_one(float z, float m, float is, float g, float be) {
+  return tanhf(fmaf(g, (z - m) * is, be));
+}
+__device__ __forceinline__ float bn_dz_one(float dh, float z, float m, float is, float gis, float s1, float s2) {
+  return gis * (dh - s1 - (z - m) * is * s2);
+}
 
 enum Src : int { SRC_DENSE = 0, SRC_RING = 1 };
 
@@ -238,9 +270,19 @@ bool bbh_fused_supported(int c_in, const int* co, int stages);
 int bbh_fused_tiles(int W);  // blocks (pooled-head shares) per window
 hipError_t launch_bbh_fused(const BbFusedP& p, hipStream_t st);
 
+// training: the input's transform and the epilogue's operands
+struct F32Train {
+  BnBwdP in;        // PRO_ACT (in.bn only), PRO_DZ
+  BnP out;          // EPI_BNBWD: the normalisation of the layer the gradient reaches
+  const float* z;   // EPI_BNBWD: its z
+  double* partial;  // EPI_STATS, EPI_BNBWD: [channel][block][2]
+};
+
 // ---- launchers (defined in the .hip files) ----
 hipError_t launch_conv_fp32(const ConvP& p, bool transposed, int epi, int src, hipStream_t st);
-hipError_t launch_conv_bf16(const ConvP& p, bool transposed, int epi, int src, hipStream_t st);
+hipError_t launch_conv_bf16(const ConvP& p, bool transposed, int epi, int src, hipStream_t st,
+                            const F32Train* t = nullptr);
+int conv_bf16_stats_blocks(int n, int Lout, int k, int s, int pad, bool tr);  // blocks (= partials) of EPI_STATS
 // FP32 matrix-core convolutions (conv_f32m.hip).  Their weight fragments are
 // packed by launch_pack_f32m, one launch for all of a network's layers.
 struct F32Pack {
@@ -262,14 +304,16 @@ size_t f32m_packed_floats(int Ci, int Co, int k, int s, int pad, bool tr);
 hipError_t launch_pack_f32m(const F32PackTab& t, hipStream_t st);
 // whether a compiled kernel takes the layer (Cs: shortcut channels of a
 // residual epilogue, else 0)
-bool conv_f32m_supported(int Ci, int Co, int k, int s, int pad, bool tr, int epi, int Cs);
+bool conv_f32m_supported(int Ci, int Co, int k, int s, int pad, bool tr, int epi, int Cs, int pro = PRO_NONE);
 int conv_f32m_gap_parts(int Co, int Lout);  // GAP partial sums per window (EPI_RESID_GAP)
 struct F32Frags {
   const float* w;    // the convolution's fragments
   const float* ws;   // the 1x1 shortcut's (residual epilogues)
   double* gap_part;  // EPI_RESID_GAP: per-block partial sums of the pooled head
 };
-hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool transposed, int epi, hipStream_t st);
+int conv_f32m_blocks(int Ci, int Co, int n, int Lout, int k, int s, int pad, bool tr);  // blocks (= partials)
+hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool transposed, int epi, hipStream_t st,
+                            int pro = PRO_NONE, const F32Train* t = nullptr);
 bool conv_bf16_supported(int Ci, int Co, int k, int stride, bool transposed);
 int conv_bf16_gap_parts(int Ci, int Co, int Lout, int n);  // GAP partial sums per window (EPI_RESID_GAP), -1 if none
 // Fused DeepClean network (21->8->16->32->64 convs, 64->32->16->8->8
@@ -334,6 +378,34 @@ hipError_t launch_bn_tanh_backward(const float* g, const float* a, const float* 
                                    float* dgamma, float* dbeta, hipStream_t st);
 hipError_t launch_channel_sum(const float* x, int n, int C, int L, double* partial, int nchunk,
                               float* out, hipStream_t st);
+// final sums of the convolutions' statistics (EPI_STATS, EPI_BNBWD partials
+// [C][nblk][2]) over N values per channel
+hipError_t launch_stats_final(const double* partial, int nblk, int C, int64_t N, float* mean, float* invstd,
+                              hipStream_t st);
+hipError_t launch_bnbwd_final(const double* partial, int nblk, int C, int64_t N, float* dgamma, float* dbeta,
+                              hipStream_t st);
+// Weight gradients of the reference network's layer l (wgrad.hip): P and Q
+// raw, as z (activations) or as (dh, z) by the layer's position
+struct Wg2Args {
+  const float* p;
+  const float* q;
+  BnBwdP pbn, qbn;
+  int n, Lp, Lq;
+  float* partial;  // wgrad2_partial_floats
+  float* dw;
+};
+struct Wg2Red {
+  const float* partial;
+  float* dw;
+  int nw, G, blocks;
+};
+struct Wg2Tab {
+  int n;
+  Wg2Red e[9];
+};
+size_t wgrad2_partial_floats(int l, int n, int Lp);
+hipError_t launch_wgrad2(int l, const Wg2Args& a, Wg2Red* red, hipStream_t st);
+hipError_t launch_wgrad2_reduce(const Wg2Tab& t, hipStream_t st);
 size_t wgrad_scratch_bytes(int n, int Lp, int nw);
 // LDS per block: 4*(Ca*64 + Cc*(stride*63 + k)) bytes, must be <= 64 KiB.
 hipError_t launch_wgrad(const float* P, int Ca, int Lp, const float* Q, int Cc, int Lq, int n,

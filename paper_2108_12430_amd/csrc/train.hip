@@ -170,6 +170,18 @@ hipError_t launch_bn_stats(const float* z, int n, int C, int L, double* partial,
   return hipGetLastError();
 }
 
+hipError_t launch_stats_final(const double* partial, int nblk, int C, int64_t N, float* mean, float* invstd,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(chan_final<R_STATS>, dim3(C), dim3(256), 0, st, partial, nblk, N, mean, invstd);
+  return hipGetLastError();
+}
+
+hipError_t launch_bnbwd_final(const double* partial, int nblk, int C, int64_t N, float* dgamma, float* dbeta,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(chan_final<R_BNBWD>, dim3(C), dim3(256), 0, st, partial, nblk, N, dbeta, dgamma);
+  return hipGetLastError();
+}
+
 hipError_t launch_channel_sum(const float* x, int n, int C, int L, double* partial, int nchunk,
                               float* out, hipStream_t st) {
   RedP p{};

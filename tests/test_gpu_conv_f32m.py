@@ -35,6 +35,15 @@ def test_bbhnet_fp32_tile_edges(n, L):
     assert np.array_equal(m.forward(x=off).cpu().numpy(), got)
 
 
+def train(m, x, dn, flags, precision):
+    n, W = dn.shape
+    noise = torch.empty((n, W), device=DEV)
+    ws = m.forward(x=x, noise=noise, flags=flags, precision=precision)
+    dp = torch.empty_like(m.params)
+    m.backward(x, dn, ws, dp, flags=flags, precision=precision)
+    return noise.cpu().numpy(), dp.cpu().numpy()
+
+
 # W / 16 = 2, 3, 33, 129: every layer's length straddles its tile differently
 # (W = 16 is left out: batch statistics over two or three values amplify
 # rounding by 1 / (their difference), far past any FP32 bound)
@@ -50,9 +59,26 @@ def test_training_fp32_tile_edges(n, q):
     en = ref.deepclean_forward(params, x, layers, train=True)
     eg = ref.deepclean_grad(params, x, dn, layers)
     for flags in (gs.TRAIN, gs.TRAIN | gs.RECOMPUTE):
-        noise = torch.empty((n, W), device=DEV)
-        ws = m.forward(x=xt, noise=noise, flags=flags)
-        dp = torch.empty_like(m.params)
-        m.backward(xt, dnt, ws, dp, flags=flags)
-        assert rel(noise.cpu().numpy(), en) <= BOUND
-        assert rel(dp.cpu().numpy(), eg) <= BOUND
+        noise, dp = train(m, xt, dnt, flags, gs.FP32)
+        assert rel(noise, en) <= BOUND
+        assert rel(dp, eg) <= BOUND
+        # split-BF16 forward: its stated bound
+        noise, dp = train(m, xt, dnt, flags, gs.BF16)
+        assert rel(noise, en) <= 2e-2
+        assert rel(dp, eg) <= 2e-2
+
+
+def test_training_unaligned_windows_bitwise():
+    """Windows at an address 4 bytes past 16-byte alignment train to the same bits."""
+    m = gs.DeepClean(torch.from_numpy(synth.deepclean_params(2)).to(DEV), synth.deepclean_layers())
+    x = torch.from_numpy(synth.gaussian(11, (2, 21, 528))).to(DEV)
+    dn = torch.from_numpy(synth.gaussian(12, (2, 528))).to(DEV)
+    shifted = []
+    for t in (x, dn):
+        buf = torch.empty(t.numel() + 1, device=DEV)
+        buf[1:] = t.reshape(-1)
+        shifted.append(buf[1:].view(t.shape))
+    for precision in (gs.FP32, gs.BF16):
+        a = train(m, x, dn, gs.TRAIN | gs.RECOMPUTE, precision)
+        b = train(m, *shifted, gs.TRAIN | gs.RECOMPUTE, precision)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
