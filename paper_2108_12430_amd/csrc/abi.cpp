@@ -1612,6 +1612,12 @@ extern "C" int deepclean_forward_cached(const gw_model* m, gw_pool* pool, const 
     }
   }
   const int L = (int)m->layers.size();
+  int tiles = 0, smax = 0;
+  if (m->fused)
+    for (const auto& it : items) {
+      tiles = std::max(tiles, gw::cache_band_tiles(it.shift, W));
+      smax = std::max(smax, it.s);
+    }
   const void* dev = nullptr;
   StageGuard guard;
   CHK(pool->stager.stage_raw(items.data(), items.size() * sizeof(gw::CacheItem), st, &dev, &guard));
@@ -1626,7 +1632,10 @@ extern "C" int deepclean_forward_cached(const gw_model* m, gw_pool* pool, const 
     P.scale[l] = reinterpret_cast<const float*>(m->packed + ly.scale);
     P.shift[l] = reinterpret_cast<const float*>(m->packed + ly.shift);
   }
-  LAUNCH("cache_forward", st, gw::launch_cache_forward(dit, n, pool->arena, P, strain, noise, clean, st));
+  if (m->fused)
+    LAUNCH("cache_forward", st, gw::launch_cache_band(dit, n, pool->arena, P, tiles, smax, strain, noise, clean, st));
+  else
+    LAUNCH("cache_forward", st, gw::launch_cache_forward(dit, n, pool->arena, P, strain, noise, clean, st));
   // every cache now holds the current window
   for (int i = 0; i < n; ++i) {
     auto& sl = pool->slots[slots[i]];

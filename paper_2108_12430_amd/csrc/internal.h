@@ -250,6 +250,14 @@ inline bool cache_layer_fits(const CacheGeo& g) {
 hipError_t launch_cache_forward(const CacheItem* items, int n, const void* arena, const CacheLayerP& P,
                                 const float* strain, float* noise, float* clean, hipStream_t st);
 
+// The same for the reference network, from the receptive fields of the outputs
+// that change (dc_band.hip; of the cache only the noise ring is used).  tiles:
+// the most cache_band_tiles(shift, W) of the items, smax: the longest clean
+// span.
+int cache_band_tiles(int shift, int W);
+hipError_t launch_cache_band(const CacheItem* items, int n, const void* arena, const CacheLayerP& P, int tiles, int smax,
+                             const float* strain, float* noise, float* clean, hipStream_t st);
+
 // ---- fused BBHnet (reference shape: 2 -> 32 -> 64 -> 128, k7) ----
 struct BbFusedP {
   const void* arena;      // pool arena (ring input) or null
