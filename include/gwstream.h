@@ -269,17 +269,16 @@ int deepclean_forward(const gw_model* model, gw_pool* pool, const int32_t* slots
  * strides, samples, offsets) followed by deepclean_forward(model, pool,
  * slots, NULL, n, W, strides, delays, strain, noise, clean, precision, flags,
  * ws, ws_bytes), with the same arguments, results and errors as those two
- * calls: each stream's new samples are also its clean stride.  For BF16
- * inference on the fused network (precision GW_BF16, flags 0; noise, clean
- * or both as for deepclean_forward) it is one launch with one staged item
- * table: each tile
- * writes the new samples its input rows hold to the ring and its shadow
- * (rounded as snapshot_update rounds them) before reading its rows, and no
- * tile reads the ring positions those samples replace; outputs, rings and
- * host state are bitwise those of the two calls.  Otherwise it makes the two
- * calls.  On the one-launch path every argument is checked before any
- * launch; on the other, an error from the forward's checks comes after the
- * update has been enqueued.
+ * calls: each stream's new samples are also its clean stride.  For inference
+ * on the fused network (any precision; flags 0, or GW_CAUSAL without delays)
+ * it is one launch: each tile writes the new samples its input rows hold to
+ * the ring and its shadow (rounded as snapshot_update rounds them) before
+ * reading its rows, and no tile reads the ring positions those samples
+ * replace; outputs, rings and host state are bitwise those of the two calls.
+ * Otherwise it makes the two calls.  For precision GW_BF16 with flags 0 every
+ * argument is checked before any launch and a refused call changes nothing;
+ * otherwise an error from the forward's checks comes after the update has
+ * been enqueued.
  */
 int deepclean_update_forward(const gw_model* model, gw_pool* pool, int32_t n, const int32_t* slots,
                              const int32_t* strides, const float* samples, const int64_t* offsets, int32_t W,

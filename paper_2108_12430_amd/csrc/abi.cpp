@@ -44,8 +44,9 @@ inline hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 struct Stager;
 
-// Records a staged table's reuse event when the entry point that staged it
-// returns, i.e. after every launch that reads the table has been enqueued.
+// Records a staging slot's event when the entry point that took the slot
+// returns, however it returns: after the table's copy and every launch that
+// reads it have been enqueued.
 struct StageGuard {
   Stager* s = nullptr;
   int k = -1;
@@ -101,22 +102,26 @@ struct Stager {
     *out = reinterpret_cast<const Item*>(d);
     return GW_OK;
   }
-  // Any table of at most cap * sizeof(Item) bytes (same slots and reuse rule).
-  int stage_raw(const void* data, size_t bytes, hipStream_t st, const void** out, StageGuard* guard) {
-    if (bytes > (size_t)cap * sizeof(Item)) return fail(GW_EINVAL, "too many items in one call");
+  // A slot for a call whose table rides in its kernel arguments: only the
+  // slot's event is used (the call's completion).
+  int reserve(hipStream_t st, StageGuard* guard) {
     const int k = next;
     next = (next + 1) % K;
     if (used[k]) HIPCHK(hipEventSynchronize(ev[k]));
     ++gen[k];
-    std::memcpy(host + (size_t)k * cap, data, bytes);
-    HIPCHK(hipMemcpyAsync(dev + (size_t)k * cap, host + (size_t)k * cap, bytes, hipMemcpyHostToDevice, st));
-    // provisional record (covers the copy if the call ends before its launches);
-    // the guard records again after the launches
-    HIPCHK(hipEventRecord(ev[k], st));
     used[k] = true;
     guard->s = this;
     guard->k = k;
     guard->st = st;
+    return GW_OK;
+  }
+  // Any table of at most cap * sizeof(Item) bytes (same slots and reuse rule).
+  int stage_raw(const void* data, size_t bytes, hipStream_t st, const void** out, StageGuard* guard) {
+    if (bytes > (size_t)cap * sizeof(Item)) return fail(GW_EINVAL, "too many items in one call");
+    CHK(reserve(st, guard));
+    const int k = guard->k;
+    std::memcpy(host + (size_t)k * cap, data, bytes);
+    HIPCHK(hipMemcpyAsync(dev + (size_t)k * cap, host + (size_t)k * cap, bytes, hipMemcpyHostToDevice, st));
     *out = dev + (size_t)k * cap;
     return GW_OK;
   }
@@ -1171,8 +1176,8 @@ static gw::BnP bn_params(const gw_model* m, const DcWs& w, const char* ws, int l
           m->params + m->layers[l].g, m->params + m->layers[l].be};
 }
 
-// deepclean_forward; with upd set (fused BF16 inference on pool input only),
-// the launch also performs the snapshot update whose new samples sit at
+// deepclean_forward; with upd set (the fused inference kernels on pool input
+// only), the launch also performs the snapshot update whose new samples sit at
 // upd + upd_off[i]: the slots' host heads have already been advanced, so the
 // items carry the heads after the update
 static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, const float* x, int32_t n, int32_t W,
@@ -1261,13 +1266,20 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
       }
     }
   }
+  const bool f16 = precision == GW_FP16;
+  const bool one_kernel = m->fused && !(flags & (GW_TRAIN | GW_LAYERWISE));
+  // the fused kernels take the items of a small call as an argument
+  const bool in_args = one_kernel && n <= gw::kItemArgs;
   const Item* dev_items = nullptr;
   StageGuard guard;
   if (need_items) {
     if (pool) {
-      CHK(pool->stager.stage(items, st, &dev_items, &guard));
+      if (in_args)
+        CHK(pool->stager.reserve(st, &guard));
+      else
+        CHK(pool->stager.stage(items, st, &dev_items, &guard));
       pool->mark_used(slots, n, guard);
-    } else {
+    } else if (!in_args) {
       CHK(const_cast<gw_model*>(m)->stager.stage(items, st, &dev_items, &guard));
     }
   }
@@ -1275,56 +1287,48 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   char* wsb = reinterpret_cast<char*>(ws);
   const int L = (int)m->layers.size();
   const void* arena = pool ? pool->arena : nullptr;
-  const bool f16 = precision == GW_FP16;
-  if (!(flags & GW_TRAIN) && (precision == GW_BF16 || f16) && m->fused && !(flags & GW_LAYERWISE)) {
+  if (one_kernel) {
     // whole network in one kernel, activations on chip
-    gw::ConvP p{};
-    p.n = n;
-    p.items = dev_items;
-    p.arena = arena;
-    p.x = x ? x + a_band : nullptr;
-    p.ldx = x ? W : 0;
-    p.noise = noise;
-    p.clean = clean;
-    p.strain = strain;
-    p.upd = upd;
+    gw::DcIn io{};
+    io.items = dev_items;
+    io.arena = arena;
+    io.x = x ? x + a_band : nullptr;
+    io.ldx = x ? W : 0;
+    io.noise = noise;
+    io.clean = clean;
+    io.strain = strain;
+    io.upd = upd;
+    io.Lin = Wb;
+    io.causal = flags & GW_CAUSAL ? 1 : 0;
+    int64_t t256 = (int64_t)n * ((Wb + 255) / 256);
+    if (io.causal) {
+      // tiles count from the band's end; those outside an item's span are left out
+      t256 = 0;
+      for (int i = 0; i < n; ++i) t256 += (items[i].s + items[i].delay + 255) / 256 - items[i].delay / 256;
+    }
+    io.tiles256 = (int)std::min<int64_t>(t256, 1 << 30);
+    gw::ItemArgs args;
+    if (need_items && in_args) std::memcpy(args.e, items.data(), n * sizeof(Item));
     const uint16_t* wpk[9];
+    const float* wpk32[9];
     const float* sc[9];
     const float* sh[9];
     for (int l = 0; l < 9; ++l) {
       const LayerD& ly = m->layers[l];
       const size_t off = gw::dc_fused_special(l) ? (f16 ? ly.wfs16 : ly.wfs) : (f16 ? ly.wf16 : ly.wbf);
       wpk[l] = reinterpret_cast<const uint16_t*>(m->packed + off);
-      sc[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].scale);
-      sh[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].shift);
+      wpk32[l] = reinterpret_cast<const float*>(m->packed + ly.wf32);
+      sc[l] = reinterpret_cast<const float*>(m->packed + ly.scale);
+      sh[l] = reinterpret_cast<const float*>(m->packed + ly.shift);
     }
-    LAUNCH(f16 ? "dc_fused_f16" : "dc_fused_bf16", st,
-           gw::launch_dc_fused_bf16(p, wpk, sc, sh, Wb, pool != nullptr, m->cu_budget, st, f16, upd != nullptr));
+    if (precision == GW_FP32)
+      LAUNCH("dc_f32", st, gw::launch_dc_f32(io, args, wpk32, sc, sh, n, pool != nullptr, m->cu_budget, st));
+    else
+      LAUNCH(f16 ? "dc_fused_f16" : "dc_fused_bf16", st,
+             gw::launch_dc_fused_bf16(io, args, wpk, sc, sh, n, pool != nullptr, m->cu_budget, st, f16));
     return GW_OK;
   }
-  if (!(flags & GW_TRAIN) && precision == GW_FP32 && m->fused && !(flags & GW_LAYERWISE)) {
-    // the same in FP32
-    gw::ConvP p{};
-    p.n = n;
-    p.items = dev_items;
-    p.arena = arena;
-    p.x = x ? x + a_band : nullptr;
-    p.ldx = x ? W : 0;
-    p.noise = noise;
-    p.clean = clean;
-    p.strain = strain;
-    const float* wpk[9];
-    const float* sc[9];
-    const float* sh[9];
-    for (int l = 0; l < 9; ++l) {
-      wpk[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].wf32);
-      sc[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].scale);
-      sh[l] = reinterpret_cast<const float*>(m->packed + m->layers[l].shift);
-    }
-    LAUNCH("dc_f32", st, gw::launch_dc_f32(p, wpk, sc, sh, Wb, pool != nullptr, m->cu_budget, st));
-    return GW_OK;
-  }
-  if (upd) return fail(GW_EINVAL, "the fused update runs on the fused BF16 inference path only");
+  if (upd) return fail(GW_EINVAL, "the fused update runs on the fused inference path only");
   if (!(flags & GW_TRAIN)) {
     const float* in = x ? x + a_band : nullptr;
     for (int l = 0; l < L; ++l) {
@@ -1498,7 +1502,13 @@ extern "C" int deepclean_update_forward(const gw_model* m, gw_pool* pool, int32_
   if (n == 0) return GW_OK;
   if (n < 0 || n > pool->max_items) return fail(GW_EINVAL, "n out of range");
   if (!slots || !strides || !samples || !offsets) return fail(GW_EINVAL, "null argument");
-  const bool one_launch = m->kind == GW_MODEL_DEEPCLEAN && precision == GW_BF16 && m->fused && flags == 0;
+  // GW_CAUSAL computes only the tiles of the clean spans, which hold every new
+  // sample unless a span is delayed
+  bool delayed = false;
+  for (int i = 0; delays && i < n; ++i) delayed = delayed || delays[i] != 0;
+  const bool one_launch = m->kind == GW_MODEL_DEEPCLEAN && m->fused &&
+                          (flags == 0 || (flags == GW_CAUSAL && !delayed)) &&
+                          (precision == GW_BF16 || precision == GW_FP16 || precision == GW_FP32);
   if (!one_launch) {
     CHK(snapshot_update(pool, n, slots, strides, samples, offsets, hip_stream));
     return deepclean_forward(m, pool, slots, nullptr, n, W, strides, delays, strain, noise, clean, precision, flags,
@@ -1524,12 +1534,20 @@ extern "C" int deepclean_update_forward(const gw_model* m, gw_pool* pool, int32_
   }
   const int rc = dc_forward(m, pool, slots, nullptr, n, W, strides, delays, strain, noise, clean, precision, flags,
                             ws, ws_bytes, S(hip_stream), samples, offsets);
-  if (rc != GW_OK)
+  if (rc != GW_OK) {
     for (int i = 0; i < n; ++i) {
       auto& sl = pool->slots[slots[i]];
       sl.head = prev[i].first;
       sl.n_seen = prev[i].second;
     }
+    // outside BF16 without flags, a call that the forward refuses has made
+    // its update (the error is the forward's)
+    if (rc != GW_EHIP && !(precision == GW_BF16 && flags == 0)) {
+      const std::string why = g_err;
+      CHK(snapshot_update(pool, n, slots, strides, samples, offsets, hip_stream));
+      g_err = why;
+    }
+  }
   return rc;
 }
 

@@ -897,61 +897,28 @@ namespace gw {
 // ===========================================================================
 namespace fused {
 
-#ifndef GW_FUSED_T
-#define GW_FUSED_T 768
-#endif
-constexpr int T = GW_FUSED_T;  // output samples per block (a multiple of 256)
-static_assert(T % 256 == 0, "tile must hold whole 16-column MFMA tiles at every layer");
-#ifndef GW_FUSED_WAVES
-#define GW_FUSED_WAVES 12
-#endif
-constexpr int NW = GW_FUSED_WAVES;  // waves per block
-constexpr int NTHR = 64 * NW;
 constexpr int C[10] = {21, 8, 16, 32, 64, 32, 16, 8, 8, 1};
 constexpr int cip(int c) { return (c + 7) / 8 * 8; }
 // LDS row stride (elements): an odd multiple of 8, so 16 lanes reading 16 B
 // from 16 consecutive rows hit 16 distinct 16 B bank groups
 constexpr int rs(int c) { return (cip(c) / 8) % 2 ? cip(c) : cip(c) + 8; }
-// row counts of the layer outputs a1..a8 (and x); row 0 of a_l sits at
-// (tile start scaled to layer l) + LO[l]
+// row 0 of a_l (and x) sits at (tile start scaled to layer l) + LO[l]
 constexpr int LO[10] = {-93, -45, -21, -9, -3, -3, -3, -3, -3, 0};
-constexpr int NR[10] = {T + 187, T / 2 + 91, T / 4 + 43, T / 8 + 19, T / 16 + 7,
-                        T / 8 + 7, T / 4 + 7, T / 2 + 7, T + 6, T};
-// output columns of layer l: one per output row for the stride-2 convs L1..L3;
-// two output rows (2c, 2c + 1) per column for the first conv, whose MFMA
-// rows stack the two output times; one input-aligned position per column
-// for the transposed layers (rows 2c - 1 and 2c); one per row for the output
-// conv
-constexpr int NCOL[9] = {(NR[1] + 1) / 2, NR[2], NR[3], NR[4], T / 16 + 4, T / 8 + 4, T / 4 + 4, T / 2 + 4, T};
-constexpr int NT(int l) { return (NCOL[l] + 15) / 16; }
+constexpr int mx(int a, int b) { return a > b ? a : b; }
+constexpr int mn(int a, int b) { return a < b ? a : b; }
+constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
 constexpr int SC(int l) { return l < 4 ? 2 : 1; }
 // input rows between adjacent columns, and input rows one column reads
 constexpr int CSTEP(int l) { return l == 0 ? 4 : SC(l); }
 constexpr int KT(int l) { return l == 0 ? 9 : l < 4 || l == 8 ? 7 : 4; }
-// rows of layer l's input buffer that its (padded) columns may read
-constexpr int rows_read(int l) { return CSTEP(l) * (16 * NT(l) - 1) + KT(l); }
-constexpr int cap0(int l) { return (rows_read(l) > NR[l] ? rows_read(l) : NR[l]); }
 // inputs read with a column step of 2 or 4 rows are stored split by row
 // residue (row r at (r mod F) PART + r / F), so adjacent columns read
 // adjacent LDS rows; the others row by row
 constexpr int SPLITF(int l) { return l < 9 && CSTEP(l) > 1 ? CSTEP(l) : 1; }
-constexpr int PART(int l) { return (cap0(l) + SPLITF(l) - 1) / SPLITF(l); }
 // the output conv's input rows are stored with one spare row after every 16
 // (row r at r + r / 16): its A-operand reads take rows 16 apart in 16 lanes,
 // which the spare rows spread over distinct bank groups
 constexpr int prow8(int r) { return r + (r >> 4); }
-// LDS row of row r of layer l's input buffer
-__host__ __device__ constexpr int phys(int l, int r) {
-  return SPLITF(l) > 1 ? (r % SPLITF(l)) * PART(l) + r / SPLITF(l) : l == 8 ? prow8(r) : r;
-}
-constexpr int cap(int l) {  // LDS rows of layer l's input buffer
-  return SPLITF(l) > 1 ? SPLITF(l) * PART(l) : l == 8 ? prow8(cap0(l) - 1) + 1 : cap0(l);
-}
-constexpr int mx(int a, int b) { return a > b ? a : b; }
-// ping-pong: inputs of layers 0,2,4,6,8 in buffer A, of layers 1,3,5,7 in B
-constexpr int BUFA = mx(mx(mx(cap(0) * rs(C[0]), cap(2) * rs(C[2])), mx(cap(4) * rs(C[4]), cap(6) * rs(C[6]))),
-                        cap(8) * rs(C[8]));
-constexpr int BUFB = mx(mx(cap(1) * rs(C[1]), cap(3) * rs(C[3])), mx(cap(5) * rs(C[5]), cap(7) * rs(C[7])));
 constexpr int MT(int l) { return (C[l + 1] + 15) / 16; }
 constexpr int NPH(int l) { return l >= 4 && l < 8 ? 2 : 1; }
 constexpr int KS(int l) { return (KT(l) * cip(C[l]) + 31) / 32; }
@@ -967,32 +934,9 @@ constexpr int ROFF(int l) { return l == 0 ? 0 : -1; }
 // d - 3], B[(d, i)][n] = w[i][d - n] (zero outside the kernel), K = 24
 // offsets x 8 channels; one MFMA tile covers 256 outputs
 constexpr bool TOEP(int l) { return l == 8; }
-constexpr int TB = T / 256;  // 256-output tiles of the output conv
 constexpr int KS8 = 6;       // K steps of the Toeplitz product (offsets 22, 23 carry zero weights)
 // (phase, channel tile) pairs per column tile
 constexpr int QP(int l) { return STACK(l) ? 1 : NPH(l) * MT(l); }
-
-}  // namespace fused
-
-struct FusedP {
-  const uint16_t* wpk[9];
-  const float* scale[9];
-  const float* shift[9];
-  int L[10];  // signal length of x and of each layer output (window W, W/2, ...)
-};
-
-// tanh for the fused epilogue from z = 2 x log2(e) (the factor is folded into
-// the BN scale and shift): 1 - 2 / (2^z + 1) on the hardware exp2 and
-// reciprocal.  2^z overflows to +inf for large z, giving exactly 1; relative
-// error is far below the BF16 rounding of the stored activations.
-__device__ __forceinline__ float tanh_scaled(float z) {
-  return fmaf(-2.0f, __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(z) + 1.0f), 1.0f);
-}
-constexpr float kTwoLog2e = 2.8853900817779268f;
-
-namespace fused {
-constexpr int cdiv(int a, int b) { return (a + b - 1) / b; }
-constexpr int mn(int a, int b) { return a < b ? a : b; }
 // 8-channel layers: the valid accumulator rows sit in lanes 0..31, so two
 // column tiles share one epilogue pass (lanes 32..63 take the second tile)
 constexpr bool COMPACT(int l) { return l < 8 && !STACK(l) && MT(l) == 1 && cip(C[l + 1]) == 8; }
@@ -1005,33 +949,95 @@ constexpr int FMAX = 8;
 constexpr int SPL(int l) {
   return COMPACT(l) || STACK(l) || QP(l) * KS(l) <= FMAX ? 1 : QP(l) / 2 * KS(l) <= FMAX && QP(l) % 2 == 0 ? 2 : 4;
 }
-// column tiles per work unit: enough that every layer is one round of at
-// most NW units (at most 4)
-constexpr int NTC(int l) {
-  return COMPACT(l) ? mn(4, 2 * cdiv(NT(l), 2 * NW)) : mn(4, cdiv(NT(l), NW / SPL(l)));
-}
-constexpr int NG(int l) { return cdiv(NT(l), NTC(l)); }
-constexpr int NU(int l) { return TOEP(l) ? TB : NG(l) * SPL(l); }              // units of layer l
 constexpr int NF(int l) { return TOEP(l) ? KS8 : QP(l) / SPL(l) * KS(l); }   // fragments per unit
 // fragments requested during the previous layer: at most 7, so that the
 // request fits beside that layer's epilogue without spilling; a unit's
 // remaining fragment (the last its MFMAs read) is requested as it starts
 constexpr int PF(int l) { return NF(l) < 7 ? NF(l) : 7; }
-// per-layer table of B-fragment row offsets: KOFF[l][lg][ks] (elements) for
-// the 8 channels at kappa = 32 ks + 8 lg, i.e. tap jj = kappa / C_in and
-// channel i0 = kappa mod C_in; taps past the kernel (zero weights) read tap
-// K-1 instead, a row that holds finite values
 constexpr int KSMAX = 8;
-__host__ __device__ constexpr int koff(int l, int lg, int ks) {
-  const int kappa = 32 * ks + 8 * lg, jj = kappa / cip(C[l]), i0 = kappa - jj * cip(C[l]);
-  const int j = jj < KT(l) ? jj : KT(l) - 1;
-  return phys(l, j) * rs(C[l]) + i0;
-}
-constexpr bool units_fit(int l) {
-  return l == 9 || (NU(l) <= NW && NF(l) <= FMAX && QP(l) % SPL(l) == 0 && units_fit(l + 1));
-}
-static_assert(units_fit(0), "every layer is one round of units of at most FMAX fragments");
+constexpr int XG = cip(C[0]) / 4;  // channel groups of x
+
+// The geometry of a tile of T_ output samples (a multiple of 256) computed by
+// a block of NW_ waves.
+template <int T_, int NW_>
+struct Geom {
+  static constexpr int T = T_, NW = NW_, NTHR = 64 * NW_;
+  static_assert(T % 256 == 0, "tile must hold whole 16-column MFMA tiles at every layer");
+  // row counts of x and of the layer outputs a1..a8
+  static constexpr int NR(int l) {
+    return l == 0 ? T + 187 : l == 1 ? T / 2 + 91 : l == 2 ? T / 4 + 43 : l == 3 ? T / 8 + 19 : l == 4 ? T / 16 + 7
+         : l == 5 ? T / 8 + 7 : l == 6 ? T / 4 + 7 : l == 7 ? T / 2 + 7 : l == 8 ? T + 6 : T;
+  }
+  // output columns of layer l: one per output row for the stride-2 convs L1..L3;
+  // two output rows (2c, 2c + 1) per column for the first conv, whose MFMA
+  // rows stack the two output times; one input-aligned position per column
+  // for the transposed layers (rows 2c - 1 and 2c); one per row for the output
+  // conv
+  static constexpr int NCOL(int l) {
+    return l == 0 ? (NR(1) + 1) / 2 : l < 4 ? NR(l + 1) : l == 4 ? T / 16 + 4 : l == 5 ? T / 8 + 4
+         : l == 6 ? T / 4 + 4 : l == 7 ? T / 2 + 4 : T;
+  }
+  static constexpr int NT(int l) { return (NCOL(l) + 15) / 16; }
+  // rows of layer l's input buffer that its (padded) columns may read
+  static constexpr int rows_read(int l) { return CSTEP(l) * (16 * NT(l) - 1) + KT(l); }
+  static constexpr int cap0(int l) { return (rows_read(l) > NR(l) ? rows_read(l) : NR(l)); }
+  static constexpr int PART(int l) { return (cap0(l) + SPLITF(l) - 1) / SPLITF(l); }
+  // LDS row of row r of layer l's input buffer
+  __host__ __device__ static constexpr int phys(int l, int r) {
+    return SPLITF(l) > 1 ? (r % SPLITF(l)) * PART(l) + r / SPLITF(l) : l == 8 ? prow8(r) : r;
+  }
+  static constexpr int cap(int l) {  // LDS rows of layer l's input buffer
+    return SPLITF(l) > 1 ? SPLITF(l) * PART(l) : l == 8 ? prow8(cap0(l) - 1) + 1 : cap0(l);
+  }
+  // ping-pong: inputs of layers 0,2,4,6,8 in buffer A, of layers 1,3,5,7 in B
+  static constexpr int BUFA = mx(mx(mx(cap(0) * rs(C[0]), cap(2) * rs(C[2])), mx(cap(4) * rs(C[4]), cap(6) * rs(C[6]))),
+                                 cap(8) * rs(C[8]));
+  static constexpr int BUFB = mx(mx(cap(1) * rs(C[1]), cap(3) * rs(C[3])), mx(cap(5) * rs(C[5]), cap(7) * rs(C[7])));
+  static constexpr int TB = T / 256;  // 256-output tiles of the output conv
+  // column tiles per work unit: enough that every layer is one round of at
+  // most NW units (at most 4)
+  static constexpr int NTC(int l) {
+    return COMPACT(l) ? mn(4, 2 * cdiv(NT(l), 2 * NW)) : mn(4, cdiv(NT(l), NW / SPL(l)));
+  }
+  static constexpr int NG(int l) { return cdiv(NT(l), NTC(l)); }
+  static constexpr int NU(int l) { return TOEP(l) ? TB : NG(l) * SPL(l); }  // units of layer l
+  // per-layer table of B-fragment row offsets: KOFF[l][lg][ks] (elements) for
+  // the 8 channels at kappa = 32 ks + 8 lg, i.e. tap jj = kappa / C_in and
+  // channel i0 = kappa mod C_in; taps past the kernel (zero weights) read tap
+  // K-1 instead, a row that holds finite values
+  __host__ __device__ static constexpr int koff(int l, int lg, int ks) {
+    const int kappa = 32 * ks + 8 * lg, jj = kappa / cip(C[l]), i0 = kappa - jj * cip(C[l]);
+    const int j = jj < KT(l) ? jj : KT(l) - 1;
+    return phys(l, j) * rs(C[l]) + i0;
+  }
+  static constexpr bool units_fit(int l) {
+    return l == 9 || (NU(l) <= NW && NF(l) <= FMAX && QP(l) % SPL(l) == 0 && units_fit(l + 1));
+  }
+  // staged input rows: every row layer 0's columns read (a column's MFMA rows
+  // take both output times, so rows past the needed range are read with zero
+  // weights and must hold finite values: they get the window's real samples)
+  static constexpr int XROWS = cap0(0);
+  static constexpr int XCH = (XROWS + 7 + 7) / 8;          // chunks covering XROWS rows at any alignment
+  static constexpr int XITEMS = cdiv(XG * XCH, NTHR);      // items per thread
+};
+
 }  // namespace fused
+
+struct FusedP {
+  const char* w;     // the packed weights: layer l's fragments at w + off[l]
+  uint32_t off[9];   // (one pointer and nine words stay in SGPRs across the tile loop)
+  const float* scale[9];
+  const float* shift[9];
+};
+
+// tanh for the fused epilogue from z = 2 x log2(e) (the factor is folded into
+// the BN scale and shift): 1 - 2 / (2^z + 1) on the hardware exp2 and
+// reciprocal.  2^z overflows to +inf for large z, giving exactly 1; relative
+// error is far below the BF16 rounding of the stored activations.
+__device__ __forceinline__ float tanh_scaled(float z) {
+  return fmaf(-2.0f, __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(z) + 1.0f), 1.0f);
+}
+constexpr float kTwoLog2e = 2.8853900817779268f;
 
 // Two floats -> packed bf16 pair, first in the low half: the hardware
 // conversion, which rounds to nearest even exactly like bf16_rne (NaNs
@@ -1077,13 +1083,13 @@ __device__ __forceinline__ f32x4 mfma16(const uint4& a, const uint4& b, const f3
 // write.  Positions outside the layer's signal are stored as zeros (the next
 // layer's padding); only tiles at a window edge (EDGE) have any.  Every
 // C_out here is a multiple of 8, so no stored channel is padding.
-template <int l, bool EDGE, bool F16>
+template <class Z, int l, bool EDGE, bool F16>
 __device__ __forceinline__ void epi_row(uint16_t* out, int row, int o0, f32x4 v, float4 sc, float4 sh, int pos0,
                                         int Lout) {
   using namespace fused;
   constexpr int RSO = rs(C[l + 1]);
   static_assert(C[l + 1] % 8 == 0, "stored channel groups are never padding");
-  if (row < 0 || row >= NR[l + 1]) return;
+  if (row < 0 || row >= Z::NR(l + 1)) return;
   float t0 = tanh_scaled(fmaf(v[0], sc.x, sh.x)), t1 = tanh_scaled(fmaf(v[1], sc.y, sh.y));
   float t2 = tanh_scaled(fmaf(v[2], sc.z, sh.z)), t3 = tanh_scaled(fmaf(v[3], sc.w, sh.w));
   if (EDGE) {
@@ -1094,17 +1100,17 @@ __device__ __forceinline__ void epi_row(uint16_t* out, int row, int o0, f32x4 v,
     t2 = live ? t2 : 0.0f;
     t3 = live ? t3 : 0.0f;
   }
-  const int prow = phys(l + 1, row);
+  const int prow = Z::phys(l + 1, row);
   *reinterpret_cast<uint2*>(out + prow * RSO + o0) = make_uint2(pack2<F16>(t0, t1), pack2<F16>(t2, t3));
 }
 
 // Epilogue of one work unit (see fused_layer).
-template <int l, bool EDGE, int NTCl, int Q, bool F16>
+template <class Z, int l, bool EDGE, int NTCl, int Q, bool F16>
 __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, int sp, int lc, int lg, uint16_t* out,
-                                          const float* ksc, const float* ksh, int pos0, int Lout, const ConvP* op,
+                                          const float* ksc, const float* ksh, int pos0, int Lout, const DcIn* op,
                                           int b, int Wout) {
   using namespace fused;
-  constexpr int CIPO = cip(C[l + 1]), M = MT(l), P = NPH(l), NTn = NT(l), SP = SPL(l);
+  constexpr int CIPO = cip(C[l + 1]), M = MT(l), P = NPH(l), NTn = Z::NT(l), SP = SPL(l);
   (void)op;
   (void)b;
   (void)Wout;
@@ -1120,7 +1126,7 @@ __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, 
     for (int a = 0; a < NTCl; ++a) {
       if (nt0 + a >= NTn) break;
       const int c = (nt0 + a) * 16 + lc;
-      epi_row<l, EDGE, F16>(out, 2 * c + ph + ROFF(l), o0, acc[a][0], sc4, sh4, pos0, Lout);
+      epi_row<Z, l, EDGE, F16>(out, 2 * c + ph + ROFF(l), o0, acc[a][0], sc4, sh4, pos0, Lout);
     }
   } else if constexpr (COMPACT(l)) {
     // tiles a, a+1: lanes 0..31 keep tile a's channels 0..7, lanes 32..63
@@ -1142,13 +1148,13 @@ __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, 
             v[r] = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][ph][r]),
                                                                     __float_as_uint(acc[a + 1][ph][r]), false,
                                                                     false)[0]);
-          epi_row<l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, v, sc4, sh4, pos0, Lout);
+          epi_row<Z, l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, v, sc4, sh4, pos0, Lout);
         }
       } else if (lg < 2) {
         const int c = (nt0 + a) * 16 + lc;
 #pragma unroll
         for (int ph = 0; ph < P; ++ph)
-          epi_row<l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, acc[a][ph], sc4, sh4, pos0, Lout);
+          epi_row<Z, l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, acc[a][ph], sc4, sh4, pos0, Lout);
       }
     }
   } else {
@@ -1164,14 +1170,14 @@ __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, 
       for (int a = 0; a < NTCl; ++a) {
         if (nt0 + a >= NTn) break;
         const int c = (nt0 + a) * 16 + lc;
-        epi_row<l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, acc[a][k], sc4, sh4, pos0, Lout);
+        epi_row<Z, l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, acc[a][k], sc4, sh4, pos0, Lout);
       }
     }
   }
 }
 
 // One layer of the fused network: LDS in -> LDS out (or global for the last).
-// Work units are (group of NTC column tiles, share of the (phase, channel
+// Work units are (group of Z::NTC column tiles, share of the (phase, channel
 // tile) pairs); every layer has at most NW units and unit u runs on wave u.
 // The 92 KB of packed weights stay in L2, shared by every block; a unit's
 // fragments (at most FMAX) arrive in wf, requested while the previous
@@ -1183,10 +1189,10 @@ __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, 
 // fragment i = k KS + ks (pair q = sp + k SPL, K step ks) of unit `wave`,
 // sp = wave mod SPL, at [q][ks][lane] in the layer's pack (the output conv:
 // fragment ks at [ks][lane]).
-template <int l, int I0, int I1>
+template <class Z, int l, int I0, int I1>
 __device__ __forceinline__ void fused_frags(u32x4 (&wf)[fused::FMAX], const uint4* wg, int wave, int lane) {
   using namespace fused;
-  if (I0 >= I1 || wave >= NU(l)) return;  // wave-uniform
+  if (I0 >= I1 || wave >= Z::NU(l)) return;  // wave-uniform
   const u32x4* wq = reinterpret_cast<const u32x4*>(wg) + lane;
   if constexpr (TOEP(l)) {
 #pragma unroll
@@ -1199,23 +1205,23 @@ __device__ __forceinline__ void fused_frags(u32x4 (&wf)[fused::FMAX], const uint
   }
 }
 
-// The output conv as a Toeplitz product (see TOEP): wave w < TB computes
+// The output conv as a Toeplitz product (see TOEP): wave w < Z::TB computes
 // outputs [256 w, 256 w + 256) of the tile with KS8 MFMAs whose A operand
 // (8 channels at one time offset per lane) comes from LDS and whose B
 // operand (the banded weights) from the packed fragments; the epilogue
 // writes the noise and the fully-online clean output.  The fragments of the
 // next tile's first layer are requested after the MFMAs (wgn).
-template <bool F16>
+template <class Z, bool F16>
 __device__ __forceinline__ void fused_toeplitz(int tid, const uint16_t* in, u32x4 (&wf)[fused::FMAX],
                                                const uint4* wgn, const float* ksc, const float* ksh, int pos0,
-                                               const ConvP* op, int b, int Wout) {
+                                               const DcIn* op, int b, int Wout) {
   using namespace fused;
   constexpr int RSI = rs(C[8]);
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lc = lane & 15, lg = lane >> 4;
   static_assert(PF(8) == NF(8), "the output conv's fragments all arrive with the previous layer");
-  if (wave >= TB) {  // wave-uniform
-    fused_frags<0, 0, PF(0)>(wf, wgn, wave, lane);
+  if (wave >= Z::TB) {  // wave-uniform
+    fused_frags<Z, 0, 0, PF(0)>(wf, wgn, wave, lane);
     return;
   }
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1228,7 +1234,7 @@ __device__ __forceinline__ void fused_toeplitz(int tid, const uint16_t* in, u32x
     const uint4 av = *reinterpret_cast<const uint4*>(in + prow8(r) * RSI);
     acc = mfma16<F16>(av, __builtin_bit_cast(uint4, wf[ks]), acc);
   }
-  fused_frags<0, 0, PF(0)>(wf, wgn, wave, lane);
+  fused_frags<Z, 0, 0, PF(0)>(wf, wgn, wave, lane);
   __builtin_amdgcn_s_setprio(1);  // epilogue ahead of MFMA chains, as in fused_layer_mm
   // D[m = 4 lg + q][n = lc]: output 16 m + n of this wave's 256
   const float sc = ksc[0], sh = ksh[0];
@@ -1250,15 +1256,15 @@ __device__ __forceinline__ void fused_toeplitz(int tid, const uint16_t* in, u32x
   __builtin_amdgcn_s_setprio(0);
 }
 
-template <int l, bool F16>
+template <class Z, int l, bool F16>
 __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint16_t* out, u32x4 (&wf)[fused::FMAX],
                                                const uint4* wg, const uint4* wgn, const int* kt, const float* ksc,
-                                               const float* ksh, int pos0, int Lout, const ConvP* op, int b,
+                                               const float* ksh, int pos0, int Lout, const DcIn* op, int b,
                                                int Wout) {
   using namespace fused;
   constexpr int RSI = rs(C[l]);
-  constexpr int KSn = KS(l), NTn = NT(l);
-  constexpr int NTCl = NTC(l), SP = SPL(l), Q = QP(l) / SP;
+  constexpr int KSn = KS(l), NTn = Z::NT(l);
+  constexpr int NTCl = Z::NTC(l), SP = SPL(l), Q = QP(l) / SP;
   constexpr int SX = SPLITF(l) > 1 ? 1 : CSTEP(l);  // LDS rows between adjacent columns
   static_assert(KSn <= KSMAX, "offset table width");
   // the wave index is uniform: in an SGPR, unit selection and the weight
@@ -1274,12 +1280,12 @@ __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint
     ko[4] = k1.x; ko[5] = k1.y; ko[6] = k1.z; ko[7] = k1.w;
   }
   // window-edge tiles store zeros outside the signal
-  const bool edge = pos0 < 0 || pos0 + NR[l + 1] > Lout;
-  if (wave >= NU(l)) {  // wave-uniform
-    fused_frags<l + 1, 0, PF(l + 1)>(wf, wgn, wave, lane);
+  const bool edge = pos0 < 0 || pos0 + Z::NR(l + 1) > Lout;
+  if (wave >= Z::NU(l)) {  // wave-uniform
+    fused_frags<Z, l + 1, 0, PF(l + 1)>(wf, wgn, wave, lane);
     return;
   }
-  fused_frags<l, PF(l), NF(l)>(wf, wg, wave, lane);
+  fused_frags<Z, l, PF(l), NF(l)>(wf, wg, wave, lane);
   {
     const int unit = wave;
     const int nt0 = (unit / SP) * NTCl, sp = unit % SP;  // wave-uniform
@@ -1306,26 +1312,26 @@ __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint
         for (int k = 0; k < Q; ++k)
           acc[a][k] = mfma16<F16>(__builtin_bit_cast(uint4, wf[k * KSn + ks]), bb[a], acc[a][k]);
     }
-    fused_frags<l + 1, 0, PF(l + 1)>(wf, wgn, wave, lane);
+    fused_frags<Z, l + 1, 0, PF(l + 1)>(wf, wgn, wave, lane);
     // a layer ends when its slowest wave's epilogue does: waves in their
     // epilogue issue ahead of waves still in their MFMA chains
     __builtin_amdgcn_s_setprio(1);
     if (edge)
-      fused_epi<l, true, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout, op, b, Wout);
+      fused_epi<Z, l, true, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout, op, b, Wout);
     else
-      fused_epi<l, false, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout, op, b, Wout);
+      fused_epi<Z, l, false, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout, op, b, Wout);
     __builtin_amdgcn_s_setprio(0);
   }
 }
 
-template <int l, bool F16>
+template <class Z, int l, bool F16>
 __device__ __forceinline__ void fused_layer(int tid, const uint16_t* in, uint16_t* out, u32x4 (&wf)[fused::FMAX],
                                             const uint4* wg, const uint4* wgn, const int* kt, const float* ksc,
-                                            const float* ksh, int pos0, int Lout, const ConvP* op, int b, int Wout) {
+                                            const float* ksh, int pos0, int Lout, const DcIn* op, int b, int Wout) {
   if constexpr (fused::TOEP(l))
-    fused_toeplitz<F16>(tid, in, wf, wgn, ksc, ksh, pos0, op, b, Wout);
+    fused_toeplitz<Z, F16>(tid, in, wf, wgn, ksc, ksh, pos0, op, b, Wout);
   else
-    fused_layer_mm<l, F16>(tid, in, out, wf, wg, wgn, kt, ksc, ksh, pos0, Lout, op, b, Wout);
+    fused_layer_mm<Z, l, F16>(tid, in, out, wf, wg, wgn, kt, ksc, ksh, pos0, Lout, op, b, Wout);
 }
 
 // ---------------------------------------------------------------------------
@@ -1337,146 +1343,122 @@ __device__ __forceinline__ void fused_layer(int tid, const uint16_t* in, uint16_
 // are contiguous in LDS.  Rows are stored even rows first, then odd rows
 // (layer 0 reads with stride 2).
 // ---------------------------------------------------------------------------
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-namespace fused {
-constexpr int XG = cip(C[0]) / 4;                  // channel groups of x
-// staged input rows: every row layer 0's columns read (a column's MFMA rows
-// take both output times, so rows past the needed range are read with zero
-// weights and must hold finite values: they get the window's real samples)
-constexpr int XROWS = cap0(0);
-constexpr int XCH = (XROWS + 7 + 7) / 8;           // chunks covering XROWS rows at any alignment
-constexpr int XITEMS = cdiv(XG * XCH, NTHR);       // items per thread
-}  // namespace fused
-
-template <int IN>
+template <class Z, int IN>
 struct XRaw {
   static constexpr int NV = IN == IN_F32 || IN == IN_RING_F32 ? 2 : 1;  // 16 B pieces per channel chunk
-  u32x4 v[fused::XITEMS][4][NV];
+  u32x4 v[Z::XITEMS][4][NV];
 };
 
-// one channel's 8-sample chunk at positions [qc, qc + 8) of the window; zeros
-// outside [0, Lin) and for channels >= Ci
-template <int IN>
-__device__ __forceinline__ void load_chunk(u32x4 (&d)[XRaw<IN>::NV], const uint16_t* hrow, const float* frow,
-                                           int head, int ld, int Lin, int qc, bool vec) {
-  constexpr int NV = XRaw<IN>::NV;
-  constexpr bool F32SRC = IN == IN_F32 || IN == IN_RING_F32;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) d[k] = u32x4{0u, 0u, 0u, 0u};
+// Where a tile's chunks start: a multiple of 8 samples in the input's own
+// memory, at or before row 0 (window position q0).  For a ring that is al =
+// head mod 8 past a multiple of 8 in the window, so that a chunk is one
+// aligned load whatever the head, and never straddles the ring's end.
+__device__ __forceinline__ int chunk0(int q0, int al) { return q0 - ((q0 + al) & 7); }
+
+// one channel's 8-sample chunk at positions [qc, qc + 8) of a dense window;
+// zeros outside [0, Lin)
+__device__ __forceinline__ void load_dense(u32x4 (&d)[2], const float* row, int Lin, int qc, bool vec) {
+  d[0] = d[1] = u32x4{0u, 0u, 0u, 0u};
   if (vec && qc >= 0 && qc + 8 <= Lin) {
-    if (IN == IN_F32) {
-      d[0] = *reinterpret_cast<const u32x4*>(frow + qc);
-      d[NV - 1] = *reinterpret_cast<const u32x4*>(frow + qc + 4);
-    } else if (IN == IN_RING_F32) {
-      // an aligned 8-sample chunk never straddles the ring's wrap point
-      int ph = head + qc;
-      if (ph >= ld) ph -= ld;
-      d[0] = *reinterpret_cast<const u32x4*>(frow + ph);
-      d[NV - 1] = *reinterpret_cast<const u32x4*>(frow + ph + 4);
-    } else {
-      int ph = qc;
-      if (IN == IN_RING) {
-        ph = head + qc;
-        if (ph >= ld) ph -= ld;
-      }
-      d[0] = *reinterpret_cast<const u32x4*>(hrow + ph);
-    }
+    d[0] = *reinterpret_cast<const u32x4*>(row + qc);
+    d[1] = *reinterpret_cast<const u32x4*>(row + qc + 4);
   } else {
     uint32_t w[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int q = qc + e;
-      w[e] = 0;
-      if (q >= 0 && q < Lin) {
-        if (IN == IN_F32) {
-          w[e] = __float_as_uint(frow[q]);
-        } else if (IN == IN_RING_F32) {
-          int ph = head + q;
-          if (ph >= ld) ph -= ld;
-          w[e] = __float_as_uint(frow[ph]);
-        } else {
-          int ph = q;
-          if (IN == IN_RING) {
-            ph = head + q;
-            if (ph >= ld) ph -= ld;
-          }
-          w[e] = hrow[ph];
-        }
-      }
-    }
-    if (F32SRC) {
-      d[0] = u32x4{w[0], w[1], w[2], w[3]};
-      d[NV - 1] = u32x4{w[4], w[5], w[6], w[7]};
-    } else {
-      d[0] = u32x4{w[0] | (w[1] << 16), w[2] | (w[3] << 16), w[4] | (w[5] << 16), w[6] | (w[7] << 16)};
-    }
+    for (int e = 0; e < 8; ++e) w[e] = qc + e >= 0 && qc + e < Lin ? __float_as_uint(row[qc + e]) : 0u;
+    d[0] = u32x4{w[0], w[1], w[2], w[3]};
+    d[1] = u32x4{w[4], w[5], w[6], w[7]};
   }
 }
 
-// Issue the loads of a tile's input rows [q0, q0 + XROWS) of window b
-// (tid: the thread index).
-template <int IN>
-__device__ __forceinline__ void load_x(XRaw<IN>& R, const ConvP& p, int b, int q0, int tid) {
+// Issue the loads of a tile's input rows [q0, q0 + XROWS) of window b (tid:
+// the thread index).  Returns al (see chunk0), for store_x.  A ring's length
+// and start are multiples of 8 samples (the network's windows are multiples of
+// 16, a pool's rings 256-byte aligned).  A ring's chunk that lies partly outside the
+// window is loaded whole; store_x drops what is outside.
+template <class Z, int IN>
+__device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int q0, int tid) {
   using namespace fused;
-  const int Ci = p.Ci, Lin = p.Lin;
-  const int qa = q0 - (((q0 % 8) + 8) % 8);
-  const int nch = (q0 + XROWS - qa + 7) / 8;
-  int head = 0, ld = p.ldx ? p.ldx : Lin;
+  constexpr int Ci = C[0], NV = XRaw<Z, IN>::NV;
+  constexpr bool RING = IN != IN_F32;
+  const int Lin = p.Lin;
+  int head = 0, ld = p.ldx;
   const uint16_t* hbase = nullptr;
   const float* fbase = nullptr;
-  bool vec;
-  if (IN == IN_RING) {
+  bool vec = true;
+  if (RING) {
     const Item& it = p.items[b];
     head = it.head;
     ld = it.W;
-    hbase = reinterpret_cast<const uint16_t*>(p.arena) + it.shadow;
-    vec = (ld & 7) == 0 && (head & 7) == 0 && (it.shadow & 7) == 0;
-  } else if (IN == IN_RING_F32) {
-    const Item& it = p.items[b];
-    head = it.head;
-    ld = it.W;
-    fbase = reinterpret_cast<const float*>(p.arena) + it.ring;
-    vec = (ld & 7) == 0 && (head & 7) == 0 && (it.ring & 3) == 0;
+    if (IN == IN_RING)
+      hbase = reinterpret_cast<const uint16_t*>(p.arena) + it.shadow;
+    else
+      fbase = reinterpret_cast<const float*>(p.arena) + it.ring;
   } else {
     fbase = p.x + (int64_t)b * Ci * ld;
-    vec = (ld & 7) == 0 && (reinterpret_cast<uintptr_t>(p.x) & 15) == 0;
+    vec = (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(p.x) & 15) == 0;
   }
+  const int al = RING ? head & 7 : 0;
+  const int qa = chunk0(q0, al), nch = (q0 + Z::XROWS - qa + 7) / 8;
 #pragma unroll
-  for (int it = 0; it < XITEMS; ++it) {
-    const int e = tid + NTHR * it;
+  for (int it = 0; it < Z::XITEMS; ++it) {
+    const int e = tid + Z::NTHR * it;
     const int g = e % XG, ch = e / XG;
     const int qc = qa + 8 * ch;
+    if constexpr (RING) {
+      int ph = head + qc;
+      if (ph < 0) ph += ld;
+      if (ph >= ld) ph -= ld;
+      const bool in = ch < nch && qc + 8 > 0 && qc < Lin;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = 4 * g + k;
-      const bool on = ch < nch && i < Ci;
-      const int64_t ro = (int64_t)(on ? i : 0) * ld;
-      load_chunk<IN>(R.v[it][k], hbase + (IN == IN_RING ? ro : 0), fbase + (IN != IN_RING ? ro : 0), head, ld,
-                     on ? Lin : 0, qc, vec);
+      for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) R.v[it][k][v] = u32x4{0u, 0u, 0u, 0u};
+        if (in && 4 * g + k < Ci) {
+          const int64_t o = (int64_t)(4 * g + k) * ld + ph;
+          if constexpr (IN == IN_RING) {
+            R.v[it][k][0] = *reinterpret_cast<const u32x4*>(hbase + o);
+          } else {
+            R.v[it][k][0] = *reinterpret_cast<const u32x4*>(fbase + o);
+            R.v[it][k][NV - 1] = *reinterpret_cast<const u32x4*>(fbase + o + 4);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int i = 4 * g + k;
+        const bool on = ch < nch && i < Ci;
+        load_dense(R.v[it][k], fbase + (int64_t)(on ? i : 0) * ld, on ? Lin : 0, qc, vec);
+      }
     }
   }
+  return al;
 }
 
 // Write the staged rows to LDS (row stride RS, split by row residue mod 4).
-template <int IN, bool F16>
-__device__ __forceinline__ void store_x(uint16_t* tile, const XRaw<IN>& R, int q0, int tid) {
+// AL0: al is 0, so a chunk's rows have residues known at compile time and a
+// chunk lies inside the window or outside (lengths are multiples of 16); else
+// its rows outside [0, Lin) are zeroed here.
+template <class Z, int IN, bool F16, bool AL0>
+__device__ __forceinline__ void store_rows(uint16_t* tile, const XRaw<Z, IN>& R, int q0, int al, int Lin, int tid) {
   static_assert(!(F16 && IN == IN_RING), "the ring's 16-bit shadow is BF16");
   using namespace fused;
-  constexpr int RS = rs(C[0]), ROWS = XROWS;
+  constexpr int RS = rs(C[0]), ROWS = Z::XROWS;
   static_assert(SPLITF(0) == 4, "layer 0's columns step four input rows");
-  const int qa = q0 - (((q0 % 8) + 8) % 8);
+  const int qa = chunk0(q0, AL0 ? 0 : al);
   const int nch = (q0 + ROWS - qa + 7) / 8;
 #pragma unroll
-  for (int it = 0; it < XITEMS; ++it) {
-    const int e = tid + NTHR * it;
+  for (int it = 0; it < Z::XITEMS; ++it) {
+    const int e = tid + Z::NTHR * it;
     const int g = e % XG, ch = e / XG;
     if (ch >= nch) continue;
-    // bf16 pairs of each channel: c[k][d] holds samples 2d, 2d+1
+    // 16-bit pairs of each channel: c[k][d] holds samples 2d, 2d+1
     uint32_t c[4][4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (IN == IN_F32 || IN == IN_RING_F32) {
-        const u32x4 a = R.v[it][k][0], z = R.v[it][k][XRaw<IN>::NV - 1];
+        const u32x4 a = R.v[it][k][0], z = R.v[it][k][XRaw<Z, IN>::NV - 1];
         c[k][0] = pack2<F16>(__uint_as_float(a.x), __uint_as_float(a.y));
         c[k][1] = pack2<F16>(__uint_as_float(a.z), __uint_as_float(a.w));
         c[k][2] = pack2<F16>(__uint_as_float(z.x), __uint_as_float(z.y));
@@ -1500,92 +1482,150 @@ __device__ __forceinline__ void store_x(uint16_t* tile, const XRaw<IN>& R, int q
         hi = (c[2][d] & 0xffffu) | (c[3][d] << 16);
       }
       const int r = r0 + t;
+      if (!AL0 && (q0 + r < 0 || q0 + r >= Lin)) lo = hi = 0u;
       if (full || (r >= 0 && r < ROWS))
-        *reinterpret_cast<uint2*>(tile + phys(0, r) * RS + 4 * g) = make_uint2(lo, hi);
+        *reinterpret_cast<uint2*>(tile + Z::phys(0, r) * RS + 4 * g) = make_uint2(lo, hi);
     }
   }
 }
 
+template <class Z, int IN, bool F16>
+__device__ __forceinline__ void store_x(uint16_t* tile, const XRaw<Z, IN>& R, int q0, int al, int Lin, int tid) {
+  if (IN == IN_F32 || al == 0)  // block-uniform
+    store_rows<Z, IN, F16, true>(tile, R, q0, 0, Lin, tid);
+  else
+    store_rows<Z, IN, F16, false>(tile, R, q0, al, Lin, tid);
+}
+
 // Fused snapshot update: the item carries the head after the update, and
-// its [C][s] new samples (FP32 at p.upd + src) belong at window positions
-// [W - s, W), ring positions h0, h0+1, ... (mod W), h0 = head - s.  Before a
-// tile stages its input rows [q0, q0 + XROWS), the block writes the new
-// samples among them (widened to whole groups of four) to the ring and its
+// its [C][s] new samples (FP32 at upd + src) belong at positions [Lin - s,
+// Lin) of the analysed window (or causal band, which ends where the window
+// ends), ring positions h0, h0+1, ... (mod W), h0 the newest position - s.
+// Before a tile stages its input rows [q0, q0 + XROWS), the block writes the
+// new samples among them (widened to whole groups of four) to the ring and its
 // BF16 shadow, exactly as the snapshot update writes them; after a barrier
-// the rows are read from the shadow as usual.  Every new position lies in
+// the rows are read from the ring as usual.  Every new position lies in
 // some tile's rows, so the launch writes them all; blocks whose rows overlap
 // write the same values.  No tile reads the positions the new samples
 // replace (they held the oldest samples, which left the window).
 // Returns false, writing nothing, when the rows hold no new sample
-// (block-uniform).
-__device__ __forceinline__ bool upd_stage(const ConvP& p, int b, int q0, int tid) {
+// (block-uniform).  A wave takes one channel at a time, so no lane divides.
+template <class Z>
+__device__ __forceinline__ bool upd_stage(const DcIn& p, int b, int q0, int tid) {
   const Item& it = p.items[b];
-  const int s = it.s, W = it.W, snew = W - s;
-  int lo = q0 > snew ? q0 : snew, hi = q0 + fused::XROWS < W ? q0 + fused::XROWS : W;
+  const int s = it.s, W = it.W, snew = p.Lin - s;
+  int lo = q0 > snew ? q0 : snew, hi = q0 + Z::XROWS < p.Lin ? q0 + Z::XROWS : p.Lin;
   if (lo >= hi) return false;
   // the arena is the pool's device memory; the launch owns these positions
   float* ring = reinterpret_cast<float*>(const_cast<void*>(p.arena)) + it.ring;
   uint16_t* sh = reinterpret_cast<uint16_t*>(const_cast<void*>(p.arena)) + it.shadow;
   const float* src = p.upd + it.src;
-  int h0 = it.head - s;
-  if (h0 < 0) h0 += W;
+  int h0 = it.head + snew;  // head: the ring position of the window's (band's) first sample
+  if (h0 >= W) h0 -= W;
   const bool vec = ((s | h0 | W) & 3) == 0 && (it.src & 3) == 0 && (it.ring & 3) == 0 && (it.shadow & 3) == 0 &&
                    (reinterpret_cast<uintptr_t>(p.upd) & 15) == 0;
-  if (vec) {
-    // groups of four samples of one channel; snew, W, s and h0 are multiples
-    // of 4, so a group stays inside [snew, W) and never straddles the wrap
-    lo = lo - ((lo - snew) & 3);
-    const int n4 = (hi - lo + 3) / 4, total = it.C * n4;
-    for (int g = tid; g < total; g += fused::NTHR) {
-      const int c = g / n4, q = lo + 4 * (g - c * n4) - snew;  // sample index within the new block
-      int ph = h0 + q;
-      if (ph >= W) ph -= W;
-      const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)c * s + q);
-      *reinterpret_cast<float4*>(ring + (int64_t)c * W + ph) = v;
-      ushort4 h;
-      h.x = f2bf(v.x);
-      h.y = f2bf(v.y);
-      h.z = f2bf(v.z);
-      h.w = f2bf(v.w);
-      *reinterpret_cast<ushort4*>(sh + (int64_t)c * W + ph) = h;
-    }
-  } else {
-    const int n1 = hi - lo, total = it.C * n1;
-    for (int g = tid; g < total; g += fused::NTHR) {
-      const int c = g / n1, q = lo + (g - c * n1) - snew;
-      int ph = h0 + q;
-      if (ph >= W) ph -= W;
-      const float v = src[(int64_t)c * s + q];
-      ring[(int64_t)c * W + ph] = v;
-      sh[(int64_t)c * W + ph] = f2bf(v);
+  const int lane = tid & 63;
+  // groups of four samples of one channel; with s, W and h0 multiples of 4 a
+  // group stays inside the new samples and never straddles the wrap.  Two (four)
+  // loads are in flight per lane, no more: this runs beside live fragments
+  if (vec) lo -= (lo - snew) & 3;
+  for (int c = tid >> 6; c < it.C; c += Z::NW) {
+    const float* sc = src + (int64_t)c * s - snew;
+    float* rrow = ring + (int64_t)c * W;
+    uint16_t* srow = sh + (int64_t)c * W;
+    if (vec) {
+      for (int q0 = lo + 4 * lane; q0 < hi; q0 += 512) {
+        float4 v[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          if (q0 + 256 * j < hi) v[j] = *reinterpret_cast<const float4*>(sc + q0 + 256 * j);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int q = q0 + 256 * j;
+          if (q >= hi) continue;
+          int ph = h0 + q - snew;
+          if (ph >= W) ph -= W;
+          *reinterpret_cast<float4*>(rrow + ph) = v[j];
+          ushort4 h;
+          h.x = f2bf(v[j].x);
+          h.y = f2bf(v[j].y);
+          h.z = f2bf(v[j].z);
+          h.w = f2bf(v[j].w);
+          *reinterpret_cast<ushort4*>(srow + ph) = h;
+        }
+      }
+    } else {
+      for (int q0 = lo + lane; q0 < hi; q0 += 256) {
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (q0 + 64 * j < hi) v[j] = sc[q0 + 64 * j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int q = q0 + 64 * j;
+          if (q >= hi) continue;
+          int ph = h0 + q - snew;
+          if (ph >= W) ph -= W;
+          rrow[ph] = v[j];
+          srow[ph] = f2bf(v[j]);
+        }
+      }
     }
   }
   return true;
 }
 
-#ifndef GW_FUSED_WAVES_PER_SIMD
-#define GW_FUSED_WAVES_PER_SIMD 6
-#endif
-template <int IN, bool F16, bool UPD = false>
-__global__ __launch_bounds__(fused::NTHR, GW_FUSED_WAVES_PER_SIMD) void dc_fused(ConvP p, FusedP f, int ntile) {
+// The items of a small call ride in the kernel arguments (first parameter, at
+// the start of the argument segment); larger tables sit in device memory.
+template <class Z, int IN, bool F16, bool UPD, bool CAUSAL>
+__global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, FusedP f, int ntile) {
   using namespace fused;
-  __shared__ __attribute__((aligned(16))) uint16_t bufA[BUFA];
-  __shared__ __attribute__((aligned(16))) uint16_t bufB[BUFB];
+  static_assert(Z::units_fit(0), "every layer is one round of units of at most FMAX fragments");
+  (void)args;
+  if (!p.items) p.items = arg_items();
+  __shared__ __attribute__((aligned(16))) uint16_t bufA[Z::BUFA];
+  __shared__ __attribute__((aligned(16))) uint16_t bufB[Z::BUFB];
   __shared__ __attribute__((aligned(16))) int ktab[9][4][KSMAX];
   __shared__ __attribute__((aligned(16))) float ksc[9][64];
   __shared__ __attribute__((aligned(16))) float ksh[9][64];
 
-  const int W = f.L[0];
-  const int tpw = (W + T - 1) / T;  // tiles per window
+  const int W = p.Lin;
+  const int tpw = (W + Z::T - 1) / Z::T;  // tiles per window
   const int G = gridDim.x, j = blockIdx.x;
-  const int t0 = (int)((int64_t)ntile * j / G), t1 = (int)((int64_t)ntile * (j + 1) / G);
-  if (t0 >= t1) return;  // block-uniform
+  // A block walks a contiguous run of tiles, so that neighbours' input halos
+  // meet in L2.  Causal: one tile a block (most windows have only one); tile k
+  // of a band counts from its newest end, a window's outputs being the newest
+  // ones, and the newest tiles of all windows are dealt out first, so that
+  // the tiles without outputs, which end at once, come last.
+  int t = CAUSAL ? j : (int)((int64_t)ntile * j / G);
+  const int tend = CAUSAL ? j + 1 : (int)((int64_t)ntile * (j + 1) / G);
+  if (t >= tend) return;  // block-uniform
+  // window and first output of tile t
+  auto where = [&](int t, int* b, int* u0) {
+    if (CAUSAL) {
+      const int k = t / p.n;
+      *b = t - k * p.n;
+      *u0 = W - Z::T * (k + 1);
+    } else {
+      *b = t / tpw;
+      *u0 = (t - *b * tpw) * Z::T;
+    }
+  };
 
-  XRaw<IN> raw;
-  if (UPD && upd_stage(p, t0 / tpw, (t0 % tpw) * T + LO[0], threadIdx.x)) __syncthreads();
-  load_x<IN>(raw, p, t0 / tpw, (t0 % tpw) * T + LO[0], threadIdx.x);
+  XRaw<Z, IN> raw;
+  int b0, u00;
+  where(t, &b0, &u00);
+  if (CAUSAL) {
+    // only tiles with an output in the window's clean span [W - s - delay,
+    // W - delay); with the update folded in there are no delays, so that every
+    // new sample lies among such a tile's rows
+    const Item& it = p.items[b0];
+    if (u00 + Z::T <= W - it.s - it.delay || u00 >= W - it.delay) return;
+  }
+  if (UPD && upd_stage<Z>(p, b0, u00 + LO[0], threadIdx.x)) __syncthreads();
+  const int al0 = load_x<Z, IN>(raw, p, b0, u00 + LO[0], threadIdx.x);
   u32x4 wf[FMAX];  // this wave's weight fragments of the current layer
-  fused_frags<0, 0, PF(0)>(wf, reinterpret_cast<const uint4*>(f.wpk[0]),
+  fused_frags<Z, 0, 0, PF(0)>(wf, reinterpret_cast<const uint4*>(f.w + f.off[0]),
                            __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
 #pragma unroll
   for (int l = 0; l < 9; ++l) {
@@ -1597,17 +1637,16 @@ __global__ __launch_bounds__(fused::NTHR, GW_FUSED_WAVES_PER_SIMD) void dc_fused
     }
     if (threadIdx.x < 4 * KSMAX) {
       const int lg = threadIdx.x / KSMAX, ks = threadIdx.x % KSMAX;
-      ktab[l][lg][ks] = ks < KS(l) ? koff(l, lg, ks) : 0;
+      ktab[l][lg][ks] = ks < KS(l) ? Z::koff(l, lg, ks) : 0;
     }
   }
   // input tile rows [u0 - 93, u0 + T + 93) in [time][channel] layout
-  store_x<IN, F16>(bufA, raw, (t0 % tpw) * T + LO[0], threadIdx.x);
+  store_x<Z, IN, F16>(bufA, raw, u00 + LO[0], al0, W, threadIdx.x);
   __syncthreads();
 
-  for (int t = t0; t < t1; ++t) {
-    const int b = t / tpw, u0 = (t % tpw) * T;
-    const bool more = t + 1 < t1;  // block-uniform
-
+  while (true) {
+    int b, u0;
+    where(t, &b, &u0);
     // layer l reads the buffer holding a_l and writes a_{l+1}; u0 scaled per
     // layer; an opaque copy of the thread index keeps each layer's address
     // arithmetic inside the tile loop instead of live across it
@@ -1615,8 +1654,8 @@ __global__ __launch_bounds__(fused::NTHR, GW_FUSED_WAVES_PER_SIMD) void dc_fused
     {                                                                                                       \
       int tid = threadIdx.x;                                                                                \
       asm volatile("" : "+v"(tid));                                                                         \
-      fused_layer<l, F16>(tid, IN_BUF, OUT_BUF, wf, reinterpret_cast<const uint4*>(f.wpk[l]),               \
-                          reinterpret_cast<const uint4*>(f.wpk[(l + 1) % 9]), &ktab[l][0][0], ksc[l], ksh[l],  \
+      fused_layer<Z, l, F16>(tid, IN_BUF, OUT_BUF, wf, reinterpret_cast<const uint4*>(f.w + f.off[l]),               \
+                          reinterpret_cast<const uint4*>(f.w + f.off[(l + 1) % 9]), &ktab[l][0][0], ksc[l], ksh[l],  \
                           u0 / (SCALE_DIV) + LO[l + 1], W / (SCALE_DIV), &p, b, W);                         \
       __syncthreads();                                                                                      \
     }
@@ -1630,19 +1669,19 @@ __global__ __launch_bounds__(fused::NTHR, GW_FUSED_WAVES_PER_SIMD) void dc_fused
     GW_FUSED_LAYER(7, bufB, bufA, 1)
     GW_FUSED_LAYER(8, bufA, bufB, 1)
 #undef GW_FUSED_LAYER
-    if (more) {
-      // the next tile's input: the other block on the CU hides its latency
-      // (an opaque copy of the thread index, as for the layers)
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));
-      const int nq = ((t + 1) % tpw) * T + LO[0];
-      if (UPD && upd_stage(p, (t + 1) / tpw, nq, tid)) __syncthreads();
-      __builtin_amdgcn_s_setprio(2);  // ahead of the other block's epilogues
-      load_x<IN>(raw, p, (t + 1) / tpw, nq, tid);
-      store_x<IN, F16>(bufA, raw, nq, tid);
-      __builtin_amdgcn_s_setprio(0);
-      __syncthreads();
-    }
+    if (CAUSAL || ++t >= tend) break;  // block-uniform
+    // the next tile's input: the other block on the CU hides its latency
+    // (an opaque copy of the thread index, as for the layers)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    where(t, &b, &u0);
+    const int nq = u0 + LO[0];
+    if (UPD && upd_stage<Z>(p, b, nq, tid)) __syncthreads();
+    __builtin_amdgcn_s_setprio(2);  // ahead of the other block's epilogues
+    const int al = load_x<Z, IN>(raw, p, b, nq, tid);
+    store_x<Z, IN, F16>(bufA, raw, nq, al, W, tid);
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();
   }
 }
 
@@ -1707,56 +1746,83 @@ bool dc_fused_supported(const int* ci, const int* co, const int* type, const int
   return true;
 }
 
-// p: n, items (ring input or clean outputs), arena, x (+ ldx), noise, clean,
-// strain; W = window (or band) length, a multiple of 16.
-hipError_t launch_dc_fused_bf16(const ConvP& p, const uint16_t* const* wpk, const float* const* scale,
-                                const float* const* shift, int W, bool ring, int cu_budget, hipStream_t st,
-                                bool f16, bool upd) {
-  using namespace fused;
+template <class Z, int IN, bool F16, bool UPD, bool CAUSAL>
+static hipError_t launch_dc_t(const DcIn& p, const ItemArgs& args, const FusedP& f, int n, int cu_budget,
+                              hipStream_t st) {
+  const int64_t ntile = (int64_t)n * ((p.Lin + Z::T - 1) / Z::T);
+  if (ntile > (int64_t)1 << 30) return hipErrorInvalidValue;
+  // one resident grid: (blocks per CU) x CUs, at most one block per tile
+  static const int occ = [] {
+    int k = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, dc_fused<Z, IN, F16, UPD, CAUSAL>, Z::NTHR, 0) == hipSuccess && k > 0
+               ? k
+               : 1;
+  }();
+  const int64_t grid = CAUSAL ? ntile : std::min<int64_t>(ntile, (int64_t)occ * cu_budget);
+  hipLaunchKernelGGL((dc_fused<Z, IN, F16, UPD, CAUSAL>), dim3((unsigned)grid), dim3(Z::NTHR), 0, st, args, p, f, (int)ntile);
+  return hipGetLastError();
+}
+
+template <class Z, bool CAUSAL>
+static hipError_t launch_dc_c(const DcIn& p, const ItemArgs& args, const FusedP& f, int n, bool ring, bool f16,
+                              int ncu, hipStream_t st) {
+  // (ring or dense input) x (BF16 or FP16) x (with the snapshot update or
+  // without); the FP16 variant reads the ring's FP32 samples
+  const bool upd = p.upd != nullptr;
+  if (!ring)
+    return f16 ? launch_dc_t<Z, IN_F32, true, false, CAUSAL>(p, args, f, n, ncu, st)
+               : launch_dc_t<Z, IN_F32, false, false, CAUSAL>(p, args, f, n, ncu, st);
+  if (f16)
+    return upd ? launch_dc_t<Z, IN_RING_F32, true, true, CAUSAL>(p, args, f, n, ncu, st)
+               : launch_dc_t<Z, IN_RING_F32, true, false, CAUSAL>(p, args, f, n, ncu, st);
+  return upd ? launch_dc_t<Z, IN_RING, false, true, CAUSAL>(p, args, f, n, ncu, st)
+             : launch_dc_t<Z, IN_RING, false, false, CAUSAL>(p, args, f, n, ncu, st);
+}
+
+template <class Z>
+static hipError_t launch_dc_z(const DcIn& p, const ItemArgs& args, const FusedP& f, int n, bool ring, bool f16,
+                              int ncu, hipStream_t st) {
+  return p.causal ? launch_dc_c<Z, true>(p, args, f, n, ring, f16, ncu, st)
+                  : launch_dc_c<Z, false>(p, args, f, n, ring, f16, ncu, st);
+}
+
+// io: arena and items (ring input or clean outputs), x (+ ldx), noise, clean,
+// strain, upd; Lin = window (or band) length, a multiple of 16.  args: the
+// items when io.items is null.
+hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint16_t* const* wpk,
+                                const float* const* scale, const float* const* shift, int n, bool ring, int cu_budget,
+                                hipStream_t st, bool f16) {
+  const int W = io.Lin;
   if (W < 16 || W % 16) return hipErrorInvalidValue;
-  if (upd && (!ring || f16 || !p.upd)) return hipErrorInvalidValue;
+  if (io.upd && !ring) return hipErrorInvalidValue;
+  // the fragments lie in one buffer (the model's packed data)
   FusedP f;
+  const uint16_t* lo = *std::min_element(wpk, wpk + 9);
+  f.w = reinterpret_cast<const char*>(lo);
   for (int l = 0; l < 9; ++l) {
-    f.wpk[l] = wpk[l];
+    const size_t off = 2 * (size_t)(wpk[l] - lo);
+    if (off >> 32) return hipErrorInvalidValue;
+    f.off[l] = (uint32_t)off;
     f.scale[l] = scale[l];
     f.shift[l] = shift[l];
   }
-  f.L[0] = W;
-  f.L[1] = W / 2;
-  f.L[2] = W / 4;
-  f.L[3] = W / 8;
-  f.L[4] = W / 16;
-  f.L[5] = W / 8;
-  f.L[6] = W / 4;
-  f.L[7] = W / 2;
-  f.L[8] = W;
-  f.L[9] = W;
-  ConvP q = p;
-  q.Lin = W;
-  q.Ci = C[0];
-  const int64_t ntile = (int64_t)p.n * ((W + T - 1) / T);
-  if (ntile > (int64_t)1 << 30) return hipErrorInvalidValue;
-  // one resident grid: (blocks per CU) x CUs, at most one block per tile
-  // variants: (ring or dense input) x (BF16 or FP16); the FP16 variant reads
-  // the ring's FP32 samples (its 16-bit shadow is BF16)
-  // and the ring variant under a fused snapshot update
-  void (*kern[5])(ConvP, FusedP, int) = {dc_fused<IN_F32, false>, dc_fused<IN_RING, false>,
-                                         dc_fused<IN_F32, true>, dc_fused<IN_RING_F32, true>,
-                                         dc_fused<IN_RING, false, true>};
-  static int occ[5] = {0, 0, 0, 0, 0}, cus = 0;
-  const int v = upd ? 4 : (ring ? 1 : 0) + (f16 ? 2 : 0);
-  if (!occ[v]) {
-    int dev = 0, n = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern[v], NTHR, 0);
-    if (e != hipSuccess) return e;
-    occ[v] = n > 0 ? n : 1;
-  }
+  DcIn p = io;
+  if (!p.ldx) p.ldx = W;
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
   const int ncu = cu_budget > 0 && cu_budget < cus ? cu_budget : cus;
-  const int64_t grid = std::min<int64_t>(ntile, (int64_t)occ[v] * ncu);
-  hipLaunchKernelGGL(kern[v], dim3((unsigned)grid), dim3(NTHR), 0, st, q, f, (int)ntile);
-  return hipGetLastError();
+  p.n = n;
+  // Tile size.  A tile of 256 outputs runs its chain of nine layers in 14.5 us
+  // against 17.3 us for 768, but computes 1.4 times as many activations per
+  // output: it is taken while every tile has a CU of its own.  Measured (21 x
+  // 32768, launches of n windows, 256 against 768): n = 1 14.6 and 17.1 us, 2
+  // 14.9 and 17.3, 4 (512 tiles of 256) 18.9 and 17.8, 8 30 and 23; causal
+  // bands of 256 samples, n = 1 14.2 and 16.8, 179 of mixed strides (417 tiles
+  // of 256) 33 and 27.
+  if (io.tiles256 <= ncu) return launch_dc_z<fused::Geom<256, 12>>(p, args, f, n, ring, f16, ncu, st);
+  return launch_dc_z<fused::Geom<768, 12>>(p, args, f, n, ring, f16, ncu, st);
 }
 
 }  // namespace gw

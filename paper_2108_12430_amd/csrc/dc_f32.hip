@@ -133,17 +133,28 @@ hipError_t launch_pack_dc_f32(const float* w, float* out, int l, hipStream_t st)
 // [0, Lin)).  A thread takes one sample of every channel, so it computes one
 // address and its 21 loads are in flight together, each coalesced over the
 // wave; nothing is assumed of alignment, and a ring's wrap is one compare.
-template <int T, int SRC>
-__device__ __forceinline__ void f32d_stage(float* xt, const ConvP& p, int b, int p0, int tid) {
+// UPD: the newest s samples come from the request (p.upd) and are written to
+// the ring and its BF16 shadow on the way; tiles that share a sample write the
+// same values, and no tile reads the ring positions they replace.
+template <int T, int SRC, bool UPD>
+__device__ __forceinline__ void f32d_stage(float* xt, const DcIn& p, int b, int p0, int tid) {
   using namespace f32d;
   constexpr int XW = G<T>::XW;
   const float* base;
-  int ld, head = 0;
+  int ld, head = 0, snew = p.Lin, s = 0;
+  uint16_t* sh = nullptr;
+  const float* src = nullptr;
   if (SRC == SRC_RING) {
     const Item& it = p.items[b];
     base = reinterpret_cast<const float*>(p.arena) + it.ring;
     ld = it.W;
     head = it.head;
+    if (UPD) {
+      s = it.s;
+      snew = p.Lin - s;
+      sh = reinterpret_cast<uint16_t*>(const_cast<void*>(p.arena)) + it.shadow;
+      src = p.upd + it.src;
+    }
   } else {
     ld = p.ldx;
     base = p.x + (int64_t)b * C[0] * ld;
@@ -157,9 +168,20 @@ __device__ __forceinline__ void f32d_stage(float* xt, const ConvP& p, int b, int
       at += head;
       if (at >= ld) at -= ld;
     }
+    const bool fresh = UPD && live && q >= snew;
+    const float* from = fresh ? src + (q - snew) : base + at;
+    const int64_t step = fresh ? s : ld;
     float v[C[0]];
 #pragma unroll
-    for (int i = 0; i < C[0]; ++i) v[i] = base[(int64_t)i * ld + at];
+    for (int i = 0; i < C[0]; ++i) v[i] = from[i * step];
+    if (fresh) {
+      float* ring = const_cast<float*>(base) + at;
+#pragma unroll
+      for (int i = 0; i < C[0]; ++i) {
+        ring[(int64_t)i * ld] = v[i];
+        sh[(int64_t)i * ld + at] = f2bf(v[i]);
+      }
+    }
     if (c < XW)
 #pragma unroll
       for (int i = 0; i < C[0]; ++i) xt[i * XW + c] = live ? v[i] : 0.0f;
@@ -324,9 +346,11 @@ __device__ __forceinline__ void f32d_layer(int tid, const float* in, float* out,
   if (wave >= g::NU(l)) f32d_first<T, l + 1>(af, wn, wave, lane);
 }
 
-template <int T, int SRC>
-__global__ __launch_bounds__(f32d::NTHR, 4) void dc_f32(ConvP p, DcF32P f, int ntile) {
+template <int T, int SRC, bool UPD>
+__global__ __launch_bounds__(f32d::NTHR, 4) void dc_f32(ItemArgs args, DcIn p, DcF32P f, int ntile) {
   using namespace f32d;
+  (void)args;
+  if (!p.items) p.items = arg_items();
   using g = G<T>;
   __shared__ __attribute__((aligned(16))) float bufA[g::BUFA];
   __shared__ __attribute__((aligned(16))) float bufB[g::BUFB];
@@ -347,7 +371,7 @@ __global__ __launch_bounds__(f32d::NTHR, 4) void dc_f32(ConvP p, DcF32P f, int n
     const int b = t / tpw, u0 = (t - b * tpw) * T;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // keeps the layers' address arithmetic inside the loop
-    f32d_stage<T, SRC>(bufA, p, b, u0 + LO[0], tid);
+    f32d_stage<T, SRC, UPD>(bufA, p, b, u0 + LO[0], tid);
     f32d_first<T, 0>(af, f.wpk[0], __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
     __syncthreads();
 #define GW_LAYER(l, IN, OUT, DIV)                                                                                    \
@@ -397,31 +421,41 @@ __global__ __launch_bounds__(f32d::NTHR, 4) void dc_f32(ConvP p, DcF32P f, int n
   }
 }
 
-template <int T, int SRC>
-static hipError_t launch_dc_f32_t(const ConvP& p, const DcF32P& f, int cu, int cus, hipStream_t st) {
-  const int64_t ntile = (int64_t)p.n * ((p.Lin + T - 1) / T);
+template <int T, int SRC, bool UPD>
+static hipError_t launch_dc_f32_t(const DcIn& p, const ItemArgs& args, const DcF32P& f, int n, int ncu,
+                                  hipStream_t st) {
+  const int64_t ntile = (int64_t)n * ((p.Lin + T - 1) / T);
   if (ntile > (int64_t)1 << 30) return hipErrorInvalidValue;
   static const int occ = [] {
     int k = 0;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, dc_f32<T, SRC>, f32d::NTHR, 0) == hipSuccess && k > 0 ? k : 1;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, dc_f32<T, SRC, UPD>, f32d::NTHR, 0) == hipSuccess && k > 0
+               ? k
+               : 1;
   }();
-  const int ncu = cu > 0 && cu < cus ? cu : cus;
   const int64_t grid = std::min<int64_t>(ntile, (int64_t)occ * ncu);
-  hipLaunchKernelGGL((dc_f32<T, SRC>), dim3((unsigned)grid), dim3(f32d::NTHR), 0, st, p, f, (int)ntile);
+  hipLaunchKernelGGL((dc_f32<T, SRC, UPD>), dim3((unsigned)grid), dim3(f32d::NTHR), 0, st, args, p, f, (int)ntile);
   return hipGetLastError();
 }
 
-hipError_t launch_dc_f32(const ConvP& p, const float* const* wpk, const float* const* scale, const float* const* shift,
-                         int W, bool ring, int cu_budget, hipStream_t st) {
-  if (W < 16 || W % 16) return hipErrorInvalidValue;
+template <int T>
+static hipError_t launch_dc_f32_s(const DcIn& p, const ItemArgs& args, const DcF32P& f, int n, bool ring, int ncu,
+                                  hipStream_t st) {
+  if (!ring) return launch_dc_f32_t<T, SRC_DENSE, false>(p, args, f, n, ncu, st);
+  return p.upd ? launch_dc_f32_t<T, SRC_RING, true>(p, args, f, n, ncu, st)
+               : launch_dc_f32_t<T, SRC_RING, false>(p, args, f, n, ncu, st);
+}
+
+hipError_t launch_dc_f32(const DcIn& io, const ItemArgs& args, const float* const* wpk, const float* const* scale,
+                         const float* const* shift, int n, bool ring, int cu_budget, hipStream_t st) {
+  const int W = io.Lin;
+  if (W < 16 || W % 16 || (io.upd && !ring)) return hipErrorInvalidValue;
   DcF32P f;
   for (int l = 0; l < 9; ++l) {
     f.wpk[l] = wpk[l];
     f.scale[l] = scale[l];
     f.shift[l] = shift[l];
   }
-  ConvP q = p;
-  q.Lin = W;
+  DcIn q = io;
   if (!q.ldx) q.ldx = W;
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -436,18 +470,13 @@ hipError_t launch_dc_f32(const ConvP& p, const float* const* wpk, const float* c
   // n = 1: 17.7 (T = 256: 21.1); 2: 21.4 (25.3 at 128, 30.2 at 512); 4: 30.9
   // (33.4 at 256); 16: 101 (124 at 256, 178 at 128).
   auto cost = [&](int T, int one, int two) {
-    const int64_t tiles = (int64_t)p.n * ((W + T - 1) / T);
+    const int64_t tiles = (int64_t)n * ((W + T - 1) / T);
     return tiles <= ncu ? (int64_t)one : (tiles + 2 * ncu - 1) / (2 * ncu) * two;
   };
   const int64_t c128 = cost(128, 175, 230), c256 = cost(256, 210, 315), c512 = cost(512, 300, 500);
-  if (c128 <= c256 && c128 <= c512)
-    return ring ? launch_dc_f32_t<128, SRC_RING>(q, f, cu_budget, cus, st)
-                : launch_dc_f32_t<128, SRC_DENSE>(q, f, cu_budget, cus, st);
-  if (c256 <= c512)
-    return ring ? launch_dc_f32_t<256, SRC_RING>(q, f, cu_budget, cus, st)
-                : launch_dc_f32_t<256, SRC_DENSE>(q, f, cu_budget, cus, st);
-  return ring ? launch_dc_f32_t<512, SRC_RING>(q, f, cu_budget, cus, st)
-              : launch_dc_f32_t<512, SRC_DENSE>(q, f, cu_budget, cus, st);
+  if (c128 <= c256 && c128 <= c512) return launch_dc_f32_s<128>(q, args, f, n, ring, ncu, st);
+  if (c256 <= c512) return launch_dc_f32_s<256>(q, args, f, n, ring, ncu, st);
+  return launch_dc_f32_s<512>(q, args, f, n, ring, ncu, st);
 }
 
 }  // namespace gw

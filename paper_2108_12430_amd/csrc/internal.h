@@ -104,11 +104,36 @@ struct ConvP {
   // Lin (a band at the end of longer windows); 0 means Lin.  Ring inputs wrap
   // at their item's W and read positions [head + q] for q in [0, Lin).
   int ldx;
-  // fused snapshot update (ring input, fused kernel only): item i's newest s
-  // samples, [C][s] FP32 at upd + items[i].src, are read from here rather
-  // than from the ring, and written to the ring and its shadow by the launch
-  const float* upd;
 };
+
+// Input and outputs of the fused DeepClean kernels.
+struct DcIn {
+  const float* x;      // dense input [n][C][ldx], or null: the items' rings
+  const void* arena;   // pool arena
+  const Item* items;   // descriptors in device memory, or null: the kernel's ItemArgs
+  float* noise;        // [n][W] or null
+  const float* strain; // packed, or null
+  float* clean;        // packed, or null
+  // fused snapshot update (ring input): item i's newest s samples, [C][s]
+  // FP32 at upd + items[i].src, are written to the ring and its shadow by the
+  // launch before they are read; null: the rings are current
+  const float* upd;
+  int Lin;             // window, or band at the window's end (then head is the band's first sample)
+  int ldx;
+  int n;
+  int causal;          // only the items' clean spans are wanted
+  int tiles256;        // tiles of 256 outputs with something to compute
+};
+// Item descriptors of a small call as the first kernel argument: no table copy
+// ahead of the launch.  60 of them leave room for the other arguments in 4 KB.
+constexpr int kItemArgs = 60;
+struct ItemArgs {
+  Item e[kItemArgs];
+};
+// the ItemArgs of the running kernel, which must be its first parameter
+__device__ __forceinline__ const Item* arg_items() {
+  return (const Item*)__builtin_amdgcn_kernarg_segment_ptr();
+}
 
 // Geometry of the polyphase/strided column view of a layer (host + device).
 struct Geo {
@@ -328,16 +353,15 @@ int conv_bf16_gap_parts(int Ci, int Co, int Lout, int n);  // GAP partial sums p
 // transposed convs, 8->1 output conv, all k7 p3; BN+tanh on all but the last)
 bool dc_fused_supported(const int* ci, const int* co, const int* type, const int* k, const int* s,
                         const int* pad, const int* op, const int* bn, int L);
-hipError_t launch_dc_fused_bf16(const ConvP& p, const uint16_t* const* wpk, const float* const* scale,
-                                const float* const* shift, int W, bool ring, int cu_budget, hipStream_t st,
-                                bool f16 = false, bool upd = false);
+hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint16_t* const* wpk,
+                                const float* const* scale, const float* const* shift, int n, bool ring, int cu_budget,
+                                hipStream_t st, bool f16);
 // The fused FP32 forward of the same network (dc_f32.hip): fragments of its
-// special layers (the others: launch_pack_f32m), and the launch (p as for
-// launch_dc_fused_bf16).
+// special layers (the others: launch_pack_f32m), and the launch.
 size_t dc_f32_special_floats(int l);
 hipError_t launch_pack_dc_f32(const float* w, float* out, int l, hipStream_t st);
-hipError_t launch_dc_f32(const ConvP& p, const float* const* wpk, const float* const* scale, const float* const* shift,
-                         int W, bool ring, int cu_budget, hipStream_t st);
+hipError_t launch_dc_f32(const DcIn& io, const ItemArgs& args, const float* const* wpk, const float* const* scale,
+                         const float* const* shift, int n, bool ring, int cu_budget, hipStream_t st);
 size_t conv_bf16_packed_elems(int Ci, int Co, int k, bool transposed);
 // layers of the fused network whose weights the fused kernel takes in its own
 // fragment layout (stacked transposed layers, Toeplitz output conv)
