@@ -1075,7 +1075,7 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
       w.invstd[l] = take(4 * ly.co);
       w.z[l] = take((size_t)n * ly.co * lout[l] * esz);
       if (!rec) w.a[l] = take((size_t)n * ly.co * lout[l] * esz);
-      const int nblk = std::max(gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr),
+      const int nblk = std::max(gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr, gw::EPI_STATS),
                                 gw::conv_bf16_stats_blocks(n, lout[l], ly.k, ly.s, ly.p, tr));
       part = std::max(part, (size_t)ly.co * nblk * 2 * sizeof(double));
     }
@@ -1392,7 +1392,7 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
       if (l == L - 1) break;
       const int nblk = precision == GW_BF16
                            ? gw::conv_bf16_stats_blocks(n, lout[l], ly.k, ly.s, ly.p, tr)
-                           : gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr);
+                           : gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr, gw::EPI_STATS);
       LAUNCH(nm("bn_stats", "L", l), st,
              gw::launch_stats_final(partial, nblk, ly.co, (int64_t)n * lout[l],
                                     reinterpret_cast<float*>(wsb + w.mean[l]),
@@ -1701,7 +1701,7 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
       if (l == L - 1) part = std::max(part, (size_t)gw::red_chunks(n, lout[l]) * 2 * sizeof(double));  // its bias
       if (l == 0) continue;
       mg = std::max(mg, (size_t)n * ly.ci * lin[l] * 4);
-      const int nblk = gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr);
+      const int nblk = gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD);
       part = std::max(part, (size_t)ly.ci * nblk * 2 * sizeof(double));
     }
     b.g[0] = take(mg);
@@ -1827,7 +1827,7 @@ static int backward_fused(const gw_model* m, int n, const float* x, const float*
            gw::launch_conv_f32m(p, {wa[l], nullptr, nullptr}, !tr, gw::EPI_BNBWD, st, top ? gw::PRO_NONE : gw::PRO_DZ, &t));
     const LayerD& lo = m->layers[l - 1];
     LAUNCH(nm("bn_bwd", "L", l - 1), st,
-           gw::launch_bnbwd_final(partial, gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr), ly.ci,
+           gw::launch_bnbwd_final(partial, gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD), ly.ci,
                                   (int64_t)n * lin[l], dparams + lo.g, dparams + lo.be, st));
     g = gout;
   }

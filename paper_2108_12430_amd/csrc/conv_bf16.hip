@@ -391,7 +391,8 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, F32Train tr, int padc,
   constexpr int TNO = NPH * TN;
   constexpr bool OTILE = EPI != EPI_OUT && EPI != EPI_RESID_GAP && !OUT_F32;
   // the input tile's LDS is reused for the BF16 output tile [C_out][NPH*TN]
-  constexpr int TILE = (ROWS + 1) * RS > 16 * MTB * TNO ? (ROWS + 1) * RS : 16 * MTB * TNO;
+  constexpr int TST = EPI == EPI_STATS ? 2 * train_tile_floats(16 * MTB, TNO) : 16 * MTB * TNO;
+  constexpr int TILE = (ROWS + 1) * RS > TST ? (ROWS + 1) * RS : TST;
   // split operands (IN_F32S): a second tile of low terms, weights read per wave
   constexpr bool SPL = split_in(IN);
   static_assert(!SPL || (AM == 0 && CSP == 0 && OUT_F32), "split operands: FP32-output layers, AM = 0");
@@ -407,7 +408,6 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, F32Train tr, int padc,
   __shared__ __attribute__((aligned(16))) uint4 achunk[2 * ACH];
   __shared__ float cst[2][16 * MTB];
   __shared__ float wsum[4];
-  __shared__ double csum[EPI == EPI_STATS ? 4 : 1][16 * MTB][2];
 
   // block j computes output-channel tiles [ms MTB, (ms + 1) MTB), ms = j mod MS,
   // of the column tiles j / MS, j / MS + gridDim.x / MS, ... (gridDim.x is a
@@ -596,14 +596,7 @@ __global__ __launch_bounds__(256) void conv_mfma(ConvP p, F32Train tr, int padc,
     uint16_t* otile = tile;
     if (OTILE) __syncthreads();  // every wave is done reading the input tile
     if constexpr (EPI == EPI_STATS) {
-#pragma unroll
-      for (int mt = 0; mt < MTB; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          train_out<MTB, NPH, NTW, EPI>(p, tr, acc, csum[wave][16 * mt + 4 * lg + r], mt, r, o_lo + 16 * mt + 4 * lg + r,
-                                        b, col0 + wave * NTW * 16, ncol, lc);
-      __syncthreads();
-      train_sums<MTB>(csum, tr.partial, o_lo, p.Co, total, t, threadIdx.x);
+      train_epilogue<MTB, NPH, NTW, EPI>(p, tr, acc, reinterpret_cast<float*>(tile), b, col0, t, total, threadIdx.x);
       continue;  // one tile per block
     }
     float gsum = 0.0f;           // EPI_RESID_GAP: this lane's share of sum_o hw[o] y[o][t]
@@ -855,7 +848,7 @@ hipError_t launch_conv_bf16(const ConvP& p, bool tr, int epi, int src, hipStream
   k.epi = epi;
   const F32Train tt = t ? *t : F32Train{};
   k.in = src == SRC_RING ? IN_RING : (p.xh ? IN_BF16 : (p.wpk_lo ? (tt.in.bn.mean ? IN_F32A : IN_F32S) : IN_F32));
-  if (epi == EPI_STATS && (!tt.partial || !p.y || (g.nph == 2 && (p.Lout & 1 || reinterpret_cast<uintptr_t>(p.y) & 7))))
+  if (epi == EPI_STATS && (!tt.partial || !p.y || !train_epilogue_fits(p.Co, (p.Co + 15) / 16)))
     return hipErrorInvalidValue;
   k.out_f32 = (epi == EPI_OUT || p.yh == nullptr) ? 1 : 0;
   const bool res = epi == EPI_RESID_RELU || epi == EPI_RESID_GAP;

@@ -229,13 +229,13 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, F32Train 
   constexpr int KS = (KT * CIP + 15) / 16;
   constexpr int NA = NPH * MTB;
   constexpr int RSX = CSP ? rs(CSP) : 4, KSX = CSP ? (CSP + 15) / 16 : 0;
-  constexpr int TILE = (HALF ? 2 * HALF : ROWS) * RS;
+  constexpr bool SUMS = EPI == EPI_STATS || EPI == EPI_BNBWD;
+  constexpr int TIN = (HALF ? 2 * HALF : ROWS) * RS, TOUT = SUMS ? train_tile_floats(16 * MTB, TN * NPH) : 0;
+  constexpr int TILE = TIN > TOUT ? TIN : TOUT;
   static_assert(CSP == 0 || (SC == 1 && NPH == 1 && TN * RSX <= TILE), "the shortcut's tile reuses the input's");
   __shared__ __attribute__((aligned(16))) float tile[TILE];
   __shared__ double wsum[4];
   __shared__ float cb[PRO == PRO_NONE ? 1 : 6 * CIP];
-  constexpr bool SUMS = EPI == EPI_STATS || EPI == EPI_BNBWD;
-  __shared__ double csum[SUMS ? 4 : 1][16 * MTB][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lc = lane & 15, lg = lane >> 4;
   const int MS = MT / MTB, tiles = (ncol + TN - 1) / TN;
@@ -336,6 +336,10 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, F32Train 
       f32m_step<NA, NTW>(av, bv, acc);
     }
   }
+  if constexpr (SUMS) {
+    train_epilogue<MTB, NPH, NTW, EPI>(p, tr, acc, tile, b, col0, b * tiles + ct, (int)gridDim.x, tid);
+    return;
+  }
   // epilogue: lane (lc, lg) holds channels 16 mt + 4 lg + r of column c
   double gsum = 0.0;  // FP64: the pooled head's terms cancel
 #pragma unroll
@@ -343,11 +347,6 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, F32Train 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int o = 16 * (ms * MTB + m) + 4 * lg + r;
-      if constexpr (SUMS) {
-        train_out<MTB, NPH, NTW, EPI>(p, tr, acc, csum[wave][16 * m + 4 * lg + r], m, r, o, b,
-                                           col0 + wave * NTW * 16, ncol, lc);
-        continue;
-      }
       if (o >= p.Co) continue;
       float kb = 0.0f, ka = 1.0f;
       if (EPI == EPI_OUT) {
@@ -397,10 +396,6 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, F32Train 
         }
       }
     }
-  if constexpr (SUMS) {
-    __syncthreads();
-    train_sums<MTB>(csum, tr.partial, 16 * ms * MTB, p.Co, (int)(gridDim.x / MS), b * tiles + ct, tid);
-  }
   if constexpr (EPI == EPI_RESID_GAP) {
     // fixed-order reduction: lanes of a wave, then the four waves
     for (int off = 32; off > 0; off >>= 1) gsum += __shfl_down(gsum, off, 64);
@@ -438,12 +433,12 @@ __global__ __launch_bounds__(256) void conv_f32m(ConvP p, F32Frags fr, F32Train 
   /* DeepClean training, the reference network: activations taken from z as   \
      they are staged, statistics in the epilogue; adjoint convolutions whose  \
      input is dz and whose output is the next layer's dh */                   \
-  X(24, 1, 1, 7, 2, EPI_STATS, 0, 1, 4, PRO_NONE) \
+  X(24, 1, 1, 7, 2, EPI_STATS, 0, 1, 2, PRO_NONE) \
   X(8, 1, 1, 7, 2, EPI_STATS, 0, 1, 4, PRO_ACT) \
   X(16, 2, 1, 7, 2, EPI_STATS, 0, 2, 2, PRO_ACT) \
   X(32, 4, 1, 7, 2, EPI_STATS, 0, 4, 2, PRO_ACT) \
-  X(64, 2, 2, 4, 1, EPI_STATS, 0, 2, 2, PRO_ACT) \
-  X(32, 1, 2, 4, 1, EPI_STATS, 0, 1, 4, PRO_ACT) \
+  X(64, 2, 2, 4, 1, EPI_STATS, 0, 2, 1, PRO_ACT) \
+  X(32, 1, 2, 4, 1, EPI_STATS, 0, 1, 2, PRO_ACT) \
   X(16, 1, 2, 4, 1, EPI_STATS, 0, 1, 4, PRO_ACT) \
   X(8, 1, 2, 4, 1, EPI_STATS, 0, 1, 4, PRO_ACT) \
   X(8, 1, 1, 7, 1, EPI_OUT, 0, 1, 4, PRO_ACT) \
@@ -480,12 +475,12 @@ int conv_f32m_gap_parts(int Co, int Lout) {
   return (Lout + 127) / 128 * ((Co + 15) / 16 / 2);  // the pooled variant's column tiles x channel shares
 }
 
-int conv_f32m_blocks(int Ci, int Co, int n, int Lout, int k, int s, int pad, bool tr) {
+int conv_f32m_blocks(int Ci, int Co, int n, int Lout, int k, int s, int pad, bool tr, int epi) {
   const Geo g = make_geo(tr, k, s, pad, Lout);
   const int cip = f32m::cip4(Ci), mt = (Co + 15) / 16;
 #define GW_BLK(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW, PRO)                                       \
   if (cip == CIP && mt == MT && g.nph == NPH && g.kt == KT && g.sc == SC &&                         \
-      (EPI == EPI_STATS || EPI == EPI_BNBWD))                                                        \
+      EPI == epi)                                                                                   \
     return n * ((g.ncol + 64 * NTW - 1) / (64 * NTW));
   GW_F32M_SHAPES(GW_BLK)
 #undef GW_BLK
@@ -501,10 +496,8 @@ hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool tr, int epi,
   if (p.ldx && p.ldx != p.Lin) return hipErrorInvalidValue;
   const F32Train tt = t ? *t : F32Train{};
   if ((epi == EPI_STATS || epi == EPI_BNBWD) && (!tt.partial || !p.y)) return hipErrorInvalidValue;
-  // the training epilogues store whole columns of both phases
-  if ((epi == EPI_STATS || epi == EPI_BNBWD) && g.nph == 2 && (p.Lout & 1 || reinterpret_cast<uintptr_t>(p.y) & 7))
-    return hipErrorInvalidValue;
-  if (epi == EPI_BNBWD && (!tt.z || (g.nph == 2 && reinterpret_cast<uintptr_t>(tt.z) & 7))) return hipErrorInvalidValue;
+  if ((epi == EPI_STATS || epi == EPI_BNBWD) && !train_epilogue_fits(p.Co, (p.Co + 15) / 16)) return hipErrorInvalidValue;
+  if (epi == EPI_BNBWD && !tt.z) return hipErrorInvalidValue;
   if (pro == PRO_DZ && !tt.in.z) return hipErrorInvalidValue;
   const int cip = f32m::cip4(p.Ci), mt = (p.Co + 15) / 16, csp = res ? f32m::cip4(p.Cs) : 0;
 #define GW_LAUNCH(CIP, MT, NPH, KT, SC, EPI, CSP, MTB, NTW, PRO)                                                       \

@@ -344,7 +344,8 @@ struct F32Frags {
   const float* ws;   // the 1x1 shortcut's (residual epilogues)
   double* gap_part;  // EPI_RESID_GAP: per-block partial sums of the pooled head
 };
-int conv_f32m_blocks(int Ci, int Co, int n, int Lout, int k, int s, int pad, bool tr);  // blocks (= partials)
+// blocks (= partials) of EPI_STATS or EPI_BNBWD
+int conv_f32m_blocks(int Ci, int Co, int n, int Lout, int k, int s, int pad, bool tr, int epi);
 hipError_t launch_conv_f32m(const ConvP& p, const F32Frags& f, bool transposed, int epi, hipStream_t st,
                             int pro = PRO_NONE, const F32Train* t = nullptr);
 bool conv_bf16_supported(int Ci, int Co, int k, int stride, bool transposed);
