@@ -1678,7 +1678,7 @@ struct BwWs {
   size_t partial = 0;
   size_t wg = 0;
   size_t wf32 = 0, wa32 = 0;  // FP32 matrix-core fragments: forward (recomputation) and adjoint
-  std::vector<size_t> wgp;    // the reference network's weight-gradient partials, per layer
+  std::vector<size_t> dh;     // the reference network: dh of layers 0 .. 7
   size_t total = 0;
 };
 
@@ -1693,19 +1693,19 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
     return o;
   };
   if (m->fused) {
-    size_t mg = 256, part = 256;
+    size_t part = 256;
+    std::vector<int> Lp(L);
     for (int l = 0; l < L; ++l) {
       const LayerD& ly = m->layers[l];
       const bool tr = ly.type == GW_LAYER_CONVT;
-      b.wgp.push_back(take(4 * gw::wgrad2_partial_floats(l, n, tr ? lin[l] : lout[l])));
-      if (l == L - 1) part = std::max(part, (size_t)gw::red_chunks(n, lout[l]) * 2 * sizeof(double));  // its bias
+      Lp[l] = tr ? lin[l] : lout[l];
+      if (l + 1 < L) b.dh.push_back(take((size_t)n * ly.co * lout[l] * 4));
       if (l == 0) continue;
-      mg = std::max(mg, (size_t)n * ly.ci * lin[l] * 4);
-      const int nblk = gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD);
+      const int nblk =
+          gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD);
       part = std::max(part, (size_t)ly.ci * nblk * 2 * sizeof(double));
     }
-    b.g[0] = take(mg);
-    b.g[1] = take(mg);
+    b.wg = take(gw::wgrad2_scratch_bytes(n, Lp.data()));
     b.partial = take(part);
     b.wa32 = take(f32_conv_bytes(m, true));
     b.total = off;
@@ -1760,9 +1760,10 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
 
 // The reference network's backward.  Each adjoint convolution takes dz of its
 // layer from (dh, z) as it stages its input, turns its output into dh of the
-// layer before and sums that layer's (dh, dh xhat); each weight gradient takes
-// dz and the activations the same way.  FP32 products and sums in both
-// precisions (the split-BF16 variant differs in the forward's convolutions).
+// layer before and sums that layer's (dh, dh xhat); the weight gradients take
+// dz and the activations the same way, all layers in one launch at the end.
+// FP32 products and sums in both precisions (the split-BF16 variant differs in
+// the forward's convolutions).
 static int backward_fused(const gw_model* m, int n, const float* x, const float* dnoise, const DcWs& w, const char* sv,
                           float* dparams, const BwWs& b, char* sc, const std::vector<int>& lin,
                           const std::vector<int>& lout, hipStream_t st) {
@@ -1771,9 +1772,9 @@ static int backward_fused(const gw_model* m, int n, const float* x, const float*
   auto z_of = [&](int l) { return reinterpret_cast<const float*>(sv + w.z[l]); };
   std::vector<const float*> wa;
   LAUNCH("pack_f32m", st, pack_f32_convs(m, true, sc + b.wa32, wa, st));
-  gw::Wg2Tab red{};
+  gw::Wg2Args wg[9];
+  std::vector<gw::F32Range> zero;
   const float* g = dnoise;  // dL/dnoise, then dh of the layer at hand
-  int gi = 0;
   for (int l = L - 1; l >= 0; --l) {
     const LayerD& ly = m->layers[l];
     const bool tr = ly.type == GW_LAYER_CONVT, top = l == L - 1;
@@ -1784,26 +1785,22 @@ static int backward_fused(const gw_model* m, int n, const float* x, const float*
       dz.sum_dh = dparams + ly.be;
       dz.sum_dhx = dparams + ly.g;
       dz.invN = (float)(1.0 / ((double)n * lout[l]));
-    } else {
       // a conv bias followed by batch-statistics normalisation has an exactly
-      // zero gradient; the output conv's has not
-      LAUNCH(nm("bias_grad", "L", l), st,
-             gw::launch_channel_sum(dnoise, n, ly.co, lout[l], partial, gw::red_chunks(n, lout[l]), dparams + ly.b, st));
+      // zero gradient, and so have the running statistics (mean, then variance)
+      zero.push_back({dparams + ly.b, ly.co});
+      zero.push_back({dparams + ly.m, 2 * ly.co});
     }
     if (l) act.bn = bn_params(m, w, sv, l - 1);
     const float* a_in = l ? z_of(l - 1) : x;
-    gw::Wg2Args wg{};
-    wg.p = tr ? a_in : g;
-    wg.q = tr ? g : a_in;
-    wg.pbn = tr ? act : dz;
-    wg.qbn = tr ? dz : act;
-    wg.n = n;
-    wg.Lp = tr ? lin[l] : lout[l];
-    wg.Lq = tr ? lout[l] : lin[l];
-    wg.partial = reinterpret_cast<float*>(sc + b.wgp[l]);
-    wg.dw = dparams + ly.w;
-    LAUNCH(nm("wgrad", "L", l), st, gw::launch_wgrad2(l, wg, &red.e[red.n], st));
-    ++red.n;
+    const bool in_p = tr || top;  // the layer's input is P
+    wg[l].p = in_p ? a_in : g;
+    wg[l].q = in_p ? g : a_in;
+    wg[l].pbn = in_p ? act : dz;
+    wg[l].qbn = in_p ? dz : act;
+    wg[l].n = n;
+    wg[l].Lp = tr ? lin[l] : lout[l];
+    wg[l].Lq = tr ? lout[l] : lin[l];
+    wg[l].dw = dparams + ly.w;
     if (l == 0) break;
     gw::ConvP p{};
     p.n = n;
@@ -1815,8 +1812,7 @@ static int backward_fused(const gw_model* m, int n, const float* x, const float*
     p.stride = ly.s;
     p.pad = ly.p;
     p.x = g;
-    float* gout = reinterpret_cast<float*>(sc + b.g[gi]);
-    gi ^= 1;
+    float* gout = reinterpret_cast<float*>(sc + b.dh[l - 1]);
     p.y = gout;
     gw::F32Train t{};
     t.in = dz;
@@ -1826,12 +1822,13 @@ static int backward_fused(const gw_model* m, int n, const float* x, const float*
     LAUNCH(nm("dgrad", "L", l), st,
            gw::launch_conv_f32m(p, {wa[l], nullptr, nullptr}, !tr, gw::EPI_BNBWD, st, top ? gw::PRO_NONE : gw::PRO_DZ, &t));
     const LayerD& lo = m->layers[l - 1];
+    const int nblk = gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD);
     LAUNCH(nm("bn_bwd", "L", l - 1), st,
-           gw::launch_bnbwd_final(partial, gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD), ly.ci,
-                                  (int64_t)n * lin[l], dparams + lo.g, dparams + lo.be, st));
+           gw::launch_bnbwd_final(partial, nblk, ly.ci, (int64_t)n * lin[l], dparams + lo.g, dparams + lo.be, st));
     g = gout;
   }
-  LAUNCH("wgrad_reduce", st, gw::launch_wgrad2_reduce(red, st));
+  LAUNCH("wgrad", st,
+         gw::launch_wgrad2(wg, sc + b.wg, dparams + m->layers[L - 1].b, zero.data(), (int)zero.size(), st));
   return GW_OK;
 }
 
@@ -1923,7 +1920,6 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
   const char* sv = reinterpret_cast<const char*>(saved);
   char* sc = reinterpret_cast<char*>(scratch);
   if (m->fused) {
-    LAUNCH("zero", st, gw::launch_zero_floats(dparams, m->n_params, st));
     return backward_fused(m, n, x, dnoise, w, sv, dparams, b, sc, lin, lout, st);
   }
   double* partial = reinterpret_cast<double*>(sc + b.partial);

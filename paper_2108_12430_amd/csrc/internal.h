@@ -417,28 +417,25 @@ hipError_t launch_stats_final(const double* partial, int nblk, int C, int64_t N,
                               hipStream_t st);
 hipError_t launch_bnbwd_final(const double* partial, int nblk, int C, int64_t N, float* dgamma, float* dbeta,
                               hipStream_t st);
-// Weight gradients of the reference network's layer l (wgrad.hip): P and Q
-// raw, as z (activations) or as (dh, z) by the layer's position
+// Weight gradients of the reference network's nine layers (wgrad.hip), the
+// output conv's bias gradient, and zeros for the gradients that are zero.  P
+// is the layer's input for the transposed convs and the output conv, else its
+// output's gradient; Q the other.  The input is z (taken as activations), raw
+// for layer 0; the gradient (dh, z), raw for layer 8.
 struct Wg2Args {
   const float* p;
   const float* q;
   BnBwdP pbn, qbn;
   int n, Lp, Lq;
-  float* partial;  // wgrad2_partial_floats
   float* dw;
 };
-struct Wg2Red {
-  const float* partial;
-  float* dw;
-  int nw, G, blocks;
-};
-struct Wg2Tab {
+struct F32Range {
+  float* p;
   int n;
-  Wg2Red e[9];
 };
-size_t wgrad2_partial_floats(int l, int n, int Lp);
-hipError_t launch_wgrad2(int l, const Wg2Args& a, Wg2Red* red, hipStream_t st);
-hipError_t launch_wgrad2_reduce(const Wg2Tab& t, hipStream_t st);
+size_t wgrad2_scratch_bytes(int n, const int* Lp);  // Lp: P's length per layer
+hipError_t launch_wgrad2(const Wg2Args (&a)[9], void* scratch, float* dbias, const F32Range* zero, int nzero,
+                         hipStream_t st);
 size_t wgrad_scratch_bytes(int n, int Lp, int nw);
 // LDS per block: 4*(Ca*64 + Cc*(stride*63 + k)) bytes, must be <= 64 KiB.
 hipError_t launch_wgrad(const float* P, int Ca, int Lp, const float* Q, int Cc, int Lq, int n,

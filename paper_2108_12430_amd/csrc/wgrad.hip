@@ -21,10 +21,18 @@
 // Block sums are written as FP32 partials; one launch adds the partials of
 // every layer in FP64 in a fixed order.
 //
-// Measured, batch 32 x 21 x 32768, all nine layers with their reductions: 384
-// us with operands read from memory as they are and a launch pair per layer
-// for the reduction, 302 us here, without the 190 us that wrote dz and the
-// activations.
+// One launch runs every layer: its 512 blocks (two per CU) are shared out by
+// the layers' work, so that they end together, a block's partials stay few,
+// and no layer pays for a launch of its own to fill and drain.  No wave holds
+// more than ten accumulator tiles: 128 registers, so that two blocks of eight
+// waves share a CU, hold them and a chunk's loads without spilling.
+//
+// Measured, batch 32 x 21 x 32768: nine launches with operands read from memory
+// as they are and a launch pair per layer for the reduction 384 us (and 190 us
+// more to write dz and the activations); nine launches of this kernel's
+// blocks, with the reduction, the output conv's bias sum and the zero fill
+// 314 us; one launch and its reduction 195 us (matrix cores 70 us, memory at
+// copy rate 106 us).
 #include "internal.h"
 
 namespace gw {
@@ -34,13 +42,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 enum Mode : int { RAW = 0, ACT = 1, DZ = 2 };
 
-template <int CA_, int CC_, int S_, int WT_, int NW_, int PM_, int QM_>
+// CA rows, CC columns' channels, stride, chunk of times, the operands' modes
+template <int CA_, int CC_, int S_, int WT_, int PM_, int QM_>
 struct Cfg {
-  static constexpr int CA = CA_, CC = CC_, S = S_, WT = WT_, NW = NW_, PM = PM_, QM = QM_;
+  static constexpr int CA = CA_, CC = CC_, S = S_, WT = WT_, NW = 8, PM = PM_, QM = QM_;
   static constexpr int NTHR = 64 * NW;
   static constexpr int NK = CC * 7, MA = (CA + 15) / 16, NB = (NK + 15) / 16;
   static constexpr int KC = WT / 16;                    // K steps per chunk
-  static constexpr int NS = KC < NW ? KC : NW;          // K slices
+  static constexpr int NT = MA * NB;                    // accumulator tiles: at most ten a wave
+  static constexpr int NS = NT > 40 ? 1 : NT > 20 ? 2 : NT > 10 ? 4 : KC < NW ? KC : NW;  // K slices
   static constexpr int NGR = NW / NS;                   // column groups
   static constexpr int NBW = (NB + NGR - 1) / NGR;      // column tiles per wave
   static constexpr int PS = WT + 4;                     // P row stride (floats): an odd multiple of 16 bytes
@@ -52,6 +62,11 @@ struct Cfg {
   static constexpr int LDS = STAGE > RED ? STAGE : RED;
   static constexpr int IP = (CA * WT / 4 + NTHR - 1) / NTHR;
   static constexpr int IQ = (CC * QW / 4 + NTHR - 1) / NTHR;
+  // The output conv has one row and eight channels: the products are the same
+  // with the operands exchanged and the taps in reverse, and fill 8 x 7 of one
+  // tile instead of 1 x 56 of four.
+  static constexpr bool REV = CC == 1;
+  static_assert(!REV || QW / 4 <= NTHR, "one item of Q per thread");
   static_assert(WT % 16 == 0 && KC % NS == 0 && NW % NS == 0 && (NS & (NS - 1)) == 0, "slices");
 };
 
@@ -62,8 +77,13 @@ struct Opnd {
 
 struct P2 {
   Opnd p, q;
-  int n, Lp, Lq, tchunks, nchunk;
+  int Lp, Lq, tchunks, nchunk, blocks;
   float* partial;  // [blocks][CA * NK]
+  double* bsum;    // [blocks] sums of Q (REV)
+};
+
+struct All {
+  P2 e[9];
 };
 
 // constants of a transformed operand, [6][C]
@@ -110,11 +130,10 @@ __device__ __forceinline__ float4 transform(float4 v, const float4& z, const flo
 
 }  // namespace wg2
 
+// block bi of layer p
 template <class K>
-__global__ __launch_bounds__(K::NTHR, 4) void wgrad2(wg2::P2 p) {
+__device__ __forceinline__ void wgrad2_body(const wg2::P2& p, int bi, float* lds, float* cp, float* cq) {
   using namespace wg2;
-  __shared__ __attribute__((aligned(16))) float lds[K::LDS];
-  __shared__ float cp[K::PM == RAW ? 1 : 6 * K::CA], cq[K::QM == RAW ? 1 : 6 * K::CC];
   float* Ps = lds;
   float* Qs = lds + K::CA * K::PS;
   const int tid = threadIdx.x;
@@ -176,23 +195,26 @@ __global__ __launch_bounds__(K::NTHR, 4) void wgrad2(wg2::P2 p) {
   static_assert(K::MA == 1 || K::CA % 16 == 0, "whole row tiles");
   const float* ap = Ps + (lr < K::CA ? lr : K::CA - 1) * K::PS + 4 * lk;
   // sample of (t, tap j): S t - 3 + j, staged from S t0 - 4 on
-  const float* bp[K::NBW];
+  int bp[K::NBW];
 #pragma unroll
   for (int u = 0; u < K::NBW; ++u) {
     const int n0 = 16 * (grp * K::NBW + u) + lr, nn = n0 < K::NK ? n0 : K::NK - 1, c = nn / 7, j = nn - 7 * c;
-    bp[u] = Qs + (K::S == 2 ? (2 * c + ((1 + j) & 1)) * K::QP + (1 + j) / 2 : c * K::QP + 1 + j) + 4 * lk;
+    bp[u] = (K::S == 2 ? (2 * c + ((1 + j) & 1)) * K::QP + (1 + j) / 2 : c * K::QP + 1 + j) + 4 * lk;
   }
   f32x4 acc[K::MA][K::NBW];
 #pragma unroll
   for (int m = 0; m < K::MA; ++m)
 #pragma unroll
     for (int u = 0; u < K::NBW; ++u) acc[m][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int G = gridDim.x;
-  const int c0 = (int)((int64_t)p.nchunk * blockIdx.x / G), c1 = (int)((int64_t)p.nchunk * (blockIdx.x + 1) / G);
+  const int G = p.blocks;
+  const int c0 = (int)((int64_t)p.nchunk * bi / G), c1 = (int)((int64_t)p.nchunk * (bi + 1) / G);
+  double bsum = 0.0;  // REV: this thread's share of the sum of Q
   if (c0 < c1) fetch(c0);
   for (int chunk = c0; chunk < c1; ++chunk) {
     __syncthreads();  // the constants are there; the previous chunk's reads are done
     stage(chunk);
+    if (K::REV && tid >= 1 && tid <= PC)  // the chunk's own times, without the taps' reach
+      bsum += ((double)qv[0].x + (double)qv[0].y) + ((double)qv[0].z + (double)qv[0].w);
     __syncthreads();
     if (chunk + 1 < c1) fetch(chunk + 1);  // in flight during this chunk's MFMAs
 #pragma unroll 1
@@ -205,7 +227,7 @@ __global__ __launch_bounds__(K::NTHR, 4) void wgrad2(wg2::P2 p) {
         if (K::NGR > 1 && grp * K::NBW + u >= K::NB) break;  // wave-uniform
         float bv[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bv[e] = bp[u][16 * ks + e];
+        for (int e = 0; e < 4; ++e) bv[e] = Qs[bp[u] + 16 * ks + e];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -213,6 +235,18 @@ __global__ __launch_bounds__(K::NTHR, 4) void wgrad2(wg2::P2 p) {
             acc[m][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(reinterpret_cast<const float*>(&av[m])[e], bv[e],
                                                              acc[m][u], 0, 0, 0);
       }
+    }
+  }
+  if (K::REV) {
+    __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) bsum += __shfl_down(bsum, off, 64);
+    double* bs = reinterpret_cast<double*>(lds);
+    if (lane == 0) bs[wave] = bsum;
+    __syncthreads();
+    if (tid == 0) {
+      double t = bs[0];
+      for (int w = 1; w < K::NW; ++w) t += bs[w];
+      p.bsum[bi] = t;
     }
   }
   // the slices' sums, a fixed tree: the upper half hands over to the lower
@@ -236,7 +270,7 @@ __global__ __launch_bounds__(K::NTHR, 4) void wgrad2(wg2::P2 p) {
   }
   if (slice > 0) return;
   // D[row = 4 lk + r][col = lr]: weight (a, n)
-  float* out = p.partial + (int64_t)blockIdx.x * (K::CA * K::NK);
+  float* out = p.partial + (int64_t)bi * (K::CA * K::NK);
 #pragma unroll
   for (int m = 0; m < K::MA; ++m)
 #pragma unroll
@@ -245,19 +279,103 @@ __global__ __launch_bounds__(K::NTHR, 4) void wgrad2(wg2::P2 p) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int a = 16 * m + 4 * lk + r;
-        if (a < K::CA && nn < K::NK) out[a * K::NK + nn] = acc[m][u][r];
+        if (a < K::CA && nn < K::NK) out[a * K::NK + (K::REV ? K::NK - 1 - nn : nn)] = acc[m][u][r];
       }
     }
 }
 
-// Sum of every layer's partials, one launch: a block takes 64 weights of one
-// layer, its four waves a quarter of the partials each (in order), FP64.
-__global__ __launch_bounds__(256) void wgrad2_reduce(Wg2Tab t) {
+namespace wg2 {
+typedef Cfg<8, 21, 2, 128, DZ, RAW> C0;
+typedef Cfg<16, 8, 2, 256, DZ, ACT> C1;
+typedef Cfg<32, 16, 2, 128, DZ, ACT> C2;
+typedef Cfg<64, 32, 2, 64, DZ, ACT> C3;
+typedef Cfg<64, 32, 2, 64, ACT, DZ> C4;
+typedef Cfg<32, 16, 2, 128, ACT, DZ> C5;
+typedef Cfg<16, 8, 2, 256, ACT, DZ> C6;
+typedef Cfg<8, 8, 2, 256, ACT, DZ> C7;
+typedef Cfg<8, 1, 1, 512, ACT, RAW> C8;
+
+// each layer's share of the 512 blocks, from its blocks' run times in the
+// common launch (batch 32 x 21 x 32768: all end within 163 .. 193 us)
+constexpr int kShare[9] = {124, 27, 44, 58, 64, 53, 35, 51, 56};
+
+constexpr int mx(int a, int b) { return a > b ? a : b; }
+constexpr int LDS =
+    mx(mx(mx(mx(C0::LDS, C1::LDS), mx(C2::LDS, C3::LDS)), mx(mx(C4::LDS, C5::LDS), mx(C6::LDS, C7::LDS))), C8::LDS);
+static_assert(LDS * 4 + 12 * 64 * 4 <= 80 * 1024, "two blocks per CU");
+
+struct Geo2 {
+  int wt, ca, nk;
+};
+template <class K>
+constexpr Geo2 geo() {
+  return {K::WT, K::CA, K::NK};
+}
+constexpr Geo2 kGeo[9] = {geo<C0>(), geo<C1>(), geo<C2>(), geo<C3>(), geo<C4>(), geo<C5>(), geo<C6>(), geo<C7>(), geo<C8>()};
+
+int64_t chunks(int l, int n, int Lp) { return (int64_t)n * ((Lp + kGeo[l].wt - 1) / kGeo[l].wt); }
+int blocks(int l, int n, int Lp) { return (int)std::min<int64_t>(chunks(l, n, Lp), kShare[l]); }
+}  // namespace wg2
+
+__global__ __launch_bounds__(512, 4) void wgrad2(wg2::All t) {
+  using namespace wg2;
+  __shared__ __attribute__((aligned(16))) float lds[wg2::LDS];
+  __shared__ float cp[6 * 64], cq[6 * 64];
+  int bi = blockIdx.x, s = 0;
+  while (bi >= t.e[s].blocks) bi -= t.e[s++].blocks;  // block-uniform
+#define GW_SUB(i, K) \
+  case i: wgrad2_body<K>(t.e[i], bi, lds, cp, cq); break;
+  switch (s) {
+    GW_SUB(0, C0)
+    GW_SUB(1, C1)
+    GW_SUB(2, C2)
+    GW_SUB(3, C3)
+    GW_SUB(4, C4)
+    GW_SUB(5, C5)
+    GW_SUB(6, C6)
+    GW_SUB(7, C7)
+    GW_SUB(8, C8)
+  }
+#undef GW_SUB
+}
+
+// Sums of the partials, one launch: a block takes 64 weights of one layer, its four waves a quarter of the partials each (in order), FP64.
+// The last block adds the output conv's bias sums and clears the gradients
+// that are exactly zero: the biases under batch normalisation and the running
+// statistics.
+struct Wg2Red {
+  const float* partial;
+  float* dw;
+  int nw, G, blocks;
+};
+struct Wg2Zero {
+  float* p;
+  int n;
+};
+struct Wg2RedTab {
+  Wg2Red e[9];
+  const double* bsum;
+  float* db;
+  int nb;
+  Wg2Zero zero[16];
+};
+__global__ __launch_bounds__(256) void wgrad2_reduce(Wg2RedTab t) {
   __shared__ double s[4][64];
   int blk = blockIdx.x, l = 0;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (blk == (int)gridDim.x - 1) {
+    for (int z = 0; z < 16; ++z)
+      for (int i = threadIdx.x; i < t.zero[z].n; i += 256) t.zero[z].p[i] = 0.0f;
+    if (threadIdx.x == 0) {
+      double acc = 0.0;
+      for (int g = 0; g < t.nb; ++g) acc += t.bsum[g];
+      *t.db = (float)acc;
+    }
+    return;
+  }
   while (blk >= t.e[l].blocks) blk -= t.e[l++].blocks;
   const Wg2Red& q = t.e[l];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blk * 64 + lane;
+  const int e = blk * 64 + lane;
   const int g0 = q.G * wave / 4, g1 = q.G * (wave + 1) / 4;
   double acc = 0.0;
   if (e < q.nw) {
@@ -276,71 +394,51 @@ __global__ __launch_bounds__(256) void wgrad2_reduce(Wg2Tab t) {
   if (wave == 0 && e < q.nw) q.dw[e] = (float)(((s[0][lane] + s[1][lane]) + s[2][lane]) + s[3][lane]);
 }
 
-namespace wg2 {
-// per layer of the reference network; chunks of about 35 KB, two blocks per CU
-// (one of 16 waves for the 64-channel layers, whose partials are the largest)
-typedef Cfg<8, 21, 2, 128, 8, DZ, RAW> L0;
-typedef Cfg<16, 8, 2, 256, 8, DZ, ACT> L1;
-typedef Cfg<32, 16, 2, 128, 8, DZ, ACT> L2;
-typedef Cfg<64, 32, 2, 64, 16, DZ, ACT> L3;
-typedef Cfg<64, 32, 2, 64, 16, ACT, DZ> L4;
-typedef Cfg<32, 16, 2, 128, 8, ACT, DZ> L5;
-typedef Cfg<16, 8, 2, 256, 8, ACT, DZ> L6;
-typedef Cfg<8, 8, 2, 256, 8, ACT, DZ> L7;
-typedef Cfg<1, 8, 1, 512, 8, RAW, ACT> L8;
+static size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-template <class K>
-int blocks(int n, int Lp) {
-  const int64_t chunks = (int64_t)n * ((Lp + K::WT - 1) / K::WT);
-  return (int)std::min<int64_t>(chunks, K::NW == 16 ? 256 : 512);
+// Lp: per layer, the length of its P (the conv's output, the transposed
+// conv's input)
+size_t wgrad2_scratch_bytes(int n, const int* Lp) {
+  size_t b = 0;
+  for (int l = 0; l < 9; ++l) b += up256(4 * (size_t)wg2::blocks(l, n, Lp[l]) * wg2::kGeo[l].ca * wg2::kGeo[l].nk);
+  return b + up256(8 * (size_t)wg2::blocks(8, n, Lp[8]));
 }
 
-template <class K>
-hipError_t launch(const Wg2Args& a, Wg2Red* red, hipStream_t st) {
-  P2 p{};
-  p.p = {a.p, a.pbn};
-  p.q = {a.q, a.qbn};
-  p.n = a.n;
-  p.Lp = a.Lp;
-  p.Lq = a.Lq;
-  p.tchunks = (a.Lp + K::WT - 1) / K::WT;
-  const int64_t chunks = (int64_t)a.n * p.tchunks;
-  if (chunks > (int64_t)1 << 30) return hipErrorInvalidValue;
-  p.nchunk = (int)chunks;
-  p.partial = a.partial;
-  const int G = blocks<K>(a.n, a.Lp);
-  hipLaunchKernelGGL(wgrad2<K>, dim3(G), dim3(K::NTHR), 0, st, p);
-  *red = {a.partial, a.dw, K::CA * K::NK, G, (K::CA * K::NK + 63) / 64};
-  return hipGetLastError();
-}
-}  // namespace wg2
-
-#define GW_WG2(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
-
-size_t wgrad2_partial_floats(int l, int n, int Lp) {
-  switch (l) {
-#define GW_CASE(i) \
-  case i: return (size_t)wg2::blocks<wg2::L##i>(n, Lp) * (wg2::L##i::CA * wg2::L##i::NK);
-    GW_WG2(GW_CASE)
-#undef GW_CASE
-    default: return 0;
+hipError_t launch_wgrad2(const Wg2Args (&a)[9], void* scratch, float* dbias, const F32Range* zero, int nzero,
+                         hipStream_t st) {
+  using namespace wg2;
+  All t{};
+  Wg2RedTab r{};
+  if (nzero > 16) return hipErrorInvalidValue;
+  char* at = reinterpret_cast<char*>(scratch);
+  int grid = 0, rgrid = 1;
+  for (int l = 0; l < 9; ++l) {
+    const Wg2Args& w = a[l];
+    const Geo2& g = kGeo[l];
+    const int64_t nch = chunks(l, w.n, w.Lp);
+    if (nch > (int64_t)1 << 30) return hipErrorInvalidValue;
+    P2& p = t.e[l];
+    p.p = {w.p, w.pbn};
+    p.q = {w.q, w.qbn};
+    p.Lp = w.Lp;
+    p.Lq = w.Lq;
+    p.tchunks = (w.Lp + g.wt - 1) / g.wt;
+    p.nchunk = (int)nch;
+    p.blocks = blocks(l, w.n, w.Lp);
+    p.partial = reinterpret_cast<float*>(at);
+    const int nw = g.ca * g.nk;
+    at += up256(4 * (size_t)p.blocks * nw);
+    grid += p.blocks;
+    r.e[l] = {p.partial, w.dw, nw, p.blocks, (nw + 63) / 64};
+    rgrid += r.e[l].blocks;
   }
-}
-
-hipError_t launch_wgrad2(int l, const Wg2Args& a, Wg2Red* red, hipStream_t st) {
-  switch (l) {
-#define GW_CASE(i) \
-  case i: return wg2::launch<wg2::L##i>(a, red, st);
-    GW_WG2(GW_CASE)
-#undef GW_CASE
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t launch_wgrad2_reduce(const Wg2Tab& t, hipStream_t st) {
-  int blocks = 0;
-  for (int l = 0; l < t.n; ++l) blocks += t.e[l].blocks;
-  hipLaunchKernelGGL(wgrad2_reduce, dim3(blocks), dim3(256), 0, st, t);
+  t.e[8].bsum = reinterpret_cast<double*>(at);
+  r.bsum = t.e[8].bsum;
+  r.db = dbias;
+  r.nb = t.e[8].blocks;
+  for (int z = 0; z < nzero; ++z) r.zero[z] = {zero[z].p, zero[z].n};
+  hipLaunchKernelGGL(wgrad2, dim3(grid), dim3(512), 0, st, t);
+  hipLaunchKernelGGL(wgrad2_reduce, dim3(rgrid), dim3(256), 0, st, r);
   return hipGetLastError();
 }
 
