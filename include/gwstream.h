@@ -425,7 +425,7 @@ int gw_bandpass_mse(int32_t n, int32_t W, float fs, float f_lo, float f_hi, cons
  * harnesses that forbid hipMalloc).  Same arguments and results as
  * gw_bandpass_mse (the same kernels, so bitwise the same outputs) without the
  * workspace: the projection scratch is a library-owned static device array of
- * 1 MiB per GPU, held until the process ends, so n x (number of band bins)
+ * 5 MiB per GPU, held until the process ends, so n x (number of band bins)
  * must not exceed 131072 (else GW_EINVAL, nothing enqueued).  The call
  * allocates nothing; the first call on a device looks up that device's copy
  * of the array.  Calls that overlap on one GPU (concurrent streams, or

@@ -2055,7 +2055,7 @@ extern "C" int gw_bandpass_workspace(int32_t n, int32_t W, float fs, float f_lo,
   if (!bytes || n < 1) return fail(GW_EINVAL, "bad argument");
   int lo, hi;
   CHK(band(W, fs, f_lo, f_hi, &lo, &hi));
-  *bytes = r256(gw::bandpass_ws_floats(n, W, hi - lo + 1) * sizeof(float));
+  *bytes = r256(gw::bandpass_ws_bytes(n, W, hi - lo + 1));
   return GW_OK;
 }
 
@@ -2065,23 +2065,25 @@ extern "C" int gw_bandpass_mse(int32_t n, int32_t W, float fs, float f_lo, float
   if (n < 1 || !strain || !noise || !ws || (!loss && !dnoise)) return fail(GW_EINVAL, "bad argument");
   int lo, hi;
   CHK(band(W, fs, f_lo, f_hi, &lo, &hi));
-  if (ws_bytes < gw::bandpass_ws_floats(n, W, hi - lo + 1) * sizeof(float))
+  if (ws_bytes < gw::bandpass_ws_bytes(n, W, hi - lo + 1))
     return fail(GW_EINVAL, "workspace too small");
-  LAUNCH("bandpass", S(hip_stream), gw::launch_bandpass(n, W, lo, hi, strain, noise, reinterpret_cast<float*>(ws), loss, dnoise,
+  LAUNCH("bandpass", S(hip_stream), gw::launch_bandpass(n, W, lo, hi, strain, noise, ws, loss, dnoise,
                              S(hip_stream)));
   return GW_OK;
 }
 
 // ---------------------------------------------------------------------------
 // Band-passed MSE without allocation.  The projection scratch of
-// gw_bandpass_mse (n x bins (cos, sin) pairs) lives in a file-scope device
-// array: every GPU the library runs on holds one copy until the process ends.
+// gw_bandpass_mse (n x bins (cos, sin) pairs, and their FP64 partial sums)
+// lives in a file-scope device array: every GPU the library runs on holds one copy until the process ends.
 // In host code `scratch` names a host-side stand-in, not device memory, so
 // the kernels get the address that hipGetSymbolAddress returns for the
 // stream's device (looked up once per device, with that device current).
 // ---------------------------------------------------------------------------
 namespace {
-constexpr size_t kNoAllocScratchBytes = size_t(1) << 20;
+constexpr size_t kNoAllocPairs = size_t(1) << 17;
+// a pair and its partial sums: 24 bytes, or the pair and 4 MiB for all partials
+constexpr size_t kNoAllocScratchBytes = 8 * kNoAllocPairs + (size_t(4) << 20);
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 std::mutex g_scratch_mu;
@@ -2117,16 +2119,16 @@ extern "C" int gw_bandpass_mse_noalloc(int32_t n, int32_t W, float fs, float f_l
   if (n < 1 || !strain || !noise || (!loss && !dnoise)) return fail(GW_EINVAL, "bad argument");
   int lo, hi;
   CHK(band(W, fs, f_lo, f_hi, &lo, &hi));
-  const size_t need = gw::bandpass_ws_floats(n, W, hi - lo + 1) * sizeof(float);
-  if (need > kNoAllocScratchBytes)
-    return fail(GW_EINVAL, "n x band bins = " + std::to_string((size_t)n * (hi - lo + 1)) +
+  const size_t pairs = (size_t)n * (hi - lo + 1);
+  if (pairs > kNoAllocPairs)
+    return fail(GW_EINVAL, "n x band bins = " + std::to_string(pairs) +
                                " exceeds the no-allocation scratch limit of " +
-                               std::to_string(kNoAllocScratchBytes / (2 * sizeof(float))));
+                               std::to_string(kNoAllocPairs));
+  if (gw::bandpass_ws_bytes(n, W, hi - lo + 1) > kNoAllocScratchBytes) return fail(GW_EINVAL, "scratch too small");
   void* ptr = nullptr;
   CHK(scratch_for_stream(S(hip_stream), &ptr));
-  // every (window, bin) pair the loss and gradient read is written first by
-  // this call's projection kernel, so nothing in the array needs clearing
-  HIPCHK(gw::launch_bandpass(n, W, lo, hi, strain, noise, reinterpret_cast<float*>(ptr), loss, dnoise,
+  // every value the kernels read from it is written first by this call, so nothing in the array needs clearing
+  HIPCHK(gw::launch_bandpass(n, W, lo, hi, strain, noise, ptr, loss, dnoise,
                              S(hip_stream)));
   return GW_OK;
 }

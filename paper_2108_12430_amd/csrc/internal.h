@@ -441,9 +441,9 @@ size_t wgrad_scratch_bytes(int n, int Lp, int nw);
 hipError_t launch_wgrad(const float* P, int Ca, int Lp, const float* Q, int Cc, int Lq, int n,
                         int k, int stride, int pad, void* scratch, float* dw, hipStream_t st);
 // workspace of the band-passed loss: the n x nb (cos, sin) projections
-size_t bandpass_ws_floats(int n, int W, int nb);
+size_t bandpass_ws_bytes(int n, int W, int nb);
 hipError_t launch_bandpass(int n, int W, int k_lo, int k_hi, const float* strain,
-                           const float* noise, float* proj, float* loss, float* dnoise,
+                           const float* noise, void* ws, float* loss, float* dnoise,
                            hipStream_t st);
 
 }  // namespace gw

@@ -31,25 +31,6 @@ __device__ __forceinline__ void block_sum2(double& a, double& b) {
   __syncthreads();
 }
 
-// Fixed-order block reduction of N doubles per thread over 256 lanes: the
-// same pairing tree as block_sum2 for every value, all values per round.
-template <int N>
-__device__ __forceinline__ void block_sum_n(double (&v)[N]) {
-  __shared__ double sv[N][256];
-#pragma unroll
-  for (int j = 0; j < N; ++j) sv[j][threadIdx.x] = v[j];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-#pragma unroll
-      for (int j = 0; j < N; ++j) sv[j][threadIdx.x] += sv[j][threadIdx.x + w];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int j = 0; j < N; ++j) v[j] = sv[j][0];
-  __syncthreads();
-}
-
 enum RMode { R_STATS = 0, R_BNBWD = 1, R_SUM = 2 };
 
 struct RedP {
@@ -659,188 +640,288 @@ hipError_t launch_wgrad(const float* P, int Ca, int Lp, const float* Q, int Cc, 
 //   P r[t]    = sum_k c_k (A_k cos_k[t] + B_k sin_k[t]),
 // with c_k = 2/W (c_k = 1/W for k = 0 or k = W/2).  Angles are reduced
 // exactly in integers, m = (k t mod W), before the sin/cos evaluation; the
-// index advances by a constant per step (one compare and subtract) instead
-// of a 64-bit division per sample.
+// index advances by a constant per step (one compare and subtract).
+//
+// Both directions are matrix products with the basis, which is evaluated in
+// registers where the matrix cores want it: a lane's (cos, sin) pair is its
+// element of two operands, and serves 16 windows a matrix instruction.
+//
+// Measured, 32 windows of 32768, 81 bins, loss and gradient: one thread per
+// (sample, bin) with vector FP64 sums, four windows a basis value 99 us;
+// these kernels 47 us.  Left: the basis evaluations, the FP64 products at
+// half of the vector FP32 rate (5 us), and three dependent launches.
 // ---------------------------------------------------------------------------
-// Projections A_k, B_k: block (x, y) takes bins [NB x, NB x + NB) of windows
-// [NBW y, NBW y + NBW), so each residual sample is read once per NB bins
-// and each basis value evaluated once per NBW windows.  A thread keeps FP64
-// running sums over samples t = tid, tid + 256, ... for every (window, bin)
-// of the block; one fixed block tree adds the threads' sums.
-template <int NBW, int NB>
-__global__ __launch_bounds__(256) void bp_project(const float* strain, const float* noise, int n, int nb, int W,
-                                                  int k_lo, float* proj) {
-  const int kb = blockIdx.x * NB, nbk = min(NB, nb - kb);
-  const int b0 = blockIdx.y * NBW, nbw = min(NBW, n - b0);
-  double acc[2 * NBW * NB];  // (A, B) of (window bb, bin q) at 2 (bb NB + q)
-#pragma unroll
-  for (int j = 0; j < 2 * NBW * NB; ++j) acc[j] = 0.0;
-  const float twoW = 2.0f / (float)W;
-  // m[q] = (k_lo + kb + q) t mod W for t = threadIdx.x, threadIdx.x + 256, ...
-  int m[NB], step[NB];
-#pragma unroll
-  for (int q = 0; q < NB; ++q) {
-    const int64_t k = k_lo + kb + q;
-    m[q] = (int)((k * threadIdx.x) % W);
-    step[q] = (int)((k * 256) % W);
+namespace bp {
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// k t mod W
+__device__ __forceinline__ int mulmod(int k, int t, int W) {
+  if (W < 1 << 24) {  // the product is exact, the quotient off by one at most
+    const double v = (double)k * (double)t;
+    const double r = fma(-floor(v * (1.0 / (double)W)), (double)W, v);
+    int m = (int)r;
+    if (m < 0) m += W;
+    return m >= W ? m - W : m;
   }
-  for (int t = threadIdx.x; t < W; t += 256) {
-    float r[NBW];
+  return (int)((int64_t)k * t % W);
+}
+
+}  // namespace bp
+
+// Projections: D[window][bin] += r[window][t] basis[t][bin] over a slice of the
+// samples, on v_mfma_f64_16x16x4_f64: FP32 residuals and basis values, exact
+// products, FP64 sums.  A block takes 16 bins (cos and sin) of 16 MT windows;
+// its eight waves take 16 samples each of every 128 of the slice, lane l
+// sample 4 (l / 16) + e in step e.  The waves' sums are added through LDS.
+template <int MT>
+__global__ __launch_bounds__(512) void bp_project(const float* strain, const float* noise, int n, int nb, int W,
+                                                  int k_lo, int S, double* partial) {
+  using namespace bp;
+  __shared__ double red[4][MT * 2 * 4 * 64];
+  const int tile = blockIdx.x / S, slice = blockIdx.x - tile * S;
+  const int b0 = blockIdx.y * 16 * MT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int rounds = (W + 127) / 128;
+  const int c0 = (int)((int64_t)rounds * slice / S), c1 = (int)((int64_t)rounds * (slice + 1) / S);
+  const bool vec = ((W & 3) | ((reinterpret_cast<uintptr_t>(strain) | reinterpret_cast<uintptr_t>(noise)) & 15)) == 0;
+  const int k = k_lo + min(16 * tile + lr, nb - 1);
+  int t = 128 * c0 + 16 * wave + 4 * lk;
+  int m = mulmod(k, t, W);
+  const int step = mulmod(k, 128, W);
+  f64x4 acc[MT][2];
 #pragma unroll
-    for (int bb = 0; bb < NBW; ++bb) {
-      const int64_t o = (int64_t)(b0 + (bb < nbw ? bb : 0)) * W + t;
-      r[bb] = strain[o] - noise[o];
-    }
+  for (int g = 0; g < MT; ++g) acc[g][0] = acc[g][1] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const float* sp[MT];
+  const float* np[MT];
 #pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      float sn, cs;
-      sincospif(twoW * (float)m[q], &sn, &cs);
+  for (int g = 0; g < MT; ++g) {  // rows past n read the last one; their sums are dropped
+    const int64_t o = (int64_t)min(b0 + 16 * g + lr, n - 1) * W;
+    sp[g] = strain + o;
+    np[g] = noise + o;
+  }
+  float r[MT][4], nx[MT][4];
+  auto load = [&](float (&v)[MT][4], int t) {
 #pragma unroll
-      for (int bb = 0; bb < NBW; ++bb) {
-        acc[2 * (bb * NB + q)] += (double)(r[bb] * cs);
-        acc[2 * (bb * NB + q) + 1] += (double)(r[bb] * sn);
+    for (int g = 0; g < MT; ++g) {
+      if (vec && t + 4 <= W) {
+        const float4 a = *reinterpret_cast<const float4*>(sp[g] + t), b = *reinterpret_cast<const float4*>(np[g] + t);
+        v[g][0] = a.x - b.x;
+        v[g][1] = a.y - b.y;
+        v[g][2] = a.z - b.z;
+        v[g][3] = a.w - b.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[g][e] = t + e < W ? sp[g][t + e] - np[g][t + e] : 0.0f;
       }
-      m[q] += step[q];
-      if (m[q] >= W) m[q] -= W;
     }
+  };
+  const float twoW = 2.0f / (float)W;
+  if (c0 < c1) load(nx, t);
+  for (int c = c0; c < c1; ++c, t += 128) {
+#pragma unroll
+    for (int g = 0; g < MT; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[g][e] = nx[g][e];
+    if (c + 1 < c1) load(nx, t + 128);
+    int me = m;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float sn, cs;
+      sincospif(twoW * (float)me, &sn, &cs);
+#pragma unroll
+      for (int g = 0; g < MT; ++g) {
+        acc[g][0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)r[g][e], (double)cs, acc[g][0], 0, 0, 0);
+        acc[g][1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)r[g][e], (double)sn, acc[g][1], 0, 0, 0);
+      }
+      me += k;
+      if (me >= W) me -= W;
+    }
+    m += step;
+    if (m >= W) m -= W;
   }
-  block_sum_n(acc);
-  if (threadIdx.x < NBW * NB) {
-    const int bb = threadIdx.x / NB, q = threadIdx.x - bb * NB;
-    if (bb < nbw && q < nbk) {
-      proj[((int64_t)(b0 + bb) * nb + kb + q) * 2 + 0] = (float)acc[2 * (bb * NB + q)];
-      proj[((int64_t)(b0 + bb) * nb + kb + q) * 2 + 1] = (float)acc[2 * (bb * NB + q) + 1];
-    }
+  // waves 4 .. 7 hand over to 0 .. 3, whose sums are added in wave order
+  auto slot = [&](int g, int q, int i) { return ((g * 2 + q) * 4 + i) * 64 + lane; };
+  if (wave >= 4)
+#pragma unroll
+    for (int g = 0; g < MT; ++g)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave - 4][slot(g, q, i)] = acc[g][q][i];
+  __syncthreads();
+  if (wave < 4)
+#pragma unroll
+    for (int g = 0; g < MT; ++g)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave][slot(g, q, i)] += acc[g][q][i];
+  __syncthreads();
+  // lane 16 lk + bin holds windows 4 i + lk in element i
+  for (int e = tid; e < MT * 512; e += 512) {
+    const int q = e & 1, bb = (e >> 1) % (16 * MT), bin = e / (32 * MT);
+    const int o = (((bb >> 4) * 2 + q) * 4 + ((bb & 15) >> 2)) * 64 + 16 * (bb & 3) + bin;
+    const int kk = 16 * tile + bin, b = b0 + bb;
+    if (kk < nb && b < n)
+      partial[(((int64_t)slice * nb + kk) * n + b) * 2 + q] = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
   }
 }
 
-__device__ __forceinline__ float bin_weight(int k, int W) {
-  return (k == 0 || 2 * k == W) ? 1.0f / (float)W : 2.0f / (float)W;
+// proj[bin][window][2] = the slices' sums, rounded once: a block takes 64
+// values, its four waves a quarter of the slices each, in order
+__global__ __launch_bounds__(256) void bp_final(const double* partial, int64_t nv, int S, float* proj) {
+  __shared__ double s[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int s1 = S * (wave + 1) / 4;
+  double acc = 0.0;
+  if (e < nv) {
+    int g = S * wave / 4;
+    for (; g + 8 <= s1; g += 8) {
+      double v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = partial[(int64_t)(g + j) * nv + e];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc += v[j];
+    }
+    for (; g < s1; ++g) acc += partial[(int64_t)g * nv + e];
+  }
+  s[wave][lane] = acc;
+  __syncthreads();
+  if (wave == 0 && e < nv) proj[e] = (float)(((s[0][lane] + s[1][lane]) + s[2][lane]) + s[3][lane]);
 }
 
-__global__ __launch_bounds__(256) void bp_loss(const float* proj, int n, int nb, int W, int k_lo,
-                                               float* loss) {
+// weight of bin k against the others': c_k W / 2, exact
+__device__ __forceinline__ float bin_weight(int k, int W) { return k == 0 || 2 * k == W ? 0.5f : 1.0f; }
+
+__device__ __forceinline__ void bp_loss_block(const float* proj, int n, int nb, int W, int k_lo, float* loss) {
   double s = 0.0, unused = 0.0;
-  for (int e = threadIdx.x; e < n * nb; e += 256) {
-    const int kk = e % nb;
-    const double a = proj[2 * e], b = proj[2 * e + 1];
-    s += (double)bin_weight(k_lo + kk, W) * (a * a + b * b);
+  const int64_t np = (int64_t)n * nb;
+  const double first = bin_weight(k_lo, W), last = bin_weight(k_lo + nb - 1, W);
+#pragma unroll 4
+  for (int64_t e = threadIdx.x; e < np; e += 256) {
+    const float2 v = reinterpret_cast<const float2*>(proj)[e];
+    s += (e < n ? first : e >= np - n ? last : 1.0) * ((double)v.x * v.x + (double)v.y * v.y);
   }
   block_sum2(s, unused);
-  if (threadIdx.x == 0) loss[0] = (float)(s / ((double)n * W));
+  if (threadIdx.x == 0) loss[0] = (float)(s * (2.0 / (double)W) / ((double)n * W));
 }
 
-// dL/dnoise[t] = scale * sum_k c_k (A_k cos_k[t] + B_k sin_k[t]).  Block
-// (x, y) covers samples [64 x, 64 x + 64) of windows [NBW y, NBW y + NBW);
-// its four waves take a quarter of the bins each (in order), evaluate each
-// bin's basis value once per sample for all of the windows, and their four
-// partial sums are added in wave order.  The windows' projections are staged
-// in LDS bin-major, [bin][window][2], so one bin's values for every window
-// are read with 16-byte loads (the same address across the wave: broadcast).
-template <int NBW>
+__global__ __launch_bounds__(256) void bp_loss(const float* proj, int n, int nb, int W, int k_lo, float* loss) {
+  bp_loss_block(proj, n, nb, W, k_lo, loss);
+}
+
+// dL/dnoise[window][t] = scale * sum over bins of weight (A cos[t] + B sin[t]),
+// on v_mfma_f32_16x16x4_f32: a wave takes 16 samples of 16 MT windows and four
+// bins a step; cos, sin, and alternate steps have their own sums.  The last
+// block of the first row computes the loss, if that is asked for.
+template <int MT>
 __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb, int W, int k_lo, float scale,
-                                               float* dnoise) {
-  static_assert(NBW % 2 == 0, "two windows per 16-byte load");
-  extern __shared__ __attribute__((aligned(16))) float sp[];  // [nb][NBW][2], then [4][NBW][64] partials
-  float* red = sp + (size_t)nb * NBW * 2;
-  const int b0 = blockIdx.y * NBW, nbw = min(NBW, n - b0);
-  for (int e = threadIdx.x; e < nb * NBW; e += 256) {
-    const int kk = e / NBW, bb = e - kk * NBW;
-    const bool on = bb < nbw;
-    const int64_t o = ((int64_t)(b0 + (on ? bb : 0)) * nb + kk) * 2;
-    sp[2 * e] = on ? proj[o] : 0.0f;
-    sp[2 * e + 1] = on ? proj[o + 1] : 0.0f;
+                                               float* dnoise, float* loss) {
+  using namespace bp;
+  if (loss && blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.y == 0) bp_loss_block(proj, n, nb, W, k_lo, loss);
+    return;
   }
-  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * 64 + lane;
-  const int k0 = nb * wave / 4, k1 = nb * (wave + 1) / 4;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int b0 = blockIdx.y * 16 * MT;
+  const int t = blockIdx.x * 64 + 16 * wave + lr, tc = min(t, W - 1);
+  int m = mulmod(min(k_lo + lk, W - 1), tc, W);
+  const int step = mulmod(4, tc, W);
   const float twoW = 2.0f / (float)W;
-  float acc[NBW];
+  const float2* src[MT];
 #pragma unroll
-  for (int bb = 0; bb < NBW; ++bb) acc[bb] = 0.0f;
-  if (t < W) {
-    int m = (int)(((int64_t)(k_lo + k0) * t) % W);
-    for (int kk = k0; kk < k1; ++kk) {
+  for (int g = 0; g < MT; ++g)
+    src[g] = reinterpret_cast<const float2*>(proj) + min(b0 + 16 * g + lr, n - 1);
+  f32x4 acc[MT][2][2];
+#pragma unroll
+  for (int g = 0; g < MT; ++g)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[g][q >> 1][q & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kk0 = 0; kk0 < nb; kk0 += 8) {
+    float2 v[2][MT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kk = kk0 + 4 * h + lk;
+      const float w = kk < nb ? bin_weight(k_lo + kk, W) : 0.0f;
+#pragma unroll
+      for (int g = 0; g < MT; ++g) {
+        const float2 p = src[g][(int64_t)min(kk, nb - 1) * n];
+        v[h][g] = kk < nb ? make_float2(w * p.x, w * p.y) : make_float2(0.f, 0.f);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
       float sn, cs;
       sincospif(twoW * (float)m, &sn, &cs);
-      const float wk = bin_weight(k_lo + kk, W);
-      const float4* q = reinterpret_cast<const float4*>(sp + kk * NBW * 2);
 #pragma unroll
-      for (int j = 0; j < NBW / 2; ++j) {
-        const float4 v = q[j];  // (A, B) of windows 2j, 2j + 1
-        acc[2 * j] = fmaf(wk, fmaf(v.x, cs, v.y * sn), acc[2 * j]);
-        acc[2 * j + 1] = fmaf(wk, fmaf(v.z, cs, v.w * sn), acc[2 * j + 1]);
+      for (int g = 0; g < MT; ++g) {
+        acc[g][h][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[h][g].x, cs, acc[g][h][0], 0, 0, 0);
+        acc[g][h][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[h][g].y, sn, acc[g][h][1], 0, 0, 0);
       }
-      m += t;
+      m += step;
       if (m >= W) m -= W;
     }
   }
-#pragma unroll
-  for (int bb = 0; bb < NBW; ++bb) red[(wave * NBW + bb) * 64 + lane] = acc[bb];
-  __syncthreads();
-  for (int e = threadIdx.x; e < NBW * 64; e += 256) {
-    const int bb = e >> 6, ln = e & 63, tt = blockIdx.x * 64 + ln;
-    if (bb < nbw && tt < W) {
-      float v = red[bb * 64 + ln];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) v += red[(w * NBW + bb) * 64 + ln];
-      dnoise[(int64_t)(b0 + bb) * W + tt] = scale * v;
-    }
-  }
-}
-
-// The same gradient for bands too wide to stage: one window per block, the
-// projections read from global memory.
-__global__ __launch_bounds__(256) void bp_grad_wide(const float* proj, int nb, int W, int k_lo,
-                                               float scale, float* dnoise) {
-  const int b = blockIdx.y;
-  const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= W) return;
-  const float* pr = proj + (int64_t)b * nb * 2;
-  const float twoW = 2.0f / (float)W;
-  // m = k t mod W for k = k_lo, k_lo + 1, ...: advances by t each bin
-  int m = (int)(((int64_t)k_lo * t) % W);
-  float acc = 0.0f;
-  for (int kk = 0; kk < nb; ++kk) {
-    const int k = k_lo + kk;
-    float sn, cs;
-    sincospif(twoW * (float)m, &sn, &cs);
-    acc = fmaf(bin_weight(k, W), fmaf(pr[2 * kk], cs, pr[2 * kk + 1] * sn), acc);
-    m += t;
-    if (m >= W) m -= W;
-  }
-  dnoise[(int64_t)b * W + t] = scale * acc;
+#pragma unroll
+  for (int g = 0; g < MT; ++g)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int b = b0 + 16 * g + 4 * lk + i;
+      if (b < n)
+        dnoise[(int64_t)b * W + t] =
+            scale * ((acc[g][0][0][i] + acc[g][1][0][i]) + (acc[g][0][1][i] + acc[g][1][1][i]));
+    }
 }
 
-size_t bandpass_ws_floats(int n, int W, int nb) {
-  (void)W;
-  return (size_t)n * nb * 2;
+namespace bp {
+// Windows per block: 32, or 16 where that covers them all.  Slices of the
+// samples: as many as make 512 blocks (16 waves a CU), of 128 samples at
+// least, in multiples of eight so that a slice's bin tiles, which read the same
+// samples, meet in one XCD's cache.
+int windows(int n) { return n > 16 ? 32 : 16; }
+int slices(int n, int W, int nb) {
+  const int64_t blocks = (int64_t)((nb + 15) / 16) * ((n + windows(n) - 1) / windows(n));
+  const int64_t s = std::max<int64_t>(1, std::min<int64_t>(512 / blocks, (W + 127) / 128));
+  return (int)(s >= 8 ? s / 8 * 8 : s);
+}
+}  // namespace bp
+
+// The slices' FP64 sums lie before the projections.  They take at most 16 n nb
+// bytes, or 4 MiB where there is more than one slice.
+size_t bandpass_ws_bytes(int n, int W, int nb) {
+  return 8 * (size_t)n * nb * (1 + 2 * (size_t)bp::slices(n, W, nb));
 }
 
 hipError_t launch_bandpass(int n, int W, int k_lo, int k_hi, const float* strain,
-                           const float* noise, float* proj, float* loss, float* dnoise,
+                           const float* noise, void* ws, float* loss, float* dnoise,
                            hipStream_t st) {
   const int nb = k_hi - k_lo + 1;
   if (nb <= 0) return hipErrorInvalidValue;
-  constexpr int PW = 4, PB = 1;  // windows and bins per projection block
-  hipLaunchKernelGGL((bp_project<PW, PB>), dim3((nb + PB - 1) / PB, (n + PW - 1) / PW), dim3(256), 0, st, strain,
-                     noise, n, nb, W, k_lo, proj);
-  if (loss) hipLaunchKernelGGL(bp_loss, dim3(1), dim3(256), 0, st, proj, n, nb, W, k_lo, loss);
+  const int nw = bp::windows(n), S = bp::slices(n, W, nb);
+  const int64_t nv = 2 * (int64_t)n * nb;
+  double* partial = reinterpret_cast<double*>(ws);
+  float* proj = reinterpret_cast<float*>(partial + S * nv);
+  const dim3 pg((nb + 15) / 16 * S, (n + nw - 1) / nw);  // 16-bin tiles x slices, windows
+  if (nw == 32)
+    hipLaunchKernelGGL(bp_project<2>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial);
+  else
+    hipLaunchKernelGGL(bp_project<1>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial);
+  hipLaunchKernelGGL(bp_final, dim3((unsigned)((nv + 63) / 64)), dim3(256), 0, st, partial, nv, S, proj);
   if (dnoise) {
-    const float scale = (float)(-2.0 / ((double)n * W));
-    // windows per block: all of a training batch's when the projections fit
-    // in LDS, else fewer; LDS = projections + the four waves' partial sums
-    const size_t per = sizeof(float) * (2 * (size_t)nb + 4 * 64);
-    if (32 * per <= 64 * 1024)
-      hipLaunchKernelGGL(bp_grad<32>, dim3((W + 63) / 64, (n + 31) / 32), dim3(256), 32 * per, st, proj, n, nb, W,
-                         k_lo, scale, dnoise);
-    else if (2 * per <= 64 * 1024)
-      hipLaunchKernelGGL(bp_grad<2>, dim3((W + 63) / 64, (n + 1) / 2), dim3(256), 2 * per, st, proj, n, nb, W,
-                         k_lo, scale, dnoise);
+    const float scale = (float)(-2.0 / ((double)n * W) * (2.0 / (double)W));
+    const dim3 gg((W + 63) / 64 + (loss ? 1 : 0), pg.y);
+    if (nw == 32)
+      hipLaunchKernelGGL(bp_grad<2>, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
     else
-      hipLaunchKernelGGL(bp_grad_wide, dim3((W + 255) / 256, n), dim3(256), 0, st, proj, nb, W, k_lo, scale,
-                         dnoise);
+      hipLaunchKernelGGL(bp_grad<1>, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
+  } else if (loss) {
+    hipLaunchKernelGGL(bp_loss, dim3(1), dim3(256), 0, st, proj, n, nb, W, k_lo, loss);
   }
   return hipGetLastError();
 }
