@@ -104,22 +104,48 @@ __global__ __launch_bounds__(256) void chan_partial(RedP p) {
   }
 }
 
-// Stage 2: one block per channel combines the chunk partials in a fixed tree.
+// Stage 2: one block per channel combines the chunk partials in a fixed tree:
+// a thread's, a wave's by lane exchange, the waves' in order.  Bound by latency
+// (the launch, one round trip to memory, the tree), so all of a thread's loads
+// go out at once and the tree has one barrier.
 // Outputs (by mode):
 //   R_STATS: o0 = mean, o1 = 1/sqrt(var + eps) (biased variance)
 //   R_BNBWD: o0 = dbeta = sum dh, o1 = dgamma = sum dh*xhat
 //   R_SUM:   o0 = sum
 template <int MODE>
-__global__ __launch_bounds__(256) void chan_final(const double* partial, int nchunk, int64_t N,
+__global__ __launch_bounds__(512) void chan_final(const double* partial, int nchunk, int64_t N,
                                                   float* o0, float* o1) {
-  const int c = blockIdx.x;
+  const int c = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double2* src = reinterpret_cast<const double2*>(partial) + (int64_t)c * nchunk;
   double s0 = 0.0, s1 = 0.0;
-  for (int q = threadIdx.x; q < nchunk; q += 256) {
-    s0 += partial[((int64_t)c * nchunk + q) * 2 + 0];
-    s1 += partial[((int64_t)c * nchunk + q) * 2 + 1];
+  for (int q = threadIdx.x; q < nchunk; q += 512 * 8) {
+    double2 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int e = q + 512 * j;
+      v[j] = src[e < nchunk ? e : nchunk - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (q + 512 * j < nchunk) {
+        s0 += v[j].x;
+        s1 += v[j].y;
+      }
   }
-  block_sum2(s0, s1);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    s0 += __shfl_down(s0, off, 64);
+    s1 += __shfl_down(s1, off, 64);
+  }
+  __shared__ double2 sw[8];
+  if (lane == 0) sw[wave] = make_double2(s0, s1);
+  __syncthreads();
   if (threadIdx.x != 0) return;
+#pragma unroll
+  for (int w = 1; w < 8; ++w) {
+    s0 += sw[w].x;
+    s1 += sw[w].y;
+  }
   if (MODE == R_STATS) {
     const double m = s0 / (double)N;
     double v = s1 / (double)N - m * m;
@@ -146,20 +172,20 @@ hipError_t launch_bn_stats(const float* z, int n, int C, int L, double* partial,
   p.nchunk = nchunk;
   p.partial = partial;
   hipLaunchKernelGGL(chan_partial<R_STATS>, dim3(nchunk, C), dim3(256), 0, st, p);
-  hipLaunchKernelGGL(chan_final<R_STATS>, dim3(C), dim3(256), 0, st, partial, nchunk,
+  hipLaunchKernelGGL(chan_final<R_STATS>, dim3(C), dim3(512), 0, st, partial, nchunk,
                      (int64_t)n * L, mean, invstd);
   return hipGetLastError();
 }
 
 hipError_t launch_stats_final(const double* partial, int nblk, int C, int64_t N, float* mean, float* invstd,
                               hipStream_t st) {
-  hipLaunchKernelGGL(chan_final<R_STATS>, dim3(C), dim3(256), 0, st, partial, nblk, N, mean, invstd);
+  hipLaunchKernelGGL(chan_final<R_STATS>, dim3(C), dim3(512), 0, st, partial, nblk, N, mean, invstd);
   return hipGetLastError();
 }
 
 hipError_t launch_bnbwd_final(const double* partial, int nblk, int C, int64_t N, float* dgamma, float* dbeta,
                               hipStream_t st) {
-  hipLaunchKernelGGL(chan_final<R_BNBWD>, dim3(C), dim3(256), 0, st, partial, nblk, N, dbeta, dgamma);
+  hipLaunchKernelGGL(chan_final<R_BNBWD>, dim3(C), dim3(512), 0, st, partial, nblk, N, dbeta, dgamma);
   return hipGetLastError();
 }
 
@@ -173,7 +199,7 @@ hipError_t launch_channel_sum(const float* x, int n, int C, int L, double* parti
   p.nchunk = nchunk;
   p.partial = partial;
   hipLaunchKernelGGL(chan_partial<R_SUM>, dim3(nchunk, C), dim3(256), 0, st, p);
-  hipLaunchKernelGGL(chan_final<R_SUM>, dim3(C), dim3(256), 0, st, partial, nchunk,
+  hipLaunchKernelGGL(chan_final<R_SUM>, dim3(C), dim3(512), 0, st, partial, nchunk,
                      (int64_t)n * L, out, (float*)nullptr);
   return hipGetLastError();
 }
@@ -289,7 +315,7 @@ hipError_t launch_bn_tanh_backward(const float* g, const float* a, const float* 
   p.nchunk = nchunk;
   p.partial = partial;
   hipLaunchKernelGGL(chan_partial<R_BNBWD>, dim3(nchunk, C), dim3(256), 0, st, p);
-  hipLaunchKernelGGL(chan_final<R_BNBWD>, dim3(C), dim3(256), 0, st, partial, nchunk,
+  hipLaunchKernelGGL(chan_final<R_BNBWD>, dim3(C), dim3(512), 0, st, partial, nchunk,
                      (int64_t)n * L, dbeta, dgamma);
   const int64_t rows = (int64_t)n * C;
   const float invN = (float)(1.0 / ((double)n * L));
