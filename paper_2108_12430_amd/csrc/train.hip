@@ -674,14 +674,12 @@ hipError_t launch_wgrad(const float* P, int Ca, int Lp, const float* Q, int Cc, 
 //
 // Measured, 32 windows of 32768, 81 bins, loss and gradient: one thread per
 // (sample, bin) with vector FP64 sums, four windows a basis value 99 us;
-// these kernels 47 us.  Left: the basis evaluations, the FP64 products at
+// these kernels 44 us.  Left: the basis evaluations, the FP64 products at
 // half of the vector FP32 rate (5 us), and three dependent launches.
 // ---------------------------------------------------------------------------
 namespace bp {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 // k t mod W
 __device__ __forceinline__ int mulmod(int k, int t, int W) {
   if (W < 1 << 24) {  // the product is exact, the quotient off by one at most
@@ -841,11 +839,12 @@ __global__ __launch_bounds__(256) void bp_loss(const float* proj, int n, int nb,
 }
 
 // dL/dnoise[window][t] = scale * sum over bins of weight (A cos[t] + B sin[t]),
-// on v_mfma_f32_16x16x4_f32: a wave takes 16 samples of 16 MT windows and four
-// bins a step; cos, sin, and alternate steps have their own sums.  The last
+// on the same instruction: a wave takes 16 samples of 16 MT windows and four
+// bins a step.  (With FP32 sums it took 11 us instead of 17, and had up to 1.4 times
+// the error of the kernel before it.)  The last
 // block of the first row computes the loss, if that is asked for.
 template <int MT>
-__global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb, int W, int k_lo, float scale,
+__global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb, int W, int k_lo, double scale,
                                                float* dnoise, float* loss) {
   using namespace bp;
   if (loss && blockIdx.x == gridDim.x - 1) {
@@ -863,31 +862,38 @@ __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb,
 #pragma unroll
   for (int g = 0; g < MT; ++g)
     src[g] = reinterpret_cast<const float2*>(proj) + min(b0 + 16 * g + lr, n - 1);
-  f32x4 acc[MT][2][2];
+  f64x4 acc[MT][2];
 #pragma unroll
   for (int g = 0; g < MT; ++g)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[g][q >> 1][q & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < 2; ++q) acc[g][q] = f64x4{0.0, 0.0, 0.0, 0.0};
+  float2 next[2][MT];
+  auto load = [&](int kk0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int g = 0; g < MT; ++g) next[h][g] = src[g][(int64_t)min(kk0 + 4 * h + lk, nb - 1) * n];
+  };
+  load(0);
   for (int kk0 = 0; kk0 < nb; kk0 += 8) {
     float2 v[2][MT];
 #pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int g = 0; g < MT; ++g) v[h][g] = next[h][g];
+    load(kk0 + 8);  // in flight during this step's basis values
+#pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int kk = kk0 + 4 * h + lk;
-      const float w = kk < nb ? bin_weight(k_lo + kk, W) : 0.0f;
-#pragma unroll
-      for (int g = 0; g < MT; ++g) {
-        const float2 p = src[g][(int64_t)min(kk, nb - 1) * n];
-        v[h][g] = kk < nb ? make_float2(w * p.x, w * p.y) : make_float2(0.f, 0.f);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
+      const float w = bin_weight(k_lo + kk, W);
       float sn, cs;
       sincospif(twoW * (float)m, &sn, &cs);
 #pragma unroll
       for (int g = 0; g < MT; ++g) {
-        acc[g][h][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[h][g].x, cs, acc[g][h][0], 0, 0, 0);
-        acc[g][h][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[h][g].y, sn, acc[g][h][1], 0, 0, 0);
+        // bins past the band have zero coefficients, whatever was read
+        v[h][g] = kk < nb ? make_float2(w * v[h][g].x, w * v[h][g].y) : make_float2(0.f, 0.f);
+        acc[g][0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[h][g].x, (double)cs, acc[g][0], 0, 0, 0);
+        acc[g][1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[h][g].y, (double)sn, acc[g][1], 0, 0, 0);
       }
       m += step;
       if (m >= W) m -= W;
@@ -898,10 +904,8 @@ __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb,
   for (int g = 0; g < MT; ++g)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int b = b0 + 16 * g + 4 * lk + i;
-      if (b < n)
-        dnoise[(int64_t)b * W + t] =
-            scale * ((acc[g][0][0][i] + acc[g][1][0][i]) + (acc[g][0][1][i] + acc[g][1][1][i]));
+      const int b = b0 + 16 * g + 4 * i + lk;
+      if (b < n) dnoise[(int64_t)b * W + t] = (float)(scale * (acc[g][0][i] + acc[g][1][i]));
     }
 }
 
@@ -940,7 +944,7 @@ hipError_t launch_bandpass(int n, int W, int k_lo, int k_hi, const float* strain
     hipLaunchKernelGGL(bp_project<1>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial);
   hipLaunchKernelGGL(bp_final, dim3((unsigned)((nv + 63) / 64)), dim3(256), 0, st, partial, nv, S, proj);
   if (dnoise) {
-    const float scale = (float)(-2.0 / ((double)n * W) * (2.0 / (double)W));
+    const double scale = -2.0 / ((double)n * W) * (2.0 / (double)W);
     const dim3 gg((W + 63) / 64 + (loss ? 1 : 0), pg.y);
     if (nw == 32)
       hipLaunchKernelGGL(bp_grad<2>, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
