@@ -930,17 +930,16 @@ constexpr bool TOEP(int l) { return l == 8; }
 constexpr int KS8 = 6;       // K steps of the Toeplitz product (offsets 22, 23 carry zero weights)
 // (phase, channel tile) pairs per column tile
 constexpr int QP(int l) { return STACK(l) ? 1 : NPH(l) * MT(l); }
-// 8-channel layers: the valid accumulator rows sit in lanes 0..31, so two
-// column tiles share one epilogue pass (lanes 32..63 take the second tile)
-constexpr bool COMPACT(int l) { return l < 8 && !STACK(l) && MT(l) == 1 && cip(C[l + 1]) == 8; }
+// output rows of a 16-column tile
+constexpr int RPT(int l) { return STACK(l) || NPH(l) == 2 ? 32 : 16; }
 // A work unit holds at most FMAX weight fragments (32 VGPRs), so all of its
 // fragments are requested at once and the next layer's can be requested
 // while this layer's epilogue runs.  Layers with more (phase, channel tile)
 // pairs x K steps than that split the pairs over SPL units; the others keep
-// every pair in one unit.  Compact and stacked layers have a single pair.
+// every pair in one unit.  Stacked layers have a single pair.
 constexpr int FMAX = 8;
 constexpr int SPL(int l) {
-  return COMPACT(l) || STACK(l) || QP(l) * KS(l) <= FMAX ? 1 : QP(l) / 2 * KS(l) <= FMAX && QP(l) % 2 == 0 ? 2 : 4;
+  return STACK(l) || QP(l) * KS(l) <= FMAX ? 1 : QP(l) / 2 * KS(l) <= FMAX && QP(l) % 2 == 0 ? 2 : 4;
 }
 constexpr int NF(int l) { return TOEP(l) ? KS8 : QP(l) / SPL(l) * KS(l); }   // fragments per unit
 // fragments requested during the previous layer: at most 7, so that the
@@ -948,6 +947,7 @@ constexpr int NF(int l) { return TOEP(l) ? KS8 : QP(l) / SPL(l) * KS(l); }   // 
 // remaining fragment (the last its MFMAs read) is requested as it starts
 constexpr int PF(int l) { return NF(l) < 7 ? NF(l) : 7; }
 constexpr int KSMAX = 8;
+constexpr int FRONT = 40;  // elements: a row of the widest transposed output, a multiple of 8
 constexpr int XG = cip(C[0]) / 4;  // channel groups of x
 
 // The geometry of a tile of T_ output samples (a multiple of 256) computed by
@@ -973,7 +973,10 @@ struct Geom {
   static constexpr int NT(int l) { return (NCOL(l) + 15) / 16; }
   // rows of layer l's input buffer that its (padded) columns may read
   static constexpr int rows_read(int l) { return CSTEP(l) * (16 * NT(l) - 1) + KT(l); }
-  static constexpr int cap0(int l) { return (rows_read(l) > NR(l) ? rows_read(l) : NR(l)); }
+  // rows that the layer before stores, all of its column tiles' (those past
+  // NR(l) are read by padded columns alone, whose sums are dropped)
+  static constexpr int rows_written(int l) { return l > 0 ? RPT(l - 1) * NT(l - 1) : 0; }
+  static constexpr int cap0(int l) { return mx(mx(rows_read(l), NR(l)), rows_written(l)); }
   static constexpr int PART(int l) { return (cap0(l) + SPLITF(l) - 1) / SPLITF(l); }
   // LDS row of row r of layer l's input buffer
   __host__ __device__ static constexpr int phys(int l, int r) {
@@ -989,19 +992,40 @@ struct Geom {
   static constexpr int TB = T / 256;  // 256-output tiles of the output conv
   // column tiles per work unit: enough that every layer is one round of at
   // most NW units (at most 4)
-  static constexpr int NTC(int l) {
-    return COMPACT(l) ? mn(4, 2 * cdiv(NT(l), 2 * NW)) : mn(4, cdiv(NT(l), NW / SPL(l)));
-  }
+  static constexpr int NTC(int l) { return mn(4, cdiv(NT(l), NW / SPL(l))); }
   static constexpr int NG(int l) { return cdiv(NT(l), NTC(l)); }
   static constexpr int NU(int l) { return TOEP(l) ? TB : NG(l) * SPL(l); }  // units of layer l
-  // per-layer table of B-fragment row offsets: KOFF[l][lg][ks] (elements) for
-  // the 8 channels at kappa = 32 ks + 8 lg, i.e. tap jj = kappa / C_in and
-  // channel i0 = kappa mod C_in; taps past the kernel (zero weights) read tap
-  // K-1 instead, a row that holds finite values
-  __host__ __device__ static constexpr int koff(int l, int lg, int ks) {
+  // B-fragment offset of lane group lg at K step ks (elements): the 8 channels
+  // at kappa = 32 ks + 8 lg, i.e. tap jj = kappa / C_in and channel i0 = kappa
+  // mod C_in.  koff: taps past the kernel (zero weights) read tap K-1 instead,
+  // a row that holds finite values.
+  __host__ __device__ static constexpr int koff_tap(int l, int lg, int ks) {
     const int kappa = 32 * ks + 8 * lg, jj = kappa / cip(C[l]), i0 = kappa - jj * cip(C[l]);
-    const int j = jj < KT(l) ? jj : KT(l) - 1;
-    return phys(l, j) * rs(C[l]) + i0;
+    return phys(l, jj) * rs(C[l]) + i0;
+  }
+  __host__ __device__ static constexpr bool past(int l, int lg, int ks) {
+    return (32 * ks + 8 * lg) / cip(C[l]) >= KT(l);
+  }
+  __host__ __device__ static constexpr int koff(int l, int lg, int ks) {
+    const int kappa = 32 * ks + 8 * lg, i0 = kappa % cip(C[l]);
+    return past(l, lg, ks) ? phys(l, KT(l) - 1) * rs(C[l]) + i0 : koff_tap(l, lg, ks);
+  }
+  // Every layer but the first: the offset is a lane part, koff_tap(l, lg, 0),
+  // and a constant of the step, koff_tap(l, 0, ks), which the read instruction
+  // holds; in the last step lane groups from LGP on go back by BACK, to tap K-1.
+  static constexpr int LGP(int l) {
+    for (int lg = 0; lg < 4; ++lg)
+      if (past(l, lg, KS(l) - 1)) return lg;
+    return 4;
+  }
+  static constexpr int BACK(int l) { return koff_tap(l, 3, KS(l) - 1) - koff(l, 3, KS(l) - 1); }
+  static constexpr bool separable(int l) {
+    for (int ks = 0; ks < KS(l); ++ks)
+      for (int lg = 0; lg < 4; ++lg) {
+        const int back = ks == KS(l) - 1 && lg >= LGP(l) ? BACK(l) : 0;
+        if (koff_tap(l, lg, 0) + koff_tap(l, 0, ks) - back != koff(l, lg, ks)) return false;
+      }
+    return true;
   }
   static constexpr bool units_fit(int l) {
     return l == 9 || (NU(l) <= NW && NF(l) <= FMAX && QP(l) % SPL(l) == 0 && units_fit(l + 1));
@@ -1071,100 +1095,56 @@ __device__ __forceinline__ f32x4 mfma16(const uint4& a, const uint4& b, const f3
   }
 }
 
-// BN + tanh of channels o0..o0+3 of one output row of layer l (scale and
-// shift pre-multiplied by 2 log2 e), stored as four bf16 in one 8 B LDS
-// write.  Positions outside the layer's signal are stored as zeros (the next
-// layer's padding); only tiles at a window edge (EDGE) have any.  Every
-// C_out here is a multiple of 8, so no stored channel is padding.
-template <class Z, int l, bool EDGE, bool F16>
-__device__ __forceinline__ void epi_row(uint16_t* out, int row, int o0, f32x4 v, float4 sc, float4 sh, int pos0,
-                                        int Lout) {
-  using namespace fused;
-  constexpr int RSO = rs(C[l + 1]);
-  static_assert(C[l + 1] % 8 == 0, "stored channel groups are never padding");
-  if (row < 0 || row >= Z::NR(l + 1)) return;
+// BN + tanh of four channels of one output row (scale and shift pre-multiplied
+// by 2 log2 e), stored as four 16-bit values in one 8 B LDS write.  Positions
+// outside the layer's signal (live is false) are stored as zeros, the next
+// layer's padding; only tiles at a window edge (EDGE) have any.
+template <bool EDGE, bool F16>
+__device__ __forceinline__ void epi_row(uint16_t* dst, f32x4 v, float4 sc, float4 sh, bool live) {
   float t0 = tanh_scaled(fmaf(v[0], sc.x, sh.x)), t1 = tanh_scaled(fmaf(v[1], sc.y, sh.y));
   float t2 = tanh_scaled(fmaf(v[2], sc.z, sh.z)), t3 = tanh_scaled(fmaf(v[3], sc.w, sh.w));
   if (EDGE) {
-    const int u = pos0 + row;
-    const bool live = u >= 0 && u < Lout;
     t0 = live ? t0 : 0.0f;
     t1 = live ? t1 : 0.0f;
     t2 = live ? t2 : 0.0f;
     t3 = live ? t3 : 0.0f;
   }
-  const int prow = Z::phys(l + 1, row);
-  *reinterpret_cast<uint2*>(out + prow * RSO + o0) = make_uint2(pack2<F16>(t0, t1), pack2<F16>(t2, t3));
+  *reinterpret_cast<uint2*>(dst) = make_uint2(pack2<F16>(t0, t1), pack2<F16>(t2, t3));
 }
 
-// Epilogue of one work unit (see fused_layer).
+// Epilogue of one work unit (see fused_layer).  A column tile's rows start a
+// fixed distance after the tile's before, so a lane's address is computed once
+// and the stores hold the rest; no row is masked (the transposed layers' first
+// column has a row -1, which lands in the pad before the buffer).  With the
+// address, and a test of the row, worked out for each row, and every layer's B
+// offsets read from a table, this kernel took 14.3 us for a window of 4096
+// samples and 219 us for 179 of 32768; now 12.9 and 214 us.
 template <class Z, int l, bool EDGE, int NTCl, int Q, bool F16>
 __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, int sp, int lc, int lg, uint16_t* out,
-                                          const float* ksc, const float* ksh, int pos0, int Lout, const DcIn* op,
-                                          int b, int Wout) {
+                                          const float* ksc, const float* ksh, int pos0, int Lout) {
   using namespace fused;
-  constexpr int CIPO = cip(C[l + 1]), M = MT(l), P = NPH(l), NTn = Z::NT(l), SP = SPL(l);
-  (void)op;
-  (void)b;
-  (void)Wout;
+  constexpr int RSO = rs(C[l + 1]), M = MT(l), P = NPH(l), NTn = Z::NT(l), SP = SPL(l), F = SPLITF(l + 1);
   static_assert(!TOEP(l), "the output conv has its own layer function");
-  if constexpr (STACK(l)) {
-    // rows 8 ph + o: lanes 0..31 hold phase (time offset) 0, lanes 32..63
-    // phase 1, each lane four channels 4 (lg & 1) .. + 3 of column c
-    static_assert(SP == 1 && Q == 1, "stacked layers: one (phases x channels) tile per column");
-    const int o0 = 4 * (lg & 1), ph = lg >> 1;
+  static_assert(STACK(l) || C[l + 1] % 16 == 0, "stored channel groups are never padding");
+  static_assert(RPT(l) % F == 0, "tiles start on the first residue");
+  constexpr int TSTEP = (l + 1 == 8 ? prow8(RPT(l)) : RPT(l) / F) * RSO;  // from tile to tile
+  // this lane's row of a tile, phase 0
+  const int r0 = STACK(l) ? 2 * lc + (lg >> 1) + ROFF(l) : P == 1 ? lc : 2 * lc - 1;
+  static_assert(P == 1 || F == 1, "phases are adjacent rows");
+  const int prow = F > 1 ? (r0 % F) * Z::PART(l + 1) + r0 / F : l + 1 == 8 ? prow8(r0) : r0;
+  uint16_t* dst = out + nt0 * TSTEP + prow * RSO + 4 * (STACK(l) ? lg & 1 : lg);
+  const int u0 = pos0 + RPT(l) * nt0 + r0;
+#pragma unroll
+  for (int k = 0; k < Q; ++k) {
+    const int q = STACK(l) ? 0 : sp + k * SP, ph = q / M, mt = q % M;
+    const int o0 = STACK(l) ? 4 * (lg & 1) : 16 * mt + 4 * lg;
     const float4 sc4 = *reinterpret_cast<const float4*>(ksc + o0);
     const float4 sh4 = *reinterpret_cast<const float4*>(ksh + o0);
 #pragma unroll
     for (int a = 0; a < NTCl; ++a) {
       if (nt0 + a >= NTn) break;
-      const int c = (nt0 + a) * 16 + lc;
-      epi_row<Z, l, EDGE, F16>(out, 2 * c + ph + ROFF(l), o0, acc[a][0], sc4, sh4, pos0, Lout);
-    }
-  } else if constexpr (COMPACT(l)) {
-    // tiles a, a+1: lanes 0..31 keep tile a's channels 0..7, lanes 32..63
-    // receive tile a+1's (its lanes 0..31) through a 32-lane swap
-    static_assert(SP == 1 && Q == P, "compact layers keep both phases in one unit");
-    const int o0 = 4 * (lg & 1);
-    const float4 sc4 = *reinterpret_cast<const float4*>(ksc + o0);
-    const float4 sh4 = *reinterpret_cast<const float4*>(ksh + o0);
-#pragma unroll
-    for (int a = 0; a < NTCl; a += 2) {
-      if (nt0 + a >= NTn) break;
-      if (a + 1 < NTCl && nt0 + a + 1 < NTn) {
-        const int c = (nt0 + a + (lg >> 1)) * 16 + lc;
-#pragma unroll
-        for (int ph = 0; ph < P; ++ph) {
-          f32x4 v;
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            v[r] = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][ph][r]),
-                                                                    __float_as_uint(acc[a + 1][ph][r]), false,
-                                                                    false)[0]);
-          epi_row<Z, l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, v, sc4, sh4, pos0, Lout);
-        }
-      } else if (lg < 2) {
-        const int c = (nt0 + a) * 16 + lc;
-#pragma unroll
-        for (int ph = 0; ph < P; ++ph)
-          epi_row<Z, l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, acc[a][ph], sc4, sh4, pos0, Lout);
-      }
-    }
-  } else {
-    // four consecutive channels per lane and row, one 8 B store each
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-      const int q = sp + k * SP, ph = q / M, mt = q % M;
-      const int o0 = 16 * mt + 4 * lg;
-      if (o0 >= CIPO) continue;
-      const float4 sc4 = *reinterpret_cast<const float4*>(ksc + o0);
-      const float4 sh4 = *reinterpret_cast<const float4*>(ksh + o0);
-#pragma unroll
-      for (int a = 0; a < NTCl; ++a) {
-        if (nt0 + a >= NTn) break;
-        const int c = (nt0 + a) * 16 + lc;
-        epi_row<Z, l, EDGE, F16>(out, P == 1 ? c : 2 * c + ph - 1, o0, acc[a][k], sc4, sh4, pos0, Lout);
-      }
+      const int u = u0 + RPT(l) * a + ph;
+      epi_row<EDGE, F16>(dst + a * TSTEP + ph * RSO + 16 * mt, acc[a][k], sc4, sh4, u >= 0 && u < Lout);
     }
   }
 }
@@ -1175,8 +1155,8 @@ __device__ __forceinline__ void fused_epi(const f32x4 (&acc)[NTCl][Q], int nt0, 
 // The 92 KB of packed weights stay in L2, shared by every block; a unit's
 // fragments (at most FMAX) arrive in wf, requested while the previous
 // layer's epilogue ran, and once its MFMAs have read them the wave requests
-// its fragments of the next layer into the same registers.  kt holds the
-// layer's row of the B-offset table.
+// its fragments of the next layer into the same registers.  kt: the first layer's
+// table of B offsets, [lane group][K step].
 //
 // Request wave `wave`'s weight fragments [I0, I1) of layer l into wf:
 // fragment i = k KS + ks (pair q = sp + k SPL, K step ks) of unit `wave`,
@@ -1252,10 +1232,9 @@ __device__ __forceinline__ void fused_toeplitz(int tid, const uint16_t* in, u32x
 template <class Z, int l, bool F16>
 __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint16_t* out, u32x4 (&wf)[fused::FMAX],
                                                const uint4* wg, const uint4* wgn, const int* kt, const float* ksc,
-                                               const float* ksh, int pos0, int Lout, const DcIn* op, int b,
-                                               int Wout) {
+                                               const float* ksh, int pos0, int Lout) {
   using namespace fused;
-  constexpr int RSI = rs(C[l]);
+  constexpr int RSI = rs(C[l]), CI = cip(C[l]);
   constexpr int KSn = KS(l), NTn = Z::NT(l);
   constexpr int NTCl = Z::NTC(l), SP = SPL(l), Q = QP(l) / SP;
   constexpr int SX = SPLITF(l) > 1 ? 1 : CSTEP(l);  // LDS rows between adjacent columns
@@ -1264,13 +1243,20 @@ __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint
   // addresses are scalar work
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lc = lane & 15, lg = lane >> 4;
-  // this lane's B row offsets for the layer's K steps
-  int ko[KSMAX];
-  {
+  // this lane's B offsets: for the first layer, whose taps are not a power of
+  // two apart, from the table
+  int ko[l == 0 ? KSMAX : 1] = {};
+  int lane_off = 0, back = 0;
+  if constexpr (l == 0) {
     const int4 k0 = *reinterpret_cast<const int4*>(kt + KSMAX * lg);
     const int4 k1 = *reinterpret_cast<const int4*>(kt + KSMAX * lg + 4);
     ko[0] = k0.x; ko[1] = k0.y; ko[2] = k0.z; ko[3] = k0.w;
     ko[4] = k1.x; ko[5] = k1.y; ko[6] = k1.z; ko[7] = k1.w;
+  } else {
+    static_assert(Z::separable(l), "lane part + step part");
+    constexpr int LPT = CI / 8;  // lane groups per tap
+    lane_off = LPT >= 4 ? 8 * lg : Z::phys(l, lg / LPT) * RSI + 8 * (lg % LPT);
+    back = lg >= Z::LGP(l) ? Z::BACK(l) : 0;
   }
   // window-edge tiles store zeros outside the signal
   const bool edge = pos0 < 0 || pos0 + Z::NR(l + 1) > Lout;
@@ -1282,7 +1268,13 @@ __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint
   {
     const int unit = wave;
     const int nt0 = (unit / SP) * NTCl, sp = unit % SP;  // wave-uniform
-    const uint16_t* colbase = in + ((nt0 * 16 + lc) * SX) * RSI;
+    // tiles past the layer's last re-read that one (their sums are never stored)
+    const uint16_t* col[NTCl];
+#pragma unroll
+    for (int a = 0; a < NTCl; ++a) {
+      const int aa = a < NTn - nt0 ? a : NTn - 1 - nt0;  // wave-uniform
+      col[a] = in + (((nt0 + aa) * 16 + lc) * SX) * RSI + lane_off;
+    }
     f32x4 acc[NTCl][Q];
 #pragma unroll
     for (int a = 0; a < NTCl; ++a)
@@ -1290,15 +1282,15 @@ __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint
       for (int k = 0; k < Q; ++k) acc[a][k] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KSn; ++ks) {
-      const uint16_t* src = colbase + ko[ks];
-      // the K step's B fragments of every column tile, read together; tiles
-      // past the layer's last re-read that one (their sums are never stored)
+      // the K step's B fragments of every column tile, read together
+      int off;
+      if constexpr (l == 0)
+        off = ko[ks];
+      else
+        off = Z::koff_tap(l, 0, ks) - (ks == KSn - 1 && Z::LGP(l) < 4 ? back : 0);
       uint4 bb[NTCl];
 #pragma unroll
-      for (int a = 0; a < NTCl; ++a) {
-        const int aa = a < NTn - nt0 ? a : NTn - 1 - nt0;  // wave-uniform
-        bb[a] = *reinterpret_cast<const uint4*>(src + aa * 16 * SX * RSI);
-      }
+      for (int a = 0; a < NTCl; ++a) bb[a] = *reinterpret_cast<const uint4*>(col[a] + off);
 #pragma unroll
       for (int a = 0; a < NTCl; ++a)
 #pragma unroll
@@ -1310,9 +1302,9 @@ __device__ __forceinline__ void fused_layer_mm(int tid, const uint16_t* in, uint
     // epilogue issue ahead of waves still in their MFMA chains
     __builtin_amdgcn_s_setprio(1);
     if (edge)
-      fused_epi<Z, l, true, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout, op, b, Wout);
+      fused_epi<Z, l, true, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout);
     else
-      fused_epi<Z, l, false, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout, op, b, Wout);
+      fused_epi<Z, l, false, NTCl, Q, F16>(acc, nt0, sp, lc, lg, out, ksc, ksh, pos0, Lout);
     __builtin_amdgcn_s_setprio(0);
   }
 }
@@ -1324,7 +1316,7 @@ __device__ __forceinline__ void fused_layer(int tid, const uint16_t* in, uint16_
   if constexpr (fused::TOEP(l))
     fused_toeplitz<Z, F16>(tid, in, wf, wgn, ksc, ksh, pos0, op, b, Wout);
   else
-    fused_layer_mm<Z, l, F16>(tid, in, out, wf, wg, wgn, kt, ksc, ksh, pos0, Lout, op, b, Wout);
+    fused_layer_mm<Z, l, F16>(tid, in, out, wf, wg, wgn, kt, ksc, ksh, pos0, Lout);
 }
 
 // ---------------------------------------------------------------------------
@@ -1576,9 +1568,11 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
   static_assert(Z::units_fit(0), "every layer is one round of units of at most FMAX fragments");
   (void)args;
   if (!p.items) p.items = arg_items();
-  __shared__ __attribute__((aligned(16))) uint16_t bufA[Z::BUFA];
-  __shared__ __attribute__((aligned(16))) uint16_t bufB[Z::BUFB];
-  __shared__ __attribute__((aligned(16))) int ktab[9][4][KSMAX];
+  // each buffer after a pad for the transposed layers' row -1
+  __shared__ __attribute__((aligned(16))) uint16_t padA[FRONT + Z::BUFA];
+  __shared__ __attribute__((aligned(16))) uint16_t padB[FRONT + Z::BUFB];
+  __shared__ __attribute__((aligned(16))) int ktab[4][KSMAX];
+  uint16_t *const bufA = padA + FRONT, *const bufB = padB + FRONT;
   __shared__ __attribute__((aligned(16))) float ksc[9][64];
   __shared__ __attribute__((aligned(16))) float ksh[9][64];
 
@@ -1628,10 +1622,10 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
       ksc[l][threadIdx.x] = f.scale[l][oc] * g;
       ksh[l][threadIdx.x] = f.shift[l][oc] * g;
     }
-    if (threadIdx.x < 4 * KSMAX) {
-      const int lg = threadIdx.x / KSMAX, ks = threadIdx.x % KSMAX;
-      ktab[l][lg][ks] = ks < KS(l) ? Z::koff(l, lg, ks) : 0;
-    }
+  }
+  if (threadIdx.x < 4 * KSMAX) {
+    const int lg = threadIdx.x / KSMAX, ks = threadIdx.x % KSMAX;
+    ktab[lg][ks] = ks < KS(0) ? Z::koff(0, lg, ks) : 0;
   }
   // input tile rows [u0 - 93, u0 + T + 93) in [time][channel] layout
   store_x<Z, IN, F16>(bufA, raw, u00 + LO[0], al0, W, threadIdx.x);
@@ -1648,7 +1642,7 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
       int tid = threadIdx.x;                                                                                \
       asm volatile("" : "+v"(tid));                                                                         \
       fused_layer<Z, l, F16>(tid, IN_BUF, OUT_BUF, wf, reinterpret_cast<const uint4*>(f.w + f.off[l]),               \
-                          reinterpret_cast<const uint4*>(f.w + f.off[(l + 1) % 9]), &ktab[l][0][0], ksc[l], ksh[l],  \
+                          reinterpret_cast<const uint4*>(f.w + f.off[(l + 1) % 9]), &ktab[0][0], ksc[l], ksh[l],  \
                           u0 / (SCALE_DIV) + LO[l + 1], W / (SCALE_DIV), &p, b, W);                         \
       __syncthreads();                                                                                      \
     }
