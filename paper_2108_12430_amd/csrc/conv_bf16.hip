@@ -977,7 +977,9 @@ struct Geom {
   // NR(l) are read by padded columns alone, whose sums are dropped)
   static constexpr int rows_written(int l) { return l > 0 ? RPT(l - 1) * NT(l - 1) : 0; }
   static constexpr int cap0(int l) { return mx(mx(rows_read(l), NR(l)), rows_written(l)); }
-  static constexpr int PART(int l) { return (cap0(l) + SPLITF(l) - 1) / SPLITF(l); }
+  // the input's partitions each have two spare rows at their end: a staged
+  // chunk's rows before the first and after the last land there
+  static constexpr int PART(int l) { return (cap0(l) + SPLITF(l) - 1) / SPLITF(l) + (l == 0 ? 2 : 0); }
   // LDS row of row r of layer l's input buffer
   __host__ __device__ static constexpr int phys(int l, int r) {
     return SPLITF(l) > 1 ? (r % SPLITF(l)) * PART(l) + r / SPLITF(l) : l == 8 ? prow8(r) : r;
@@ -1218,7 +1220,7 @@ __device__ __forceinline__ void fused_toeplitz(int tid, const uint16_t* in, u32x
     const float v = fmaf(acc[q], sc, sh);
     if (op->noise) op->noise[(int64_t)b * Wout + u] = v;
     if (op->clean) {
-      const Item& it = op->items[b];
+      const Item it = uniform_item(op->items, b);
       const int t0 = Wout - it.s - it.delay;
       if (u >= t0 && u < t0 + it.s) {
         const int64_t idx = it.out + (u - t0);
@@ -1372,7 +1374,7 @@ __device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int 
   const float* fbase = nullptr;
   bool vec = true;
   if (RING) {
-    const Item& it = p.items[b];
+    const Item it = uniform_item(p.items, b);
     head = it.head;
     ld = it.W;
     if (IN == IN_RING)
@@ -1396,16 +1398,24 @@ __device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int 
       if (ph >= ld) ph -= ld;
       const bool in = ch < nch && qc + 8 > 0 && qc < Lin;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < 4; ++k)
 #pragma unroll
         for (int v = 0; v < NV; ++v) R.v[it][k][v] = u32x4{0u, 0u, 0u, 0u};
-        if (in && 4 * g + k < Ci) {
-          const int64_t o = (int64_t)(4 * g + k) * ld + ph;
-          if constexpr (IN == IN_RING) {
-            R.v[it][k][0] = *reinterpret_cast<const u32x4*>(hbase + o);
-          } else {
-            R.v[it][k][0] = *reinterpret_cast<const u32x4*>(fbase + o);
-            R.v[it][k][NV - 1] = *reinterpret_cast<const u32x4*>(fbase + o + 4);
+      static_assert(Ci % 4 == 1, "the last group has one channel");
+      if constexpr (IN == IN_RING) {
+        const uint16_t* src = hbase + ((int64_t)(4 * g) * ld + ph);
+        if (in) R.v[it][0][0] = *reinterpret_cast<const u32x4*>(src);
+        if (in && g < Ci / 4) {
+#pragma unroll
+          for (int k = 1; k < 4; ++k) R.v[it][k][0] = *reinterpret_cast<const u32x4*>(src + (int64_t)k * ld);
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (in && 4 * g + k < Ci) {
+            const float* src = fbase + ((int64_t)(4 * g + k) * ld + ph);
+            R.v[it][k][0] = *reinterpret_cast<const u32x4*>(src);
+            R.v[it][k][NV - 1] = *reinterpret_cast<const u32x4*>(src + 4);
           }
         }
       }
@@ -1422,54 +1432,55 @@ __device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int 
 }
 
 // Write the staged rows to LDS (row stride RS, split by row residue mod 4).
-// AL0: al is 0, so a chunk's rows have residues known at compile time and a
-// chunk lies inside the window or outside (lengths are multiples of 16); else
-// its rows outside [0, Lin) are zeroed here.
+// No row is masked: a chunk's rows before row 0 or past the last go to the
+// partitions' spare rows (those before partition 0 to the buffer's front pad).
+// AL0: al is 0, so a chunk starts three rows before a multiple of 8 (tiles
+// start on multiples of 8 samples), every row's residue is known at compile
+// time, and a chunk lies inside the window or outside (lengths are multiples of
+// 16); else its rows outside [0, Lin) are zeroed here.  With every row's
+// address, range and halves worked out one by one this and the load were 40% of
+// the kernel's vector instructions; without, the kernel went from 220 to 210 us
+// at 179 streams of 32768 samples (44.5 to 41.5 at 24 ragged ones, and in FP16
+// 87.3 to 84.8 at 48).
 template <class Z, int IN, bool F16, bool AL0>
 __device__ __forceinline__ void store_rows(uint16_t* tile, const XRaw<Z, IN>& R, int q0, int al, int Lin, int tid) {
   static_assert(!(F16 && IN == IN_RING), "the ring's 16-bit shadow is BF16");
   using namespace fused;
   constexpr int RS = rs(C[0]), ROWS = Z::XROWS;
   static_assert(SPLITF(0) == 4, "layer 0's columns step four input rows");
-  const int qa = chunk0(q0, AL0 ? 0 : al);
-  const int nch = (q0 + ROWS - qa + 7) / 8;
+  static_assert((ROWS + 6) / 4 < Z::PART(0) && RS <= FRONT, "spare rows");
+  const int o = AL0 ? LO[0] & 7 : (q0 + al) & 7;  // rows of the first chunk before row 0
+  const int nch = (ROWS + o + 7) / 8;
 #pragma unroll
   for (int it = 0; it < Z::XITEMS; ++it) {
     const int e = tid + Z::NTHR * it;
     const int g = e % XG, ch = e / XG;
     if (ch >= nch) continue;
-    // 16-bit pairs of each channel: c[k][d] holds samples 2d, 2d+1
-    uint32_t c[4][4];
+    constexpr int NV = XRaw<Z, IN>::NV;
+    uint32_t c[4][4 * NV];  // the channels' samples (16-bit: pairs)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if (IN == IN_F32 || IN == IN_RING_F32) {
-        const u32x4 a = R.v[it][k][0], z = R.v[it][k][XRaw<Z, IN>::NV - 1];
-        c[k][0] = pack2<F16>(__uint_as_float(a.x), __uint_as_float(a.y));
-        c[k][1] = pack2<F16>(__uint_as_float(a.z), __uint_as_float(a.w));
-        c[k][2] = pack2<F16>(__uint_as_float(z.x), __uint_as_float(z.y));
-        c[k][3] = pack2<F16>(__uint_as_float(z.z), __uint_as_float(z.w));
-      } else {
-        const u32x4 a = R.v[it][k][0];
-        c[k][0] = a.x; c[k][1] = a.y; c[k][2] = a.z; c[k][3] = a.w;
+      const u32x4 a = R.v[it][k][0], z = R.v[it][k][NV - 1];
+      c[k][0] = a.x; c[k][1] = a.y; c[k][2] = a.z; c[k][3] = a.w;
+      if (NV == 2) {
+        c[k][4 * NV - 4] = z.x; c[k][4 * NV - 3] = z.y; c[k][4 * NV - 2] = z.z; c[k][4 * NV - 1] = z.w;
       }
     }
-    const int r0 = qa + 8 * ch - q0;  // row of the chunk's first sample
-    const bool full = r0 >= 0 && r0 + 8 <= ROWS;
+    uint16_t* const base = tile + 4 * g + 2 * ch * RS;  // row 8 ch
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-      const int d = t >> 1;
-      uint32_t lo, hi;
-      if (t & 1) {
-        lo = (c[0][d] >> 16) | (c[1][d] & 0xffff0000u);
-        hi = (c[2][d] >> 16) | (c[3][d] & 0xffff0000u);
-      } else {
-        lo = (c[0][d] & 0xffffu) | (c[1][d] << 16);
-        hi = (c[2][d] & 0xffffu) | (c[3][d] << 16);
+      uint32_t lo, hi;  // the group's channels 0, 1 and 2, 3
+      if constexpr (NV == 2) {
+        lo = pack2<F16>(__uint_as_float(c[0][t]), __uint_as_float(c[1][t]));
+        hi = pack2<F16>(__uint_as_float(c[2][t]), __uint_as_float(c[3][t]));
+      } else {  // the even or odd halves of two channels' pairs
+        const uint32_t sel = t & 1 ? 0x07060302u : 0x05040100u;
+        lo = __builtin_amdgcn_perm(c[1][t >> 1], c[0][t >> 1], sel);
+        hi = __builtin_amdgcn_perm(c[3][t >> 1], c[2][t >> 1], sel);
       }
-      const int r = r0 + t;
-      if (!AL0 && (q0 + r < 0 || q0 + r >= Lin)) lo = hi = 0u;
-      if (full || (r >= 0 && r < ROWS))
-        *reinterpret_cast<uint2*>(tile + Z::phys(0, r) * RS + 4 * g) = make_uint2(lo, hi);
+      const int r = t - o;  // row, from row 8 ch
+      if (!AL0 && (uint32_t)(q0 + 8 * ch + r) >= (uint32_t)Lin) lo = hi = 0u;
+      *reinterpret_cast<uint2*>(base + ((r & 3) * Z::PART(0) + (r >> 2)) * RS) = make_uint2(lo, hi);
     }
   }
 }
@@ -1497,7 +1508,7 @@ __device__ __forceinline__ void store_x(uint16_t* tile, const XRaw<Z, IN>& R, in
 // (block-uniform).  A wave takes one channel at a time, so no lane divides.
 template <class Z>
 __device__ __forceinline__ bool upd_stage(const DcIn& p, int b, int q0, int tid) {
-  const Item& it = p.items[b];
+  const Item& it = p.items[b];  // in vector registers: as scalars they spill (FP16: 88 -> 108 us at 48 streams)
   const int s = it.s, W = it.W, snew = p.Lin - s;
   int lo = q0 > snew ? q0 : snew, hi = q0 + Z::XROWS < p.Lin ? q0 + Z::XROWS : p.Lin;
   if (lo >= hi) return false;
@@ -1606,7 +1617,7 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
     // only tiles with an output in the window's clean span [W - s - delay,
     // W - delay); with the update folded in there are no delays, so that every
     // new sample lies among such a tile's rows
-    const Item& it = p.items[b0];
+    const Item it = uniform_item(p.items, b0);
     if (u00 + Z::T <= W - it.s - it.delay || u00 >= W - it.delay) return;
   }
   if (UPD && upd_stage<Z>(p, b0, u00 + LO[0], threadIdx.x)) __syncthreads();

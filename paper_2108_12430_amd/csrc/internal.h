@@ -135,6 +135,24 @@ __device__ __forceinline__ const Item* arg_items() {
   return (const Item*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// items[b] for a b that is the same in every lane, through the scalar cache
+__device__ __forceinline__ Item uniform_item(const Item* items, int b) {
+  typedef const __attribute__((address_space(4))) int64_t* P;
+  const P q = (P)(uintptr_t)(items + __builtin_amdgcn_readfirstlane(b));
+  Item it;
+  it.ring = q[0];
+  it.shadow = q[1];
+  it.src = q[2];
+  it.out = q[3];
+  it.head = (int32_t)q[4];
+  it.s = (int32_t)(q[4] >> 32);
+  it.C = (int32_t)q[5];
+  it.W = (int32_t)(q[5] >> 32);
+  it.delay = (int32_t)q[6];
+  it.pad_ = 0;
+  return it;
+}
+
 // Geometry of the polyphase/strided column view of a layer (host + device).
 struct Geo {
   int nph;    // phases (1 for conv, stride for transposed)
