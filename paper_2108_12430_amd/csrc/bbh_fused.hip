@@ -32,20 +32,31 @@ constexpr int T3 = 64;     // last-stage positions per block
 constexpr int NW = 8;      // waves per block
 constexpr int NTHR = 64 * NW;
 
-// per tensor: channels (padded), LDS row stride, row offset LO (row 0 sits at
-// scaled tile start + LO), needed rows NR, buffer rows CAP, even/odd split
+// per tensor: channels (padded), row offset LO (row 0 sits at scaled tile start
+// + LO), needed rows NR, buffer rows CAP, even/odd split.
+// A tensor lies in LDS as planes of 16 channels, rows of 32 bytes (x: one plane
+// of 8, rows of 16).  A 16-byte read is served 16 lanes at a time, eight of one
+// lane group (here: 8 channels) and the other eight rows of the next, and
+// reaches 256 bytes a cycle if the 16 hit distinct bank groups: with 32-byte
+// rows the one group's eight are the even bank groups, the other's the odd
+// ones; x's two row parities lie a multiple of 16 rows apart.  (Rows padded to
+// an odd multiple of 16 bytes, as before, take 8.4 cycles a read instead of 4.6.)
 //                     x     h0    a1    h1    a2    h2    a3
 constexpr int CH[7] = {8, 32, 32, 64, 64, 128, 128};
-constexpr int RS[7] = {8, 40, 40, 72, 72, 136, 0};
 constexpr int LO[7] = {-63, -30, -27, -12, -9, -3, 0};
 constexpr int NR[7] = {637, 315, 309, 152, 146, 70, 64};
 // CAP: the deepest row a padding column reads, + 1 (x: the a1 shortcut's
 // row 2 * 319 + 9; h0: 319 + 6; a1: the a2 shortcut's 2 * 159 + 9; h1: 159 + 6;
-// a2: h2's 2 * 79 + 6, rounded up to even for the split; h2: 63 + 6)
-constexpr int CAP[7] = {648, 326, 328, 166, 166, 70, 0};
+// a2: h2's 2 * 79 + 6, rounded up to even for the split, x to 32; h2: 63 + 6)
+constexpr int CAP[7] = {672, 326, 328, 166, 166, 70, 0};
 constexpr int SPLIT[7] = {1, 0, 1, 0, 1, 0, 0};
 constexpr int HALF(int t) { return SPLIT[t] ? CAP[t] / 2 : 0; }
 __host__ __device__ constexpr int prow(int t, int r) { return SPLIT[t] ? (r & 1) * HALF(t) + (r >> 1) : r; }
+constexpr int RS(int t) { return CH[t] < 16 ? CH[t] : 16; }  // row (elements)
+constexpr int PL(int t) { return CAP[t] * RS(t); }           // plane
+static_assert(HALF(0) % 16 == 0, "x: row parities on the same banks");
+// element offset of channel c (a multiple of 4) of stored row q
+__host__ __device__ constexpr int at(int t, int q, int c) { return CH[t] < 16 ? q * RS(t) + c : (c >> 4) * PL(t) + q * 16 + (c & 15); }
 // scale of tensor t's positions relative to the last stage (x: 8, h0/a1: 4, ...)
 constexpr int SCL[7] = {8, 4, 4, 2, 2, 1, 1};
 
@@ -64,9 +75,9 @@ static_assert(2 * (NR[3] - 1) + 6 < NR[2] && NR[4] - 1 + 6 < NR[3] && 2 * (NR[4]
 static_assert(2 * (NR[5] - 1) + 6 < NR[4] && NR[6] - 1 + 6 < NR[5] && 2 * (NR[6] - 1) + 9 < NR[4], "stage 2");
 
 // LDS regions: R0 holds h0 then h1, R1 a1 then h2, R2 x then a2
-constexpr int R0 = mx(CAP[1] * RS[1], CAP[3] * RS[3]);
-constexpr int R1 = mx(CAP[2] * RS[2], CAP[5] * RS[5]);
-constexpr int R2 = mx(CAP[0] * RS[0], CAP[4] * RS[4]);
+constexpr int R0 = mx(CAP[1] * CH[1], CAP[3] * CH[3]);
+constexpr int R1 = mx(CAP[2] * CH[2], CAP[5] * CH[5]);
+constexpr int R2 = mx(CAP[0] * CH[0], CAP[4] * CH[4]);
 
 }  // namespace bbf
 
@@ -131,7 +142,7 @@ __device__ __forceinline__ float conv_phase(const uint16_t* in, const uint16_t* 
     for (int a = 0; a < NTW; ++a) {
       if (ct0 + a >= NT) break;
       const int r = (ct0 + a) * 16 + lc;
-      const uint4 bv = *reinterpret_cast<const uint4*>(in + prow(TI, SCI * r + jj) * RS[TI] + i0);
+      const uint4 bv = *reinterpret_cast<const uint4*>(in + at(TI, prow(TI, SCI * r + jj), i0));
 #pragma unroll
       for (int m = 0; m < MTW; ++m)
         acc[m][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[m]),
@@ -150,7 +161,7 @@ __device__ __forceinline__ float conv_phase(const uint16_t* in, const uint16_t* 
       for (int a = 0; a < NTW; ++a) {
         if (ct0 + a >= NT) break;
         const int r = (ct0 + a) * 16 + lc;
-        const uint4 bv = *reinterpret_cast<const uint4*>(sin + prow(TS, 2 * r + 9) * RS[TS] + i0);
+        const uint4 bv = *reinterpret_cast<const uint4*>(sin + at(TS, prow(TS, 2 * r + 9), i0));
 #pragma unroll
         for (int m = 0; m < MTW; ++m)
           acc[m][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[m]),
@@ -186,7 +197,7 @@ __device__ __forceinline__ float conv_phase(const uint16_t* in, const uint16_t* 
       } else {
         const uint32_t lo = rne2(v[0], v[1]);
         const uint32_t hi = rne2(v[2], v[3]);
-        *reinterpret_cast<uint2*>(out + prow(TO, r) * RS[TO] + 16 * mt + 4 * lg) = make_uint2(lo, hi);
+        *reinterpret_cast<uint2*>(out + at(TO, prow(TO, r), 16 * mt + 4 * lg)) = make_uint2(lo, hi);
       }
     }
   }
@@ -231,7 +242,7 @@ __global__ __launch_bounds__(bbf::NTHR, 4) void bbh_fused(BbFusedP p) {
           c01 = (uint32_t)bbf::rne(fx[pos]) | ((uint32_t)bbf::rne(fx[W + pos]) << 16);
         }
       }
-      *reinterpret_cast<uint4*>(r2 + prow(0, r) * RS[0]) = make_uint4(c01, 0u, 0u, 0u);
+      *reinterpret_cast<uint4*>(r2 + at(0, prow(0, r), 0)) = make_uint4(c01, 0u, 0u, 0u);
     }
   }
   __syncthreads();
