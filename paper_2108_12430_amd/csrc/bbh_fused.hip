@@ -206,7 +206,7 @@ __device__ __forceinline__ float conv_phase(const uint16_t* in, const uint16_t* 
 
 }  // namespace bbf
 
-// two 8-wave blocks per CU (LDS 76 KB each): four waves per SIMD, at most 128 VGPRs
+// two 8-wave blocks per CU (LDS 63 KB each): four waves per SIMD, at most 128 VGPRs
 __global__ __launch_bounds__(bbf::NTHR, 4) void bbh_fused(BbFusedP p) {
   using namespace bbf;
   __shared__ __attribute__((aligned(16))) uint16_t r0[R0];

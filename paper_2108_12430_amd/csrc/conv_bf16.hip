@@ -892,9 +892,14 @@ namespace fused {
 
 constexpr int C[10] = {21, 8, 16, 32, 64, 32, 16, 8, 8, 1};
 constexpr int cip(int c) { return (c + 7) / 8 * 8; }
-// LDS row stride (elements): an odd multiple of 8, so 16 lanes reading 16 B
-// from 16 consecutive rows hit 16 distinct 16 B bank groups
-constexpr int rs(int c) { return (cip(c) / 8) % 2 ? cip(c) : cip(c) + 8; }
+// LDS row stride (elements).  A 16-byte read is served 16 lanes at a time: eight
+// rows of one lane group, the eight rows between of the next.  Where the next
+// lane group reads the next 8 channels the 16 hit distinct 16 B bank groups if
+// the stride is 32 bytes mod 64 (4.6 cycles a read; 8.4 at odd multiples of 16
+// bytes).  8-byte writes want odd multiples (8.3 cycles; 16.2 at even ones), so
+// only the layers with many reads a write, of 32 and 64 channels, are so
+// padded; the others have the odd multiple.
+constexpr int rs(int c) { return cip(c) >= 32 ? cip(c) + 16 : (cip(c) / 8) % 2 ? cip(c) : cip(c) + 8; }
 // row 0 of a_l (and x) sits at (tile start scaled to layer l) + LO[l]
 constexpr int LO[10] = {-93, -45, -21, -9, -3, -3, -3, -3, -3, 0};
 constexpr int mx(int a, int b) { return a > b ? a : b; }
@@ -908,10 +913,10 @@ constexpr int KT(int l) { return l == 0 ? 9 : l < 4 || l == 8 ? 7 : 4; }
 // residue (row r at (r mod F) PART + r / F), so adjacent columns read
 // adjacent LDS rows; the others row by row
 constexpr int SPLITF(int l) { return l < 9 && CSTEP(l) > 1 ? CSTEP(l) : 1; }
-// the output conv's input rows are stored with one spare row after every 16
-// (row r at r + r / 16): its A-operand reads take rows 16 apart in 16 lanes,
-// which the spare rows spread over distinct bank groups
-constexpr int prow8(int r) { return r + (r >> 4); }
+// the output conv's input rows are stored with two spare rows after every 16
+// (row r at r + 2 (r / 16)): its A-operand reads take rows 16 apart in 16 lanes
+// and the next row in the next lane group, which so hit distinct bank groups
+constexpr int prow8(int r) { return r + 2 * (r >> 4); }
 constexpr int MT(int l) { return (C[l + 1] + 15) / 16; }
 constexpr int NPH(int l) { return l >= 4 && l < 8 ? 2 : 1; }
 constexpr int KS(int l) { return (KT(l) * cip(C[l]) + 31) / 32; }
@@ -947,7 +952,7 @@ constexpr int NF(int l) { return TOEP(l) ? KS8 : QP(l) / SPL(l) * KS(l); }   // 
 // remaining fragment (the last its MFMAs read) is requested as it starts
 constexpr int PF(int l) { return NF(l) < 7 ? NF(l) : 7; }
 constexpr int KSMAX = 8;
-constexpr int FRONT = 40;  // elements: a row of the widest transposed output, a multiple of 8
+constexpr int FRONT = 48;  // elements: a row of the widest transposed output, a multiple of 8
 constexpr int XG = cip(C[0]) / 4;  // channel groups of x
 
 // The geometry of a tile of T_ output samples (a multiple of 256) computed by
@@ -979,7 +984,12 @@ struct Geom {
   static constexpr int cap0(int l) { return mx(mx(rows_read(l), NR(l)), rows_written(l)); }
   // the input's partitions each have two spare rows at their end: a staged
   // chunk's rows before the first and after the last land there
-  static constexpr int PART(int l) { return (cap0(l) + SPLITF(l) - 1) / SPLITF(l) + (l == 0 ? 2 : 0); }
+  // The second layer's are 16 rows of 16 bytes apart, whose lane groups read
+  // one and the other.
+  static constexpr int PART(int l) {
+    const int part = (cap0(l) + SPLITF(l) - 1) / SPLITF(l);
+    return l == 0 ? part + 2 : l == 1 ? cdiv(part, 16) * 16 : part;
+  }
   // LDS row of row r of layer l's input buffer
   __host__ __device__ static constexpr int phys(int l, int r) {
     return SPLITF(l) > 1 ? (r % SPLITF(l)) * PART(l) + r / SPLITF(l) : l == 8 ? prow8(r) : r;
