@@ -114,7 +114,7 @@ __device__ __forceinline__ void f32m_stage(float* tile, const float* x, const fl
   constexpr int NCH = STEP == 1 ? (ROWS + 3 + 3) / 4 : ROWS / RPC;
   const int qa = q0 & ~3;                               // floor to a multiple of 4 (q0 may be negative)
   const int off = q0 - qa;                              // STEP 2: always 0
-  constexpr int ITEMS = (NCH * G + 255) / 256, BM = PRO == PRO_DZ ? 2 : 4, BATCH = ITEMS < BM ? ITEMS : BM;
+  constexpr int ITEMS = (NCH * G + 255) / 256, BM = PRO == PRO_DZ ? 2 : 6, BATCH = ITEMS < BM ? ITEMS : BM;
 #pragma unroll 1
   for (int i0 = 0; i0 < ITEMS; i0 += BATCH) {
     float4 v[BATCH][4], z[PRO == PRO_DZ ? BATCH : 1][4];
