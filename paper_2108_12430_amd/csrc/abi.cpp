@@ -1632,8 +1632,12 @@ extern "C" int deepclean_forward_cached(const gw_model* m, gw_pool* pool, const 
   const int L = (int)m->layers.size();
   int tiles = 0, smax = 0;
   if (m->fused)
-    for (const auto& it : items) {
-      tiles = std::max(tiles, gw::cache_band_tiles(it.shift, W));
+    for (auto& it : items) {
+      int zl, zr;
+      gw::cache_band_zones(it.shift, W, &zl, &zr);
+      it.zl = zl;
+      it.zr = zr;
+      tiles = std::max(tiles, gw::cache_band_tiles(zl, zr, W));
       smax = std::max(smax, it.s);
     }
   const void* dev = nullptr;

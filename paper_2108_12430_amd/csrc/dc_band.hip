@@ -22,10 +22,12 @@
 // 256 outputs); the matrix work is 344 MFMAs of 16 cycles a tile.  The kernel
 // before kept every layer's activations as rings and walked a stream's dirty
 // positions layer by layer in one block, about 21 dependent rounds.  Measured,
-// 179 streams of 21 x 32768, strides 256, 512 and 1024 in turn: 125 -> 33 us a
-// launch; all of 256: 83 -> 26 us; one stream: 78 -> 14 us.  T = 256: other
-// sizes take 39 (128), 37 (192) and 32 us (288) on the mixed strides, but 24,
-// 24 and 27 us (256: 26) on strides of 256 and 12, 13 and 15 us (14) alone.
+// 179 streams of 21 x 32768, strides 256, 512 and 1024 in turn: 125 -> 27 us a
+// launch; all of 256: 83 -> 22 us; one stream: 78 -> 12 us.  (34, 26 and 14 us
+// with the zones worked out by every wave and every stored row's address and
+// range by every lane.)  T = 256: measured in that form, other sizes took 39
+// (128), 37 (192) and 32 us (288) on the mixed strides, where 256 took 33, but
+// 24, 24 and 27 us (256: 26) on strides of 256 and 12, 13 and 15 us (14) alone.
 #include "internal.h"
 
 namespace gw {
@@ -40,6 +42,7 @@ constexpr int NTHR = 64 * NW;
 constexpr int C[10] = {21, 8, 16, 32, 64, 32, 16, 8, 8, 1};
 constexpr int cip(int c) { return (c + 7) / 8 * 8; }
 constexpr int rs(int c) { return (cip(c) / 8) % 2 ? cip(c) : cip(c) + 8; }  // an odd multiple of 16 bytes
+constexpr int FRONT = 40;  // elements: a row of the widest transposed output, a multiple of 8
 constexpr int LO[10] = {-93, -45, -21, -9, -3, -3, -3, -3, -3, 0};
 constexpr int NR[10] = {T + 187, T / 2 + 91, T / 4 + 43, T / 8 + 19, T / 16 + 7,
                         T / 8 + 7, T / 4 + 7, T / 2 + 7, T + 6, T};
@@ -64,7 +67,11 @@ constexpr int NU(int l) { return cdiv(NT(l), NTC(l)) * QU(l); }
 constexpr int NF(int l) { return NP(l) * KS(l); }  // weight fragments per unit
 constexpr int FMAX = 8;
 constexpr int SC(int l) { return l < 4 ? 2 : 1; }
-constexpr int ROWS(int l) { return mx(SC(l) * (16 * NT(l) - 1) + KT(l), NR[l]); }
+// rows that columns read, or that the layer before stores (all of its column
+// tiles': those past NR feed padded columns alone)
+constexpr int ROWS(int l) {
+  return mx(mx(SC(l) * (16 * NT(l) - 1) + KT(l), NR[l]), l > 0 ? (TR(l - 1) ? 32 : 16) * NT(l - 1) : 0);
+}
 constexpr int HALF(int l) { return l < 4 ? (ROWS(l) + 1) / 2 : 0; }  // even rows, then odd rows
 constexpr int prow(int l, int r) { return l < 4 ? (r & 1) * HALF(l) + (r >> 1) : r; }
 constexpr int SZ(int l) { return (HALF(l) ? 2 * HALF(l) : ROWS(l)) * rs(C[l]); }
@@ -102,17 +109,13 @@ __device__ __forceinline__ void frags(uint4 (&wf)[FMAX], const uint16_t* w, int 
   }
 }
 
-// normalisation + tanh of channels o0 .. o0 + 3 of output row `row`
-template <int l>
-__device__ __forceinline__ void epi(uint16_t* out, int row, int o0, f32x4 v, const float4& sc, const float4& sh,
-                                    int pos0, int Lout) {
-  if (row < 0 || row >= NR[l + 1]) return;
-  const int u = pos0 + row;
-  uint2 d = make_uint2(0u, 0u);  // the next layer's padding outside the signal
-  if (u >= 0 && u < Lout)
-    d = make_uint2(pack2(tanhf(fmaf(v[0], sc.x, sh.x)), tanhf(fmaf(v[1], sc.y, sh.y))),
-                   pack2(tanhf(fmaf(v[2], sc.z, sh.z)), tanhf(fmaf(v[3], sc.w, sh.w))));
-  *reinterpret_cast<uint2*>(out + prow(l + 1, row) * rs(C[l + 1]) + o0) = d;
+// normalisation + tanh of four channels of an output row; zeros outside the
+// signal (the next layer's padding).  Rows are not masked: row -1 of a
+// transposed layer lands in the pad before the buffer.
+__device__ __forceinline__ void epi(uint16_t* dst, f32x4 v, const float4& sc, const float4& sh, bool live) {
+  const uint2 d = make_uint2(pack2(tanhf(fmaf(v[0], sc.x, sh.x)), tanhf(fmaf(v[1], sc.y, sh.y))),
+                             pack2(tanhf(fmaf(v[2], sc.z, sh.z)), tanhf(fmaf(v[3], sc.w, sh.w))));
+  *reinterpret_cast<uint2*>(dst) = live ? d : make_uint2(0u, 0u);
 }
 
 __device__ __forceinline__ float swap32(float a, float b) {  // lanes 0..31: a's; 32..63: b's lanes 0..31
@@ -157,7 +160,9 @@ __device__ __forceinline__ void layer(int tid, const uint16_t* in, uint16_t* out
                                                             __builtin_bit_cast(bf16x8, bv[a]), acc[a][k], 0, 0, 0);
   }
   frags<l + 1>(wf, wn, wave, lane);
-  // lane (lc, lg) holds rows 4 lg .. 4 lg + 3 of column 16 (nt0 + a) + lc
+  // lane (lc, lg) holds rows 4 lg .. 4 lg + 3 of column 16 (nt0 + a) + lc; a
+  // tile's rows start TSTEP elements after those of the tile before
+  constexpr int RSO = l < 8 ? rs(C[l + 1]) : 0, RPT = TR(l) ? 32 : 16, TSTEP = (l + 1 < 4 ? RPT / 2 : RPT) * RSO;
   if constexpr (l == 8) {
     if (lg == 0)
 #pragma unroll
@@ -169,6 +174,9 @@ __device__ __forceinline__ void layer(int tid, const uint16_t* in, uint16_t* out
     const int o0 = 4 * (lg & 1);
     const float4 sc = *reinterpret_cast<const float4*>(ksc + o0), sh = *reinterpret_cast<const float4*>(ksh + o0);
     constexpr int ST = NPl == 2 ? 1 : 2;
+    const int r0 = NPl == 2 ? 2 * lc - 1 + (lg >> 1) : 16 * (lg >> 1) + lc;  // row of tile 0
+    uint16_t* dst = out + prow(l + 1, r0) * RSO + o0 + nt0 * TSTEP;
+    const int u0 = pos0 + RPT * nt0 + r0;
 #pragma unroll
     for (int a = 0; a < NTCl; a += ST) {
       if (nt0 + a >= NTn) break;
@@ -178,29 +186,32 @@ __device__ __forceinline__ void layer(int tid, const uint16_t* in, uint16_t* out
       for (int r = 0; r < 4; ++r)
         v[r] = swap32(acc[a][0][r], NPl == 2 ? acc[a][NPl - 1][r] : acc[a + 1 < NTCl ? a + 1 : a][0][r]);
       if (!pair && lg >= 2) continue;
-      const int c = (nt0 + a) * 16 + lc;
-      epi<l>(out, NPl == 2 ? 2 * c - 1 + (lg >> 1) : c + 16 * (lg >> 1), o0, v, sc, sh, pos0, Lout);
+      epi(dst + a * TSTEP, v, sc, sh, u0 + RPT * a >= 0 && u0 + RPT * a < Lout);
     }
   } else {
     const int o0 = 16 * mt + 4 * lg;
     const float4 sc = *reinterpret_cast<const float4*>(ksc + o0), sh = *reinterpret_cast<const float4*>(ksh + o0);
+    const int r0 = TR(l) ? 2 * lc - 1 + ph : lc;
+    uint16_t* dst = out + prow(l + 1, r0) * RSO + o0 + nt0 * TSTEP;
+    const int u0 = pos0 + RPT * nt0 + r0;
 #pragma unroll
     for (int a = 0; a < NTCl; ++a) {
       if (nt0 + a >= NTn) break;
-      const int c = (nt0 + a) * 16 + lc;
-      epi<l>(out, TR(l) ? 2 * c - 1 + ph : c, o0, acc[a][0], sc, sh, pos0, Lout);
+      epi(dst + a * TSTEP, acc[a][0], sc, sh, u0 + RPT * a >= 0 && u0 + RPT * a < Lout);
     }
   }
 }
 
 // first output of the right zone's tiles
-__host__ __device__ inline int right0(int zr) { return zr & ~15; }
+__host__ __device__ constexpr int right0(int zr) { return zr & ~15; }
+
+}  // namespace band
 
 // the outputs that change when a window of W samples slides by shift
-__host__ __device__ inline void zones(int shift, int W, int* zl, int* zr) {
+void cache_band_zones(int shift, int W, int* zl, int* zr) {
+  using namespace band;
   CacheGeo g[9];
   int L = W;
-#pragma unroll
   for (int l = 0; l < 9; ++l) {
     const int Lo = l < 4 ? L / 2 : l < 8 ? 2 * L : L;
     g[l] = CacheGeo{TR(l) ? 1 : 0, C[l], C[l + 1], 7, l == 8 ? 1 : 2, 3, TR(l) ? 1 : 0, L, Lo, W / Lo, l < 8, l == 8};
@@ -209,25 +220,21 @@ __host__ __device__ inline void zones(int shift, int W, int* zl, int* zr) {
   cache_band(g, 8, shift, W, zl, zr);
 }
 
-}  // namespace band
-
-int cache_band_tiles(int shift, int W) {
-  int zl, zr;
-  band::zones(shift, W, &zl, &zr);
+int cache_band_tiles(int zl, int zr, int W) {
   return band::cdiv(zl, band::T) + band::cdiv(W - band::right0(zr), band::T);
 }
 
 __global__ __launch_bounds__(band::NTHR, 4) void cache_band_kernel(const CacheItem* items, const void* arena,
                                                                     band::P p) {
   using namespace band;
-  __shared__ __attribute__((aligned(16))) uint16_t bufA[BUFA];
-  __shared__ __attribute__((aligned(16))) uint16_t bufB[BUFB];
+  __shared__ __attribute__((aligned(16))) uint16_t padA[FRONT + BUFA];
+  __shared__ __attribute__((aligned(16))) uint16_t padB[FRONT + BUFB];
+  uint16_t *const bufA = padA + FRONT, *const bufB = padB + FRONT;
   __shared__ __attribute__((aligned(16))) float ksc[9][64], ksh[9][64];
   const int per = p.tiles + p.copies, item = (int)blockIdx.x / per, t = (int)blockIdx.x - item * per;
   const CacheItem it = items[item];
   const int W = p.W, tid0 = threadIdx.x;
-  int zl, zr;
-  zones(it.shift, W, &zl, &zr);
+  const int zl = it.zl, zr = it.zr;
   float* ring = reinterpret_cast<float*>(reinterpret_cast<char*>(it.cache) + p.ring);
   const int s0 = W - it.s - it.delay;  // clean span [s0, s0 + s)
   auto emit = [&](int k, float v) {

@@ -213,9 +213,12 @@ struct CacheItem {
   int64_t out;        // offset of the item's [s] block in strain/clean
   int32_t in_head;    // ring index of the snapshot's oldest sample
   int32_t T;          // the cache's window start modulo W (a multiple of 16): layer l's ring head is T / f_l
-  int32_t shift;      // samples the window advanced since the cache was last made current; -1: recompute all
+  union {
+    int32_t shift;    // samples the window advanced since the cache was last made current; -1: recompute all
+    int32_t zl;       // the reference network's kernel: outputs [0, zl) and [zr, W) change
+  };
   int32_t s, delay;   // clean output span [W - s - delay, W - delay)
-  int32_t pad_;
+  int32_t zr;
 };
 static_assert(sizeof(CacheItem) == 48, "CacheItem layout");
 
@@ -295,9 +298,10 @@ hipError_t launch_cache_forward(const CacheItem* items, int n, const void* arena
 
 // The same for the reference network, from the receptive fields of the outputs
 // that change (dc_band.hip; of the cache only the noise ring is used).  tiles:
-// the most cache_band_tiles(shift, W) of the items, smax: the longest clean
+// the most cache_band_tiles(zl, zr, W) of the items, smax: the longest clean
 // span.
-int cache_band_tiles(int shift, int W);
+void cache_band_zones(int shift, int W, int* zl, int* zr);
+int cache_band_tiles(int zl, int zr, int W);
 hipError_t launch_cache_band(const CacheItem* items, int n, const void* arena, const CacheLayerP& P, int tiles, int smax,
                              const float* strain, float* noise, float* clean, hipStream_t st);
 
