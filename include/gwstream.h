@@ -57,7 +57,8 @@ extern "C" {
 #define GW_EUNSUPPORTED 5  /* precision or shape without a compiled kernel       */
 
 /* ---- enums ------------------------------------------------------------- */
-#define GW_FP32 0          /* FP32 direct convolution on the vector ALUs        */
+#define GW_FP32 0          /* FP32 products and sums (matrix cores; other shapes than
+                              the compiled ones: vector ALUs)                   */
 #define GW_BF16 1          /* BF16 MFMA implicit GEMM, FP32 accumulate/epilogue */
 #define GW_FP16 2          /* FP16 operands in the fused DeepClean kernel (the
                               reference network's inference only; the precision
@@ -254,9 +255,9 @@ int deepclean_workspace(const gw_model* model, int32_t n, int32_t W, int32_t pre
  * Returns GW_EINVAL if ws_bytes is too small (the size deepclean_workspace
  * returns for the same n, W, precision and flags always suffices).
  * W must be a multiple of 16 (four stride-2 stages).  For the reference
- * network shape, GW_BF16 inference runs one fused kernel that keeps every
- * intermediate activation on chip (unless GW_LAYERWISE is given); both
- * variants agree within the BF16 tolerance and each is bitwise reproducible.
+ * network shape, inference runs one fused kernel in every precision that keeps
+ * every intermediate activation on chip (GW_BF16: unless GW_LAYERWISE is given);
+ * both variants agree within the BF16 tolerance and each is bitwise reproducible.
  */
 int deepclean_forward(const gw_model* model, gw_pool* pool, const int32_t* slots, const float* x,
                       int32_t n, int32_t W, const int32_t* strides, const int32_t* delays,
@@ -290,10 +291,12 @@ int deepclean_update_forward(const gw_model* model, gw_pool* pool, int32_t n, co
  * stateful model hands each request's full window to the static model
  * (App. B.1), whose update step the paper names as the online bottleneck
  * (main text, online results).  Between two requests the window only slides:
- * with a per-stream cache of every layer's activations of the last window,
- * a request recomputes only the positions whose receptive field reaches the
- * new samples or the window's left edge, and the full predicted-noise window
- * comes out as if recomputed.
+ * with a per-stream cache of the last window, a request recomputes only the
+ * positions whose receptive field reaches the new samples or the window's left
+ * edge, and the full predicted-noise window comes out as if recomputed.  The
+ * cache is laid out as every layer's activations; for the reference network
+ * shape only the predicted noise is kept there, and changed outputs are computed
+ * from their receptive fields.
  *
  * deepclean_cache_bytes: device bytes of one stream's cache for windows of W
  * samples: every layer's activations as a ring, C_out x L_out BF16 (FP32 for
@@ -394,11 +397,13 @@ int deepclean_overlap_average(const gw_model* model, int32_t n, int32_t W, const
  * deepclean_forward call with GW_TRAIN and the same n, W, x, flags and
  * precision).  dparams (device, n_params float32) is overwritten, not
  * accumulated; running-statistics entries get 0.  With GW_RECOMPUTE the
- * activations are recomputed from checkpoints; the result is bitwise equal
- * to the stored-activation path.  `scratch` needs deepclean_backward_scratch
+ * activations are recomputed from checkpoints (the reference network shape:
+ * taken from the layers' saved pre-normalisation values, with or without
+ * GW_RECOMPUTE); the result is bitwise equal to the stored-activation path.  `scratch` needs deepclean_backward_scratch
  * bytes.  All reductions have a fixed order (deterministic).  precision must
  * equal the forward's: GW_BF16 runs the forward (and recomputed) convolutions
- * on BF16 matrix cores with FP32 activations, statistics and gradients.
+ * on BF16 matrix cores with FP32 activations, statistics and gradients; the
+ * backward's products are FP32 in both.
  */
 int deepclean_backward_scratch(const gw_model* model, int32_t n, int32_t W, uint32_t flags,
                                size_t* bytes);

@@ -1822,13 +1822,13 @@ hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint
   if (e != hipSuccess) return e;
   const int ncu = cu_budget > 0 && cu_budget < cus ? cu_budget : cus;
   p.n = n;
-  // Tile size.  A tile of 256 outputs runs its chain of nine layers in 14.5 us
-  // against 17.3 us for 768, but computes 1.4 times as many activations per
+  // Tile size.  A tile of 256 outputs runs its chain of nine layers in 12.9 us
+  // against 15.1 us for 768, but computes 1.4 times as many activations per
   // output: it is taken while every tile has a CU of its own.  Measured (21 x
-  // 32768, launches of n windows, 256 against 768): n = 1 14.6 and 17.1 us, 2
-  // 14.9 and 17.3, 4 (512 tiles of 256) 18.9 and 17.8, 8 30 and 23; causal
-  // bands of 256 samples, n = 1 14.2 and 16.8, 179 of mixed strides (417 tiles
-  // of 256) 33 and 27.
+  // 32768, launches of n windows, 256 against 768): n = 1 12.9 and 15.1 us, 2
+  // 13.4 and 15.1, 4 (512 tiles of 256) 16.9 and 16.0, 8 27.6 and 21.2; causal
+  // bands of 256 samples, n = 1 12.3 and 14.3, 179 of mixed strides (417 tiles
+  // of 256) 30.1 and 26.4.
   if (io.tiles256 <= ncu) return launch_dc_z<fused::Geom<256, 12>>(p, args, f, n, ring, f16, ncu, st);
   return launch_dc_z<fused::Geom<768, 12>>(p, args, f, n, ring, f16, ncu, st);
 }
