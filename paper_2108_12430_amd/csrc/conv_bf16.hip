@@ -1830,6 +1830,24 @@ hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint
   // bands of 256 samples, n = 1 12.3 and 14.3, 179 of mixed strides (417 tiles
   // of 256) 30.1 and 26.4.
   if (io.tiles256 <= ncu) return launch_dc_z<fused::Geom<256, 12>>(p, args, f, n, ring, f16, ncu, st);
+  // Tiles of 512 in blocks of eight waves, three a CU, where they take a round
+  // less than tiles of 768, two a CU, and the rounds are few: a round of 512
+  // costs more, so from six rounds on the gain is gone.  Measured (us, 21 x
+  // 32768, 768 against 512, on two boxes): n = 11 (one round each) 21.7 and
+  // 24.5, 12 (2 and 1) 32.4 and 25.1, 20 (2 and 2) 34.2 and 34.6, 24 (3 and 2)
+  // 45.2 and 40.3, 36 (4 and 3) 58 and 53, 48 (5 and 4) 70 and 64 .. 69, 72 (7 and
+  // 6) 92 and 88 .. 94, 96 (9 and 8) 114 and 112 .. 121.  Not for FP32 samples
+  // (dense windows, FP16): their two items a thread spill.
+  if (ring && !f16 && !p.causal) {
+    auto rounds = [&](int T, int per_cu) {
+      const int64_t cap = (int64_t)per_cu * ncu;
+      return ((int64_t)n * ((W + T - 1) / T) + cap - 1) / cap;
+    };
+    const int64_t r768 = rounds(768, 2), r512 = rounds(512, 3);
+    if (r512 < r768 && r768 <= 5)
+      return p.upd ? launch_dc_t<fused::Geom<512, 8>, IN_RING, false, true, false>(p, args, f, n, ncu, st)
+                   : launch_dc_t<fused::Geom<512, 8>, IN_RING, false, false, false>(p, args, f, n, ncu, st);
+  }
   return launch_dc_z<fused::Geom<768, 12>>(p, args, f, n, ring, f16, ncu, st);
 }
 
