@@ -1343,7 +1343,10 @@ __device__ __forceinline__ void fused_layer(int tid, const uint16_t* in, uint16_
 template <class Z, int IN>
 struct XRaw {
   static constexpr int NV = IN == IN_F32 || IN == IN_RING_F32 ? 2 : 1;  // 16 B pieces per channel chunk
-  u32x4 v[Z::XITEMS][4][NV];
+  // items a thread holds at once: FP32 samples take 32 registers an item
+  static constexpr int NI = NV == 2 ? 1 : Z::XITEMS;
+  static constexpr int PASSES = Z::XITEMS / NI;
+  u32x4 v[NI][4][NV];
 };
 
 // Where a tile's chunks start: a multiple of 8 samples in the input's own
@@ -1373,7 +1376,7 @@ __device__ __forceinline__ void load_dense(u32x4 (&d)[2], const float* row, int 
 // and start are multiples of 8 samples (the network's windows are multiples of
 // 16, a pool's rings 256-byte aligned).  A ring's chunk that lies partly outside the
 // window is loaded whole; store_x drops what is outside.
-template <class Z, int IN>
+template <class Z, int IN, int PASS = 0>
 __device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int q0, int tid) {
   using namespace fused;
   constexpr int Ci = C[0], NV = XRaw<Z, IN>::NV;
@@ -1398,8 +1401,8 @@ __device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int 
   const int al = RING ? head & 7 : 0;
   const int qa = chunk0(q0, al), nch = (q0 + Z::XROWS - qa + 7) / 8;
 #pragma unroll
-  for (int it = 0; it < Z::XITEMS; ++it) {
-    const int e = tid + Z::NTHR * it;
+  for (int it = 0; it < XRaw<Z, IN>::NI; ++it) {
+    const int e = tid + Z::NTHR * (PASS + it);
     const int g = e % XG, ch = e / XG;
     const int qc = qa + 8 * ch;
     if constexpr (RING) {
@@ -1452,7 +1455,7 @@ __device__ __forceinline__ int load_x(XRaw<Z, IN>& R, const DcIn& p, int b, int 
 // the kernel's vector instructions; without, the kernel went from 220 to 210 us
 // at 179 streams of 32768 samples (44.5 to 41.5 at 24 ragged ones, and in FP16
 // 87.3 to 84.8 at 48).
-template <class Z, int IN, bool F16, bool AL0>
+template <class Z, int IN, bool F16, bool AL0, int PASS>
 __device__ __forceinline__ void store_rows(uint16_t* tile, const XRaw<Z, IN>& R, int q0, int al, int Lin, int tid) {
   static_assert(!(F16 && IN == IN_RING), "the ring's 16-bit shadow is BF16");
   using namespace fused;
@@ -1462,8 +1465,8 @@ __device__ __forceinline__ void store_rows(uint16_t* tile, const XRaw<Z, IN>& R,
   const int o = AL0 ? LO[0] & 7 : (q0 + al) & 7;  // rows of the first chunk before row 0
   const int nch = (ROWS + o + 7) / 8;
 #pragma unroll
-  for (int it = 0; it < Z::XITEMS; ++it) {
-    const int e = tid + Z::NTHR * it;
+  for (int it = 0; it < XRaw<Z, IN>::NI; ++it) {
+    const int e = tid + Z::NTHR * (PASS + it);
     const int g = e % XG, ch = e / XG;
     if (ch >= nch) continue;
     constexpr int NV = XRaw<Z, IN>::NV;
@@ -1495,12 +1498,24 @@ __device__ __forceinline__ void store_rows(uint16_t* tile, const XRaw<Z, IN>& R,
   }
 }
 
-template <class Z, int IN, bool F16>
+template <class Z, int IN, bool F16, int PASS = 0>
 __device__ __forceinline__ void store_x(uint16_t* tile, const XRaw<Z, IN>& R, int q0, int al, int Lin, int tid) {
   if (IN == IN_F32 || al == 0)  // block-uniform
-    store_rows<Z, IN, F16, true>(tile, R, q0, 0, Lin, tid);
+    store_rows<Z, IN, F16, true, PASS>(tile, R, q0, 0, Lin, tid);
   else
-    store_rows<Z, IN, F16, false>(tile, R, q0, al, Lin, tid);
+    store_rows<Z, IN, F16, false, PASS>(tile, R, q0, al, Lin, tid);
+}
+
+// The items that a thread's registers did not hold at once (512 threads: a few
+// past the first 512), after the others are stored.
+template <class Z, int IN, bool F16>
+__device__ __forceinline__ void stage_rest(uint16_t* tile, XRaw<Z, IN>& R, const DcIn& p, int b, int q0, int tid) {
+  static_assert(XRaw<Z, IN>::PASSES <= 2, "one more pass at most");
+  if constexpr (XRaw<Z, IN>::PASSES == 2) {
+    if (__builtin_amdgcn_readfirstlane(tid) + Z::NTHR >= fused::XG * Z::XCH) return;  // wave-uniform
+    const int al = load_x<Z, IN, 1>(R, p, b, q0, tid);
+    store_x<Z, IN, F16, 1>(tile, R, q0, al, p.Lin, tid);
+  }
 }
 
 // Fused snapshot update: the item carries the head after the update, and
@@ -1650,6 +1665,7 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
   }
   // input tile rows [u0 - 93, u0 + T + 93) in [time][channel] layout
   store_x<Z, IN, F16>(bufA, raw, u00 + LO[0], al0, W, threadIdx.x);
+  stage_rest<Z, IN, F16>(bufA, raw, p, b0, u00 + LO[0], threadIdx.x);
   __syncthreads();
 
   while (true) {
@@ -1688,6 +1704,7 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
     __builtin_amdgcn_s_setprio(2);  // ahead of the other block's epilogues
     const int al = load_x<Z, IN>(raw, p, b, nq, tid);
     store_x<Z, IN, F16>(bufA, raw, nq, al, W, tid);
+    stage_rest<Z, IN, F16>(bufA, raw, p, b, nq, tid);
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
   }
@@ -1836,17 +1853,23 @@ hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint
   // 32768, 768 against 512, on two boxes): n = 11 (one round each) 21.7 and
   // 24.5, 12 (2 and 1) 32.4 and 25.1, 20 (2 and 2) 34.2 and 34.6, 24 (3 and 2)
   // 45.2 and 40.3, 36 (4 and 3) 58 and 53, 48 (5 and 4) 70 and 64 .. 69, 72 (7 and
-  // 6) 92 and 88 .. 94, 96 (9 and 8) 114 and 112 .. 121.  Not for FP32 samples
-  // (dense windows, FP16): their two items a thread spill.
-  if (ring && !f16 && !p.causal) {
+  // 6) 92 and 88 .. 94, 96 (9 and 8) 114 and 112 .. 121; FP16: 12 37.3 and 28.6, 24
+  // 53 and 45, 36 67 and 60.5, 48 82 and 76.  (Dense windows keep 768: a pool's
+  // streams are what comes in such numbers.)
+  if (ring && !p.causal) {
     auto rounds = [&](int T, int per_cu) {
       const int64_t cap = (int64_t)per_cu * ncu;
       return ((int64_t)n * ((W + T - 1) / T) + cap - 1) / cap;
     };
     const int64_t r768 = rounds(768, 2), r512 = rounds(512, 3);
-    if (r512 < r768 && r768 <= 5)
-      return p.upd ? launch_dc_t<fused::Geom<512, 8>, IN_RING, false, true, false>(p, args, f, n, ncu, st)
-                   : launch_dc_t<fused::Geom<512, 8>, IN_RING, false, false, false>(p, args, f, n, ncu, st);
+    using Z = fused::Geom<512, 8>;
+    if (r512 < r768 && r768 <= 5) {
+      if (f16)
+        return p.upd ? launch_dc_t<Z, IN_RING_F32, true, true, false>(p, args, f, n, ncu, st)
+                     : launch_dc_t<Z, IN_RING_F32, true, false, false>(p, args, f, n, ncu, st);
+      return p.upd ? launch_dc_t<Z, IN_RING, false, true, false>(p, args, f, n, ncu, st)
+                   : launch_dc_t<Z, IN_RING, false, false, false>(p, args, f, n, ncu, st);
+    }
   }
   return launch_dc_z<fused::Geom<768, 12>>(p, args, f, n, ring, f16, ncu, st);
 }

@@ -25,7 +25,8 @@ def cdiv(a, b):
     (7, 1008, 6),     # 14 and 14: two tiles a window, the last one short
     (1, 13328, 8),    # one long window: 18 and 27 tiles in 2 and 2 rounds (768 stays)
 ])
-def test_tiles_of_512(n, W, budget):
+@pytest.mark.parametrize("precision", [pytest.param(gs.BF16, id="bf16"), pytest.param(gs.FP16, id="fp16")])
+def test_tiles_of_512(n, W, budget, precision):
     r768, r512 = cdiv(n * cdiv(W, 768), 2 * budget), cdiv(n * cdiv(W, 512), 3 * budget)
     assert (r512 < r768) == (W != 13328) and n * cdiv(W, 256) > budget
     params = torch.from_numpy(synth.deepclean_params(3)).to(DEV)
@@ -46,7 +47,7 @@ def test_tiles_of_512(n, W, budget):
             clean = torch.full((sum(s),), 7.0, device=DEV)
             noise = torch.full((n, W), 7.0, device=DEV)
             kw = dict(pool=pool, slots=slots, W=W, strides=s, strain=strain, noise=noise, clean=clean,
-                      precision=gs.BF16)
+                      precision=precision)
             if side == 0:    # the whole chip: 256 outputs a tile
                 full.update_forward(samples=x, offsets=off, **kw)
             elif side == 1:  # with the update folded in
