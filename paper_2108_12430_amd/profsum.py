@@ -30,7 +30,8 @@ COPY_KERNEL = "__amd_rocclr_copyBuffer"
 # hash is unchanged
 KERNELS = {
     # the serving step's launch: the fused network with the snapshot update
-    "dc_fused_bf16": ("void gw::dc_fused<2, false, true>(gw::ConvP, gw::FusedP, int)",
+    "dc_fused_bf16": ("void gw::dc_fused<gw::fused::Geom<768, 12>, 2, false, true, false>"
+                      "(gw::ItemArgs, gw::DcIn, gw::FusedP, int)",
                       "paper_2108_12430_amd/csrc/conv_bf16.hip"),
     "bbh_fused": ("gw::bbh_fused(gw::BbFusedP)", "paper_2108_12430_amd/csrc/bbh_fused.hip"),
     "snapshot": ("gw::snapshot_kernel(char*, gw::Item const*, float const*)",
