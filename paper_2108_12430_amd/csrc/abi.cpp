@@ -102,9 +102,14 @@ struct Stager {
     *out = reinterpret_cast<const Item*>(d);
     return GW_OK;
   }
-  // A slot for a call whose table rides in its kernel arguments: only the
-  // slot's event is used (the call's completion).
-  int reserve(hipStream_t st, StageGuard* guard) {
+  // A slot for a call of n items whose table rides in its kernel arguments: only
+  // the slot's event is used (the call's completion).  The bound on a call's
+  // items is the same whichever way they travel.
+  int reserve(size_t n, hipStream_t st, StageGuard* guard) {
+    if (n > (size_t)cap) return fail(GW_EINVAL, "too many items in one call");
+    return take_slot(st, guard);
+  }
+  int take_slot(hipStream_t st, StageGuard* guard) {
     const int k = next;
     next = (next + 1) % K;
     if (used[k]) HIPCHK(hipEventSynchronize(ev[k]));
@@ -118,7 +123,7 @@ struct Stager {
   // Any table of at most cap * sizeof(Item) bytes (same slots and reuse rule).
   int stage_raw(const void* data, size_t bytes, hipStream_t st, const void** out, StageGuard* guard) {
     if (bytes > (size_t)cap * sizeof(Item)) return fail(GW_EINVAL, "too many items in one call");
-    CHK(reserve(st, guard));
+    CHK(take_slot(st, guard));
     const int k = guard->k;
     std::memcpy(host + (size_t)k * cap, data, bytes);
     HIPCHK(hipMemcpyAsync(dev + (size_t)k * cap, host + (size_t)k * cap, bytes, hipMemcpyHostToDevice, st));
@@ -1275,7 +1280,7 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   if (need_items) {
     if (pool) {
       if (in_args)
-        CHK(pool->stager.reserve(st, &guard));
+        CHK(pool->stager.reserve(items.size(), st, &guard));
       else
         CHK(pool->stager.stage(items, st, &dev_items, &guard));
       pool->mark_used(slots, n, guard);
