@@ -21,18 +21,24 @@
 // Block sums are written as FP32 partials; one launch adds the partials of
 // every layer in FP64 in a fixed order.
 //
-// One launch runs every layer: its 512 blocks (two per CU) are shared out by
-// the layers' work, so that they end together, a block's partials stay few,
-// and no layer pays for a launch of its own to fill and drain.  No wave holds
-// more than ten accumulator tiles: 128 registers, so that two blocks of eight
-// waves share a CU, hold them and a chunk's loads without spilling.
+// One launch runs every layer, so that no layer pays for a launch of its own to
+// fill and drain.  Its 1536 blocks are three for each place on the chip (two per
+// CU), shared out among the layers.  A block's sums are FP32, so a layer has so
+// many blocks that no sum takes more products than in the per-layer launches of
+// 256 blocks (wgrad_partial): 256 chains, a chain being one K slice of a block,
+// or 512 where those split their chunks in two.  (512 blocks, all resident and
+// ending together, left chains up to 4.4 times as long.)  No wave holds more than
+// ten accumulator tiles: 128 registers, so that two blocks of eight waves share a
+// CU, hold them and a chunk's loads without spilling.
 //
 // Measured, batch 32 x 21 x 32768: nine launches with operands read from memory
 // as they are and a launch pair per layer for the reduction 384 us (and 190 us
 // more to write dz and the activations); nine launches of this kernel's
 // blocks, with the reduction, the output conv's bias sum and the zero fill
-// 314 us; one launch and its reduction 195 us (matrix cores 70 us, memory at
-// copy rate 106 us).
+// 314 us; one launch and its reduction 207 us (512 blocks: 198; at batch 128 712
+// and 745; matrix cores 70 us, memory at copy rate 106 us).  512 blocks that close
+// their sums one to five times on the way: 248 us, the chunks' loop is slower with
+// the closing in it.
 #include "internal.h"
 
 namespace gw {
@@ -295,9 +301,9 @@ typedef Cfg<16, 8, 2, 256, ACT, DZ> C6;
 typedef Cfg<8, 8, 2, 256, ACT, DZ> C7;
 typedef Cfg<8, 1, 1, 512, ACT, RAW> C8;
 
-// each layer's share of the 512 blocks, from its blocks' run times in the
-// common launch (batch 32 x 21 x 32768: all end within 163 .. 193 us)
-constexpr int kShare[9] = {124, 27, 44, 58, 64, 53, 35, 51, 56};
+// each layer's blocks.  chains_ok holds from 32, 64, 64, 256, 256 and then 64 on;
+// with 124 for layer 0 and those the launch takes 222 us, as long blocks end alone
+constexpr int kShare[9] = {256, 128, 128, 256, 256, 128, 128, 128, 128};
 
 constexpr int mx(int a, int b) { return a > b ? a : b; }
 constexpr int LDS =
@@ -305,13 +311,19 @@ constexpr int LDS =
 static_assert(LDS * 4 + 12 * 64 * 4 <= 80 * 1024, "two blocks per CU");
 
 struct Geo2 {
-  int wt, ca, nk;
+  int wt, ca, nk, ns;
 };
 template <class K>
 constexpr Geo2 geo() {
-  return {K::WT, K::CA, K::NK};
+  return {K::WT, K::CA, K::NK, K::NS};
 }
 constexpr Geo2 kGeo[9] = {geo<C0>(), geo<C1>(), geo<C2>(), geo<C3>(), geo<C4>(), geo<C5>(), geo<C6>(), geo<C7>(), geo<C8>()};
+
+// layer l's chains at least those of its per-layer launch
+constexpr bool chains_ok(int l) {
+  return l == 9 || (kShare[l] * kGeo[l].ns >= (l == 1 || l >= 6 ? 512 : 256) && chains_ok(l + 1));
+}
+static_assert(chains_ok(0), "weight gradients: FP32 sums of too many products");
 
 int64_t chunks(int l, int n, int Lp) { return (int64_t)n * ((Lp + kGeo[l].wt - 1) / kGeo[l].wt); }
 int blocks(int l, int n, int Lp) { return (int)std::min<int64_t>(chunks(l, n, Lp), kShare[l]); }
