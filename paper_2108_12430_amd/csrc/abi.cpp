@@ -1021,26 +1021,49 @@ size_t f32_conv_bytes(const gw_model* m, bool adjoint) {
   for (int l = 0; l < L; ++l) b += f32_conv(m->layers[l], adjoint, l == L - 1).bytes;
   return b;
 }
+std::vector<const float*> f32_conv_frags(const gw_model* m, bool adjoint, const char* base) {
+  const int L = (int)m->layers.size();
+  std::vector<const float*> out(L, nullptr);
+  for (int l = 0; l < L; ++l) {
+    const F32Conv f = f32_conv(m->layers[l], adjoint, l == L - 1);
+    if (f.ok) out[l] = reinterpret_cast<const float*>(base);
+    base += f.bytes;
+  }
+  return out;
+}
 hipError_t pack_f32_convs(const gw_model* m, bool adjoint, char* base, std::vector<const float*>& out,
                           hipStream_t st) {
   const int L = (int)m->layers.size();
-  out.assign(L, nullptr);
+  out = f32_conv_frags(m, adjoint, base);
   gw::F32PackTab t{};
   for (int l = 0; l < L; ++l) {
+    if (!out[l]) continue;
     const LayerD& ly = m->layers[l];
     const F32Conv f = f32_conv(ly, adjoint, l == L - 1);
-    if (!f.ok) continue;
     if (t.n == gw::kF32PackMax) {
       const hipError_t e = gw::launch_pack_f32m(t, st);
       if (e != hipSuccess) return e;
       t.n = 0;
     }
-    float* dst = reinterpret_cast<float*>(base);
-    t.e[t.n++] = gw::f32m_pack_entry(m->params + ly.w, f.wso, f.wsi, dst, f.ci, f.co, f.k, f.s, f.p, f.tr);
-    out[l] = dst;
-    base += f.bytes;
+    t.e[t.n++] = gw::f32m_pack_entry(m->params + ly.w, f.wso, f.wsi, const_cast<float*>(out[l]), f.ci, f.co, f.k, f.s,
+                                     f.p, f.tr);
   }
   return gw::launch_pack_f32m(t, st);
+}
+
+// The layers of the reference network whose z GW_RECOMPUTE does not keep: the
+// cheapest two to make again (20 and 24 us of the convolutions' 20 .. 48 at batch
+// 32 x 21 x 32768) whose z together take the place of the last layer's and are
+// read before that is written.
+constexpr int kRedo[2] = {1, 2};
+bool redo(int l) { return l == kRedo[0] || l == kRedo[1]; }
+
+// the batch-statistics partials of a training convolution, in either precision
+size_t stats_bytes(const LayerD& ly, int n, int lout) {
+  const bool tr = ly.type == GW_LAYER_CONVT;
+  const int nblk = std::max(gw::conv_f32m_blocks(ly.ci, ly.co, n, lout, ly.k, ly.s, ly.p, tr, gw::EPI_STATS),
+                            gw::conv_bf16_stats_blocks(n, lout, ly.k, ly.s, ly.p, tr));
+  return (size_t)ly.co * nblk * 2 * sizeof(double);
 }
 
 int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags, DcWs& w) {
@@ -1066,8 +1089,10 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
   }
   const bool rec = flags & GW_RECOMPUTE;
   if (m->fused) {
-    // the reference network saves every z; activations are taken from it
-    // wherever they are read (GW_TRAIN alone still reserves room for them)
+    // the reference network saves z; activations are taken from it wherever they
+    // are read (GW_TRAIN alone still reserves room for them).  GW_RECOMPUTE keeps
+    // 28 W of the 36 W floats a window: kRedo's z lie where the last one goes,
+    // gone by then, and are made again by the backward
     w.mean.assign(L, NONE);
     w.invstd.assign(L, NONE);
     w.z.assign(L, NONE);
@@ -1075,14 +1100,20 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
     size_t part = 256;
     for (int l = 0; l + 1 < L; ++l) {
       const LayerD& ly = m->layers[l];
-      const bool tr = ly.type == GW_LAYER_CONVT;
       w.mean[l] = take(4 * ly.co);
       w.invstd[l] = take(4 * ly.co);
-      w.z[l] = take((size_t)n * ly.co * lout[l] * esz);
-      if (!rec) w.a[l] = take((size_t)n * ly.co * lout[l] * esz);
-      const int nblk = std::max(gw::conv_f32m_blocks(ly.ci, ly.co, n, lout[l], ly.k, ly.s, ly.p, tr, gw::EPI_STATS),
-                                gw::conv_bf16_stats_blocks(n, lout[l], ly.k, ly.s, ly.p, tr));
-      part = std::max(part, (size_t)ly.co * nblk * 2 * sizeof(double));
+      const size_t sz = (size_t)n * ly.co * lout[l] * esz;
+      if (!(rec && redo(l))) w.z[l] = take(sz);
+      if (!rec) w.a[l] = take(sz);
+      part = std::max(part, stats_bytes(ly, n, lout[l]));
+    }
+    if (rec) {
+      size_t at = w.z[L - 2], end = off;
+      for (int l : kRedo) {
+        w.z[l] = at;
+        at += r256((size_t)n * m->layers[l].co * lout[l] * esz);
+      }
+      if (at > end) return fail(GW_EINVAL, "recomputed layers do not fit the last one's place");
     }
     w.partial = take(part);
     w.wf32 = take(f32_conv_bytes(m, false));
@@ -1179,6 +1210,28 @@ extern "C" int deepclean_workspace(const gw_model* m, int32_t n, int32_t W, int3
 static gw::BnP bn_params(const gw_model* m, const DcWs& w, const char* ws, int l) {
   return {reinterpret_cast<const float*>(ws + w.mean[l]), reinterpret_cast<const float*>(ws + w.invstd[l]),
           m->params + m->layers[l].g, m->params + m->layers[l].be};
+}
+
+// Convolution l of the reference network in training, p.x -> p.y (the last
+// layer: its outputs): it takes tanh(BN(z)) of the layer before as it stages its
+// input and sums the statistics of its own z into `partial`.  wf32: its FP32
+// fragments (GW_FP32).
+static int train_conv(const gw_model* m, const DcWs& w, const char* ws, int l, gw::ConvP& p, const float* wf32,
+                      int precision, double* partial, const char* name, hipStream_t st) {
+  const LayerD& ly = m->layers[l];
+  const bool tr = ly.type == GW_LAYER_CONVT;
+  const int epi = l == (int)m->layers.size() - 1 ? gw::EPI_OUT : gw::EPI_STATS;
+  gw::F32Train t{};
+  if (l) t.in.bn = bn_params(m, w, ws, l - 1);
+  t.partial = partial;
+  if (precision == GW_BF16) {
+    p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
+    LAUNCH(nm(name, "L", l), st, gw::launch_conv_bf16(p, tr, epi, gw::SRC_DENSE, st, &t));
+  } else {
+    LAUNCH(nm(name, "L", l), st,
+           gw::launch_conv_f32m(p, {wf32, nullptr, nullptr}, tr, epi, st, l ? gw::PRO_ACT : gw::PRO_NONE, &t));
+  }
+  return GW_OK;
 }
 
 // deepclean_forward; with upd set (the fused inference kernels on pool input
@@ -1367,19 +1420,12 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   std::vector<const float*> wf(L, nullptr);
   if (precision == GW_FP32) LAUNCH("pack_f32m", st, pack_f32_convs(m, false, wsb + w.wf32, wf, st));
   if (m->fused) {
-    // the reference network: each convolution takes tanh(BN(z)) of the layer
-    // before as it stages its input and sums the statistics of its own z
     for (int l = 0; l < L; ++l) {
       const LayerD& ly = m->layers[l];
       const bool tr = ly.type == GW_LAYER_CONVT;
       gw::ConvP p = conv_params(m, ly, n, lin[l], lout[l]);
       p.x = l ? reinterpret_cast<const float*>(wsb + w.z[l - 1]) : x;
-      gw::F32Train t{};
-      if (l) t.in.bn = bn_params(m, w, wsb, l - 1);
-      t.partial = partial;
-      int epi = gw::EPI_STATS;
       if (l == L - 1) {
-        epi = gw::EPI_OUT;
         p.items = dev_items;
         p.noise = noise;
         p.clean = clean;
@@ -1387,13 +1433,7 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
       } else {
         p.y = reinterpret_cast<float*>(wsb + w.z[l]);
       }
-      if (precision == GW_BF16) {
-        p.wpk_lo = reinterpret_cast<const uint16_t*>(m->packed + ly.wbf_lo);
-        LAUNCH(nm("dc_train_conv", "L", l), st, gw::launch_conv_bf16(p, tr, epi, gw::SRC_DENSE, st, &t));
-      } else {
-        LAUNCH(nm("dc_train_conv", "L", l), st,
-               gw::launch_conv_f32m(p, {wf[l], nullptr, nullptr}, tr, epi, st, l ? gw::PRO_ACT : gw::PRO_NONE, &t));
-      }
+      CHK(train_conv(m, w, wsb, l, p, wf[l], precision, partial, "dc_train_conv", st));
       if (l == L - 1) break;
       const int nblk = precision == GW_BF16
                            ? gw::conv_bf16_stats_blocks(n, lout[l], ly.k, ly.s, ly.p, tr)
@@ -1683,7 +1723,7 @@ namespace {
 struct BwWs {
   size_t g[2] = {0, 0};
   size_t dz = 0;
-  std::vector<size_t> z, a;  // recomputed activations (recompute mode)
+  std::vector<size_t> z, a;  // recomputed z and activations (recompute mode; NONE: kept by the forward)
   size_t partial = 0;
   size_t wg = 0;
   size_t wf32 = 0, wa32 = 0;  // FP32 matrix-core fragments: forward (recomputation) and adjoint
@@ -1709,6 +1749,11 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
       const bool tr = ly.type == GW_LAYER_CONVT;
       Lp[l] = tr ? lin[l] : lout[l];
       if (l + 1 < L) b.dh.push_back(take((size_t)n * ly.co * lout[l] * 4));
+      b.z.push_back(NONE);
+      if ((flags & GW_RECOMPUTE) && redo(l)) {
+        b.z[l] = take((size_t)n * ly.co * lout[l] * 4);
+        part = std::max(part, stats_bytes(ly, n, lout[l]));
+      }
       if (l == 0) continue;
       const int nblk =
           gw::conv_f32m_blocks(ly.co, ly.ci, n, lin[l], ly.k, ly.s, ly.p, !tr, gw::EPI_BNBWD);
@@ -1775,10 +1820,20 @@ int bw_layout(const gw_model* m, int n, int W, uint32_t flags, BwWs& b) {
 // the forward's convolutions).
 static int backward_fused(const gw_model* m, int n, const float* x, const float* dnoise, const DcWs& w, const char* sv,
                           float* dparams, const BwWs& b, char* sc, const std::vector<int>& lin,
-                          const std::vector<int>& lout, hipStream_t st) {
+                          const std::vector<int>& lout, int precision, hipStream_t st) {
   const int L = (int)m->layers.size();
   double* partial = reinterpret_cast<double*>(sc + b.partial);
-  auto z_of = [&](int l) { return reinterpret_cast<const float*>(sv + w.z[l]); };
+  auto z_of = [&](int l) { return reinterpret_cast<const float*>(b.z[l] == NONE ? sv + w.z[l] : sc + b.z[l]); };
+  // GW_RECOMPUTE: the z that were not kept, by the forward's own convolutions
+  // (and fragments); the statistics they sum again are not read
+  const std::vector<const float*> wf = f32_conv_frags(m, false, sv + w.wf32);
+  for (int l = 0; l < L; ++l) {
+    if (b.z[l] == NONE) continue;
+    gw::ConvP p = conv_params(m, m->layers[l], n, lin[l], lout[l]);
+    p.x = z_of(l - 1);
+    p.y = reinterpret_cast<float*>(sc + b.z[l]);
+    CHK(train_conv(m, w, sv, l, p, wf[l], precision, partial, "dc_recompute_conv", st));
+  }
   std::vector<const float*> wa;
   LAUNCH("pack_f32m", st, pack_f32_convs(m, true, sc + b.wa32, wa, st));
   gw::Wg2Args wg[9];
@@ -1929,7 +1984,7 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
   const char* sv = reinterpret_cast<const char*>(saved);
   char* sc = reinterpret_cast<char*>(scratch);
   if (m->fused) {
-    return backward_fused(m, n, x, dnoise, w, sv, dparams, b, sc, lin, lout, st);
+    return backward_fused(m, n, x, dnoise, w, sv, dparams, b, sc, lin, lout, precision, st);
   }
   double* partial = reinterpret_cast<double*>(sc + b.partial);
   const bool rec = flags & GW_RECOMPUTE;
