@@ -1090,13 +1090,11 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
   const bool rec = flags & GW_RECOMPUTE;
   if (m->fused) {
     // the reference network saves z; activations are taken from it wherever they
-    // are read (GW_TRAIN alone still reserves room for them).  GW_RECOMPUTE keeps
-    // 28 W of the 36 W floats a window: kRedo's z lie where the last one goes,
-    // gone by then, and are made again by the backward
+    // are read.  GW_RECOMPUTE keeps 28 W of the 36 W floats a window: kRedo's z
+    // lie where the last one goes, gone by then, and are made again by the backward
     w.mean.assign(L, NONE);
     w.invstd.assign(L, NONE);
     w.z.assign(L, NONE);
-    w.a.assign(L, NONE);
     size_t part = 256;
     for (int l = 0; l + 1 < L; ++l) {
       const LayerD& ly = m->layers[l];
@@ -1104,7 +1102,6 @@ int dc_ws_layout(const gw_model* m, int n, int W, int precision, uint32_t flags,
       w.invstd[l] = take(4 * ly.co);
       const size_t sz = (size_t)n * ly.co * lout[l] * esz;
       if (!(rec && redo(l))) w.z[l] = take(sz);
-      if (!rec) w.a[l] = take(sz);
       part = std::max(part, stats_bytes(ly, n, lout[l]));
     }
     if (rec) {

@@ -19,8 +19,9 @@ def dc():
 
 
 @pytest.mark.parametrize("precision", [pytest.param(gs.FP32, id="fp32"), pytest.param(gs.BF16, id="bf16")])
-def test_recompute_holds_28_floats_a_sample(dc, precision):
+def test_held_floats_a_sample(dc, precision):
     n, W = 32, 32768
+    assert dc.workspace_bytes(n, W, precision, gs.TRAIN) <= 36.5 * 4 * n * W
     assert dc.workspace_bytes(n, W, precision, gs.TRAIN | gs.RECOMPUTE) <= 28.5 * 4 * n * W
 
 
