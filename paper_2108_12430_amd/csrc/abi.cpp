@@ -648,32 +648,9 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
     }
     if (m.layers.back().co != 1 || m.layers.back().bn)
       return fail(GW_EINVAL, "last layer must have one output channel and no normalisation");
-    for (auto& ly : m.layers) {
-      ly.bf16 = gw::conv_bf16_supported(ly.ci, ly.co, ly.k, ly.s, ly.type == GW_LAYER_CONVT);
-      if (ly.bf16) {
-        const size_t eb = r256(2 * gw::conv_bf16_packed_elems(ly.ci, ly.co, ly.k, ly.type == GW_LAYER_CONVT));
-        ly.wbf = pk;
-        pk += eb;
-        ly.wbf_lo = pk;
-        pk += eb;
-      }
-      // the adjoint of a stride-2 conv is a stride-2 transposed conv and
-      // vice versa, with input and output channels exchanged
-      const bool conv = ly.type == GW_LAYER_CONV;
-      // (the reference network's run in FP32: backward_fused)
-      ly.dg_mfma = ly.s == 2 && gw::conv_bf16_supported(ly.co, ly.ci, ly.k, 2, conv);
-      if (ly.dg_mfma) {
-        const size_t eb = r256(2 * gw::conv_bf16_packed_elems(ly.co, ly.ci, ly.k, conv));
-        ly.wdg = pk;
-        pk += eb;
-        ly.wdg_lo = pk;
-        pk += eb;
-      }
-      m.bf16_all = m.bf16_all && ly.bf16;
-    }
-    m.c_in = m.layers[0].ci;
+    const int Ln = (int)m.layers.size();
+    bool reference;  // the shape of the fused kernels
     {
-      const int Ln = (int)m.layers.size();
       std::vector<int> ci(Ln), co(Ln), ty(Ln), k(Ln), st(Ln), pd(Ln), op(Ln), bn(Ln);
       for (int l = 0; l < Ln; ++l) {
         const auto& ly = m.layers[l];
@@ -686,27 +663,51 @@ int build_layout(int32_t kind, const int32_t* desc, int32_t len, gw_model& m) {
         op[l] = ly.op;
         bn[l] = ly.bn;
       }
-      m.fused = m.bf16_all && gw::dc_fused_supported(ci.data(), co.data(), ty.data(), k.data(), st.data(),
-                                                     pd.data(), op.data(), bn.data(), Ln);
-      if (m.fused)
-        for (int l = 0; l < Ln; ++l) {  // FP16 copies for the fused kernel's FP16 variant
-          auto& ly = m.layers[l];
-          ly.dg_mfma = false;
-          const size_t f32 = gw::dc_f32_special_floats(l);
-          ly.wf32 = pk;
-          pk += r256(4 * (f32 ? f32 : gw::f32m_packed_floats(ly.ci, ly.co, ly.k, ly.s, ly.p,
-                                                             ly.type == GW_LAYER_CONVT)));
-          ly.wf16 = pk;
-          pk += r256(2 * gw::conv_bf16_packed_elems(ly.ci, ly.co, ly.k, ly.type == GW_LAYER_CONVT));
-          if (gw::dc_fused_special(l)) {
-            const size_t eb = r256(2 * gw::dc_fused_special_elems(l));
-            ly.wfs = pk;
-            pk += eb;
-            ly.wfs16 = pk;
-            pk += eb;
-          }
-        }
+      reference = gw::dc_fused_supported(ci.data(), co.data(), ty.data(), k.data(), st.data(), pd.data(), op.data(),
+                                         bn.data(), Ln);
     }
+    for (auto& ly : m.layers) {
+      ly.bf16 = gw::conv_bf16_supported(ly.ci, ly.co, ly.k, ly.s, ly.type == GW_LAYER_CONVT);
+      if (ly.bf16) {
+        const size_t eb = r256(2 * gw::conv_bf16_packed_elems(ly.ci, ly.co, ly.k, ly.type == GW_LAYER_CONVT));
+        ly.wbf = pk;
+        pk += eb;
+        ly.wbf_lo = pk;
+        pk += eb;
+      }
+      // the adjoint of a stride-2 conv is a stride-2 transposed conv and
+      // vice versa, with input and output channels exchanged
+      // (the reference network's adjoints run in FP32: backward_fused)
+      const bool conv = ly.type == GW_LAYER_CONV;
+      ly.dg_mfma = !reference && ly.s == 2 && gw::conv_bf16_supported(ly.co, ly.ci, ly.k, 2, conv);
+      if (ly.dg_mfma) {
+        const size_t eb = r256(2 * gw::conv_bf16_packed_elems(ly.co, ly.ci, ly.k, conv));
+        ly.wdg = pk;
+        pk += eb;
+        ly.wdg_lo = pk;
+        pk += eb;
+      }
+      m.bf16_all = m.bf16_all && ly.bf16;
+    }
+    m.c_in = m.layers[0].ci;
+    m.fused = m.bf16_all && reference;
+    if (m.fused)
+      for (int l = 0; l < Ln; ++l) {  // FP32 fragments and FP16 copies for the fused kernels
+        auto& ly = m.layers[l];
+        const size_t f32 = gw::dc_f32_special_floats(l);
+        ly.wf32 = pk;
+        pk += r256(4 * (f32 ? f32 : gw::f32m_packed_floats(ly.ci, ly.co, ly.k, ly.s, ly.p,
+                                                           ly.type == GW_LAYER_CONVT)));
+        ly.wf16 = pk;
+        pk += r256(2 * gw::conv_bf16_packed_elems(ly.ci, ly.co, ly.k, ly.type == GW_LAYER_CONVT));
+        if (gw::dc_fused_special(l)) {
+          const size_t eb = r256(2 * gw::dc_fused_special_elems(l));
+          ly.wfs = pk;
+          pk += eb;
+          ly.wfs16 = pk;
+          pk += eb;
+        }
+      }
   } else if (kind == GW_MODEL_BBHNET) {
     const int Sn = desc[0];
     if (Sn < 1 || Sn > 8 || len != 2 + Sn) return fail(GW_EINVAL, "bad BBHnet description length");
