@@ -294,13 +294,14 @@ int deepclean_update_forward(const gw_model* model, gw_pool* pool, int32_t n, co
  * with a per-stream cache of the last window, a request recomputes only the
  * positions whose receptive field reaches the new samples or the window's left
  * edge, and the full predicted-noise window comes out as if recomputed.  The
- * cache is laid out as every layer's activations; for the reference network
- * shape only the predicted noise is kept there, and changed outputs are computed
- * from their receptive fields.
+ * cache holds every layer's activations; for the reference network shape only
+ * the predicted noise, and changed outputs are computed from their receptive
+ * fields.
  *
  * deepclean_cache_bytes: device bytes of one stream's cache for windows of W
  * samples: every layer's activations as a ring, C_out x L_out BF16 (FP32 for
- * the output conv).  W must be a multiple of 16; at most 16 layers.
+ * the output conv; the reference network shape: that ring alone, 4 W bytes),
+ * each rounded up to 256.  W must be a multiple of 16; at most 16 layers.
  *
  * gw_stream_attach_cache: attach a caller-owned cache (device, 256-byte
  * aligned, at least deepclean_cache_bytes for the slot's W) to an open slot,

@@ -1488,7 +1488,7 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
 namespace {
 
 // Cache geometry of a DeepClean model for windows of W samples, and the
-// byte offset of every layer's ring in a stream's cache.
+// byte offset of every ring it keeps in a stream's cache.
 int cache_layout(const gw_model* m, int W, gw::CacheLayerP& P, size_t* total) {
   if (m->kind != GW_MODEL_DEEPCLEAN) return fail(GW_ESTATE, "not a DeepClean model");
   const int L = (int)m->layers.size();
@@ -1515,8 +1515,9 @@ int cache_layout(const gw_model* m, int W, gw::CacheLayerP& P, size_t* total) {
     if (16 % g.f) return fail(GW_EUNSUPPORTED, "layer grids must divide the 16-sample shift unit");
     if (!gw::cache_layer_fits(g) || !ly.bf16)
       return fail(GW_EUNSUPPORTED, "no cached kernel for this layer shape (k7 p3 layers with compiled channel tiles)");
+    // the reference network's kernel keeps the noise ring alone
     P.off[l] = off;
-    off += r256((size_t)g.co * g.Lout * (g.f32 ? 4 : 2));
+    if (!m->fused || l == L - 1) off += r256((size_t)g.co * g.Lout * (g.f32 ? 4 : 2));
   }
   P.W = W;
   P.L = L;
