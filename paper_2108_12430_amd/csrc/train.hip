@@ -675,7 +675,9 @@ hipError_t launch_wgrad(const float* P, int Ca, int Lp, const float* Q, int Cc, 
 // Measured, 32 windows of 32768, 81 bins, loss and gradient: one thread per
 // (sample, bin) with vector FP64 sums, four windows a basis value 99 us;
 // these kernels 44 us.  Left: the basis evaluations, the FP64 products at
-// half of the vector FP32 rate (5 us), and three dependent launches.
+// half of the vector FP32 rate (5 us), and three dependent launches.  Calls of up
+// to four windows leave the matrix instructions, whose rows they do not fill, to
+// FP64 products in vector registers (the rules are at the end).
 // ---------------------------------------------------------------------------
 namespace bp {
 
@@ -701,7 +703,7 @@ __device__ __forceinline__ int mulmod(int k, int t, int W) {
 // sample 4 (l / 16) + e in step e.  The waves' sums are added through LDS.
 template <int MT>
 __global__ __launch_bounds__(512) void bp_project(const float* strain, const float* noise, int n, int nb, int W,
-                                                  int k_lo, int S, double* partial) {
+                                                  int k_lo, int S, double* partial, float* proj) {
   using namespace bp;
   __shared__ double red[4][MT * 2 * 4 * 64];
   const int tile = blockIdx.x / S, slice = blockIdx.x - tile * S;
@@ -789,8 +791,62 @@ __global__ __launch_bounds__(512) void bp_project(const float* strain, const flo
     const int q = e & 1, bb = (e >> 1) % (16 * MT), bin = e / (32 * MT);
     const int o = (((bb >> 4) * 2 + q) * 4 + ((bb & 15) >> 2)) * 64 + 16 * (bb & 3) + bin;
     const int kk = 16 * tile + bin, b = b0 + bb;
-    if (kk < nb && b < n)
-      partial[(((int64_t)slice * nb + kk) * n + b) * 2 + q] = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
+    if (kk < nb && b < n) {
+      const double v = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
+      const int64_t at = ((int64_t)kk * n + b) * 2 + q;
+      if (S == 1)
+        proj[at] = (float)v;
+      else
+        partial[slice * (2 * (int64_t)n * nb) + at] = v;
+    }
+  }
+}
+
+// The same for NW windows, up to four: there the matrix instruction's 16 rows
+// are mostly empty, and two of it cost as much as the basis values.  A wave
+// takes one bin over a slice of the samples, its lanes every 64th, with FP64
+// products and sums in vector registers; the lanes' sums are added in a fixed tree.
+template <int NW>
+__global__ __launch_bounds__(256) void bp_project_few(const float* strain, const float* noise, int nb, int W, int k_lo,
+                                                      int S, double* partial, float* proj) {
+  using namespace bp;
+  const int tile = (int)blockIdx.x / S, slice = (int)blockIdx.x - tile * S;
+  const int lane = threadIdx.x & 63;
+  const int kk = 4 * tile + (int)(threadIdx.x >> 6), k = k_lo + kk;
+  if (kk >= nb) return;  // wave-uniform; the kernel has no barrier
+  const int rounds = (W + 63) / 64;
+  const int c0 = (int)((int64_t)rounds * slice / S), c1 = (int)((int64_t)rounds * (slice + 1) / S);
+  const int step = mulmod(k, 64, W), t1 = min(64 * c1, W);
+  int m = mulmod(k, min(64 * c0 + lane, W - 1), W);
+  double a[NW], b[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) a[w] = b[w] = 0.0;
+  const float twoW = 2.0f / (float)W;
+#pragma unroll 2
+  for (int t = 64 * c0 + lane; t < t1; t += 64) {
+    float sn, cs;
+    sincospif(twoW * (float)m, &sn, &cs);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const double r = (double)(strain[(int64_t)w * W + t] - noise[(int64_t)w * W + t]);
+      a[w] = fma(r, (double)cs, a[w]);
+      b[w] = fma(r, (double)sn, b[w]);
+    }
+    m += step;
+    if (m >= W) m -= W;
+  }
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    for (int off = 32; off > 0; off >>= 1) {
+      a[w] += __shfl_down(a[w], off, 64);
+      b[w] += __shfl_down(b[w], off, 64);
+    }
+    const int64_t at = (int64_t)kk * NW + w;
+    if (lane != 0) continue;
+    if (S == 1)
+      reinterpret_cast<float2*>(proj)[at] = make_float2((float)a[w], (float)b[w]);
+    else
+      reinterpret_cast<double2*>(partial)[slice * (int64_t)nb * NW + at] = make_double2(a[w], b[w]);
   }
 }
 
@@ -821,17 +877,27 @@ __global__ __launch_bounds__(256) void bp_final(const double* partial, int64_t n
 // weight of bin k against the others': c_k W / 2, exact
 __device__ __forceinline__ float bin_weight(int k, int W) { return k == 0 || 2 * k == W ? 0.5f : 1.0f; }
 
+// in a block of 256 threads, or by the first 256 of a larger one
 __device__ __forceinline__ void bp_loss_block(const float* proj, int n, int nb, int W, int k_lo, float* loss) {
-  double s = 0.0, unused = 0.0;
+  __shared__ double sv[256];
+  const int tid = threadIdx.x;
+  double s = 0.0;
   const int64_t np = (int64_t)n * nb;
   const double first = bin_weight(k_lo, W), last = bin_weight(k_lo + nb - 1, W);
+  if (tid < 256) {
 #pragma unroll 4
-  for (int64_t e = threadIdx.x; e < np; e += 256) {
-    const float2 v = reinterpret_cast<const float2*>(proj)[e];
-    s += (e < n ? first : e >= np - n ? last : 1.0) * ((double)v.x * v.x + (double)v.y * v.y);
+    for (int64_t e = tid; e < np; e += 256) {
+      const float2 v = reinterpret_cast<const float2*>(proj)[e];
+      s += (e < n ? first : e >= np - n ? last : 1.0) * ((double)v.x * v.x + (double)v.y * v.y);
+    }
+    sv[tid] = s;
   }
-  block_sum2(s, unused);
-  if (threadIdx.x == 0) loss[0] = (float)(s * (2.0 / (double)W) / ((double)n * W));
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (tid < w) sv[tid] += sv[tid + w];
+    __syncthreads();
+  }
+  if (tid == 0) loss[0] = (float)(sv[0] * (2.0 / (double)W) / ((double)n * W));
 }
 
 __global__ __launch_bounds__(256) void bp_loss(const float* proj, int n, int nb, int W, int k_lo, float* loss) {
@@ -909,23 +975,94 @@ __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb,
     }
 }
 
+// The same for NW windows, up to four, as bp_project_few is: a block takes 64
+// samples, its eight waves an eighth of the bins each, whose sums are added in
+// wave order.
+template <int NW>
+__global__ __launch_bounds__(512) void bp_grad_few(const float* __restrict__ proj, int nb, int W, int k_lo, double scale,
+                                                   float* __restrict__ dnoise, float* loss) {
+  using namespace bp;
+  if (loss && blockIdx.x == gridDim.x - 1) {
+    bp_loss_block(proj, NW, nb, W, k_lo, loss);
+    return;
+  }
+  __shared__ double red[8][NW * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = blockIdx.x * 64 + lane, tc = min(t, W - 1);
+  const int k0 = (int)((int64_t)nb * wave / 8), k1 = (int)((int64_t)nb * (wave + 1) / 8);
+  int m = mulmod(min(k_lo + k0, W - 1), tc, W);
+  const float twoW = 2.0f / (float)W;
+  double acc[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) acc[w] = 0.0;
+#pragma unroll 2
+  for (int kk = k0; kk < k1; ++kk) {
+    const float bw = bin_weight(k_lo + kk, W);
+    float sn, cs;
+    sincospif(twoW * (float)m, &sn, &cs);
+    const float2* v = reinterpret_cast<const float2*>(proj) + (int64_t)kk * NW;  // wave-uniform
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      acc[w] = fma((double)(bw * v[w].x), (double)cs, acc[w]);
+      acc[w] = fma((double)(bw * v[w].y), (double)sn, acc[w]);
+    }
+    m += tc;
+    if (m >= W) m -= W;
+  }
+#pragma unroll
+  for (int w = 0; w < NW; ++w) red[wave][w * 64 + lane] = acc[w];
+  __syncthreads();
+  for (int e = threadIdx.x; e < NW * 64; e += 512) {
+    double a = red[0][e];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) a += red[w][e];
+    const int u = blockIdx.x * 64 + (e & 63);
+    if (u < W) dnoise[(int64_t)(e >> 6) * W + u] = (float)(scale * a);
+  }
+}
+
 namespace bp {
-// Windows per block: 32, or 16 where that covers them all.  Slices of the
-// samples: as many as make 512 blocks (16 waves a CU), of 128 samples at
-// least, in multiples of eight so that a slice's bin tiles, which read the same
-// samples, meet in one XCD's cache.
+// Windows per block: 32, or 16 where that covers them all.
 int windows(int n) { return n > 16 ? 32 : 16; }
+// Up to four windows take the kernels without matrix instructions.  Measured (us
+// of the device, loss and gradient; loss alone): one window of 32768, 20 .. 500 Hz at
+// 4096 samples a second (3841 bins) 271 and 144 (matrix 617 and 271), 55 .. 65 Hz (81
+// bins) 18 and 18 (27 and 19); four windows of 32768, 3841 bins: 417 and 234 (616 and
+// 275); five windows, every bin, in them 2426 and 1237: a second batch of four would
+// take 1600 more.
+bool few(int n) { return n <= 4; }
+
+// Slices of the samples.  bp_project: as many as make 512 blocks (16 waves a CU),
+// of 128 samples at least, in multiples of eight so that a slice's bin tiles,
+// which read the same samples, meet in one XCD's cache.  bp_project_few: as many
+// as make 4096 waves, of 512 samples at least, and up to 2048 samples one, which
+// needs no launch to add them (one of 1024, 257 bins, loss and gradient: 18.7 ->
+// 16.6 us; one of 2048, 1025 bins, the loss alone: 13.2 -> 11.9).
 int slices(int n, int W, int nb) {
+  if (few(n) && W <= 2048) return 1;
+  if (few(n)) return (int)std::max<int64_t>(1, std::min<int64_t>(4096 / nb, (W + 63) / 64 / 8));
   const int64_t blocks = (int64_t)((nb + 15) / 16) * ((n + windows(n) - 1) / windows(n));
   const int64_t s = std::max<int64_t>(1, std::min<int64_t>(512 / blocks, (W + 127) / 128));
   return (int)(s >= 8 ? s / 8 * 8 : s);
 }
 }  // namespace bp
 
-// The slices' FP64 sums lie before the projections.  They take at most 16 n nb
-// bytes, or 4 MiB where there is more than one slice.
+// The projections, and before them the slices' FP64 sums if there is more than
+// one slice (then at most 4 MiB).
 size_t bandpass_ws_bytes(int n, int W, int nb) {
-  return 8 * (size_t)n * nb * (1 + 2 * (size_t)bp::slices(n, W, nb));
+  const int S = bp::slices(n, W, nb);
+  return 8 * (size_t)n * nb * (S > 1 ? 1 + 2 * (size_t)S : 1);
+}
+
+template <int NW>
+static void launch_few(bool grad, int nb, int W, int k_lo, int S, const float* strain, const float* noise, double* partial,
+                       float* proj, double scale, float* dnoise, float* loss, hipStream_t st) {
+  if (!grad)
+    hipLaunchKernelGGL(bp_project_few<NW>, dim3((nb + 3) / 4 * S), dim3(256), 0, st, strain, noise, nb, W, k_lo, S,
+                       partial, proj);
+  else
+    hipLaunchKernelGGL(bp_grad_few<NW>, dim3((W + 63) / 64 + (loss ? 1 : 0)), dim3(512), 0, st, proj, nb, W, k_lo, scale,
+                       dnoise, loss);
 }
 
 hipError_t launch_bandpass(int n, int W, int k_lo, int k_hi, const float* strain,
@@ -933,25 +1070,31 @@ hipError_t launch_bandpass(int n, int W, int k_lo, int k_hi, const float* strain
                            hipStream_t st) {
   const int nb = k_hi - k_lo + 1;
   if (nb <= 0) return hipErrorInvalidValue;
-  const int nw = bp::windows(n), S = bp::slices(n, W, nb);
+  const int nw = bp::windows(n), S = bp::slices(n, W, nb), gy = (n + nw - 1) / nw;
   const int64_t nv = 2 * (int64_t)n * nb;
+  const double scale = -2.0 / ((double)n * W) * (2.0 / (double)W);
   double* partial = reinterpret_cast<double*>(ws);
-  float* proj = reinterpret_cast<float*>(partial + S * nv);
-  const dim3 pg((nb + 15) / 16 * S, (n + nw - 1) / nw);  // 16-bin tiles x slices, windows
-  if (nw == 32)
-    hipLaunchKernelGGL(bp_project<2>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial);
+  float* proj = S > 1 ? reinterpret_cast<float*>(partial + S * nv) : reinterpret_cast<float*>(ws);
+  const auto few = [&](bool grad) {
+    const auto f = n == 1 ? launch_few<1> : n == 2 ? launch_few<2> : n == 3 ? launch_few<3> : launch_few<4>;
+    f(grad, nb, W, k_lo, S, strain, noise, partial, proj, scale, dnoise, loss, st);
+  };
+  const dim3 pg((nb + 15) / 16 * S, gy);  // 16-bin tiles x slices, windows
+  if (bp::few(n))
+    few(false);
+  else if (nw == 32)
+    hipLaunchKernelGGL(bp_project<2>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial, proj);
   else
-    hipLaunchKernelGGL(bp_project<1>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial);
-  hipLaunchKernelGGL(bp_final, dim3((unsigned)((nv + 63) / 64)), dim3(256), 0, st, partial, nv, S, proj);
-  if (dnoise) {
-    const double scale = -2.0 / ((double)n * W) * (2.0 / (double)W);
-    const dim3 gg((W + 63) / 64 + (loss ? 1 : 0), pg.y);
-    if (nw == 32)
-      hipLaunchKernelGGL(bp_grad<2>, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
-    else
-      hipLaunchKernelGGL(bp_grad<1>, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
-  } else if (loss) {
-    hipLaunchKernelGGL(bp_loss, dim3(1), dim3(256), 0, st, proj, n, nb, W, k_lo, loss);
+    hipLaunchKernelGGL(bp_project<1>, pg, dim3(512), 0, st, strain, noise, n, nb, W, k_lo, S, partial, proj);
+  if (S > 1) hipLaunchKernelGGL(bp_final, dim3((unsigned)((nv + 63) / 64)), dim3(256), 0, st, partial, nv, S, proj);
+  if (!dnoise) {
+    if (loss) hipLaunchKernelGGL(bp_loss, dim3(1), dim3(256), 0, st, proj, n, nb, W, k_lo, loss);
+  } else if (bp::few(n)) {
+    few(true);
+  } else {
+    const dim3 gg((W + 63) / 64 + (loss ? 1 : 0), gy);
+    const auto grad = nw == 32 ? bp_grad<2> : bp_grad<1>;
+    hipLaunchKernelGGL(grad, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
   }
   return hipGetLastError();
 }
