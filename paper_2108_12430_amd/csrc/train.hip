@@ -907,9 +907,11 @@ __global__ __launch_bounds__(256) void bp_loss(const float* proj, int n, int nb,
 // dL/dnoise[window][t] = scale * sum over bins of weight (A cos[t] + B sin[t]),
 // on the same instruction: a wave takes 16 samples of 16 MT windows and four
 // bins a step.  (With FP32 sums it took 11 us instead of 17, and had up to 1.4 times
-// the error of the kernel before it.)  The last
-// block of the first row computes the loss, if that is asked for.
-template <int MT>
+// the error of the kernel before it.)  SPLIT: the block's four waves take a
+// quarter of the bins each of the same 16 samples, for launches of few blocks; else
+// 16 samples each.  The last block of the first row computes the loss, if that is
+// asked for.
+template <int MT, bool SPLIT>
 __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb, int W, int k_lo, double scale,
                                                float* dnoise, float* loss) {
   using namespace bp;
@@ -917,11 +919,14 @@ __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb,
     if (blockIdx.y == 0) bp_loss_block(proj, n, nb, W, k_lo, loss);
     return;
   }
+  __shared__ double red[SPLIT ? 4 : 1][SPLIT ? MT * 4 * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   const int b0 = blockIdx.y * 16 * MT;
-  const int t = blockIdx.x * 64 + 16 * wave + lr, tc = min(t, W - 1);
-  int m = mulmod(min(k_lo + lk, W - 1), tc, W);
+  const int t = SPLIT ? blockIdx.x * 16 + lr : blockIdx.x * 64 + 16 * wave + lr, tc = min(t, W - 1);
+  const int steps = (nb + 7) / 8;  // of eight bins
+  const int k0 = SPLIT ? 8 * (steps * wave / 4) : 0, k1 = SPLIT ? min(8 * (steps * (wave + 1) / 4), nb) : nb;
+  int m = mulmod(min(k_lo + k0 + lk, W - 1), tc, W);
   const int step = mulmod(4, tc, W);
   const float twoW = 2.0f / (float)W;
   const float2* src[MT];
@@ -940,8 +945,8 @@ __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb,
 #pragma unroll
       for (int g = 0; g < MT; ++g) next[h][g] = src[g][(int64_t)min(kk0 + 4 * h + lk, nb - 1) * n];
   };
-  load(0);
-  for (int kk0 = 0; kk0 < nb; kk0 += 8) {
+  load(k0);
+  for (int kk0 = k0; kk0 < k1; kk0 += 8) {
     float2 v[2][MT];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -965,14 +970,27 @@ __global__ __launch_bounds__(256) void bp_grad(const float* proj, int n, int nb,
       if (m >= W) m -= W;
     }
   }
-  if (t >= W) return;
+  if constexpr (SPLIT) {
 #pragma unroll
-  for (int g = 0; g < MT; ++g)
+    for (int g = 0; g < MT; ++g)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int b = b0 + 16 * g + 4 * i + lk;
-      if (b < n) dnoise[(int64_t)b * W + t] = (float)(scale * (acc[g][0][i] + acc[g][1][i]));
+      for (int i = 0; i < 4; ++i) red[wave][(4 * g + i) * 64 + lane] = acc[g][0][i] + acc[g][1][i];
+    __syncthreads();
+    for (int e = threadIdx.x; e < MT * 256; e += 256) {
+      const int l = e & 63, b = b0 + 4 * (e >> 6) + (l >> 4), u = blockIdx.x * 16 + (l & 15);
+      if (b < n && u < W)
+        dnoise[(int64_t)b * W + u] = (float)(scale * (((red[0][e] + red[1][e]) + red[2][e]) + red[3][e]));
     }
+  } else {
+    if (t >= W) return;
+#pragma unroll
+    for (int g = 0; g < MT; ++g)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int b = b0 + 16 * g + 4 * i + lk;
+        if (b < n) dnoise[(int64_t)b * W + t] = (float)(scale * (acc[g][0][i] + acc[g][1][i]));
+      }
+  }
 }
 
 // The same for NW windows, up to four, as bp_project_few is: a block takes 64
@@ -1031,7 +1049,18 @@ int windows(int n) { return n > 16 ? 32 : 16; }
 // 275); five windows, every bin, in them 2426 and 1237: a second batch of four would
 // take 1600 more.
 bool few(int n) { return n <= 4; }
-
+// The gradient so only for launches of 128 blocks or more: four windows of 4096,
+// every bin, 100 us against 64 for bp_grad with its bins split; one of 8192, 134
+// against 224.
+bool few_grad(int n, int W) { return few(n) && W >= 8192; }
+// bp_grad splits its bins where that fills the chip: 32 windows of 8192, 961 bins
+// (128 blocks unsplit) 127 -> 74 us, of 16384 (256) 290 -> 236, 32 of 512, 257 bins,
+// 37 -> 20, one of 2048, 241 bins, 25 -> 14, 16 of 8192, 81 bins, 19 -> 16.  Few bins
+// are not worth their sums' exchange: 81 in 512 blocks 41.9 against 42.8.
+bool split(int n, int W, int nb) {
+  const int64_t blocks = (int64_t)((W + 63) / 64) * ((n + windows(n) - 1) / windows(n));
+  return blocks < 1024 && nb >= (blocks <= 256 ? 64 : 256);
+}
 // Slices of the samples.  bp_project: as many as make 512 blocks (16 waves a CU),
 // of 128 samples at least, in multiples of eight so that a slice's bin tiles,
 // which read the same samples, meet in one XCD's cache.  bp_project_few: as many
@@ -1089,11 +1118,12 @@ hipError_t launch_bandpass(int n, int W, int k_lo, int k_hi, const float* strain
   if (S > 1) hipLaunchKernelGGL(bp_final, dim3((unsigned)((nv + 63) / 64)), dim3(256), 0, st, partial, nv, S, proj);
   if (!dnoise) {
     if (loss) hipLaunchKernelGGL(bp_loss, dim3(1), dim3(256), 0, st, proj, n, nb, W, k_lo, loss);
-  } else if (bp::few(n)) {
+  } else if (bp::few_grad(n, W)) {
     few(true);
   } else {
-    const dim3 gg((W + 63) / 64 + (loss ? 1 : 0), gy);
-    const auto grad = nw == 32 ? bp_grad<2> : bp_grad<1>;
+    const bool split = bp::split(n, W, nb);
+    const dim3 gg((split ? (W + 15) / 16 : (W + 63) / 64) + (loss ? 1 : 0), gy);
+    const auto grad = nw == 32 ? (split ? bp_grad<2, true> : bp_grad<2, false>) : split ? bp_grad<1, true> : bp_grad<1, false>;
     hipLaunchKernelGGL(grad, gg, dim3(256), 0, st, proj, n, nb, W, k_lo, scale, dnoise, loss);
   }
   return hipGetLastError();

@@ -51,3 +51,16 @@ def check(n, W, k_lo, k_hi, shift):
 ])
 def test_few_windows(n, W, k_lo, k_hi):
     check(n, W, k_lo, k_hi, 1)
+
+
+@pytest.mark.parametrize("n,W,k_lo,k_hi", [
+    (5, 511, 0, 62), (5, 512, 1, 64),          # one bin below the split, and at it
+    (16, 1031, 3, 70), (17, 1031, 3, 270),     # one window tile of either kind; samples not whole tiles
+    (33, 527, 0, 263), (32, 33, 0, 16),        # every bin; a few
+    (5, 16384, 1, 64), (5, 16400, 1, 64),      # 256 blocks unsplit, 257
+    (5, 16400, 1, 255), (5, 16400, 1, 256),    # the latter's bound
+    (6, 65472, 10, 265), (6, 65536, 10, 265),  # 1023 blocks, 1024
+])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_split_bins(n, W, k_lo, k_hi, shift):
+    check(n, W, k_lo, k_hi, shift)
