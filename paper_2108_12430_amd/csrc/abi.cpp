@@ -2098,15 +2098,24 @@ extern "C" int deepclean_backward(const gw_model* m, int32_t n, int32_t W, const
 namespace {
 int band(int W, float fs, float f_lo, float f_hi, int* k_lo, int* k_hi) {
   if (W < 2 || !(fs > 0) || !(f_lo >= 0) || !(f_hi >= f_lo)) return fail(GW_EINVAL, "bad band");
-  int lo = -1, hi = -2;
-  for (int k = 0; k <= W / 2; ++k) {
-    const double f = (double)k * (double)fs / (double)W;
-    if (f >= (double)f_lo && f <= (double)f_hi) {
-      if (lo < 0) lo = k;
-      hi = k;
+  // the bins k of 0 .. W / 2 with f_lo <= k fs / W <= f_hi are neighbours, k fs / W
+  // (as rounded) never falling with k: their ends by bisection.  (Tried one by
+  // one, they took 40 us of a call's 47 on the host at W = 32768.)
+  const auto f = [&](int k) { return (double)k * (double)fs / (double)W; };
+  const auto first = [&](auto past) {  // the first bin past(k) holds for, W / 2 + 1 if none
+    int a = 0, b = W / 2 + 1;
+    while (a < b) {
+      const int k = a + (b - a) / 2;
+      if (past(k))
+        b = k;
+      else
+        a = k + 1;
     }
-  }
-  if (lo < 0) return fail(GW_EINVAL, "no DFT bin inside the band");
+    return a;
+  };
+  const int lo = first([&](int k) { return f(k) >= (double)f_lo; });
+  const int hi = first([&](int k) { return f(k) > (double)f_hi; }) - 1;
+  if (lo > hi) return fail(GW_EINVAL, "no DFT bin inside the band");
   *k_lo = lo;
   *k_hi = hi;
   return GW_OK;

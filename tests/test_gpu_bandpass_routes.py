@@ -64,3 +64,12 @@ def test_few_windows(n, W, k_lo, k_hi):
 @pytest.mark.parametrize("shift", [0, 1])
 def test_split_bins(n, W, k_lo, k_hi, shift):
     check(n, W, k_lo, k_hi, shift)
+
+
+@pytest.mark.parametrize("n,W,k_lo,k_hi", [
+    (16, 1024, 9, 136), (16, 1024, 9, 137),               # eight slices of 4096 values, and of more
+    (5, 250, 0, 20), (7, 800, 30, 30), (128, 600, 3, 9),  # two, seven and five slices
+    (2, 4096, 60, 66), (5, 4096, 60, 66),                 # eight, and more
+])
+def test_loss_alone(n, W, k_lo, k_hi):
+    check(n, W, k_lo, k_hi, 0)
