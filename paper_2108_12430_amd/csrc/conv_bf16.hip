@@ -1771,19 +1771,31 @@ bool dc_fused_supported(const int* ci, const int* co, const int* type, const int
   return true;
 }
 
+// blocks of a variant that share a CU
 template <class Z, int IN, bool F16, bool UPD, bool CAUSAL>
-static hipError_t launch_dc_t(const DcIn& p, const ItemArgs& args, const FusedP& f, int n, int cu_budget,
-                              hipStream_t st) {
-  const int64_t ntile = (int64_t)n * ((p.Lin + Z::T - 1) / Z::T);
-  if (ntile > (int64_t)1 << 30) return hipErrorInvalidValue;
-  // one resident grid: (blocks per CU) x CUs, at most one block per tile
+static int dc_occ() {
   static const int occ = [] {
     int k = 0;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, dc_fused<Z, IN, F16, UPD, CAUSAL>, Z::NTHR, 0) == hipSuccess && k > 0
                ? k
                : 1;
   }();
-  const int64_t grid = CAUSAL ? ntile : std::min<int64_t>(ntile, (int64_t)occ * cu_budget);
+  return occ;
+}
+template <class Z>
+static int dc_ring_occ(bool f16, bool upd) {
+  if (f16) return upd ? dc_occ<Z, IN_RING_F32, true, true, false>() : dc_occ<Z, IN_RING_F32, true, false, false>();
+  return upd ? dc_occ<Z, IN_RING, false, true, false>() : dc_occ<Z, IN_RING, false, false, false>();
+}
+
+template <class Z, int IN, bool F16, bool UPD, bool CAUSAL>
+static hipError_t launch_dc_t(const DcIn& p, const ItemArgs& args, const FusedP& f, int n, int cu_budget,
+                              hipStream_t st) {
+  const int64_t ntile = (int64_t)n * ((p.Lin + Z::T - 1) / Z::T);
+  if (ntile > (int64_t)1 << 30) return hipErrorInvalidValue;
+  // one resident grid: (blocks per CU) x CUs, at most one block per tile
+  const int64_t grid =
+      CAUSAL ? ntile : std::min<int64_t>(ntile, (int64_t)dc_occ<Z, IN, F16, UPD, CAUSAL>() * cu_budget);
   hipLaunchKernelGGL((dc_fused<Z, IN, F16, UPD, CAUSAL>), dim3((unsigned)grid), dim3(Z::NTHR), 0, st, args, p, f, (int)ntile);
   return hipGetLastError();
 }
@@ -1854,21 +1866,29 @@ hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint
   // 24.5, 12 (2 and 1) 32.4 and 25.1, 20 (2 and 2) 34.2 and 34.6, 24 (3 and 2)
   // 45.2 and 40.3, 36 (4 and 3) 58 and 53, 48 (5 and 4) 70 and 64 .. 69, 72 (7 and
   // 6) 92 and 88 .. 94, 96 (9 and 8) 114 and 112 .. 121; FP16: 12 37.3 and 28.6, 24
-  // 53 and 45, 36 67 and 60.5, 48 82 and 76.  (Dense windows keep 768: a pool's
-  // streams are what comes in such numbers.)
+  // 53 and 45, 36 67 and 60.5, 48 82 and 76.  With the update of strides of 256 at
+  // 48 66 and 63, FP16 79 and 73; of 256, 512 and 1024 mixed 74 and 76, FP16 86 and
+  // 85: there the updates' samples weigh as much.  GW_CAUSAL keeps 768: 179 windows
+  // of mixed strides (242 tiles with work at either size) 23.2 and 24.2 with the
+  // update, 400 of 256 23.1 and 22.5 (without it 16.5 and 15.3, 17.3 and 16.3).
+  // Dense windows keep 768 only because no variant for them is compiled: they
+  // would gain the same, n = 12 32.3 and 24.2, 24 46 and 38.6, 36 59 and 52, 48 71
+  // and 66, 72 95 and 95.
   if (ring && !p.causal) {
+    const bool upd = p.upd != nullptr;
     auto rounds = [&](int T, int per_cu) {
       const int64_t cap = (int64_t)per_cu * ncu;
       return ((int64_t)n * ((W + T - 1) / T) + cap - 1) / cap;
     };
-    const int64_t r768 = rounds(768, 2), r512 = rounds(512, 3);
+    const int64_t r768 = rounds(768, dc_ring_occ<fused::Geom<768, 12>>(f16, upd));
+    const int64_t r512 = rounds(512, dc_ring_occ<fused::Geom<512, 8>>(f16, upd));
     using Z = fused::Geom<512, 8>;
     if (r512 < r768 && r768 <= 5) {
       if (f16)
-        return p.upd ? launch_dc_t<Z, IN_RING_F32, true, true, false>(p, args, f, n, ncu, st)
-                     : launch_dc_t<Z, IN_RING_F32, true, false, false>(p, args, f, n, ncu, st);
-      return p.upd ? launch_dc_t<Z, IN_RING, false, true, false>(p, args, f, n, ncu, st)
-                   : launch_dc_t<Z, IN_RING, false, false, false>(p, args, f, n, ncu, st);
+        return upd ? launch_dc_t<Z, IN_RING_F32, true, true, false>(p, args, f, n, ncu, st)
+                   : launch_dc_t<Z, IN_RING_F32, true, false, false>(p, args, f, n, ncu, st);
+      return upd ? launch_dc_t<Z, IN_RING, false, true, false>(p, args, f, n, ncu, st)
+                 : launch_dc_t<Z, IN_RING, false, false, false>(p, args, f, n, ncu, st);
     }
   }
   return launch_dc_z<fused::Geom<768, 12>>(p, args, f, n, ring, f16, ncu, st);
