@@ -222,6 +222,9 @@ struct gw_pool {
   int max_slots = 0, max_items = 0;
   size_t ring_base = 0;
   Stager stager;
+  // The last DeepClean forward from this pool filled more than a block a CU
+  // (dense, fused): the BBHnet forwards beside it choose their placement by it.
+  bool dc_fills = false;
   struct Slot {
     bool open = false;
     int C = 0, W = 0;
@@ -1326,6 +1329,8 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   const bool one_kernel = m->fused && !(flags & (GW_TRAIN | GW_LAYERWISE));
   // the fused kernels take the items of a small call as an argument
   const bool in_args = one_kernel && n <= gw::kItemArgs;
+  if (pool)
+    pool->dc_fills = one_kernel && precision != GW_FP32 && !(flags & GW_CAUSAL) && gw::dc_fused_fills(n, Wb);
   const Item* dev_items = nullptr;
   StageGuard guard;
   if (need_items) {
@@ -1687,6 +1692,7 @@ extern "C" int deepclean_forward_cached(const gw_model* m, gw_pool* pool, const 
   const void* dev = nullptr;
   StageGuard guard;
   CHK(pool->stager.stage_raw(items.data(), items.size() * sizeof(gw::CacheItem), st, &dev, &guard));
+  pool->dc_fills = false;
   // until every launch is enqueued the caches hold no known window (an error
   // below leaves them to be recomputed in full by the next call)
   for (int i = 0; i < n; ++i) pool->slots[slots[i]].cache_valid = false;
@@ -2254,7 +2260,7 @@ namespace {
 // The whole BBHnet in one kernel (blocks of 64 last-stage positions), then
 // the fixed-order sum of each window's pooled-head shares into its logit.
 int bbh_fused_forward(const gw_model* m, const void* arena, const Item* items, const float* x, int n, int W,
-                      char* gap, float* logits, hipStream_t st) {
+                      bool beside_dc, char* gap, float* logits, hipStream_t st) {
   gw::BbFusedP fp{};
   fp.arena = arena;
   fp.items = items;
@@ -2274,7 +2280,7 @@ int bbh_fused_forward(const gw_model* m, const void* arena, const Item* items, c
   fp.n = n;
   fp.W = W;
   fp.tiles = gw::bbh_fused_tiles(W);
-  LAUNCH("bbh_fused", st, gw::launch_bbh_fused(fp, st));
+  LAUNCH("bbh_fused", st, gw::launch_bbh_fused(fp, beside_dc, st));
   LAUNCH("gap_finalize", st, gw::launch_gap_finalize(fp.part, fp.tiles, P + m->head_b, logits, n, W / 8, st));
   return GW_OK;
 }
@@ -2335,14 +2341,14 @@ extern "C" int bbhnet_forward(const gw_model* m, gw_pool* pool, const int32_t* s
     pool->mark_used(slots, n, guard);
     if (fused) {
       // the fused kernel reads every window straight from its ring
-      CHK(bbh_fused_forward(m, pool->arena, dev, nullptr, n, W, wsb + b.gap, logits, st));
+      CHK(bbh_fused_forward(m, pool->arena, dev, nullptr, n, W, pool->dc_fills, wsb + b.gap, logits, st));
       return GW_OK;
     }
     float* g = reinterpret_cast<float*>(wsb + b.gath);
     LAUNCH("gather", st, gw::launch_gather(pool->arena, dev, n, m->c_in, W, g, nullptr, st));
     in = g;
   } else if (fused) {
-    CHK(bbh_fused_forward(m, nullptr, nullptr, x, n, W, wsb + b.gap, logits, st));
+    CHK(bbh_fused_forward(m, nullptr, nullptr, x, n, W, false, wsb + b.gap, logits, st));
     return GW_OK;
   }
   int L = W;

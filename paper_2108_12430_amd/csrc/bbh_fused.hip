@@ -78,6 +78,9 @@ static_assert(2 * (NR[5] - 1) + 6 < NR[4] && NR[6] - 1 + 6 < NR[5] && 2 * (NR[6]
 constexpr int R0 = mx(CAP[1] * CH[1], CAP[3] * CH[3]);
 constexpr int R1 = mx(CAP[2] * CH[2], CAP[5] * CH[5]);
 constexpr int R2 = mx(CAP[0] * CH[0], CAP[4] * CH[4]);
+// unused: makes the block's LDS kHalfCuLds bytes
+constexpr int FILL = kHalfCuLds / 2 - (R0 + R1 + R2 + 2 * NW);
+static_assert(FILL >= 0 && FILL % 8 == 0, "LDS of a block");
 
 }  // namespace bbf
 
@@ -207,11 +210,15 @@ __device__ __forceinline__ float conv_phase(const uint16_t* in, const uint16_t* 
 }  // namespace bbf
 
 // two 8-wave blocks per CU (LDS 63 KB each): four waves per SIMD, at most 128 VGPRs
+// (LDS 63,520 bytes of data in a block of 64,640, see kHalfCuLds.  A finished
+// block's 63,520 held no dc_fused block: free-running steps of 179 DeepClean
+// windows with overlap averaging beside 48 and 64 BBHnet windows 329 -> 224 us,
+// 64 ensemble streams 243 -> 198 us a step.)
 __global__ __launch_bounds__(bbf::NTHR, 4) void bbh_fused(BbFusedP p) {
   using namespace bbf;
   __shared__ __attribute__((aligned(16))) uint16_t r0[R0];
   __shared__ __attribute__((aligned(16))) uint16_t r1[R1];
-  __shared__ __attribute__((aligned(16))) uint16_t r2[R2];
+  __shared__ __attribute__((aligned(16))) uint16_t r2[R2 + FILL];
   __shared__ float wsum[NW];
   const int b = blockIdx.x / p.tiles, tile = blockIdx.x - b * p.tiles;
   if (b >= p.n) return;
@@ -284,11 +291,37 @@ bool bbh_fused_supported(int c_in, const int* co, int stages) {
 
 int bbh_fused_tiles(int W) { return (W / 8 + bbf::T3 - 1) / bbf::T3; }
 
-hipError_t launch_bbh_fused(const BbFusedP& p, hipStream_t st) {
+// Two blocks a CU, but one where a dense DeepClean launch may come beside and
+// the blocks are more than the CUs and at most 7/4 of them.  If bbh_fused gets
+// to the chip first, the CUs with two of its blocks take one 12-wave dc_fused
+// block when the first of the two ends, and the second dc_fused block only
+// when that one ends, although registers and LDS are free (blocks of 8 waves,
+// or 12-wave ones in bbh_fused's place, do not wait): one tile more for the
+// whole step.  Measured (179 DeepClean windows in steps of mixed strides,
+// us a step, two a CU and one a CU): with overlap averaging, free-running, beside 66,
+// 77, 90, 100 and 112 windows (264 .. 448 blocks) 329 and 215, 326 and 215, 303
+// and 215, 280 and 216, 299 and 217; without it 202 and 208, 203 and 209, 203 and
+// 212, 204 and 214, 204 and 217; a step at a time 226 and 234, 230 and 238, 231
+// and 238, 232 and 243, 234 and 243.  With 124 and 128 (496, 512 blocks) the
+// chip is full of bbh_fused first, and two a CU are faster: 217 and 263, 219 and
+// 272.  Beside a causal band's shorter launch two are faster throughout (77: 48
+// and 60).
+hipError_t launch_bbh_fused(const BbFusedP& p, bool beside_dc, hipStream_t st) {
   if (p.n < 1 || p.W < 8 || p.W % 8 || p.tiles != bbh_fused_tiles(p.W)) return hipErrorInvalidValue;
   const int64_t blocks = (int64_t)p.n * p.tiles;
   if (blocks > ((int64_t)1 << 31) - 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bbh_fused, dim3((unsigned)blocks), dim3(bbf::NTHR), 0, st, p);
+  unsigned more_lds = 0;
+  if (beside_dc) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    // over half of a CU's 160 KB, and a dc_fused block still fits beside
+    constexpr int kOne = 82 * 1024;
+    static_assert(2 * kOne > 160 * 1024 && kOne + kHalfCuLds <= 158 * 1024, "one a CU, with a dc_fused block");
+    if (blocks > cus && 4 * blocks <= 7 * (int64_t)cus) more_lds = kOne - kHalfCuLds;
+  }
+  hipLaunchKernelGGL(bbh_fused, dim3((unsigned)blocks), dim3(bbf::NTHR), more_lds, st, p);
   return hipGetLastError();
 }
 

@@ -1611,6 +1611,8 @@ __global__ __launch_bounds__(Z::NTHR, 6) void dc_fused(ItemArgs args, DcIn p, Fu
   uint16_t *const bufA = padA + FRONT, *const bufB = padB + FRONT;
   __shared__ __attribute__((aligned(16))) float ksc[9][64];
   __shared__ __attribute__((aligned(16))) float ksh[9][64];
+  static_assert(sizeof(padA) + sizeof(padB) + sizeof(ktab) + sizeof(ksc) + sizeof(ksh) <= kHalfCuLds,
+                "fits the half of a CU that bbh_fused leaves");
 
   const int W = p.Lin;
   const int tpw = (W + Z::T - 1) / Z::T;  // tiles per window
@@ -1821,6 +1823,13 @@ static hipError_t launch_dc_z(const DcIn& p, const ItemArgs& args, const FusedP&
                               int ncu, hipStream_t st) {
   return p.causal ? launch_dc_c<Z, true>(p, args, f, n, ring, f16, ncu, st)
                   : launch_dc_c<Z, false>(p, args, f, n, ring, f16, ncu, st);
+}
+
+bool dc_fused_fills(int n, int W) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
+  return (int64_t)n * ((W + 767) / 768) > cus;
 }
 
 // io: arena and items (ring input or clean outputs), x (+ ldx), noise, clean,

@@ -323,7 +323,16 @@ struct BbFusedP {
 
 bool bbh_fused_supported(int c_in, const int* co, int stages);
 int bbh_fused_tiles(int W);  // blocks (pooled-head shares) per window
-hipError_t launch_bbh_fused(const BbFusedP& p, hipStream_t st);
+// beside_dc: a DeepClean launch of more than one block a CU may be due on
+// another stream (see the launch)
+hipError_t launch_bbh_fused(const BbFusedP& p, bool beside_dc, hipStream_t st);
+
+// LDS of a block of dc_fused in tiles of 768 and of bbh_fused, two a CU each.
+// The two run beside each other on two streams, and a CU whose half a finished
+// bbh_fused block leaves too small for a dc_fused block keeps it empty until
+// the CU's other dc_fused block ends, one tile (150 us in a step of 179
+// windows) later: the sizes are the same.
+constexpr int kHalfCuLds = 64640;
 
 // training: the input's transform and the epilogue's operands
 struct F32Train {
@@ -379,6 +388,8 @@ bool dc_fused_supported(const int* ci, const int* co, const int* type, const int
 hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint16_t* const* wpk,
                                 const float* const* scale, const float* const* shift, int n, bool ring, int cu_budget,
                                 hipStream_t st, bool f16);
+// whether a dense launch of n windows is more than one block of 768 a CU
+bool dc_fused_fills(int n, int W);
 // The fused FP32 forward of the same network (dc_f32.hip): fragments of its
 // special layers (the others: launch_pack_f32m), and the launch.
 size_t dc_f32_special_floats(int l);
