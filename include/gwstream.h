@@ -398,10 +398,11 @@ int deepclean_overlap_average(const gw_model* model, int32_t n, int32_t W, const
  * deepclean_forward call with GW_TRAIN and the same n, W, x, flags and
  * precision).  dparams (device, n_params float32) is overwritten, not
  * accumulated; running-statistics entries get 0.  With GW_RECOMPUTE the
- * activations are recomputed from checkpoints (the reference network shape:
- * taken from the layers' saved pre-normalisation values, with or without
- * GW_RECOMPUTE); the result is bitwise equal to the stored-activation path.  `scratch` needs deepclean_backward_scratch
- * bytes.  All reductions have a fixed order (deterministic).  precision must
+ * activations are recomputed from checkpoints; the result is bitwise equal to
+ * the stored-activation path.  (The reference network shape keeps layers'
+ * pre-normalisation values: 36 W floats a window, or with GW_RECOMPUTE 28 W,
+ * the others made again.)  `scratch` needs deepclean_backward_scratch bytes.
+ * All reductions have a fixed order (deterministic).  precision must
  * equal the forward's: GW_BF16 runs the forward (and recomputed) convolutions
  * on BF16 matrix cores with FP32 activations, statistics and gradients; the
  * backward's products are FP32 in both.

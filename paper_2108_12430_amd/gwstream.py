@@ -399,7 +399,8 @@ class DeepClean(_Model):
                        precision=FP32, flags=0, ws=None, stream=None, delays=None):
         """Enqueue deepclean_update_forward: pool.update(slots, strides,
         samples, offsets) then forward(pool=pool, slots=slots, ...) with the
-        same strides, in one launch on the fused BF16 inference path."""
+        same strides, in one launch for inference on the fused network (any
+        precision; flags 0, or CAUSAL without delays)."""
         _f32(samples, "samples")
         n = len(slots)
         if ws is None:
