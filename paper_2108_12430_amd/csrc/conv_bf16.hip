@@ -1871,7 +1871,7 @@ hipError_t launch_dc_fused_bf16(const DcIn& io, const ItemArgs& args, const uint
   // Tiles of 512 in blocks of eight waves, three a CU, where they take a round
   // less than tiles of 768, two a CU, and the rounds are few: a round of 512
   // costs more, so from six rounds on the gain is gone.  Measured (us, 21 x
-  // 32768, 768 against 512, on two boxes): n = 11 (one round each) 21.7 and
+  // 32768, 768 against 512, two runs): n = 11 (one round each) 21.7 and
   // 24.5, 12 (2 and 1) 32.4 and 25.1, 20 (2 and 2) 34.2 and 34.6, 24 (3 and 2)
   // 45.2 and 40.3, 36 (4 and 3) 58 and 53, 48 (5 and 4) 70 and 64 .. 69, 72 (7 and
   // 6) 92 and 88 .. 94, 96 (9 and 8) 114 and 112 .. 121; FP16: 12 37.3 and 28.6, 24

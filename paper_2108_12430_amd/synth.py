@@ -3,7 +3,7 @@
 This module only draws random numbers and shapes them into the inputs the
 streaming networks consume.  It contains none of the networks' arithmetic
 (no convolution, normalisation, activation, ring update or loss), so both the
-device path and the FP64 checker can take their inputs from here without
+device path and the FP64 oracle can take their inputs from here without
 sharing any of the method's code.
 
 Workload shapes follow the paper's deployment: 21 witness channels of the
