@@ -223,8 +223,10 @@ struct gw_pool {
   size_t ring_base = 0;
   Stager stager;
   // The last DeepClean forward from this pool filled more than a block a CU
-  // (dense, fused): the BBHnet forwards beside it choose their placement by it.
+  // (dense, fused), and its stream: BBHnet forwards on another stream choose
+  // their placement by it (the handle is compared, never used).
   bool dc_fills = false;
+  hipStream_t dc_stream = nullptr;
   struct Slot {
     bool open = false;
     int C = 0, W = 0;
@@ -1329,8 +1331,10 @@ static int dc_forward(const gw_model* m, gw_pool* pool, const int32_t* slots, co
   const bool one_kernel = m->fused && !(flags & (GW_TRAIN | GW_LAYERWISE));
   // the fused kernels take the items of a small call as an argument
   const bool in_args = one_kernel && n <= gw::kItemArgs;
-  if (pool)
+  if (pool) {
+    pool->dc_stream = st;
     pool->dc_fills = one_kernel && precision != GW_FP32 && !(flags & GW_CAUSAL) && gw::dc_fused_fills(n, Wb);
+  }
   const Item* dev_items = nullptr;
   StageGuard guard;
   if (need_items) {
@@ -2341,7 +2345,7 @@ extern "C" int bbhnet_forward(const gw_model* m, gw_pool* pool, const int32_t* s
     pool->mark_used(slots, n, guard);
     if (fused) {
       // the fused kernel reads every window straight from its ring
-      CHK(bbh_fused_forward(m, pool->arena, dev, nullptr, n, W, pool->dc_fills, wsb + b.gap, logits, st));
+      CHK(bbh_fused_forward(m, pool->arena, dev, nullptr, n, W, pool->dc_fills && pool->dc_stream != st, wsb + b.gap, logits, st));
       return GW_OK;
     }
     float* g = reinterpret_cast<float*>(wsb + b.gath);

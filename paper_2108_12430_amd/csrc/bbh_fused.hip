@@ -291,8 +291,8 @@ bool bbh_fused_supported(int c_in, const int* co, int stages) {
 
 int bbh_fused_tiles(int W) { return (W / 8 + bbf::T3 - 1) / bbf::T3; }
 
-// Two blocks a CU, but one where a dense DeepClean launch may come beside and
-// the blocks are more than the CUs and at most 7/4 of them.  If bbh_fused gets
+// Two blocks a CU, but one where a dense DeepClean launch may come beside (the
+// pool's last one was on another stream) and the blocks are more than the CUs and at most 7/4 of them.  If bbh_fused gets
 // to the chip first, the CUs with two of its blocks take one 12-wave dc_fused
 // block when the first of the two ends, and the second dc_fused block only
 // when that one ends, although registers and LDS are free (blocks of 8 waves,
@@ -305,7 +305,7 @@ int bbh_fused_tiles(int W) { return (W / 8 + bbf::T3 - 1) / bbf::T3; }
 // and 238, 232 and 243, 234 and 243.  With 124 and 128 (496, 512 blocks) the
 // chip is full of bbh_fused first, and two a CU are faster: 217 and 263, 219 and
 // 272.  Beside a causal band's shorter launch two are faster throughout (77: 48
-// and 60).
+// and 60); alone 77 take 28 and 34.
 hipError_t launch_bbh_fused(const BbFusedP& p, bool beside_dc, hipStream_t st) {
   if (p.n < 1 || p.W < 8 || p.W % 8 || p.tiles != bbh_fused_tiles(p.W)) return hipErrorInvalidValue;
   const int64_t blocks = (int64_t)p.n * p.tiles;

@@ -35,7 +35,7 @@ def open_all(n_dc, n_bb):
 
 
 # one block a CU from 65 windows (260 blocks) to 112 (448) once the pool's
-# DeepClean forward is dense; two outside
+# DeepClean forward is dense and on another stream; two outside
 @pytest.mark.parametrize("n", [3, 64, 65, 112, 113])
 def test_logits_do_not_depend_on_the_placement(n):
     dc, bb = models()
@@ -52,14 +52,20 @@ def test_logits_do_not_depend_on_the_placement(n):
     noise = torch.empty((n_dc, DC_W), device=DEV)
     wd = torch.empty(dc.workspace_bytes(n_dc, DC_W, gs.BF16), dtype=torch.uint8, device=DEV)
     dc.forward(pool=pool, slots=dc_sl, W=DC_W, noise=noise, precision=gs.BF16, ws=wd)
-    bb.forward(pool=pool, slots=bb_sl, W=BB_W, logits=got, precision=gs.BF16, ws=ws)
     torch.cuda.synchronize()
-    assert torch.equal(got, want) and torch.equal(before, want)
+    same = torch.empty(n, device=DEV)
+    bb.forward(pool=pool, slots=bb_sl, W=BB_W, logits=same, precision=gs.BF16, ws=ws)
+    torch.cuda.synchronize()
+    bb.forward(pool=pool, slots=bb_sl, W=BB_W, logits=got, precision=gs.BF16, ws=ws, stream=torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and torch.equal(same, want) and torch.equal(before, want)
 
 
 # 179 DeepClean streams with overlap averaging: per step the time without the
-# BBHnet group is about 200 us, with it 215 .. 225 (before: 325).  The bound
-# of 1.3 lies between 1.1 and 1.6.
+# BBHnet group is about 205 us.  With it 215 where its launch comes into the
+# next dc_fused launch's tail; where it comes first, two rounds of its blocks
+# (40 us) and the averaging beside it are added: 260, 1.27 times.  A whole tile
+# more (before) made it 316 .. 330, 1.55 times.  The bound lies between the two.
 @pytest.mark.parametrize("n_bb", [48, 77])
 def test_step_is_not_held_up(n_bb):
     dc, bb = models()
@@ -101,4 +107,4 @@ def test_step_is_not_held_up(n_bb):
     alone = min(run(200, False) for _ in range(4))
     both = min(run(200, True) for _ in range(4))
     print(f"{1e6 * alone:.1f} us a step, with {n_bb} BBHnet windows {1e6 * both:.1f}")
-    assert both < 1.3 * alone
+    assert both < 1.4 * alone
